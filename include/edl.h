@@ -26,7 +26,9 @@
  *     device memory.  A handle owns (until edl_shutdown) a few small pinned
  *     host staging buffers (the mini-batch's indices, the workers' losses),
  *     HIP events, and - unless the caller brings them, see
- *     edl_set_side_streams - two non-blocking streams of default priority.
+ *     edl_set_side_streams - uses two non-blocking streams of default priority
+ *     that the jobs of a GPU share (created with the first, destroyed with the
+ *     last of them).
  *   - device work is queued on the hipStream_t given to edl_init (NULL = the
  *     default stream).  A training pass also uses the two side streams (weight
  *     gradients; the update of layers whose gradients are final), ordered
@@ -200,13 +202,13 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
 /* The two streams a training pass uses beside the job's own (see Conventions): the caller's, which must
  * differ from each other and from the job's stream, be of default priority and outlive the handle's use of
  * them; or NULL, NULL for none (everything then runs on the job's stream).  Replaces whatever the handle used
- * before (streams the library created itself are destroyed).  Synchronises the job's stream and the old side
+ * before (the library's own pair is destroyed with its last user).  Synchronises the job's stream and the old side
  * streams.  Results do not depend on the choice, bit for bit. */
 int32_t edl_set_side_streams(edl_handle* h, void* wgrad_stream, void* update_stream);
 
 /* Named integer options of the library (process-wide; see Conventions).  EDL_EINVAL for an unknown name.  Names:
  * force_tile (-1, or 0..3 = every forward / input-gradient launch on 128x128, 128x64, 128x32, 64x64 tiles),
- * wgrad_stream (1: jobs created from now on make their own side streams; 0: they do not), wgrad_tail_main,
+ * wgrad_stream (1: jobs created from now on use the library's side streams; 0: they do not), wgrad_tail_main,
  * early_update (least weights of a layer whose update starts during the backward pass; 0 = never),
  * early_blocks, join_tile, fused_stats, held_stats, fused_mask, fused_mask_cut, fused_mask_join,
  * min128, min128_long, bk64_kred, xcd, order, splitk_tiles, splitk_target, wgrad_blocks, wgrad_long_blocks,

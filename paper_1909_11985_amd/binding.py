@@ -321,7 +321,7 @@ class Job:
     raw pointers to the library."""
 
     def __init__(self, cfg, seed, device="cuda:0", stream=None, side_streams="library"):
-        """side_streams: "library" (the handle makes its own two side streams, unless the option wgrad_stream
+        """side_streams: "library" (the library's two side streams, unless the option wgrad_stream
         is 0), "torch" (two torch.cuda.Stream objects of default priority made here and handed over), or None
         (everything on the job's stream)."""
         import torch
