@@ -3,8 +3,9 @@
  * deep-learning job, native on MI355X (gfx950).
  *
  * One handle is one job on one GPU.  The p workers of the job are simulated
- * as p shards of the aggregate mini-batch, processed one after the other on
- * the handle's stream.  What the calls mean, in the paper's terms:
+ * as p shards of the aggregate mini-batch, processed on the handle's stream,
+ * as many of them together as the workspace holds (each keeps its own batch
+ * statistics, gradient buffer and loss).  What the calls mean, in the paper's terms:
  *
  *   edl_init      init() of the framework API (section 3.2, Table 1)
  *   edl_shard     elastic_shard_generator().next() (sections 3.2, 4.3)

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "kernels.h"
+
 namespace edl {
 
 typedef uint16_t bf16_t;  // raw bfloat16 bits
@@ -44,6 +46,24 @@ template <typename T> __device__ __forceinline__ Vec16<T> load_vec(const T* p) {
 }
 template <typename T> __device__ __forceinline__ void store_vec(T* p, const Vec16<T>& v) {
     *reinterpret_cast<uint4*>(p) = v.u;
+}
+
+// Shard and rows [r0, r1) of block b of a row cut.  b is uniform over the workgroup; the search is unrolled over
+// scalar loads of the kernel's arguments (a loop of dependent loads would cost their latency per shard).
+__device__ __forceinline__ int shard_of_block(const RowCut& c, int b) {
+    int s = 0;
+    if (c.p > 1) {
+        #pragma unroll
+        for (int i = 1; i < kMaxP; ++i) s = (i < c.p && b >= c.blk0[i]) ? i : s;
+    }
+    return s;
+}
+__device__ __forceinline__ int locate_block(const RowCut& c, int b, int& r0, int& r1) {
+    const int s = shard_of_block(c, b);
+    r0 = c.row0[s] + (b - c.blk0[s]) * c.rows_per_block;
+    const int end = c.row0[s + 1];
+    r1 = r0 + c.rows_per_block < end ? r0 + c.rows_per_block : end;
+    return s;
 }
 
 }  // namespace edl

@@ -74,8 +74,9 @@ static_assert(sizeof(SnapshotHeader) == 104, "snapshot header layout");
 struct Layout {
     int64_t params = 0, momentum = 0, second = -1, running = 0, shadow = 0, grads = 0, grad_stride = 0;
     int64_t idx = 0, labels = 0, row_loss = 0, losses = 0, partial = 0, partial_held = 0, coef = 0, wgrad_scratch = 0;
-    int64_t partial_side = 0, coef_side = 0, wide_sums_side = 0, splitk_side = 0;   // the branch stream's own scratch
-    int64_t wide_sums = 0, wide_sums_floats = 0;   // partial column sums of launches with more row tiles than `partial` holds
+    int64_t partial_side = 0, coef_side = 0, splitk_side = 0;   // the branch stream's own scratch
+    int64_t partial_floats = 0;          // of each of the three partial-sum pieces
+    int pass_samples = 0, pass_shards = 0;   // most samples / shards that one pass runs together
     int64_t wgrad_scratch_bytes = 0;
     int64_t wgrad_scratch2 = 0;          // for the few weight gradients that run on the main stream beside the second one
     // partial sums of forward / dgrad reductions that are cut; apart from the weight-gradient
@@ -137,9 +138,94 @@ ConvGeom geom_padded(const Graph& g, const Op& op, int n, int cpad) {
     return q;
 }
 
+// The kernels' scratch (partial results that live inside one pass) for passes of up to `samples` samples in up to
+// `shards` shards, in one contiguous piece from `o` on: a caller without an arena piece for it can run the same pass
+// on the library's static buffer (edl_step_static_scratch).  Returns its end.
+int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shards, int64_t o, Layout& L) {
+    auto take = [&](int64_t bytes) { const int64_t at = o; o += align_up(bytes); return at; };
+    int cmax = 1;
+    int64_t dwpad_bytes = 16;
+    L.wgrad_scratch_bytes = L.splitk_scratch_bytes = L.partial_floats = 0;
+    for (const Op& op : g.ops) {
+        if (op.kind == OP_CONV) {
+            cmax = std::max(cmax, op.K);
+            const Tensor& tx = g.tensors[(size_t)op.x];
+            const Tensor& ty = g.tensors[(size_t)op.y];
+            if (op.x == 0 && L.cpad != tx.C) dwpad_bytes = std::max<int64_t>(dwpad_bytes, (int64_t)op.K * op.R * op.S * L.cpad * 4 * shards);
+            for (int q = 1; q <= shards; ++q)
+                L.wgrad_scratch_bytes = std::max<int64_t>(
+                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(geom_padded(g, op, std::max(1, std::min(c.max_shard, samples / q)), L.cpad), q));
+            // the cut of a forward / dgrad reduction depends on the size of the pass: cover every size up to the largest
+            for (int n = 1; n <= samples; n = n < 8 ? n + 1 : n + n / 4)
+                L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
+                                                           (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, n)));
+            L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
+                                                       (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, samples)));
+            L.partial_floats = std::max<int64_t>(L.partial_floats, (int64_t)conv_sums_floats(geom_padded(g, op, samples, L.cpad), shards));
+            L.partial_floats = std::max<int64_t>(L.partial_floats,
+                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)samples * ty.H * ty.W, op.K, shards));
+        } else if (op.kind == OP_BN) {
+            cmax = std::max(cmax, op.K);
+            const Tensor& tx = g.tensors[(size_t)op.x];
+            L.partial_floats = std::max<int64_t>(L.partial_floats,
+                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)samples * tx.H * tx.W, op.K, shards));
+        }
+    }
+    // (room for kRedRowBlocks blocks of the widest layer in any case: what a job needs of the static buffer does not
+    // depend on how its launches happen to be cut)
+    L.partial_floats = std::max<int64_t>(L.partial_floats, 2 * (int64_t)kRedRowBlocks * cmax);
+    L.scratch_lo = o;
+    L.row_loss = take(4 * (int64_t)samples);
+    L.partial = take(4 * L.partial_floats);
+    // a second one for sums that wait while another batch norm runs (a block's last convolution, whose
+    // batch norm comes after the projection shortcut's)
+    L.partial_held = take(4 * L.partial_floats);
+    L.coef = take(4 * 2 * (int64_t)cmax * shards);
+    // the same pair for the projection shortcut's batch norm while it runs on the branch stream beside the main one
+    L.partial_side = take(4 * L.partial_floats);
+    L.coef_side = take(4 * 2 * (int64_t)cmax * shards);
+    L.wgrad_scratch = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
+    L.wgrad_scratch2 = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
+    L.splitk_scratch = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
+    // the branch stream cuts reductions exactly as the main stream would (same results, bit for bit, whichever
+    // stream a layer runs on), in a buffer of its own
+    L.splitk_side = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
+    L.dwpad = take(dwpad_bytes);
+    L.scratch_hi = o;
+    return o;
+}
+
+// How many samples and shards one pass runs together.  All of the mini-batch if it fits: a layer of p shards is then
+// one launch instead of p, with p times the workgroups (ResNet-50 bf16, aggregate batch 256 as 8 shards of 32:
+// 34.5 -> 23.4 ms per step; ResNet-20 float32, 8 shards of 16: 10.3 -> 1.84 ms; MLP, 4 shards of 16: 0.48 -> 0.17 ms).  Limits, none of which cuts a single shard:
+// 32 GB of activations and gradients (a pass of some 250 images of 224x224 gains nothing more from more of them),
+// 2 GiB per tensor (the vector kernels' 32-bit offsets), and the static scratch buffer where one shard at a time
+// fits it (the two entry points run the same passes).
+void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
+    const int64_t esz = c.dtype == EDL_DTYPE_BF16 ? 2 : 4;
+    int64_t per_sample = 1, widest = 1;
+    for (size_t t = 0; t < g.tensors.size(); ++t) {
+        if (g.tensors[t].alias_of >= 0) continue;
+        const int64_t bytes = (t == 0 ? (int64_t)g.tensors[0].H * g.tensors[0].W * L.cpad : g.tensors[t].elems()) * (g.tensors[t].fp32 ? 4 : esz);
+        per_sample += 2 * bytes;
+        widest = std::max(widest, bytes);
+    }
+    int64_t samples = std::min<int64_t>(c.B, std::min<int64_t>(32000000000ll / per_sample, 2147483647ll / widest));
+    samples = std::max<int64_t>(std::min<int64_t>(samples, 65535), c.max_shard);
+    int shards = c.p_max;
+    if (plan_scratch(c, g, c.max_shard, 1, 0, L) <= (int64_t)EDL_STATIC_SCRATCH_BYTES)
+        while (shards > 1 && plan_scratch(c, g, (int)samples, shards, 0, L) > (int64_t)EDL_STATIC_SCRATCH_BYTES) {
+            shards = (shards + 1) / 2;
+            samples = std::max<int64_t>(samples / 2, c.max_shard);
+        }
+    L.pass_shards = shards;
+    L.pass_samples = shards == 1 ? c.max_shard : (int)samples;
+}
+
 void plan_layout(const edl_config& c, const Graph& g, Layout& L) {
     const int64_t esz = c.dtype == EDL_DTYPE_BF16 ? 2 : 4;
     L.cpad = input_pad(c, g);
+    plan_pass(c, g, L);
     int64_t o = 0;
     auto take = [&](int64_t bytes) { const int64_t at = o; o += align_up(bytes); return at; };
     // The arrays the update kernel walks side by side (w, v, the bf16 copy, the p gradient buffers) start on 4 KB
@@ -162,77 +248,36 @@ void plan_layout(const edl_config& c, const Graph& g, Layout& L) {
     L.grads = take_page(4 * L.grad_stride * c.p_max, 1);
     L.running = take(4 * std::max<int64_t>(g.R, 1));
     L.idx = take(8 * c.B);
-    L.labels = take(4 * (int64_t)c.max_shard);
+    L.labels = take(4 * (int64_t)L.pass_samples);
     L.losses = take(4 * kMaxP);
-    int cmax = 1;
-    for (const Op& op : g.ops)
-        if (op.kind == OP_CONV || op.kind == OP_BN) cmax = std::max(cmax, op.K);
     const size_t nt = g.tensors.size();
     L.act.assign(nt, -1);
     L.grad.assign(nt, -1);
     for (size_t t = 0; t < nt; ++t) {
         if (g.tensors[t].alias_of >= 0) continue;
-        int64_t elems = g.tensors[t].elems() * c.max_shard;
-        if (t == 0) elems = (int64_t)g.tensors[0].H * g.tensors[0].W * L.cpad * c.max_shard;
+        int64_t elems = g.tensors[t].elems() * L.pass_samples;
+        if (t == 0) elems = (int64_t)g.tensors[0].H * g.tensors[0].W * L.cpad * L.pass_samples;
         L.act[t] = take(elems * (g.tensors[t].fp32 ? 4 : esz));
         if (t != 0) L.grad[t] = take(elems * esz);
     }
     const size_t no = g.ops.size();
     L.wT.assign(no, -1);
     L.wpad.assign(no, -1);
-    int64_t dwpad_bytes = 16;
     L.bn_save.assign(no, -1);
     L.pool_arg.assign(no, -1);
-    L.wgrad_scratch_bytes = 0;
-    L.splitk_scratch_bytes = 0;
     for (size_t i = 0; i < no; ++i) {
         const Op& op = g.ops[i];
         if (op.kind == OP_CONV) {
             const Tensor& tx = g.tensors[(size_t)op.x];
             if (storage_of(g, op.x) != 0) L.wT[i] = take((int64_t)op.K * op.R * op.S * tx.C * esz);
-            else if (op.x == 0 && L.cpad != tx.C) {
-                L.wpad[i] = take((int64_t)op.K * op.R * op.S * L.cpad * esz);
-                dwpad_bytes = std::max<int64_t>(dwpad_bytes, (int64_t)op.K * op.R * op.S * L.cpad * 4);
-            }
-            L.wgrad_scratch_bytes = std::max<int64_t>(L.wgrad_scratch_bytes,
-                                                      (int64_t)conv_wgrad_scratch_bytes(geom_padded(g, op, c.max_shard, L.cpad)));
-            // the cut of a forward / dgrad reduction depends on the shard size: cover every size up to the largest
-            for (int n = 1; n <= c.max_shard; n = n < 8 ? n + 1 : n + n / 4)
-                L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
-                                                           (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, n)));
-            L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
-                                                       (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, c.max_shard)));
-            L.wide_sums_floats = std::max<int64_t>(L.wide_sums_floats,
-                                                   (int64_t)conv_wide_sums_floats(c.dtype, geom_padded(g, op, c.max_shard, L.cpad)));
+            else if (op.x == 0 && L.cpad != tx.C) L.wpad[i] = take((int64_t)op.K * op.R * op.S * L.cpad * esz);
         } else if (op.kind == OP_BN) {
-            L.bn_save[i] = take(4 * 2 * (int64_t)op.K);
+            L.bn_save[i] = take(4 * 2 * (int64_t)op.K * L.pass_shards);
         } else if (op.kind == OP_MAXPOOL) {
-            L.pool_arg[i] = take(g.tensors[(size_t)op.y].elems() * c.max_shard);
+            L.pool_arg[i] = take(g.tensors[(size_t)op.y].elems() * L.pass_samples);
         }
     }
-    // The kernels' scratch (partial results that live inside one pass), in one contiguous piece
-    // [scratch_lo, scratch_hi): a caller without an arena piece for it can run the same pass on the library's
-    // static buffer (edl_step_static_scratch).
-    L.scratch_lo = o;
-    L.row_loss = take(4 * (int64_t)c.max_shard);
-    L.partial = take(4 * 2 * (int64_t)kRedRowBlocks * cmax);
-    // a second one for sums that wait while another batch norm runs (a block's last convolution, whose
-    // batch norm comes after the projection shortcut's)
-    L.partial_held = take(4 * 2 * (int64_t)kRedRowBlocks * cmax);
-    L.coef = take(4 * 2 * (int64_t)cmax);
-    // the same pair for the projection shortcut's batch norm while it runs on the branch stream beside the main one
-    L.partial_side = take(4 * 2 * (int64_t)kRedRowBlocks * cmax);
-    L.coef_side = take(4 * 2 * (int64_t)cmax);
-    L.wgrad_scratch = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
-    L.wgrad_scratch2 = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
-    L.wide_sums = take(std::max<int64_t>(4 * L.wide_sums_floats, 16));
-    L.splitk_scratch = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
-    // the branch stream cuts reductions and keeps wide sums exactly as the main stream would (same results, bit
-    // for bit, whichever stream a layer runs on), in buffers of its own
-    L.wide_sums_side = take(std::max<int64_t>(4 * L.wide_sums_floats, 16));
-    L.splitk_side = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
-    L.dwpad = take(dwpad_bytes);
-    L.scratch_hi = o;
+    o = plan_scratch(c, g, L.pass_samples, L.pass_shards, o, L);
     L.ttable = take((int64_t)sizeof(TransposeEntry) * 2 * std::max<size_t>(no, 1));   // element-wise entries, then vector ones
     L.total = o;
 }
@@ -660,12 +705,12 @@ int32_t edl_shard(const edl_handle* h, int64_t B, int32_t p, int64_t epoch, int6
     return edl_shard_host(h->seed, h->cfg.N, B, p, epoch, step_in_epoch, out_idx, out_off);
 }
 
-// forward + backward of one worker's shard: n samples whose indices are at
-// dev_idx; gradient into G; mean loss into dev_loss[0]
+// Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
 // op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
 // single layers from the debugging hooks, which then skip the gather)
-static void forward_shard(edl_handle* h, const int64_t* dev_idx, int n, float* dev_loss, bool update_running,
-                          size_t op_lo = 0, size_t op_hi = (size_t)-1) {
+static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_idx, float* dev_losses, bool update_running,
+                         size_t op_lo = 0, size_t op_hi = (size_t)-1) {
+    const int n = S.samples();
     const Graph& g = h->g;
     const int dt = h->cfg.dtype;
     hipStream_t st = h->st;
@@ -680,10 +725,12 @@ static void forward_shard(edl_handle* h, const int64_t* dev_idx, int n, float* d
             launch_gather(dt, h->data_x, h->data_y, dev_idx, n, tin.elems(), h->act(0), h->at<int32_t>(h->L.labels), st);
     }
     if (op_hi > g.ops.size()) op_hi = g.ops.size();
-    int stats_row_blocks = 0;   // > 0: the convolution just launched left the next batch norm's partial sums
+    RowCut sums;                // p > 0: the convolution just launched left the next batch norm's partial sums
+    const size_t pf = (size_t)h->L.partial_floats;
     // the same for a convolution whose batch norm is not the next op: its sums wait in a buffer of their own
     float* const partial_held = h->sc<float>(h->L.partial_held);
-    int held_rows = 0, held_tensor = -1;
+    RowCut held_sums;
+    int held_tensor = -1;
     auto weights_of = [&](size_t i) {
         const Op& o = g.ops[i];
         const void* wsrc = bf ? (const void*)(h->at<uint16_t>(h->L.shadow) + o.w_off) : (const void*)(h->w() + o.w_off);
@@ -713,15 +760,15 @@ static void forward_shard(edl_handle* h, const int64_t* dev_idx, int n, float* d
                 if (hipEventRecord(go, st) != hipSuccess || hipStreamWaitEvent(h->upd, go, 0) != hipSuccess) break;
                 h->branch_slot = (h->branch_slot + 1) % kBranchEvents;
                 float* const ps = h->sc<float>(h->L.partial_side);
-                // this stream's own split-reduction scratch and wide-sums buffer (the main stream's are in use)
-                const int rows = launch_conv_fwd(dt, geom_padded(g, pj, n, h->L.cpad), h->act(pj.x), weights_of(j),
-                                                 pj.bias ? h->w() + pj.b_off : nullptr, pj.relu, g.tensors[(size_t)pj.y].fp32,
-                                                 h->act(pj.y), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, ps,
-                                                 WideSums{h->sc<float>(h->L.wide_sums_side), (size_t)h->L.wide_sums_floats}, h->upd);
+                // this stream's own split-reduction scratch (the main stream's is in use)
+                const RowCut left = launch_conv_fwd(dt, geom_padded(g, pj, n, h->L.cpad), S, h->act(pj.x), weights_of(j),
+                                                    pj.bias ? h->w() + pj.b_off : nullptr, pj.relu, g.tensors[(size_t)pj.y].fp32,
+                                                    h->act(pj.y), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes,
+                                                    SumsBuf{ps, pf}, h->upd);
                 const Tensor& t = g.tensors[(size_t)pb.x];
                 launch_bn_forward(dt, h->act(pb.x), nullptr, h->act(pb.y), h->w() + pb.w_off, h->w() + pb.b_off,
                                   h->at<float>(h->L.bn_save[j + 1]), update_running ? h->running() + pb.run_off : nullptr,
-                                  (int64_t)n * t.H * t.W, t.C, pb.relu, ps, rows, h->upd);
+                                  S, t.H * t.W, t.C, pb.relu, ps, left, h->upd);
                 (void)hipEventRecord(dn, h->upd);
                 done[j] = done[j + 1] = 1;
                 join_tensor = pb.y;
@@ -740,33 +787,32 @@ static void forward_shard(edl_handle* h, const int64_t* dev_idx, int n, float* d
                 if (!bn_next && tune_held && held_tensor < 0)
                     for (size_t j = i + 2; j < op_hi && j <= i + 4 && !bn_later; ++j)
                         bn_later = g.ops[j].kind == OP_BN && g.ops[j].x == op.y;
-                const int rows = launch_conv_fwd(dt, geom_padded(g, op, n, h->L.cpad), h->act(op.x), wsrc,
-                                                 op.bias ? h->w() + op.b_off : nullptr, op.relu, g.tensors[(size_t)op.y].fp32,
-                                                 h->act(op.y), h->sc<float>(h->L.splitk_scratch),
-                                                 (size_t)h->L.splitk_scratch_bytes,
-                                                 bn_next ? partial : bn_later ? partial_held : nullptr,
-                                                 WideSums{h->sc<float>(h->L.wide_sums), (size_t)h->L.wide_sums_floats}, st);
+                const RowCut left = launch_conv_fwd(dt, geom_padded(g, op, n, h->L.cpad), S, h->act(op.x), wsrc,
+                                                    op.bias ? h->w() + op.b_off : nullptr, op.relu, g.tensors[(size_t)op.y].fp32,
+                                                    h->act(op.y), h->sc<float>(h->L.splitk_scratch),
+                                                    (size_t)h->L.splitk_scratch_bytes,
+                                                    SumsBuf{bn_next ? partial : bn_later ? partial_held : nullptr, pf}, st);
                 if (bn_later) {
-                    if (rows > 0) { held_rows = rows; held_tensor = op.y; }
-                    stats_row_blocks = 0;
+                    if (left.p > 0) { held_sums = left; held_tensor = op.y; }
+                    sums = RowCut();
                 } else {
-                    stats_row_blocks = rows;
+                    sums = left;
                 }
                 break;
             }
             case OP_BN: {
                 const Tensor& t = g.tensors[(size_t)op.x];
-                const bool held = held_tensor == op.x && held_rows > 0;
+                const bool held = held_tensor == op.x && held_sums.p > 0;
                 if (op.res >= 0 && op.res == join_tensor) {      // the shortcut's part comes from the other stream
                     (void)hipStreamWaitEvent(st, join_event, 0);
                     join_tensor = -1;
                 }
                 launch_bn_forward(dt, h->act(op.x), op.res >= 0 ? h->act(op.res) : nullptr, h->act(op.y), h->w() + op.w_off,
                                   h->w() + op.b_off, h->at<float>(h->L.bn_save[i]),
-                                  update_running ? h->running() + op.run_off : nullptr, (int64_t)n * t.H * t.W, t.C, op.relu,
-                                  held ? partial_held : partial, held ? held_rows : stats_row_blocks, st);
-                if (held) { held_rows = 0; held_tensor = -1; }
-                stats_row_blocks = 0;
+                                  update_running ? h->running() + op.run_off : nullptr, S, t.H * t.W, t.C, op.relu,
+                                  held ? partial_held : partial, held ? held_sums : sums, st);
+                if (held) { held_sums = RowCut(); held_tensor = -1; }
+                sums = RowCut();
                 break;
             }
             case OP_MAXPOOL: {
@@ -783,7 +829,7 @@ static void forward_shard(edl_handle* h, const int64_t* dev_idx, int n, float* d
             }
             case OP_LOSS:
                 launch_softmax_ce(dt, (const float*)h->act(op.x), h->at<int32_t>(h->L.labels), h->grad(op.x),
-                                  h->sc<float>(h->L.row_loss), dev_loss, n, g.classes, st);
+                                  h->sc<float>(h->L.row_loss), dev_losses, S, g.classes, st);
                 break;
         }
     }
@@ -795,8 +841,12 @@ static int apply_range(edl_handle* h, int32_t p, int64_t lo, int64_t hi, hipStre
 // early_p > 0: this is the last backward pass of a step of early_p shards, so gradients that are final may be
 // applied while the pass goes on.
 // held (debugging hook only): tensors whose gradient buffers already hold a contribution the pass adds to.
-static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, size_t op_hi = (size_t)-1, int early_p = 0,
-                           const std::vector<int>* held = nullptr) {
+static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, size_t op_hi = (size_t)-1, int early_p = 0,
+                          const std::vector<int>* held = nullptr) {
+    const int n = S.samples();
+    // the workers' gradients of the parameters from offset `off` of the flat vector on
+    auto grads_at = [&](int64_t off) { return GradDst{h->grad_buf(0) + off, h->L.grad_stride}; };
+    const GradDst no_grads = {nullptr, 0};
     const Graph& g = h->g;
     const int dt = h->cfg.dtype;
     hipStream_t st = h->st;
@@ -815,14 +865,15 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
     // per-kernel timing wants one kernel at a time
     const bool overlap = h->side != nullptr && !prof_enabled();
     bool used_side = false, used_upd = false;
-    // the projection shortcut's backward on the second side stream (see forward_shard)
+    // the projection shortcut's backward on the second side stream (see forward_pass)
     const bool branch = overlap && op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && tune().branch_stream != 0;
     std::vector<char>& done = h->op_done;
     std::fill(done.begin(), done.end(), 0);
     int join_storage = -1;               // gradient buffer the branch stream is still writing
     hipEvent_t join_event = nullptr;
     size_t fused_for = (size_t)-1;   // the layer whose masked gradient and column sums the dgrad after it left
-    int fused_rows = 0;
+    RowCut fused_sums;
+    const SumsBuf sums_buf = {partial, (size_t)h->L.partial_floats};
     size_t premasked_for = (size_t)-1;   // the layer whose gradient the max pool after it left masked by its ReLU
     for (size_t ii = op_hi; ii-- > op_lo;) {
         const Op& op = g.ops[ii];
@@ -838,10 +889,9 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
                 break;
             case OP_CONV: {
                 const ConvGeom q = geom_padded(g, op, n, h->L.cpad);
-                const int64_t M = (int64_t)n * q.Ho * q.Wo;
                 const bool padded = h->L.wpad[ii] >= 0;
-                launch_bias_relu_backward(dt, h->act(op.y), h->grad(op.y), op.bias ? G + op.b_off : nullptr, M, op.K,
-                                          op.relu && premasked_for != ii, partial, fused_for == ii ? fused_rows : 0, st);
+                launch_bias_relu_backward(dt, h->act(op.y), h->grad(op.y), op.bias ? grads_at(op.b_off) : no_grads, S, q.Ho * q.Wo, op.K,
+                                          op.relu && premasked_for != ii, partial, fused_for == ii ? fused_sums : RowCut(), st);
                 // The weight gradient needs only dy (final from here on) and the layer's input, and nothing
                 // before the update reads it: it runs on the second stream, beside the chain of input
                 // gradients, whose short kernels leave part of the chip idle.
@@ -861,10 +911,18 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
                         used_side = true;
                     }
                 }
-                launch_conv_wgrad(dt, q, h->act(op.x), h->grad(op.y), padded ? h->sc<float>(h->L.dwpad) : G + op.w_off,
-                                  wscratch, (size_t)h->L.wgrad_scratch_bytes, ws);
-                if (padded)
-                    launch_unpad_rows(h->sc<float>(h->L.dwpad), G + op.w_off, (int64_t)op.K * op.R * op.S, g.tensors[0].C, h->L.cpad, ws);
+                if (padded) {
+                    // the shards' gradients of the padded weights side by side, then compacted into the flat vectors
+                    const int64_t rows = (int64_t)op.K * op.R * op.S;
+                    ShardSet slots = S;
+                    for (int k = 0; k < S.p; ++k) slots.k[k] = k;
+                    launch_conv_wgrad(dt, q, slots, h->act(op.x), h->grad(op.y), GradDst{h->sc<float>(h->L.dwpad), rows * h->L.cpad},
+                                      wscratch, (size_t)h->L.wgrad_scratch_bytes, ws);
+                    launch_unpad_rows(h->sc<float>(h->L.dwpad), grads_at(op.w_off), S, rows, g.tensors[0].C, h->L.cpad, ws);
+                } else {
+                    launch_conv_wgrad(dt, q, S, h->act(op.x), h->grad(op.y), grads_at(op.w_off), wscratch,
+                                      (size_t)h->L.wgrad_scratch_bytes, ws);
+                }
                 // Parameters are laid out in layer order, so everything from this layer's weights on now has its
                 // final gradient: the second stream holds the weight gradients, and the event it waited for
                 // covers what the main stream has written (bias and batch-norm gradients of the later layers)
@@ -907,19 +965,18 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
                         const Op& prod = g.ops[ii - 1];
                         if (prod.relu && storage_of(g, prod.y) == sx && (prod.kind == OP_BN || prod.kind == OP_CONV)) {
                             mask.act = h->act(op.x);
-                            mask.sums = partial;
-                            mask.wide = WideSums{h->sc<float>(h->L.wide_sums), (size_t)h->L.wide_sums_floats};
+                            mask.sums = sums_buf;
                             if (prod.kind == OP_BN) {
                                 mask.xin = h->act(prod.x);
                                 mask.mean_rstd = h->at<float>(h->L.bn_save[ii - 1]);
                             }
                         }
                     }
-                    const int rows = launch_conv_dgrad(dt, q, h->grad(op.y), h->arena + h->L.wT[ii], acc, h->grad(op.x),
-                                                       h->sc<float>(h->L.splitk_scratch), (size_t)h->L.splitk_scratch_bytes,
-                                                       mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr);
+                    const RowCut left = launch_conv_dgrad(dt, q, S, h->grad(op.y), h->arena + h->L.wT[ii], acc, h->grad(op.x),
+                                                          h->sc<float>(h->L.splitk_scratch), (size_t)h->L.splitk_scratch_bytes,
+                                                          mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr);
                     h->grad_alias[(size_t)sx] = nullptr;
-                    if (rows > 0) { fused_for = ii - 1; fused_rows = rows; }
+                    if (left.p > 0) { fused_for = ii - 1; fused_sums = left; }
                     written[(size_t)sx] = 1;
                 }
                 break;
@@ -956,9 +1013,9 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
                 const void* const dy_src = h->grad_alias[sy] ? h->grad_alias[sy] : h->grad(op.y);
                 h->grad_alias[sy] = nullptr;
                 launch_bn_backward(dt, h->act(op.x), h->act(op.y), dy_src, h->grad(op.x), dres, dres_acc,
-                                   h->w() + op.w_off, h->at<float>(h->L.bn_save[ii]), G + op.w_off, G + op.b_off,
-                                   (int64_t)n * t.H * t.W, t.C, op.relu && premasked_for != ii, partial, coef,
-                                   fused_for == ii ? fused_rows : 0, st);
+                                   h->w() + op.w_off, h->at<float>(h->L.bn_save[ii]), grads_at(op.w_off), grads_at(op.b_off),
+                                   S, t.H * t.W, t.C, op.relu && premasked_for != ii, partial, coef,
+                                   fused_for == ii ? fused_sums : RowCut(), st);
                 written[(size_t)sx] = 1;
                 // The gradient of the shortcut is final now.  If the shortcut is a projection (the convolution and
                 // batch norm listed just before), its backward - batch norm, weight gradient, input gradient into
@@ -983,24 +1040,24 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
                             const void* const pdy = h->grad_alias[spy] ? h->grad_alias[spy] : h->grad(pb.y);
                             h->grad_alias[spy] = nullptr;
                             launch_bn_backward(dt, h->act(pb.x), h->act(pb.y), pdy, h->grad(pb.x), nullptr, false,
-                                               h->w() + pb.w_off, h->at<float>(h->L.bn_save[ii - 1]), G + pb.w_off, G + pb.b_off,
-                                               (int64_t)n * tb.H * tb.W, tb.C, pb.relu, ps, h->sc<float>(h->L.coef_side), 0, bs);
+                                               h->w() + pb.w_off, h->at<float>(h->L.bn_save[ii - 1]), grads_at(pb.w_off), grads_at(pb.b_off),
+                                               S, tb.H * tb.W, tb.C, pb.relu, ps, h->sc<float>(h->L.coef_side), RowCut(), bs);
                             written[(size_t)storage_of(g, pb.x)] = 1;
                             const ConvGeom qj = geom_padded(g, pj, n, h->L.cpad);
-                            launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? G + pj.b_off : nullptr,
-                                                      (int64_t)n * qj.Ho * qj.Wo, pj.K, pj.relu, ps, 0, bs);
+                            launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? grads_at(pj.b_off) : no_grads, S,
+                                                      qj.Ho * qj.Wo, pj.K, pj.relu, ps, RowCut(), bs);
                             // weight gradient: on the first side stream like every other, behind this stream's work
                             hipStream_t ws = bs;
                             if (hipEventRecord(wg, bs) == hipSuccess && hipStreamWaitEvent(h->side, wg, 0) == hipSuccess) {
                                 ws = h->side;
                                 used_side = true;
                             }
-                            launch_conv_wgrad(dt, qj, h->act(pj.x), h->grad(pj.y), G + pj.w_off,
+                            launch_conv_wgrad(dt, qj, S, h->act(pj.x), h->grad(pj.y), grads_at(pj.w_off),
                                               ws == h->side ? h->sc<float>(h->L.wgrad_scratch) : nullptr,
                                               ws == h->side ? (size_t)h->L.wgrad_scratch_bytes : 0, ws);
                             // input gradient, with this stream's own split-reduction scratch; nothing to hand over (the
                             // block's first convolution is the last to add to this gradient)
-                            launch_conv_dgrad(dt, qj, h->grad(pj.y), h->arena + h->L.wT[ii - 2], written[(size_t)pj_sx] != 0,
+                            launch_conv_dgrad(dt, qj, S, h->grad(pj.y), h->arena + h->L.wT[ii - 2], written[(size_t)pj_sx] != 0,
                                               h->grad(pj.x), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, nullptr, bs);
                             written[(size_t)pj_sx] = 1;
                             (void)hipEventRecord(dn, bs);
@@ -1054,6 +1111,11 @@ static void backward_shard(edl_handle* h, int n, float* G, size_t op_lo = 0, siz
         (void)hipEventRecord(h->ev_upd_done, h->upd);
         (void)hipStreamWaitEvent(st, h->ev_upd_done, 0);
     }
+}
+
+// how many of p equal shards of n samples one pass runs together
+static int shards_per_pass(const edl_handle* h, int64_t n, int p) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(p, std::min<int64_t>(h->L.pass_shards, h->L.pass_samples / n)));
 }
 
 static int check_p(const edl_handle* h, int32_t p) {
@@ -1128,14 +1190,22 @@ int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_
     int last_k = -1;
     for (int k = 0; k < p; ++k)
         if (sizes[k] > 0) last_k = k;
-    for (int k = 0; k < p; ++k) {
-        const int64_t nk = sizes[k];
-        if (nk > 0) {
-            forward_shard(h, dev_idx + at, (int)nk, dev_losses + k, first);
-            backward_shard(h, (int)nk, h->grad_buf(k), 0, (size_t)-1, k == last_k ? h->early_p : 0);
-            first = false;
+    // consecutive shards in passes of as many as the workspace holds
+    for (int k = 0; k <= last_k;) {
+        ShardSet S = {};
+        S.plan = equal ? shards_per_pass(h, sizes[0], p) * (int)sizes[0] : 0;
+        for (; k <= last_k; ++k) {
+            if (sizes[k] == 0) continue;
+            if (S.p > 0 && (S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
+            S.k[S.p] = k;
+            S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
+            S.p += 1;
         }
-        at += nk;
+        if (!equal) S.plan = S.samples();
+        forward_pass(h, S, dev_idx + at, dev_losses, first);
+        backward_pass(h, S, 0, (size_t)-1, k > last_k ? h->early_p : 0);
+        first = false;
+        at += S.samples();
     }
     HIP_TRY(hipGetLastError());
     if (out_loss) {
@@ -1435,6 +1505,16 @@ int32_t edl_debug_tensor_shape(const edl_handle* h, int32_t t, int32_t* H, int32
     return EDL_OK;
 }
 
+// one shard of n samples, computed as in a step of such shards
+static ShardSet one_shard(const edl_handle* h, int n, int k) {
+    ShardSet S = {};
+    S.p = 1;
+    S.off[1] = n;
+    S.plan = h->cfg.B % n == 0 && h->cfg.B / n <= h->cfg.p_max ? n * shards_per_pass(h, n, (int)(h->cfg.B / n)) : n;
+    S.k[0] = k;
+    return S;
+}
+
 static int debug_prepare(edl_handle* h, int32_t n) {
     if (!h) { set_error("null handle"); return EDL_EINVAL; }
     if (n <= 0 || n > h->cfg.max_shard || n > h->cfg.B) { set_error("n=%d outside [1, max_shard]", n); return EDL_EINVAL; }
@@ -1452,7 +1532,7 @@ int32_t edl_debug_forward(edl_handle* h, const int64_t* idx, int32_t n) {
     HIP_TRY(hipStreamSynchronize(h->st));
     memcpy(h->idx_host[0], idx, sizeof(int64_t) * (size_t)n);
     HIP_TRY(hipMemcpyAsync(h->at<int64_t>(h->L.idx), h->idx_host[0], sizeof(int64_t) * (size_t)n, hipMemcpyHostToDevice, h->st));
-    forward_shard(h, h->at<int64_t>(h->L.idx), n, h->at<float>(h->L.losses), false);
+    forward_pass(h, one_shard(h, n, 0), h->at<int64_t>(h->L.idx), h->at<float>(h->L.losses), false);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -1464,8 +1544,8 @@ int32_t edl_debug_backward(edl_handle* h, int32_t n, int32_t k) {
     if (k < 0 || k >= h->cfg.p_max) { set_error("gradient buffer %d outside [0,p_max)", k); return EDL_EINVAL; }
     const Graph& g = h->g;
     launch_softmax_ce(h->cfg.dtype, (const float*)h->act(g.logits), h->at<int32_t>(h->L.labels), h->grad(g.logits),
-                      h->sc<float>(h->L.row_loss), h->at<float>(h->L.losses), n, g.classes, h->st);
-    backward_shard(h, n, h->grad_buf(k));
+                      h->sc<float>(h->L.row_loss), h->at<float>(h->L.losses), one_shard(h, n, 0), g.classes, h->st);
+    backward_pass(h, one_shard(h, n, k));
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -1481,7 +1561,7 @@ int32_t edl_debug_forward_op(edl_handle* h, int32_t op, int32_t n) {
     int rc = debug_prepare(h, n);
     if (rc) return rc;
     if (op < 0 || (size_t)op >= h->g.ops.size()) { set_error("layer %d out of range", op); return EDL_ERANGE; }
-    forward_shard(h, nullptr, n, h->at<float>(h->L.losses), false, (size_t)op, (size_t)op + 1);
+    forward_pass(h, one_shard(h, n, 0), nullptr, h->at<float>(h->L.losses), false, (size_t)op, (size_t)op + 1);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -1491,7 +1571,7 @@ int32_t edl_debug_forward_range(edl_handle* h, int32_t op_lo, int32_t op_hi, int
     int rc = debug_prepare(h, n);
     if (rc) return rc;
     if (op_lo < 0 || op_hi < op_lo || (size_t)op_hi > h->g.ops.size()) { set_error("layers [%d, %d) out of range", op_lo, op_hi); return EDL_ERANGE; }
-    forward_shard(h, nullptr, n, h->at<float>(h->L.losses), false, (size_t)op_lo, (size_t)op_hi);
+    forward_pass(h, one_shard(h, n, 0), nullptr, h->at<float>(h->L.losses), false, (size_t)op_lo, (size_t)op_hi);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -1502,7 +1582,7 @@ int32_t edl_debug_backward_op(edl_handle* h, int32_t op, int32_t n, int32_t k) {
     if (rc) return rc;
     if (op < 0 || (size_t)op >= h->g.ops.size()) { set_error("layer %d out of range", op); return EDL_ERANGE; }
     if (k < 0 || k >= h->cfg.p_max) { set_error("gradient buffer %d outside [0,p_max)", k); return EDL_EINVAL; }
-    backward_shard(h, n, h->grad_buf(k), (size_t)op, (size_t)op + 1);
+    backward_pass(h, one_shard(h, n, k), (size_t)op, (size_t)op + 1);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -1524,7 +1604,7 @@ int32_t edl_debug_backward_range_from(edl_handle* h, int32_t op_lo, int32_t op_h
         if (held[i] <= 0 || (size_t)held[i] >= h->g.tensors.size()) { set_error("held tensor %d out of range", held[i]); return EDL_ERANGE; }
         hv.push_back(held[i]);
     }
-    backward_shard(h, n, h->grad_buf(k), (size_t)op_lo, (size_t)op_hi, 0, &hv);
+    backward_pass(h, one_shard(h, n, k), (size_t)op_lo, (size_t)op_hi, 0, &hv);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;

@@ -92,8 +92,8 @@ struct ConvArgs {
     // from where it already lies instead of from a copy.
     const void* acc_src;
     // fwd, vector path, whole reduction: if not null, the column sums of the stored output and of its
-    // squares over this tile's rows go to stats[c * kRedRowBlocks + row tile] and
-    // stats[(Nn + c) * kRedRowBlocks + row tile] (the layout of the batch-norm reduction's partial sums)
+    // squares over this tile's rows go to stats[c * row tiles + row tile] and
+    // stats[(Nn + c) * row tiles + row tile] (the layout of the batch-norm reduction's partial sums)
     float* stats;
     // dgrad, vector path, whole reduction, stride 1, not accumulating: the layer that produced this
     // convolution's input ends in a ReLU, and its backward starts with "gradient times (activation > 0)"
@@ -103,7 +103,7 @@ struct ConvArgs {
     // if xin (the producing batch norm's input) and mean_rstd ([mean[Nn], rstd[Nn]]) are given, else unused.
     const void* mask_act;
     const void* xin;
-    const float* mean_rstd;
+    const float* mean_rstd;     // of shard s at 2 * Nn * s
     float* msum;
     // ceil(2^40 / d) for d = channels per tap and d = taps per kernel row: n / d == (n * magic) >> 40
     // for n * d < 2^40, which keeps the tap bookkeeping of the load loop free of branches
@@ -112,14 +112,28 @@ struct ConvArgs {
     // (output pixels in the forward pass, the residue class's input pixels in dgrad), and for the tile grid
     unsigned long long magic_hw, magic_w, magic_gx, magic_gy;
     int stride_shift;                  // dgrad vector path: log2 of the stride (a power of two there)
-    int red_stride;                    // floats between the partial column sums of consecutive channels
     // Tile grid (gx row tiles, gy column tiles, gz cuts of the reduction), launched
     // as gx*gy*gz workgroups in one dimension.  The hardware hands consecutive
     // workgroups to the eight dies in turn and each die has its own L2, so with
     // xcd_chunked the kernel gives every die one contiguous run of the tile
     // sequence; n_fastest chooses which operand the neighbours of a run share.
     int gx, gy, gz, xcd_chunked, n_fastest;
+    // Several workers' shards in one launch (shards = cut.p > 1).  Forward / dgrad: the row tiles stay within a shard (tile_x
+    // runs over the blocks of the cut), so that the epilogue's column sums are those of one shard; without sums the
+    // rows are cut without regard to shards (cut.p == 1).  wgrad: the reduction (pixels) is cut per shard, splits
+    // pieces each (tile_z = shard * splits + piece); piece z of the sum goes to out + z * zstride floats, or with
+    // one piece per shard straight to the shard's gradient (zdirect: out + worker * zstride).
+    int shards, splits, zdirect;
+    long long zstride;
 };
+
+// The tables of a launch over several shards.  One shard takes kernels without them: the table look-ups (and the
+// argument loads that they keep from being hoisted) cost 0.3 to 0.9 us per launch, 2% of a ResNet-50 step at a shard
+// of 32.
+struct ConvArgsShards : ConvArgs { RowCut cut; };
+template <bool SHARDS> struct ArgsOf { typedef ConvArgs type; };
+template <> struct ArgsOf<true> { typedef ConvArgsShards type; };
+
 
 __device__ __forceinline__ int fast_div(int n, unsigned long long magic) {
     return (int)(((unsigned long long)(unsigned)n * magic) >> 40);
@@ -240,9 +254,9 @@ struct RowCtx {
 };
 
 template <int MODE, bool FAST>
-__device__ __forceinline__ RowCtx make_row(const ConvArgs& a, int m) {
+__device__ __forceinline__ RowCtx make_row(const ConvArgs& a, int m, int m_end) {
     RowCtx c;
-    c.valid = m < a.M;
+    c.valid = m < m_end;
     if (MODE == CONV_FWD) {
         const int hw = a.Ho * a.Wo;
         const int n = FAST ? fast_div(m, a.magic_hw) : m / hw, rem = m - n * hw;
@@ -342,8 +356,8 @@ __device__ __forceinline__ int64_t out_row(const ConvArgs& a, int row) {
 // multiple of a vector, so the kernel has no element-wise paths at all (a
 // run-time choice between the two inside the loop would force a wait after
 // every load).
-template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF>
-__global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // at least two waves per SIMD: 256 registers
+template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, bool SHARDS>
+__global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<SHARDS>::type a) {   // at least two waves per SIMD: 256 registers
     constexpr bool WG = MODE == CONV_WGRAD;
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr int VEC = Elem<T>::VEC;
@@ -395,10 +409,23 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
     const int wm = wave / WN, wn = wave % WN;
     int tile_x, tile_y, tile_z;
     tile_of_block(a, tile_x, tile_y, tile_z);
-    const int m0 = tile_x * BM, n0 = tile_y * BN;
-    const int kbeg = tile_z * a.ksplit;
-    int kend = kbeg + a.ksplit;
-    if (kend > a.Kred) kend = a.Kred;
+    const int n0 = tile_y * BN;
+    int m0 = tile_x * BM, m_end = a.M;       // rows [m0, m_end) of the output
+    int kbeg = tile_z * a.ksplit, kend = kbeg + a.ksplit;
+    int shard = 0;
+    if (!WG) {
+        if constexpr (SHARDS) shard = locate_block(a.cut, tile_x, m0, m_end);
+        if (kend > a.Kred) kend = a.Kred;
+    } else {
+        int last = a.Kred;
+        if constexpr (SHARDS) {
+            shard = tile_z / a.splits;
+            kbeg = a.cut.row0[shard] + (tile_z - shard * a.splits) * a.ksplit;
+            kend = kbeg + a.ksplit;
+            last = a.cut.row0[shard + 1];
+        }
+        if (kend > last) kend = last;        // a short shard's last pieces may be empty: they store zeros
+    }
     const int nk = (kend - kbeg + BK - 1) / BK;
 
     Vec16<T> ra[PF][NRA], rb[PF][NRB];   // PF register sets: the loads of the next PF tiles are in flight
@@ -441,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
             tap_off = (tr * a.S + ts) * a.K + tc;      // position inside a row of the transposed weights
         }
         #pragma unroll
-        for (int it = 0; it < ITER_A; ++it) rowA[it] = make_row<MODE, FAST>(a, m0 + (tid + it * 256) / KV);
+        for (int it = 0; it < ITER_A; ++it) rowA[it] = make_row<MODE, FAST>(a, m0 + (tid + it * 256) / KV, m_end);
         #pragma unroll
         for (int it = 0; it < ITER_B; ++it) {
             const int j = n0 + (tid + it * 256) / KV;
@@ -864,6 +891,12 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
     constexpr bool OUT_F32 = WG || sizeof(T) == 4;       // element type of the vector-path output
     constexpr int OSZ = OUT_F32 ? 4 : 2;
     constexpr int OVEC = 16 / OSZ;
+    int64_t zoff = 0;   // floats
+    if (WG) {
+        int z = tile_z;
+        if constexpr (SHARDS) z = a.zdirect ? a.cut.k[shard] : tile_z;
+        zoff = (int64_t)z * a.zstride;
+    }
     if (!FAST) {
         // ragged width (or float32 logits from a bf16 net): element-wise stores
         #pragma unroll
@@ -876,7 +909,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
                 #pragma unroll
                 for (int q = 0; q < 16; ++q) {
                     const int row = m0 + (wm * TM + i) * 32 + (q >> 2) * 8 + (lane >> 5) * 4 + (q & 3);
-                    if (row >= a.M) continue;
+                    if (row >= m_end) continue;
                     float v = acc[i][j][q];
                     if (MODE == CONV_FWD) {
                         v += bias;
@@ -890,7 +923,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
                         if (a.accumulate) v += Elem<T>::to_f32(a.acc_src ? ((const T*)a.acc_src)[o] : dst[o]);
                         dst[o] = Elem<T>::from_f32(v);
                     } else {
-                        ((float*)a.out)[((int64_t)tile_z * a.M + row) * a.Nn + col] = v;
+                        ((float*)a.out)[zoff + (int64_t)row * a.Nn + col] = v;
                     }
                 }
             }
@@ -900,7 +933,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
     // staged: one wave row at a time goes through LDS as float32 (one word per
     // lane and row, conflict-free), then leaves as 16-byte vectors along the output row
     float* const stage = reinterpret_cast<float*>(smem);
-    unsigned char* const outp = (unsigned char*)a.out + (WG ? (int64_t)tile_z * a.M * a.Nn * 4 : 0);
+    unsigned char* const outp = (unsigned char*)a.out + zoff * 4;
     const unsigned char* const accp = (MODE == CONV_DGRAD && a.acc_src != nullptr) ? (const unsigned char*)a.acc_src : outp;
     const bool to_partial = !WG && a.partial != nullptr;     // cut reduction: raw float32 sums, finished by another kernel
     const bool f32_out = (MODE == CONV_FWD) && a.out_fp32 && !OUT_F32;
@@ -920,9 +953,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
     for (int e = 0; e < OVEC; ++e) { mu[e] = 0.f; rs[e] = 0.f; }
     if (with_xhat) {
         const int c0 = n0 + (tid % CV) * OVEC;
+        const float* const ms = a.mean_rstd + (SHARDS ? (int64_t)shard * 2 * a.Nn : 0);
         #pragma unroll
         for (int e = 0; e < OVEC; ++e)
-            if (c0 + e < a.Nn) { mu[e] = a.mean_rstd[c0 + e]; rs[e] = a.mean_rstd[a.Nn + c0 + e]; }
+            if (c0 + e < a.Nn) { mu[e] = ms[c0 + e]; rs[e] = ms[a.Nn + c0 + e]; }
     }
     #pragma unroll
     for (int pass = 0; pass < WM; ++pass) {
@@ -935,7 +969,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
             for (int k = 0; k < NV; ++k) {
                 const int v = tid + k * 256, rl = v / CV, cv = v - rl * CV;
                 const int row = m0 + pass * STAGE_ROWS + rl, col = n0 + cv * OVEC;
-                const bool inside = v < STAGE_ROWS * CV && row < a.M && col < a.Nn;
+                const bool inside = v < STAGE_ROWS * CV && row < m_end && col < a.Nn;
                 const unsigned char* src = inside ? accp + (out_row<MODE, true>(a, row) * a.Nn + col) * OSZ : accp;
                 oldv[k] = *reinterpret_cast<const uint4*>(src);
             }
@@ -947,7 +981,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
             for (int k = 0; k < NV; ++k) {
                 const int v = tid + k * 256, rl = v / CV, cv = v - rl * CV;
                 const int row = m0 + pass * STAGE_ROWS + rl, col = n0 + cv * OVEC;
-                const bool inside = v < STAGE_ROWS * CV && row < a.M && col < a.Nn;
+                const bool inside = v < STAGE_ROWS * CV && row < m_end && col < a.Nn;
                 const int64_t at = inside ? ((int64_t)row * a.Nn + col) * OSZ : 0;
                 actv[k] = *reinterpret_cast<const uint4*>((const unsigned char*)a.mask_act + at);
                 if (with_xhat) xinv[k] = *reinterpret_cast<const uint4*>((const unsigned char*)a.xin + at);
@@ -981,7 +1015,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
             if (v >= STAGE_ROWS * CV) break;
             const int rl = v / CV, cv = v - rl * CV;
             const int row = m0 + pass * STAGE_ROWS + rl, col = n0 + cv * OVEC;
-            if (row < a.M && col < a.Nn) {
+            if (row < m_end && col < a.Nn) {
                 const float* sp = stage + rl * STAGE_LD + cv * OVEC;
                 if (to_partial || f32_out) {
                     float* d = to_partial ? a.partial + ((int64_t)tile_z * a.M + row) * a.Nn + col
@@ -1083,17 +1117,19 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(ConvArgs a) {   // a
             float s1 = 0.f, s2 = 0.f;
             #pragma unroll 8
             for (int gq = 0; gq < GROUPS; ++gq) { s1 += red[gq * BN + c]; s2 += red[(GROUPS + gq) * BN + c]; }
-            sums[(int64_t)(n0 + c) * a.red_stride + tile_x] = s1;
-            sums[(int64_t)(a.Nn + n0 + c) * a.red_stride + tile_x] = s2;
+            sums[(int64_t)(n0 + c) * a.gx + tile_x] = s1;
+            sums[(int64_t)(a.Nn + n0 + c) * a.gx + tile_x] = s2;
         }
     }
 }
 
-// dw[i] = sum over splits, in split order.  One 16-byte vector per lane and
-// split (the splits' loads are independent, so they are all in flight together).
+// dw[i] = sum over a shard's splits, in split order.  One 16-byte vector per lane and
+// split (the splits' loads are independent, so they are all in flight together).  grid: (elements, shards)
 template <int VECW>
-__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw, int64_t n,
-                                                           int splits) {
+__global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw, int64_t dw_stride,
+                                                           ShardSet S, int64_t n, int splits) {
+    part += (int64_t)blockIdx.y * splits * n;
+    dw += (int64_t)S.k[blockIdx.y] * dw_stride;
     const int64_t nv = n / VECW;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nv; i += stride) {
@@ -1129,18 +1165,17 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 template <typename T, bool MASKED>
 __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ part, void* out, const float* __restrict__ bias,
                                                             int64_t M, int Nn, int splits, int relu, int out_fp32, int accumulate,
-                                                            int rows_per_block, float* __restrict__ stats,
+                                                            RowCut cut, float* __restrict__ stats,
                                                             const T* __restrict__ mask_act, const T* __restrict__ xin,
                                                             const float* __restrict__ mean_rstd, const void* acc_src) {
     if (acc_src == nullptr) acc_src = out;      // where the gradient that is added to is read (see ConvArgs)
-    // a workgroup owns 64 columns of rows_per_block rows: 16 lanes across (4 columns each), 16 rows at a time
+    // a workgroup owns 64 columns of one block of rows: 16 lanes across (4 columns each), 16 rows at a time
+    int r0, r1;
+    const int shard = locate_block(cut, blockIdx.y, r0, r1);
     const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
     const int col = (blockIdx.x * 16 + tx) * 4;
     const bool active = col < Nn;
     const int64_t mn = M * Nn;
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
-    int64_t r1 = r0 + rows_per_block;
-    if (r1 > M) r1 = M;
     float4 bv = make_float4(0.f, 0.f, 0.f, 0.f);
     if (bias && active) bv = *reinterpret_cast<const float4*>(bias + col);
     float cs[4] = {0.f, 0.f, 0.f, 0.f}, cq[4] = {0.f, 0.f, 0.f, 0.f};
@@ -1149,7 +1184,10 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
     float mu[4] = {0.f, 0.f, 0.f, 0.f}, rs[4] = {0.f, 0.f, 0.f, 0.f};
     if (MASKED && xin != nullptr && active) {
         #pragma unroll
-        for (int e = 0; e < 4; ++e) { mu[e] = mean_rstd[col + e]; rs[e] = mean_rstd[Nn + col + e]; }
+        for (int e = 0; e < 4; ++e) {
+            mu[e] = mean_rstd[(int64_t)shard * 2 * Nn + col + e];
+            rs[e] = mean_rstd[(int64_t)shard * 2 * Nn + Nn + col + e];
+        }
     }
     if (active) {
         for (int64_t r = r0 + ty; r < r1; r += 16) {
@@ -1231,7 +1269,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
             float t = 0.f;
             #pragma unroll
             for (int j = 0; j < 16; ++j) t += red[kind][j][c];
-            stats[(int64_t)(kind * Nn + cg) * kRedRowBlocks + blockIdx.y] = t;
+            stats[(int64_t)(kind * Nn + cg) * gridDim.y + blockIdx.y] = t;
         }
     }
 }
@@ -1314,10 +1352,10 @@ static bool magic_fits(double n_max, int d) {
     return n_max * (double)d < 1.0e12 && n_max * (double)magic_of(d) < 9.0e18;
 }
 
-template <typename T, int MODE>
-static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const ConvArgs& a_in, hipStream_t st) {
+template <typename T, int MODE, bool SHARDS>
+static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<SHARDS>::type& a_in, hipStream_t st) {
     constexpr int BK = kConvBK<T>;
-    ConvArgs a = a_in;
+    typename ArgsOf<SHARDS>::type a = a_in;
     a.gx = (int)tiles.x; a.gy = (int)tiles.y; a.gz = (int)tiles.z;
     const double total = (double)a.gx * a.gy * a.gz;
     const bool mg = magic_fits(total, a.gx) && magic_fits(total, a.gy);
@@ -1339,7 +1377,7 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const ConvArgs& a_in, h
     constexpr int PF_DEEP = MODE == CONV_WGRAD ? EDL_PF_WG_DEEP : PF_BIG;
     const bool deep = MODE == CONV_WGRAD && total <= (double)tune().wgrad_deep_max;
     if (!fast) {   // element-wise kernel: one tile shape only
-        hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, false, 1>), grid, dim3(256), 0, st, a);
+        hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, false, 1, SHARDS>), grid, dim3(256), 0, st, a);
         return;
     }
     switch (t) {
@@ -1350,26 +1388,26 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const ConvArgs& a_in, h
             const int full_steps_from = (int)tune().bk64_kred;
             if constexpr (MODE == CONV_WGRAD && sizeof(T) == 2) {
                 if (deep) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_DEEP>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_DEEP, SHARDS>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
             if (BK_BIG != BK && a.Kred >= full_steps_from)
-                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_BIG>), grid, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_BIG, SHARDS>), grid, dim3(256), 0, st, a);
             else
-                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK_BIG, true, PF_HALF>), grid, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK_BIG, true, PF_HALF, SHARDS>), grid, dim3(256), 0, st, a);
             break;
         }
         case T128x64:
             if constexpr (MODE == CONV_WGRAD && sizeof(T) == 2) {
                 if (deep) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK, true, PF_DEEP>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK, true, PF_DEEP, SHARDS>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
-            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK_BIG, true, PF_HALF>), grid, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK_BIG, true, PF_HALF, SHARDS>), grid, dim3(256), 0, st, a);
             break;
-        case T128x32: hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, PF_BIG>), grid, dim3(256), 0, st, a); break;
+        case T128x32: hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, PF_BIG, SHARDS>), grid, dim3(256), 0, st, a); break;
         default:
             if constexpr (MODE != CONV_WGRAD && sizeof(T) == 2) {
                 // Three stages of a 64x64 tile are 48 KB of LDS: three workgroups per CU, 768 on the chip.  A launch
@@ -1379,11 +1417,11 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const ConvArgs& a_in, h
                 // 22.1 -> 18.2 us and 25.9 -> 22.2 us for the 3x3 layers at 28x28, 0.490 -> 0.422 ms per ResNet-50
                 // step over all launches of that size.
                 if (total > (double)tune().small_tail_from && total <= (double)tune().small_tail_to) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, EDL_PF_SMALL_TAIL>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, EDL_PF_SMALL_TAIL, SHARDS>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
-            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, PF_SMALL>), grid, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, PF_SMALL, SHARDS>), grid, dim3(256), 0, st, a);
             break;
     }
 }
@@ -1416,8 +1454,9 @@ static bool conv_magic_ok(int mode, const ConvArgs& a) {
 }
 
 template <int MODE>
-static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgs& a_in, hipStream_t st) {
-    ConvArgs a = a_in;
+static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a_in, hipStream_t st) {
+    ConvArgsShards a = a_in;
+    a.shards = a.cut.p;
     if (MODE == CONV_FWD) { a.magic_inner = magic_of(a.C); a.magic_taps = magic_of(a.S); }
     else if (MODE == CONV_DGRAD) { a.magic_inner = magic_of(a.K); a.magic_taps = magic_of(a.ns); }
     if (MODE == CONV_FWD) { a.magic_hw = magic_of(a.Ho * a.Wo); a.magic_w = magic_of(a.Wo); }
@@ -1462,63 +1501,41 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgs& a_in, h
         label = found;
     }
     ProfScope ps(label, flops, bytes, st);
-    if (dtype == 1) launch_cfg<bf16_t, MODE>(t, fast, grid, a, st);
-    else launch_cfg<float, MODE>(t, fast, grid, a, st);
+    if (a.shards > 1) {
+        if (dtype == 1) launch_cfg<bf16_t, MODE, true>(t, fast, grid, a, st);
+        else launch_cfg<float, MODE, true>(t, fast, grid, a, st);
+    } else {
+        if (dtype == 1) launch_cfg<bf16_t, MODE, false>(t, fast, grid, a, st);
+        else launch_cfg<float, MODE, false>(t, fast, grid, a, st);
+    }
 }
 
-static ConvArgs base_args(const ConvGeom& g) {
-    ConvArgs a = {};
+static ConvArgsShards base_args(const ConvGeom& g) {
+    ConvArgsShards a = {};
     a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.K = g.K; a.R = g.R; a.S = g.S;
     a.stride = g.stride; a.pad = g.pad; a.Ho = g.Ho; a.Wo = g.Wo;
     a.ph = a.pw = a.r0 = a.s0 = 0; a.nr = g.R; a.ns = g.S; a.Hc = g.H; a.Wc = g.W;
-    a.red_stride = kRedRowBlocks;
+    a.cut.p = 1;
     return a;
 }
 
-// Partial column sums of a launch with more row tiles than the reduction scratch has room for:
-// out[r][j] = sum of wide[r][j*group .. (j+1)*group), in order; r = (sum kind, channel).
-__global__ __launch_bounds__(256) void compact_sums_kernel(const float* __restrict__ wide, int tiles, int group, int out_tiles,
-                                                           float* __restrict__ out) {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    const int r = blockIdx.y;
-    if (j >= out_tiles) return;
-    const float* src = wide + (int64_t)r * tiles;
-    int e = (j + 1) * group;
-    if (e > tiles) e = tiles;
-    float s = 0.f;
-    for (int i = j * group; i < e; ++i) s += src[i];
-    out[(int64_t)r * kRedRowBlocks + j] = s;
+size_t conv_sums_floats(const ConvGeom& g, int p) {
+    // the narrowest row tile is 64 rows; the finishing kernel of a cut reduction takes kRedRowBlocks blocks at most
+    const auto blocks = [&](int64_t rows) { return std::max<int64_t>(rows / 64, std::min<int64_t>(rows / 16, kRedRowBlocks)) + 1 + p; };
+    const size_t fwd = (size_t)(2 * g.K * blocks((int64_t)g.N * g.Ho * g.Wo)), dgrad = (size_t)(2 * g.C * blocks((int64_t)g.N * g.H * g.W));
+    return g.stride == 1 ? std::max(fwd, dgrad) : fwd;
 }
 
-// Where an epilogue leaves its column sums: the reduction scratch itself if the row tiles fit it, else the wide
-// buffer (compacted afterwards by finish_sums), else nowhere (nullptr: the separate reduction kernel runs).
-static float* sums_target(float* sums, const WideSums& wide, int row_tiles, int channels, int* stride) {
-    *stride = kRedRowBlocks;
-    if (sums == nullptr || row_tiles <= kRedRowBlocks) return sums;
-    if (wide.buf == nullptr || wide.floats < (size_t)2 * channels * row_tiles) return nullptr;
-    *stride = row_tiles;
-    return wide.buf;
-}
-
-// Returns the number of partial sums per channel now in `sums`.
-static int finish_sums(float* sums, const WideSums& wide, int row_tiles, int channels, hipStream_t st) {
-    if (row_tiles <= kRedRowBlocks) return row_tiles;
-    const int group = (row_tiles + kRedRowBlocks - 1) / kRedRowBlocks;
-    const int out_tiles = (row_tiles + group - 1) / group;
-    ProfScope ps("compact_sums", 0.0, 4.0 * 2.0 * channels * ((double)row_tiles + out_tiles), st);
-    hipLaunchKernelGGL(compact_sums_kernel, dim3((out_tiles + 255) / 256, 2 * channels), dim3(256), 0, st, wide.buf, row_tiles, group,
-                       out_tiles, sums);
-    return out_tiles;
-}
-
-size_t conv_wide_sums_floats(int dtype, const ConvGeom& g) {
-    (void)dtype;
-    // the narrowest row tile is 64 rows
-    const int64_t fwd_tiles = ((int64_t)g.N * g.Ho * g.Wo + 63) / 64, dgrad_tiles = ((int64_t)g.N * g.H * g.W + 63) / 64;
-    size_t need = 0;
-    if (fwd_tiles > kRedRowBlocks) need = std::max(need, (size_t)(2 * fwd_tiles * g.K));
-    if (dgrad_tiles > kRedRowBlocks && g.stride == 1) need = std::max(need, (size_t)(2 * dgrad_tiles * g.C));
-    return need;
+// How a launch's rows are cut into row tiles of bm: within the shards if it is to leave column sums (and the shards
+// are large enough for that not to leave most of a tile idle), else without regard to them.
+static RowCut tile_cut(const ShardSet& S, int rows_per_sample, int bm, bool want_sums, bool* per_shard) {
+    *per_shard = S.samples() == S.plan && S.p == 1;
+    if (want_sums && S.smallest() * rows_per_sample >= bm) *per_shard = true;
+    if (*per_shard) return cut_rows(S, rows_per_sample, bm);
+    ShardSet all = {};
+    all.p = 1;
+    all.off[1] = all.plan = S.samples();
+    return cut_rows(all, rows_per_sample, bm);
 }
 
 // Cut of the reduction for forward / dgrad problems that give too few tiles to
@@ -1544,28 +1561,31 @@ static int plan_splitk(int dtype, int M, int Nn, int Kred, int bm, int bn, int* 
     return (Kred + ks - 1) / ks;
 }
 
-// Returns the number of row blocks whose column sums it left in stats (0 if stats is null).
+// Returns how the column sums it left in stats are cut (p == 0 if stats.buf is null or too small).
 template <typename T>
-static int launch_finish(const ConvArgs& a, int splits, float* stats, hipStream_t st, const DgradMask* mask = nullptr) {
+static RowCut launch_finish(const ConvArgs& a, const ShardSet& S, int rows_per_sample, int splits, SumsBuf stats, hipStream_t st,
+                            const DgradMask* mask = nullptr) {
     const int col_blocks = (a.Nn + 63) / 64;
     // about 1024 workgroups, at least 16 rows each
     int64_t rb = (1024 + col_blocks - 1) / col_blocks;
-    const int64_t max_rb = ((int64_t)a.M + 15) / 16;
+    const int64_t M = (int64_t)S.plan * rows_per_sample;
+    const int64_t max_rb = (M + 15) / 16;
     if (rb > max_rb) rb = max_rb;
     if (rb > kRedRowBlocks) rb = kRedRowBlocks;
     if (rb < 1) rb = 1;
-    const int rows_per_block = (int)(((int64_t)a.M + rb - 1) / rb);
-    const int row_blocks = (int)(((int64_t)a.M + rows_per_block - 1) / rows_per_block);
+    const RowCut cut = cut_rows(S, rows_per_sample, (int)((M + rb - 1) / rb));
+    const int row_blocks = cut.blk0[cut.p];
+    if (stats.buf != nullptr && stats.floats < (size_t)2 * a.Nn * row_blocks) stats.buf = nullptr;   // cannot happen: sized for it
     ProfScope ps("splitk_finish", 0.0, 4.0 * (double)a.M * a.Nn * splits + (a.out_fp32 ? 4.0 : (double)sizeof(T)) * (double)a.M * a.Nn, st);
-    if (mask != nullptr)
+    if (mask != nullptr && stats.buf != nullptr)
         hipLaunchKernelGGL((splitk_finish_kernel<T, true>), dim3(col_blocks, row_blocks), dim3(256), 0, st, a.partial, a.out, a.bias,
-                           (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, rows_per_block, stats,
+                           (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, cut, stats.buf,
                            (const T*)mask->act, (const T*)mask->xin, mask->mean_rstd, a.acc_src);
     else
         hipLaunchKernelGGL((splitk_finish_kernel<T, false>), dim3(col_blocks, row_blocks), dim3(256), 0, st, a.partial, a.out, a.bias,
-                           (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, rows_per_block, stats,
+                           (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, cut, mask != nullptr ? nullptr : stats.buf,
                            (const T*)nullptr, (const T*)nullptr, (const float*)nullptr, a.acc_src);
-    return stats ? row_blocks : 0;
+    return stats.buf ? cut : RowCut();
 }
 
 size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g) {
@@ -1583,10 +1603,10 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g) {
     return need;
 }
 
-int launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu,
-                    bool out_fp32, void* y, float* scratch, size_t scratch_bytes, float* stats, WideSums wide, hipStream_t st) {
+RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
+                       bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st) {
     const int VEC = dtype == 1 ? 8 : 4;
-    ConvArgs a = base_args(g);
+    ConvArgsShards a = base_args(g);
     a.A = x; a.B = w; a.out = y; a.bias = bias;
     a.M = g.N * g.Ho * g.Wo; a.Nn = g.K; a.Kred = g.R * g.S * g.C;
     a.relu = relu; a.out_fp32 = out_fp32;
@@ -1597,33 +1617,34 @@ int launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, 
     a.ksplit = a.Kred;
     a.ldb = a.Kred;
     int bm, bn;
-    const TileCfg t = pick_tile(a.M, a.Nn, a.Kred, &bm, &bn, a.Kred <= 128);
+    const int Mplan = S.plan * g.Ho * g.Wo;
+    const TileCfg t = pick_tile(Mplan, a.Nn, a.Kred, &bm, &bn, a.Kred <= 128);
+    const bool fast = conv_fast(dtype, CONV_FWD, a);
     int splits = 1, ks = a.Kred;
-    if (conv_fast(dtype, CONV_FWD, a)) {
-        splits = plan_splitk(dtype, a.M, a.Nn, a.Kred, bm, bn, &ks);
+    if (fast) {
+        splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks);
         if (splits > 1 && (scratch == nullptr || scratch_bytes < (size_t)splits * a.M * a.Nn * sizeof(float))) splits = 1;
     }
     if (splits > 1) { a.ksplit = ks; a.partial = scratch; }
-    const int row_tiles = (a.M + bm - 1) / bm;
-    const bool tune_stats = tune().fused_stats != 0;
-    const bool want_stats = tune_stats && stats != nullptr && !out_fp32 && conv_fast(dtype, CONV_FWD, a) && conv_magic_ok(CONV_FWD, a);
+    if (tune().fused_stats == 0 || out_fp32 || !fast || !conv_magic_ok(CONV_FWD, a)) stats.buf = nullptr;
     // whole reduction in one workgroup: the epilogue leaves the sums; cut reduction: the finishing kernel does
-    float* const target = (want_stats && splits == 1) ? sums_target(stats, wide, row_tiles, a.Nn, &a.red_stride) : nullptr;
-    const bool fused = target != nullptr;
-    a.stats = target;
+    bool per_shard;
+    a.cut = tile_cut(S, g.Ho * g.Wo, bm, stats.buf != nullptr && splits == 1, &per_shard);
+    const int row_tiles = a.cut.blk0[a.cut.p];
+    if (splits == 1 && per_shard && stats.buf != nullptr && stats.floats >= (size_t)2 * a.Nn * row_tiles) a.stats = stats.buf;
     launch_mode<CONV_FWD>(dtype, t, dim3(row_tiles, (a.Nn + bn - 1) / bn, splits), a, st);
     if (splits > 1) {
-        float* fs = want_stats ? stats : nullptr;
-        return dtype == 1 ? launch_finish<bf16_t>(a, splits, fs, st) : launch_finish<float>(a, splits, fs, st);
+        const int hw = g.Ho * g.Wo;
+        return dtype == 1 ? launch_finish<bf16_t>(a, S, hw, splits, stats, st) : launch_finish<float>(a, S, hw, splits, stats, st);
     }
-    return fused ? finish_sums(stats, wide, row_tiles, a.Nn, st) : 0;
+    return a.stats ? a.cut : RowCut();
 }
 
-int launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dy, const void* wT, bool accumulate, void* dx,
-                      float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src) {
-    int fused_rows = 0;
+RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
+                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src) {
+    RowCut left;
     const int VEC = dtype == 1 ? 8 : 4;
-    ConvArgs a = base_args(g);
+    ConvArgsShards a = base_args(g);
     a.A = dy; a.B = wT; a.out = dx;
     a.Nn = g.C;
     a.ldb = g.R * g.S * g.K;
@@ -1635,6 +1656,7 @@ int launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dy, const void* 
     const bool stride_pow2 = g.stride == 1 || g.stride == 2 || g.stride == 4;
     a.vecA = (g.K % VEC == 0) && bA < 2147483648.0 && stride_pow2; a.vecB = (a.ldb % VEC == 0) && bB < 2147483648.0;
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
+    const bool want_mask = tune().fused_mask != 0 && mask != nullptr && mask->act != nullptr && g.stride == 1;
     // one launch per residue class of the input pixel modulo the stride
     for (int ph = 0; ph < g.stride && ph < g.H; ++ph) {
         for (int pw = 0; pw < g.stride && pw < g.W; ++pw) {
@@ -1654,42 +1676,40 @@ int launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dy, const void* 
             // an epilogue that adds to the gradient already there, masks and sums it reads three more tensors
             // than it writes: 128x64 tiles (twice the workgroups, half the vectors in flight per lane; measured
             // -0.4% of the ResNet-50 step, 64x64 tiles +1.5%)
-            const int join_tile = (int)tune().join_tile;
-            const bool heavy = join_tile != 0 && mask != nullptr && mask->act != nullptr && accumulate && g.stride == 1;
-            const TileCfg t = pick_tile(a.M, a.Nn, a.Kred, &bm, &bn, heavy);
+            const bool heavy = tune().join_tile != 0 && mask != nullptr && mask->act != nullptr && accumulate && g.stride == 1;
+            const int Mplan = S.plan * a.Hc * a.Wc;
+            const TileCfg t = pick_tile(Mplan, a.Nn, a.Kred, &bm, &bn, heavy);
+            const bool fast = conv_fast(dtype, CONV_DGRAD, a);
             int splits = 1, ks = a.ksplit;
-            if (g.stride == 1 && conv_fast(dtype, CONV_DGRAD, a)) {
-                splits = plan_splitk(dtype, a.M, a.Nn, a.Kred, bm, bn, &ks);
+            if (g.stride == 1 && fast) {
+                splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks);
                 if (splits > 1 && (scratch == nullptr || scratch_bytes < (size_t)splits * a.M * a.Nn * sizeof(float))) splits = 1;
             }
             if (splits > 1) { a.ksplit = ks; a.partial = scratch; }
-            const int row_tiles = (a.M + bm - 1) / bm;
             // masked store and column sums in the epilogue: one launch that covers every pixel and leaves the
             // final gradient (it may add to what other readers of the tensor have left there)
-            const bool tune_mask = tune().fused_mask != 0;
-            float* target = nullptr;
-            if (tune_mask && mask != nullptr && mask->act != nullptr && g.stride == 1 && splits == 1 &&
-                conv_fast(dtype, CONV_DGRAD, a) && conv_magic_ok(CONV_DGRAD, a))
-                target = sums_target(mask->sums, mask->wide, row_tiles, a.Nn, &a.red_stride);
-            const bool fuse = target != nullptr;
+            const bool want = want_mask && splits == 1 && fast && conv_magic_ok(CONV_DGRAD, a);
+            bool per_shard;
+            a.cut = tile_cut(S, a.Hc * a.Wc, bm, want, &per_shard);
+            const int row_tiles = a.cut.blk0[a.cut.p];
+            const bool fuse = want && per_shard && mask->sums.floats >= (size_t)2 * a.Nn * row_tiles;
             a.mask_act = fuse ? mask->act : nullptr;
             a.xin = fuse ? mask->xin : nullptr;
             a.mean_rstd = fuse ? mask->mean_rstd : nullptr;
-            a.msum = target;
+            a.msum = fuse ? mask->sums.buf : nullptr;
             launch_mode<CONV_DGRAD>(dtype, t, dim3(row_tiles, (a.Nn + bn - 1) / bn, splits), a, st);
-            if (fuse) fused_rows = finish_sums(mask->sums, mask->wide, row_tiles, a.Nn, st);
+            if (fuse) left = a.cut;
             if (splits > 1) {
                 // a cut reduction: the finishing kernel masks and sums instead of the epilogue
-                const bool tune_cut = tune().fused_mask_cut != 0;
-                const bool cut_mask = tune_cut && tune_mask && mask != nullptr && mask->act != nullptr && mask->sums != nullptr &&
-                                      g.stride == 1 && a.Nn % 4 == 0;
+                const bool cut_mask = tune().fused_mask_cut != 0 && want_mask && mask->sums.buf != nullptr && a.Nn % 4 == 0;
                 const DgradMask* fm = cut_mask ? mask : nullptr;
-                float* fs = cut_mask ? mask->sums : nullptr;
-                fused_rows = dtype == 1 ? launch_finish<bf16_t>(a, splits, fs, st, fm) : launch_finish<float>(a, splits, fs, st, fm);
+                const SumsBuf fs = cut_mask ? mask->sums : SumsBuf{nullptr, 0};
+                const int hw = g.H * g.W;
+                left = dtype == 1 ? launch_finish<bf16_t>(a, S, hw, splits, fs, st, fm) : launch_finish<float>(a, S, hw, splits, fs, st, fm);
             }
         }
     }
-    return fused_rows;
+    return left;
 }
 
 struct WgradPlan {
@@ -1702,7 +1722,9 @@ struct WgradPlan {
 // reduction (the pixels) long, so parallelism comes from cutting the reduction;
 // every split costs a float32 partial tile that is written and read again, so
 // layers whose output already gives enough tiles are split little or not at all.
-static WgradPlan plan_wgrad(const ConvGeom& g) {
+// g.N: samples of the largest shard.  shards: how many of them the launch covers; they are as good as cuts for filling
+// the chip and cost no partial tiles (one cut per shard: straight into the worker's gradient).
+static WgradPlan plan_wgrad(const ConvGeom& g, int shards) {
     WgradPlan p;
     const int M = g.K, Nn = g.R * g.S * g.C, Kred = g.N * g.Ho * g.Wo;
     const int64_t t128 = (int64_t)((M + 127) / 128) * ((Nn + 127) / 128);
@@ -1724,14 +1746,15 @@ static WgradPlan plan_wgrad(const ConvGeom& g) {
     // the chip 3% slower per step, beside the main stream 1.4% faster; ResNet-152 1.8%; below 96 the second
     // stream becomes the longer one).
     const int target = (int)tune().wgrad_blocks;
-    int64_t splits = (target + p.tiles - 1) / p.tiles;
+    const int64_t tiles = p.tiles * shards;
+    int64_t splits = (target + tiles - 1) / tiles;
     // A long reduction (VGG-16's layers on large images at a shard of 32) is cut into two workgroups per CU
     // (all that are resident at once), as long as each cut keeps long_ks elements: the partial results are
     // small beside the operands there, and a second workgroup hides the operand latency that one per CU
     // leaves exposed.  Measured on VGG-16: 5.28 -> 5.14 ms per step; three per CU (a second, ragged round
     // of workgroups) is slower again.
     const int long_target = (int)tune().wgrad_long_blocks, long_ks = (int)tune().wgrad_long_ks;
-    const int64_t more = std::min<int64_t>(long_target / p.tiles, Kred / (long_ks > 0 ? long_ks : 1));
+    const int64_t more = std::min<int64_t>(long_target / tiles, Kred / (long_ks > 0 ? long_ks : 1));
     if (more > splits) splits = more;
     const int64_t max_splits = (Kred + 255) / 256;  // at least 4 reduction steps per split
     if (splits > max_splits) splits = max_splits;
@@ -1743,46 +1766,48 @@ static WgradPlan plan_wgrad(const ConvGeom& g) {
     return p;
 }
 
-size_t conv_wgrad_scratch_bytes(const ConvGeom& g) {
-    const WgradPlan p = plan_wgrad(g);
+size_t conv_wgrad_scratch_bytes(const ConvGeom& g, int shards) {
+    const WgradPlan p = plan_wgrad(g, shards);
     if (p.splits <= 1) return 0;
-    return (size_t)p.splits * g.K * g.R * g.S * g.C * sizeof(float);
+    return (size_t)shards * p.splits * g.K * g.R * g.S * g.C * sizeof(float);
 }
 
-void launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw, float* scratch,
+void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st) {
     const int VEC = dtype == 1 ? 8 : 4;
-    const WgradPlan p = plan_wgrad(g);
-    ConvArgs a = base_args(g);
+    ConvGeom one = g;
+    one.N = S.largest();
+    WgradPlan p = plan_wgrad(one, S.p);
+    ConvArgsShards a = base_args(g);
     a.A = dy; a.B = x;
     a.M = g.K; a.Nn = g.R * g.S * g.C; a.Kred = g.N * g.Ho * g.Wo;
     const double esz = dtype == 1 ? 2.0 : 4.0;
     const double bA = esz * (double)a.Kred * g.K, bB = esz * (double)g.N * g.H * g.W * g.C;
     a.vecA = (g.K % VEC == 0) && bA < 2147483648.0; a.vecB = (g.C % VEC == 0) && bB < 2147483648.0;
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
-    a.ksplit = p.ksplit;
     const int64_t n = (int64_t)a.M * a.Nn;
-    const bool direct = p.splits <= 1 || scratch == nullptr || scratch_bytes < (size_t)p.splits * n * sizeof(float);
+    const bool direct = p.splits <= 1 || scratch == nullptr || scratch_bytes < (size_t)S.p * p.splits * n * sizeof(float);
     if (direct) {
-        a.ksplit = a.Kred;
-        a.out = dw;
-    } else {
-        a.out = scratch;
+        p.splits = 1;
+        p.ksplit = one.N * g.Ho * g.Wo;
     }
-    const dim3 grid((a.M + p.bm - 1) / p.bm, (a.Nn + p.bn - 1) / p.bn, direct ? 1 : p.splits);
+    a.ksplit = p.ksplit;
+    a.splits = p.splits;
+    a.cut = cut_rows(S, g.Ho * g.Wo, p.ksplit);
+    a.zdirect = direct;
+    a.out = direct ? (S.p == 1 ? dw.g + S.k[0] * dw.stride : dw.g) : scratch;
+    a.zstride = direct ? dw.stride : n;
+    const dim3 grid((a.M + p.bm - 1) / p.bm, (a.Nn + p.bn - 1) / p.bn, S.p * p.splits);
     launch_mode<CONV_WGRAD>(dtype, p.t, grid, a, st);
     if (!direct) {
-        ProfScope ps("wgrad_reduce", 0.0, 4.0 * (double)n * (p.splits + 1), st);
+        ProfScope ps("wgrad_reduce", 0.0, 4.0 * (double)n * (p.splits + 1) * S.p, st);
         // dw may sit at any float offset of the flat gradient vector: vectors only if it is 16-byte aligned
-        if (n % 4 == 0 && ((uintptr_t)dw & 15) == 0) {
-            int64_t blocks = (n / 4 + 255) / 256;
-            if (blocks > 8192) blocks = 8192;
-            hipLaunchKernelGGL(wgrad_reduce_kernel<4>, dim3((int)blocks), dim3(256), 0, st, scratch, dw, n, p.splits);
-        } else {
-            int64_t blocks = (n + 255) / 256;
-            if (blocks > 8192) blocks = 8192;
-            hipLaunchKernelGGL(wgrad_reduce_kernel<1>, dim3((int)blocks), dim3(256), 0, st, scratch, dw, n, p.splits);
-        }
+        const int vec = (n % 4 == 0 && ((uintptr_t)dw.g & 15) == 0 && dw.stride % 4 == 0) ? 4 : 1;
+        int64_t blocks = (n / vec + 255) / 256;
+        if (blocks > 8192) blocks = 8192;
+        const dim3 rgrid((unsigned)blocks, S.p);
+        if (vec == 4) hipLaunchKernelGGL(wgrad_reduce_kernel<4>, rgrid, dim3(256), 0, st, scratch, dw.g, dw.stride, S, n, p.splits);
+        else hipLaunchKernelGGL(wgrad_reduce_kernel<1>, rgrid, dim3(256), 0, st, scratch, dw.g, dw.stride, S, n, p.splits);
     }
 }
 

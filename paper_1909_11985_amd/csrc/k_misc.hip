@@ -423,9 +423,11 @@ __device__ __forceinline__ float block_reduce(float v, float* sm, bool is_max) {
 
 template <typename T>
 __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
-                                                         T* __restrict__ dlogits, float* __restrict__ row_loss, int n, int C) {
+                                                         T* __restrict__ dlogits, float* __restrict__ row_loss, RowCut shards, int C) {
     __shared__ float sm[4];
     const int i = blockIdx.x;
+    const int sh = shard_of_block(shards, i);        // one block per sample
+    const int n = shards.row0[sh + 1] - shards.row0[sh];
     const float* z = logits + (int64_t)i * C;
     float mx = -INFINITY;
     for (int c = threadIdx.x; c < C; c += blockDim.x) mx = fmaxf(mx, z[c]);
@@ -442,22 +444,25 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(const float* __restrict
     if (threadIdx.x == 0) row_loss[i] = logf(s) - (z[label] - mx);
 }
 
-// mean of the n per-sample losses, summed in sample order by one wave
-__global__ void loss_mean_kernel(const float* __restrict__ row_loss, int n, float* __restrict__ out) {
+// mean of the per-sample losses of each shard, summed in sample order by one wave; grid: shards
+__global__ void loss_mean_kernel(const float* __restrict__ row_loss, ShardSet S, float* __restrict__ out) {
+    const int lo = S.off[blockIdx.x], hi = S.off[blockIdx.x + 1];
     float s = 0.f;
-    for (int i = threadIdx.x; i < n; i += 64) s += row_loss[i];
+    for (int i = lo + threadIdx.x; i < hi; i += 64) s += row_loss[i];
     for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) out[0] = s / (float)n;
+    if (threadIdx.x == 0) out[S.k[blockIdx.x]] = s / (float)(hi - lo);
 }
 
 void launch_softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss,
-                       float* loss_out, int n, int C, hipStream_t st) {
+                       float* loss_out, const ShardSet& S, int C, hipStream_t st) {
+    const int n = S.samples();
     ProfScope ps("softmax_ce", 0.0, (4.0 + (dtype == 1 ? 2.0 : 4.0)) * (double)n * C, st);
+    const RowCut shards = cut_rows(S, 1, 1);
     if (dtype == 1)
-        hipLaunchKernelGGL(softmax_ce_kernel<bf16_t>, dim3(n), dim3(256), 0, st, logits, labels, (bf16_t*)dlogits, row_loss, n, C);
+        hipLaunchKernelGGL(softmax_ce_kernel<bf16_t>, dim3(n), dim3(256), 0, st, logits, labels, (bf16_t*)dlogits, row_loss, shards, C);
     else
-        hipLaunchKernelGGL(softmax_ce_kernel<float>, dim3(n), dim3(256), 0, st, logits, labels, (float*)dlogits, row_loss, n, C);
-    hipLaunchKernelGGL(loss_mean_kernel, dim3(1), dim3(64), 0, st, row_loss, n, loss_out);
+        hipLaunchKernelGGL(softmax_ce_kernel<float>, dim3(n), dim3(256), 0, st, logits, labels, (float*)dlogits, row_loss, shards, C);
+    hipLaunchKernelGGL(loss_mean_kernel, dim3(S.p), dim3(64), 0, st, row_loss, S, loss_out);
 }
 
 // ---------------------------------------------------------------------------

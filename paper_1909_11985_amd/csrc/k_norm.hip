@@ -2,11 +2,15 @@
 // bias / ReLU backward, all as per-channel column reductions over a row-major
 // [M][C] activation matrix followed by an elementwise pass.  HBM-bound.
 //
-// Reduction scheme (deterministic, no atomics): the rows are cut into at most
-// kRedRowBlocks blocks; a workgroup of TX x TY lanes owns 32*VEC channels of
+// One launch covers every shard of the pass; statistics and parameter gradients
+// are formed per shard (a row block never crosses a shard's end).
+//
+// Reduction scheme (deterministic, no atomics): the rows are cut into about
+// kRedRowBlocks blocks at most; a workgroup of TX x TY lanes owns 32*VEC channels of
 // one row block, each lane accumulating one 16-byte channel vector over every
 // TY-th row in float32; lanes are combined through LDS; a second tiny kernel
-// adds the row blocks in float64.
+// adds a shard's row blocks in float64.
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -20,8 +24,8 @@ constexpr float kBnEps = 1e-5f;
 constexpr float kBnRunningMomentum = 0.1f;
 
 struct RedShape {
-    int TX, TY, cvecs, row_blocks, rows_per_block;
-    dim3 grid, block;
+    int TX, TY, cvecs, row_blocks, rows_per_block, col_blocks;
+    dim3 block;
 };
 
 static RedShape red_shape(int64_t M, int C, int VEC) {
@@ -31,18 +35,22 @@ static RedShape red_shape(int64_t M, int C, int VEC) {
     while (tx < s.cvecs && tx < 32) tx <<= 1;
     s.TX = tx;
     s.TY = 256 / tx;
-    const int col_blocks = (s.cvecs + tx - 1) / tx;
+    s.col_blocks = (s.cvecs + tx - 1) / tx;
     // aim at ~2048 workgroups, at least TY*4 rows each
-    int64_t rb = (2048 + col_blocks - 1) / col_blocks;
+    int64_t rb = (2048 + s.col_blocks - 1) / s.col_blocks;
     const int64_t max_rb = (M + (int64_t)s.TY * 4 - 1) / ((int64_t)s.TY * 4);
     if (rb > max_rb) rb = max_rb;
     if (rb > kRedRowBlocks) rb = kRedRowBlocks;
     if (rb < 1) rb = 1;
+    s.row_blocks = (int)rb;
     s.rows_per_block = (int)((M + rb - 1) / rb);
-    s.row_blocks = (int)((M + s.rows_per_block - 1) / s.rows_per_block);
-    s.grid = dim3(col_blocks, s.row_blocks);
     s.block = dim3(s.TX, s.TY);
     return s;
+}
+
+size_t norm_sums_floats(int dtype, int64_t M, int C, int p) {
+    const int vec = dtype == 1 ? 8 : 4;
+    return (size_t)2 * C * (red_shape(M, C, C % vec == 0 ? vec : 1).row_blocks + p);
 }
 
 // Loads VEC channels of row r starting at channel c0 (zero beyond C).
@@ -89,9 +97,11 @@ __device__ __forceinline__ void store_row(T* base, int64_t r, int C, int c0, con
 // KIND 2: a = dy' (written back in place), b=0 (bias gradient / ReLU mask)
 template <typename T, int VEC, int KIND>
 __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x, const T* __restrict__ y, T* dy,
-                                                        const float* __restrict__ mean_rstd, int64_t M, int C,
-                                                        int rows_per_block, int relu, float* __restrict__ partial) {
+                                                        const float* __restrict__ mean_rstd, RowCut cut, int C,
+                                                        int relu, float* __restrict__ partial) {
     __shared__ float red[2][256 * VEC];
+    int r0, r1;
+    const int sh = locate_block(cut, blockIdx.y, r0, r1);
     const int tx = threadIdx.x, ty = threadIdx.y, TX = blockDim.x, TY = blockDim.y;
     const int c0 = (blockIdx.x * TX + tx) * VEC;
     const bool active = c0 < C;
@@ -100,12 +110,10 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
     for (int e = 0; e < VEC; ++e) { a[e] = 0.f; b[e] = 0.f; }
     float mu[VEC], rs[VEC];
     if (KIND == 1 && active) {
+        const float* const ms = mean_rstd + (int64_t)sh * 2 * C;
         #pragma unroll
-        for (int e = 0; e < VEC; ++e) { mu[e] = mean_rstd[c0 + e]; rs[e] = mean_rstd[C + c0 + e]; }
+        for (int e = 0; e < VEC; ++e) { mu[e] = ms[c0 + e]; rs[e] = ms[C + c0 + e]; }
     }
-    const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
-    int64_t r1 = r0 + rows_per_block;
-    if (r1 > M) r1 = M;
     if (active) {
         // U rows per trip, every load of a trip issued before the first use: the loads are unconditional
         // (without ReLU y is a valid tensor that is read and ignored), so none of them waits for another.
@@ -162,32 +170,36 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
         #pragma unroll
         for (int e = 0; e < VEC; ++e) {
             if (c0 + e < C) {
-                partial[(int64_t)(c0 + e) * kRedRowBlocks + blockIdx.y] = a[e];
-                partial[(int64_t)(C + c0 + e) * kRedRowBlocks + blockIdx.y] = b[e];
+                partial[(int64_t)(c0 + e) * gridDim.y + blockIdx.y] = a[e];
+                partial[(int64_t)(C + c0 + e) * gridDim.y + blockIdx.y] = b[e];
             }
         }
     }
 }
 
-// Sum of the row blocks' partial sums of one channel: one wave per channel, lane
-// L takes blocks L, L+64, ... (coalesced) in float64, then a butterfly.
-// blockDim = 256 = 4 channels x 64 lanes.
-__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, int row_blocks, int C, int c, int sub,
+// Sums of shard sh's row blocks of one channel by W waves (64 * W lanes): lane L takes blocks L, L + 64*W, ...
+// (coalesced) in float64, then a butterfly and, for several waves, LDS.  One wave takes four channels' worth of
+// launches off the grid where the blocks are few; the four-wave form is for the first layers of large images, whose
+// thousands of blocks would be a long chain of loads for one wave.  Valid in lane 0 of the channel's lanes.
+template <int W>
+__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, const RowCut& cut, int sh, int C, int c, int sub,
                                              double& s, double& q) {
     s = 0;
     q = 0;
+    constexpr int L = 64 * W;
     if (c < C) {
-        const float* ps = partial + (int64_t)c * kRedRowBlocks;
-        const float* pq = partial + (int64_t)(C + c) * kRedRowBlocks;
+        const int stride = cut.blk0[cut.p], end = cut.blk0[sh + 1];
+        const float* ps = partial + (int64_t)c * stride;
+        const float* pq = partial + (int64_t)(C + c) * stride;
         // four loads of each kind in flight per lane (the partial sums of a channel are contiguous)
-        int j = sub;
-        for (; j + 192 < row_blocks; j += 256) {
-            const float s0 = ps[j], s1 = ps[j + 64], s2 = ps[j + 128], s3 = ps[j + 192];
-            const float q0 = pq[j], q1 = pq[j + 64], q2 = pq[j + 128], q3 = pq[j + 192];
+        int j = cut.blk0[sh] + sub;
+        for (; j + 3 * L < end; j += 4 * L) {
+            const float s0 = ps[j], s1 = ps[j + L], s2 = ps[j + 2 * L], s3 = ps[j + 3 * L];
+            const float q0 = pq[j], q1 = pq[j + L], q2 = pq[j + 2 * L], q3 = pq[j + 3 * L];
             s += (double)s0; s += (double)s1; s += (double)s2; s += (double)s3;
             q += (double)q0; q += (double)q1; q += (double)q2; q += (double)q3;
         }
-        for (; j < row_blocks; j += 64) {
+        for (; j < end; j += L) {
             s += (double)ps[j];
             q += (double)pq[j];
         }
@@ -196,22 +208,38 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
         s += __shfl_xor(s, o, 64);
         q += __shfl_xor(q, o, 64);
     }
+    if (W > 1) {
+        __shared__ double part[2][W];
+        if ((sub & 63) == 0) { part[0][sub >> 6] = s; part[1][sub >> 6] = q; }
+        __syncthreads();
+        s = 0;
+        q = 0;
+        #pragma unroll
+        for (int w = 0; w < W; ++w) { s += part[0][w]; q += part[1][w]; }
+    }
 }
 
+// grid of the finishing kernels: (channels, shards); blockDim = 256 lanes = 4 / W channels
+template <int W> __device__ __forceinline__ int fin_channel() { return W > 1 ? blockIdx.x : blockIdx.x * 4 + (threadIdx.x >> 6); }
+template <int W> __device__ __forceinline__ int fin_lane() { return W > 1 ? threadIdx.x : (threadIdx.x & 63); }
+
 // mean / rstd from the partial sums; running statistics of the worker whose
-// model a joiner would receive (unbiased variance, momentum 0.1)
-__global__ __launch_bounds__(256) void bn_stats_finalize_kernel(const float* __restrict__ partial, int row_blocks, int64_t M,
+// model a joiner would receive (unbiased variance, momentum 0.1): the pass's first shard
+template <int W>
+__global__ __launch_bounds__(256) void bn_stats_finalize_kernel(const float* __restrict__ partial, RowCut cut,
                                                                 int C, float* __restrict__ mean_rstd, float* running) {
-    const int c = blockIdx.x * 4 + (threadIdx.x >> 6), sub = threadIdx.x & 63;
+    const int c = fin_channel<W>(), sub = fin_lane<W>(), sh = blockIdx.y;
     double s, q;
-    sum_partials(partial, row_blocks, C, c, sub, s, q);
+    sum_partials<W>(partial, cut, sh, C, c, sub, s, q);
     if (c >= C || sub != 0) return;
+    const int M = cut.row0[sh + 1] - cut.row0[sh];
+    mean_rstd += (int64_t)sh * 2 * C;
     const double mean = s / (double)M;
     double var = q / (double)M - mean * mean;
     if (var < 0) var = 0;
     mean_rstd[c] = (float)mean;
     mean_rstd[C + c] = (float)(1.0 / sqrt(var + (double)kBnEps));
-    if (running) {
+    if (running && sh == 0) {
         const double unbiased = M > 1 ? var * (double)M / (double)(M - 1) : var;
         running[c] = (1.f - kBnRunningMomentum) * running[c] + kBnRunningMomentum * (float)mean;
         running[C + c] = (1.f - kBnRunningMomentum) * running[C + c] + kBnRunningMomentum * (float)unbiased;
@@ -219,55 +247,61 @@ __global__ __launch_bounds__(256) void bn_stats_finalize_kernel(const float* __r
 }
 
 // dgamma = sum dy'*xhat, dbeta = sum dy'; coef = {dbeta/M, dgamma/M}
-__global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(const float* __restrict__ partial, int row_blocks, int64_t M,
+template <int W>
+__global__ __launch_bounds__(256) void bn_bwd_finalize_kernel(const float* __restrict__ partial, RowCut cut,
                                                               int C, float* __restrict__ dgamma, float* __restrict__ dbeta,
-                                                              float* __restrict__ coef) {
-    const int c = blockIdx.x * 4 + (threadIdx.x >> 6), sub = threadIdx.x & 63;
+                                                              int64_t grad_stride, float* __restrict__ coef) {
+    const int c = fin_channel<W>(), sub = fin_lane<W>(), sh = blockIdx.y;
     double s, q;
-    sum_partials(partial, row_blocks, C, c, sub, s, q);
+    sum_partials<W>(partial, cut, sh, C, c, sub, s, q);
     if (c >= C || sub != 0) return;
-    dbeta[c] = (float)s;
-    dgamma[c] = (float)q;
+    const int M = cut.row0[sh + 1] - cut.row0[sh];
+    const int64_t to = (int64_t)cut.k[sh] * grad_stride;
+    dbeta[to + c] = (float)s;
+    dgamma[to + c] = (float)q;
+    coef += (int64_t)sh * 2 * C;
     coef[c] = (float)(s / (double)M);
     coef[C + c] = (float)(q / (double)M);
 }
 
-__global__ __launch_bounds__(256) void bias_finalize_kernel(const float* __restrict__ partial, int row_blocks, int C,
-                                                            float* __restrict__ dbias) {
-    const int c = blockIdx.x * 4 + (threadIdx.x >> 6), sub = threadIdx.x & 63;
+template <int W>
+__global__ __launch_bounds__(256) void bias_finalize_kernel(const float* __restrict__ partial, RowCut cut, int C,
+                                                            float* __restrict__ dbias, int64_t grad_stride) {
+    const int c = fin_channel<W>(), sub = fin_lane<W>(), sh = blockIdx.y;
     double s, q;
-    sum_partials(partial, row_blocks, C, c, sub, s, q);
+    sum_partials<W>(partial, cut, sh, C, c, sub, s, q);
     if (c >= C || sub != 0) return;
-    dbias[c] = (float)s;
+    dbias[(int64_t)cut.k[sh] * grad_stride + c] = (float)s;
 }
 
-// y = relu(gamma * (x - mean) * rstd + beta + res)
+// y = relu(gamma * (x - mean) * rstd + beta + res); grid: (vectors of the largest shard, shards)
 // No load sits behind a run-time branch, so that all of a lane's loads are in flight together.
 template <typename T, int VEC, bool RES, bool NT>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x, const T* __restrict__ res,
                                                        T* __restrict__ y, const float* __restrict__ gamma,
                                                        const float* __restrict__ beta, const float* __restrict__ mean_rstd,
-                                                       int64_t M, int C, int cvecs, int relu) {
-    const int64_t total = M * cvecs;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        const int64_t r = i / cvecs;
-        const int c0 = (int)(i - r * cvecs) * VEC;
-        float xv[VEC], rv[VEC], out[VEC];
-        if (NT) load_row_nt<T, VEC>(x, r, C, c0, xv); else load_row<T, VEC>(x, r, C, c0, xv);
-        if (RES) { if (NT) load_row_nt<T, VEC>(res, r, C, c0, rv); else load_row<T, VEC>(res, r, C, c0, rv); }
-        #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            const float sc = gamma[c0 + e] * mean_rstd[C + c0 + e];
-            out[e] = (xv[e] - mean_rstd[c0 + e]) * sc + beta[c0 + e];
-            if (RES) out[e] += rv[e];
-            if (relu) out[e] = out[e] > 0.f ? out[e] : 0.f;
-        }
-        store_row<T, VEC>(y, r, C, c0, out);
+                                                       RowCut shards, int C, int cvecs, int relu) {
+    const int sh = blockIdx.y, row0 = shards.row0[sh];
+    const int64_t total = (int64_t)(shards.row0[sh + 1] - row0) * cvecs;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= total) return;
+    mean_rstd += (int64_t)sh * 2 * C;
+    const int64_t rl = i / cvecs, r = row0 + rl;
+    const int c0 = (int)(i - rl * cvecs) * VEC;
+    float xv[VEC], rv[VEC], out[VEC];
+    if (NT) load_row_nt<T, VEC>(x, r, C, c0, xv); else load_row<T, VEC>(x, r, C, c0, xv);
+    if (RES) { if (NT) load_row_nt<T, VEC>(res, r, C, c0, rv); else load_row<T, VEC>(res, r, C, c0, rv); }
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        const float sc = gamma[c0 + e] * mean_rstd[C + c0 + e];
+        out[e] = (xv[e] - mean_rstd[c0 + e]) * sc + beta[c0 + e];
+        if (RES) out[e] += rv[e];
+        if (relu) out[e] = out[e] > 0.f ? out[e] : 0.f;
     }
+    store_row<T, VEC>(y, r, C, c0, out);
 }
 
-// dx = gamma*rstd*(dy' - coef0 - xhat*coef1) ; dres (+)= dy'
+// dx = gamma*rstd*(dy' - coef0 - xhat*coef1) ; dres (+)= dy'; grid as above
 // MASK: dy' = dy * (y > 0) is formed here (else dy arrives masked, or there is no ReLU, and y is not read);
 // ACC: dres already holds a gradient that dy' is added to.  Compile-time, so that no load sits behind a
 // run-time branch and none is issued that is not needed.
@@ -276,111 +310,122 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__
                                                            const T* __restrict__ dy, T* __restrict__ dx, T* dres,
                                                            const float* __restrict__ gamma,
                                                            const float* __restrict__ mean_rstd,
-                                                           const float* __restrict__ coef, int64_t M, int C, int cvecs) {
-    const int64_t total = M * cvecs;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        const int64_t r = i / cvecs;
-        const int c0 = (int)(i - r * cvecs) * VEC;
-        float xv[VEC], yv[VEC], g[VEC], old[VEC], out[VEC];
-        if (NT) load_row_nt<T, VEC>(x, r, C, c0, xv); else load_row<T, VEC>(x, r, C, c0, xv);
-        load_row<T, VEC>(dy, r, C, c0, g);
-        if (MASK) { if (NT) load_row_nt<T, VEC>(y, r, C, c0, yv); else load_row<T, VEC>(y, r, C, c0, yv); }
-        if (ACC) load_row<T, VEC>(dres, r, C, c0, old);
-        #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            if (MASK) g[e] = yv[e] > 0.f ? g[e] : 0.f;
-            const float rs = mean_rstd[C + c0 + e];
-            const float xh = (xv[e] - mean_rstd[c0 + e]) * rs;
-            out[e] = gamma[c0 + e] * rs * (g[e] - coef[c0 + e] - xh * coef[C + c0 + e]);
+                                                           const float* __restrict__ coef, RowCut shards, int C, int cvecs) {
+    const int sh = blockIdx.y, row0 = shards.row0[sh];
+    const int64_t total = (int64_t)(shards.row0[sh + 1] - row0) * cvecs;
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= total) return;
+    mean_rstd += (int64_t)sh * 2 * C;
+    coef += (int64_t)sh * 2 * C;
+    const int64_t rl = i / cvecs, r = row0 + rl;
+    const int c0 = (int)(i - rl * cvecs) * VEC;
+    float xv[VEC], yv[VEC], g[VEC], old[VEC], out[VEC];
+    if (NT) load_row_nt<T, VEC>(x, r, C, c0, xv); else load_row<T, VEC>(x, r, C, c0, xv);
+    load_row<T, VEC>(dy, r, C, c0, g);
+    if (MASK) { if (NT) load_row_nt<T, VEC>(y, r, C, c0, yv); else load_row<T, VEC>(y, r, C, c0, yv); }
+    if (ACC) load_row<T, VEC>(dres, r, C, c0, old);
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        if (MASK) g[e] = yv[e] > 0.f ? g[e] : 0.f;
+        const float rs = mean_rstd[C + c0 + e];
+        const float xh = (xv[e] - mean_rstd[c0 + e]) * rs;
+        out[e] = gamma[c0 + e] * rs * (g[e] - coef[c0 + e] - xh * coef[C + c0 + e]);
+    }
+    store_row<T, VEC>(dx, r, C, c0, out);
+    if (dres) {
+        if (ACC) {
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) g[e] += old[e];
         }
-        store_row<T, VEC>(dx, r, C, c0, out);
-        if (dres) {
-            if (ACC) {
-                #pragma unroll
-                for (int e = 0; e < VEC; ++e) g[e] += old[e];
-            }
-            store_row<T, VEC>(dres, r, C, c0, g);
-        }
+        store_row<T, VEC>(dres, r, C, c0, g);
     }
 }
 
-static inline int ew_grid(int64_t total) {
-    int64_t b = (total + 255) / 256;
-    if (b > (1 << 30)) b = 1 << 30;
-    if (b < 1) b = 1;
-    return (int)b;
+// a finishing kernel over all channels and shards: four waves per channel where a shard has many row blocks
+#define EDL_FINALIZE(KERNEL, CUT, CH, ...)                                                                                     \
+    do {                                                                                                                       \
+        int most = 0;                                                                                                          \
+        for (int s_ = 0; s_ < (CUT).p; ++s_) most = std::max(most, (CUT).blk0[s_ + 1] - (CUT).blk0[s_]);                       \
+        if (most > 512) hipLaunchKernelGGL(KERNEL<4>, dim3(CH, (CUT).p), dim3(256), 0, st, partial, CUT, CH, __VA_ARGS__);     \
+        else hipLaunchKernelGGL(KERNEL<1>, dim3(((CH) + 3) / 4, (CUT).p), dim3(256), 0, st, partial, CUT, CH, __VA_ARGS__);    \
+    } while (0)
+
+static inline dim3 ew_grid(const ShardSet& S, int hw, int cvecs) {
+    return dim3((unsigned)(((int64_t)S.largest() * hw * cvecs + 255) / 256), S.p);
 }
 
 template <typename T, int VEC>
 static void bn_forward_t(const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                         float* save, float* running, int64_t M, int C, bool relu, float* partial, int stats_row_blocks,
-                         hipStream_t st) {
-    const RedShape s = red_shape(M, C, VEC);
+                         float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                         const RowCut& sums, hipStream_t st) {
+    const int64_t M = (int64_t)S.samples() * hw;
+    const RedShape s = red_shape((int64_t)S.plan * hw, C, VEC);
     const double tb = (double)sizeof(T) * (double)M * C;   // bytes of one [M][C] tensor
-    if (stats_row_blocks <= 0) {   // else the producer of x left the partial sums
+    RowCut cut = sums;
+    if (cut.p == 0) {   // else the producer of x left the partial sums
         ProfScope ps(prof_shape_label("bn_stats", M, C), 0.0, tb, st);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 0>), s.grid, s.block, 0, st, (const T*)x, (const T*)nullptr, (T*)nullptr,
-                           (const float*)nullptr, M, C, s.rows_per_block, 0, partial);
-        stats_row_blocks = s.row_blocks;
+        cut = cut_rows(S, hw, s.rows_per_block);
+        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 0>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)x, (const T*)nullptr,
+                           (T*)nullptr, (const float*)nullptr, cut, C, 0, partial);
     }
     {
-        ProfScope ps("bn_stats_finalize", 0.0, 8.0 * (double)stats_row_blocks * C, st);
-        hipLaunchKernelGGL(bn_stats_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, partial, stats_row_blocks, M, C,
-                           save, running);
+        ProfScope ps("bn_stats_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
+        EDL_FINALIZE(bn_stats_finalize_kernel, cut, C, save, running);
     }
     ProfScope ps(prof_shape_label("bn_apply", M, C), 0.0, tb * (res ? 3.0 : 2.0), st);
     const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
+    const dim3 grid = ew_grid(S, hw, s.cvecs);
 #define EDL_BN_APPLY(RES, NT)                                                                                          \
-    hipLaunchKernelGGL((bn_apply_kernel<T, VEC, RES, NT>), dim3(ew_grid(M * s.cvecs)), dim3(256), 0, st, (const T*)x, \
-                       (const T*)res, (T*)y, gamma, beta, save, M, C, s.cvecs, relu ? 1 : 0)
+    hipLaunchKernelGGL((bn_apply_kernel<T, VEC, RES, NT>), grid, dim3(256), 0, st, (const T*)x, (const T*)res, (T*)y, gamma, beta, \
+                       save, cut, C, s.cvecs, relu ? 1 : 0)
     if (res) { if (nt) EDL_BN_APPLY(true, true); else EDL_BN_APPLY(true, false); }
     else { if (nt) EDL_BN_APPLY(false, true); else EDL_BN_APPLY(false, false); }
 #undef EDL_BN_APPLY
 }
 
 void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                       float* save, float* running, int64_t M, int C, bool relu, float* partial, int stats_row_blocks,
-                       hipStream_t st) {
+                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                       const RowCut& sums, hipStream_t st) {
     if (dtype == 1) {
-        if (C % 8 == 0) bn_forward_t<bf16_t, 8>(x, res, y, gamma, beta, save, running, M, C, relu, partial, stats_row_blocks, st);
-        else bn_forward_t<bf16_t, 1>(x, res, y, gamma, beta, save, running, M, C, relu, partial, stats_row_blocks, st);
+        if (C % 8 == 0) bn_forward_t<bf16_t, 8>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
+        else bn_forward_t<bf16_t, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
     } else {
-        if (C % 4 == 0) bn_forward_t<float, 4>(x, res, y, gamma, beta, save, running, M, C, relu, partial, stats_row_blocks, st);
-        else bn_forward_t<float, 1>(x, res, y, gamma, beta, save, running, M, C, relu, partial, stats_row_blocks, st);
+        if (C % 4 == 0) bn_forward_t<float, 4>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
+        else bn_forward_t<float, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
     }
 }
 
 template <typename T, int VEC>
 static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx, void* dres, bool dres_acc,
-                          const float* gamma, const float* save, float* dgamma, float* dbeta, int64_t M, int C,
-                          bool relu, float* partial, float* coef, int sums_row_blocks, hipStream_t st) {
-    const RedShape s = red_shape(M, C, VEC);
+                          const float* gamma, const float* save, GradDst dgamma, GradDst dbeta, const ShardSet& S, int hw, int C,
+                          bool relu, float* partial, float* coef, const RowCut& sums, hipStream_t st) {
+    const int64_t M = (int64_t)S.samples() * hw;
+    const RedShape s = red_shape((int64_t)S.plan * hw, C, VEC);
     const double tb = (double)sizeof(T) * (double)M * C;
-    const bool fused = sums_row_blocks > 0;
-    if (sums_row_blocks <= 0) {   // else the dgrad that produced dy left the sums
+    const bool fused = sums.p > 0;
+    RowCut cut = sums;
+    if (!fused) {   // else the dgrad that produced dy left the sums
         ProfScope ps(prof_shape_label("bn_bwd_reduce", M, C), 0.0, tb * (relu ? 3.0 : 2.0), st);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 1>), s.grid, s.block, 0, st, (const T*)x, (const T*)(relu ? y : x), (T*)dy, save,
-                           M, C, s.rows_per_block, relu ? 1 : 0, partial);
-        sums_row_blocks = s.row_blocks;
+        cut = cut_rows(S, hw, s.rows_per_block);
+        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 1>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)x,
+                           (const T*)(relu ? y : x), (T*)dy, save, cut, C, relu ? 1 : 0, partial);
     }
     {
-        ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)sums_row_blocks * C, st);
-        hipLaunchKernelGGL(bn_bwd_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, partial, sums_row_blocks, M, C,
-                           dgamma, dbeta, coef);
+        ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
+        EDL_FINALIZE(bn_bwd_finalize_kernel, cut, C, dgamma.g, dbeta.g, dgamma.stride, coef);
     }
     // the dgrad that left the sums also left dy masked: the activation is then not read again
     const bool mask = relu && !fused;
     const bool acc = dres && dres_acc;
     ProfScope ps(prof_shape_label("bn_bwd_apply", M, C), 0.0, tb * ((mask ? 3.0 : 2.0) + 1.0 + (dres ? (acc ? 2.0 : 1.0) : 0.0)), st);
-    const dim3 grid(ew_grid(M * s.cvecs));
+    const dim3 grid = ew_grid(S, hw, s.cvecs);
     const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
 #define EDL_BN_BWD_APPLY(MASK, ACC)                                                                                       \
     do {                                                                                                                  \
         if (nt) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, MASK, ACC, true>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
-                                   (T*)dx, (T*)dres, gamma, save, coef, M, C, s.cvecs);                                  \
+                                   (T*)dx, (T*)dres, gamma, save, coef, cut, C, s.cvecs);                                \
         else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, MASK, ACC, false>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
-                                (T*)dx, (T*)dres, gamma, save, coef, M, C, s.cvecs);                                     \
+                                (T*)dx, (T*)dres, gamma, save, coef, cut, C, s.cvecs);                                   \
     } while (0)
     if (mask) { if (acc) EDL_BN_BWD_APPLY(true, true); else EDL_BN_BWD_APPLY(true, false); }
     else { if (acc) EDL_BN_BWD_APPLY(false, true); else EDL_BN_BWD_APPLY(false, false); }
@@ -388,44 +433,46 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
 }
 
 void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy, void* dx, void* dres,
-                        bool dres_accumulate, const float* gamma, const float* save, float* dgamma, float* dbeta,
-                        int64_t M, int C, bool relu, float* partial, float* coef, int sums_row_blocks,
+                        bool dres_accumulate, const float* gamma, const float* save, GradDst dgamma, GradDst dbeta,
+                        const ShardSet& S, int hw, int C, bool relu, float* partial, float* coef, const RowCut& sums,
                         hipStream_t st) {
     if (dtype == 1) {
-        if (C % 8 == 0) bn_backward_t<bf16_t, 8>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, M, C, relu, partial, coef, sums_row_blocks, st);
-        else bn_backward_t<bf16_t, 1>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, M, C, relu, partial, coef, sums_row_blocks, st);
+        if (C % 8 == 0) bn_backward_t<bf16_t, 8>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
+        else bn_backward_t<bf16_t, 1>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
     } else {
-        if (C % 4 == 0) bn_backward_t<float, 4>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, M, C, relu, partial, coef, sums_row_blocks, st);
-        else bn_backward_t<float, 1>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, M, C, relu, partial, coef, sums_row_blocks, st);
+        if (C % 4 == 0) bn_backward_t<float, 4>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
+        else bn_backward_t<float, 1>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
     }
 }
 
 template <typename T, int VEC>
-static void bias_relu_backward_t(const void* y, void* dy, float* dbias, int64_t M, int C, bool relu, float* partial,
-                                 int sums_row_blocks, hipStream_t st) {
-    const RedShape s = red_shape(M, C, VEC);
+static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                                 const RowCut& sums, hipStream_t st) {
+    const int64_t M = (int64_t)S.samples() * hw;
+    const RedShape s = red_shape((int64_t)S.plan * hw, C, VEC);
     const double tb = (double)sizeof(T) * (double)M * C;
-    if (sums_row_blocks <= 0) {   // else dy is masked already and its column sums are in partial
+    RowCut cut = sums;
+    if (cut.p == 0) {   // else dy is masked already and its column sums are in partial
         ProfScope ps("bias_relu_bwd", 0.0, tb * (relu ? 3.0 : 1.0), st);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 2>), s.grid, s.block, 0, st, (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy,
-                           (const float*)nullptr, M, C, s.rows_per_block, relu ? 1 : 0, partial);
-        sums_row_blocks = s.row_blocks;
+        cut = cut_rows(S, hw, s.rows_per_block);
+        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 2>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)nullptr,
+                           (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial);
     }
-    if (dbias) {
-        ProfScope ps("bias_finalize", 0.0, 4.0 * (double)sums_row_blocks * C, st);
-        hipLaunchKernelGGL(bias_finalize_kernel, dim3((C + 3) / 4), dim3(256), 0, st, partial, sums_row_blocks, C, dbias);
+    if (dbias.g) {
+        ProfScope ps("bias_finalize", 0.0, 4.0 * (double)cut.blk0[cut.p] * C, st);
+        EDL_FINALIZE(bias_finalize_kernel, cut, C, dbias.g, dbias.stride);
     }
 }
 
-void launch_bias_relu_backward(int dtype, const void* y, void* dy, float* dbias, int64_t M, int C, bool relu,
-                               float* partial, int sums_row_blocks, hipStream_t st) {
-    if (!relu && !dbias) return;
+void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
+                               float* partial, const RowCut& sums, hipStream_t st) {
+    if (!relu && !dbias.g) return;
     if (dtype == 1) {
-        if (C % 8 == 0) bias_relu_backward_t<bf16_t, 8>(y, dy, dbias, M, C, relu, partial, sums_row_blocks, st);
-        else bias_relu_backward_t<bf16_t, 1>(y, dy, dbias, M, C, relu, partial, sums_row_blocks, st);
+        if (C % 8 == 0) bias_relu_backward_t<bf16_t, 8>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
+        else bias_relu_backward_t<bf16_t, 1>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
     } else {
-        if (C % 4 == 0) bias_relu_backward_t<float, 4>(y, dy, dbias, M, C, relu, partial, sums_row_blocks, st);
-        else bias_relu_backward_t<float, 1>(y, dy, dbias, M, C, relu, partial, sums_row_blocks, st);
+        if (C % 4 == 0) bias_relu_backward_t<float, 4>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
+        else bias_relu_backward_t<float, 1>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
     }
 }
 

@@ -608,18 +608,22 @@ void launch_pad_weights(int dtype, const float* src, void* dst, int64_t rows, in
     else hipLaunchKernelGGL(pad_weights_kernel<float>, dim3(grid), dim3(256), 0, st, src, (float*)dst, rows, C, Cp);
 }
 
-// dst[r][0..C) = src[r][0..C) of rows of Cp floats (gradient of the padded weights back to the flat vector)
-__global__ __launch_bounds__(256) void unpad_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t rows, int C, int Cp) {
+// dst[r][0..C) = src[r][0..C) of rows of Cp floats (gradient of the padded weights back to the flat vectors);
+// grid: (chunks, shards)
+__global__ __launch_bounds__(256) void unpad_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t dst_stride,
+                                                         ShardSet S, int64_t rows, int C, int Cp) {
     const int64_t total = rows * C;
+    src += (int64_t)blockIdx.y * rows * Cp;
+    dst += (int64_t)S.k[blockIdx.y] * dst_stride;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
         const int64_t r = i / C;
         dst[i] = src[r * Cp + (i - r * C)];
     }
 }
 
-void launch_unpad_rows(const float* src, float* dst, int64_t rows, int C, int Cp, hipStream_t st) {
-    ProfScope ps("unpad_rows", 0.0, 8.0 * (double)rows * C, st);
-    hipLaunchKernelGGL(unpad_rows_kernel, dim3(grid_for(rows * C, 256, 4096)), dim3(256), 0, st, src, dst, rows, C, Cp);
+void launch_unpad_rows(const float* src, GradDst dst, const ShardSet& S, int64_t rows, int C, int Cp, hipStream_t st) {
+    ProfScope ps("unpad_rows", 0.0, 8.0 * (double)rows * C * S.p, st);
+    hipLaunchKernelGGL(unpad_rows_kernel, dim3(grid_for(rows * C, 256, 4096), S.p), dim3(256), 0, st, src, dst.g, dst.stride, S, rows, C, Cp);
 }
 
 void launch_gather(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n,

@@ -9,10 +9,49 @@
 namespace edl {
 
 constexpr int kMaxP = 16;           // gradient buffers one update launch can average
-constexpr int kRedRowBlocks = 1024;   // upper bound of row blocks in column reductions
+constexpr int kRedRowBlocks = 1024;   // row blocks a separate column reduction aims at, at most (plus one per shard)
 
 struct GradPtrs { const float* g[kMaxP]; };
 struct ShardShares { float share[kMaxP]; };   // a shard's part of the mini-batch
+
+// The workers' shards that one pass runs together: their samples lie one after another in the activation buffers
+// (none is empty).  A layer is then one launch for all of them; what belongs to a worker alone - batch statistics,
+// the gradients of the parameters, the loss - is formed per shard.
+struct ShardSet {
+    int p;                    // shards in the pass
+    int off[kMaxP + 1];       // first sample of each, off[p] = samples of the pass
+    int k[kMaxP];             // the worker: which gradient buffer, which loss
+    // Samples that tiles and reduction cuts are chosen for: those of the pass, or of the passes this one stands for (a
+    // step's last pass may hold fewer shards than the others; a debugging hook runs one shard of such a pass).
+    // Sums are then formed in the same order for a shard of a given size whichever pass it is in.
+    int plan;
+    int samples() const { return off[p]; }
+    int largest() const { int m = 0; for (int s = 0; s < p; ++s) if (off[s + 1] - off[s] > m) m = off[s + 1] - off[s]; return m; }
+    int smallest() const { int m = off[1]; for (int s = 1; s < p; ++s) if (off[s + 1] - off[s] < m) m = off[s + 1] - off[s]; return m; }
+};
+
+// Rows of a [rows][channels] matrix cut into blocks that stay within a shard: how a launch's partial column sums
+// are laid out, sums[kind * channels + channel][block].  p == 0: there are none.
+struct RowCut {
+    int p = 0, rows_per_block = 0;
+    int row0[kMaxP + 1] = {};     // first row of each shard
+    int blk0[kMaxP + 1] = {};     // first block of each shard, blk0[p] = blocks in all
+    int k[kMaxP] = {};            // the shard's worker
+};
+inline RowCut cut_rows(const ShardSet& S, int rows_per_sample, int rows_per_block) {
+    RowCut c;
+    c.p = S.p;
+    c.rows_per_block = rows_per_block;
+    for (int s = 0; s < S.p; ++s) {
+        c.row0[s + 1] = S.off[s + 1] * rows_per_sample;
+        c.blk0[s + 1] = c.blk0[s] + (c.row0[s + 1] - c.row0[s] + rows_per_block - 1) / rows_per_block;
+        c.k[s] = S.k[s];
+    }
+    return c;
+}
+
+// The workers' gradients of one parameter tensor: worker k's starts at g + k * stride.
+struct GradDst { float* g; int64_t stride; };
 
 // ---- aggregation + update, copies ----------------------------------------
 // max_blocks > 0 holds the launch to that many workgroups (a pass that runs in the background of other work).
@@ -51,9 +90,10 @@ void launch_gather(int dtype, const float* data_x, const int32_t* data_y, const 
 // images with C channels written as pixels of one zero-padded 16-byte vector each
 void launch_gather_pad(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n, int64_t pixels,
                        int C, void* out_x, int32_t* out_y, hipStream_t st);
-// weights [rows][C] float32 -> [rows][Cp] dtype, zero padded; and the way back for their gradient
+// weights [rows][C] float32 -> [rows][Cp] dtype, zero padded; and the way back for their gradient (one per shard:
+// src holds the shards' one after another)
 void launch_pad_weights(int dtype, const float* src, void* dst, int64_t rows, int C, int Cp, hipStream_t st);
-void launch_unpad_rows(const float* src, float* dst, int64_t rows, int C, int Cp, hipStream_t st);
+void launch_unpad_rows(const float* src, GradDst dst, const ShardSet& S, int64_t rows, int C, int Cp, hipStream_t st);
 
 // ---- implicit-GEMM convolution --------------------------------------------
 enum ConvMode { CONV_FWD = 0, CONV_DGRAD = 1, CONV_WGRAD = 2 };
@@ -63,59 +103,59 @@ struct ConvGeom {
     int K, R, S, stride, pad, Ho, Wo;
 };
 
-// y = conv(x, w) (+bias) (ReLU); y is float32 if out_fp32 else dtype.
-// stats (may be null): the batch-norm reduction's partial-sum scratch.  If the launch can, it also leaves
-// there the per-row-tile column sums of y and y*y and returns the number of row tiles (what
-// launch_bn_forward takes as stats_row_blocks); it returns 0 if it left none.
-// Partial column sums of launches with more than kRedRowBlocks row tiles are written into `wide`
-// (2 * channels * row tiles floats, if it is large enough) and summed in groups into the standard scratch.
-struct WideSums { float* buf; size_t floats; };
-int launch_conv_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu,
-                    bool out_fp32, void* y, float* scratch, size_t scratch_bytes, float* stats, WideSums wide, hipStream_t st);
-// floats `wide` must hold for this layer's forward statistics and input-gradient sums (0 if never needed)
-size_t conv_wide_sums_floats(int dtype, const ConvGeom& g);
+// Partial column sums: a buffer of `floats` floats (conv_sums_floats / norm_sums_floats say how many are needed).
+struct SumsBuf { float* buf; size_t floats; };
+
+// y = conv(x, w) (+bias) (ReLU) over the pass's samples; y is float32 if out_fp32 else dtype.
+// stats.buf (may be null): if the launch can, it also leaves there the column sums of y and y*y per block of rows
+// and returns how they are cut; p == 0 if it left none.
+RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
+                       bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st);
+// floats the sums of this layer's forward and input-gradient epilogues can take over g.N samples of p shards
+size_t conv_sums_floats(const ConvGeom& g, int p);
 // What the layer that produced the convolution's input wants from the gradient dx when it ends in a ReLU:
 // dx * (act > 0), and per-channel sums of that over the rows (plain, and times (xin - mean) * rstd if xin is
-// given: a batch norm's backward sums).  sums: the column-reduction partial-sum scratch.
+// given: a batch norm's backward sums).
 struct DgradMask {
     const void* act;          // the producer's output (= this convolution's input), dtype elements
     const void* xin;          // the producing batch norm's input, or null
-    const float* mean_rstd;   // with xin: mean[C], rstd[C]
-    float* sums;
-    WideSums wide;
+    const float* mean_rstd;   // with xin: mean[C], rstd[C] of each shard
+    SumsBuf sums;
 };
 // dx (+)= conv^T(dy, wT); wT is the [C][R][S][K] copy.  mask (may be null): if the launch can (stride 1, one
 // launch over all pixels, writing), dx is stored already masked and the sums are left in mask->sums; returns
-// the number of row tiles summed (what the producer's backward takes as its row-block count), else 0 and dx
-// is the plain gradient.
+// how they are cut (what the producer's backward takes), else p == 0 and dx is the plain gradient.
 // acc_src (stride 1 with accumulate only; may be null): the gradient that is added to is read from this tensor of
 // dx's shape instead of from dx itself (dx is then written, not read).
-int launch_conv_dgrad(int dtype, const ConvGeom& g, const void* dy, const void* wT, bool accumulate, void* dx,
-                      float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st,
-                      const void* acc_src = nullptr);
+RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
+                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st,
+                         const void* acc_src = nullptr);
 // float32 scratch a forward / dgrad launch may use to cut a long reduction of a small problem
 size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g);
-// dw = x^T * dy, float32 [K][R][S][C]; scratch holds split partial sums
-void launch_conv_wgrad(int dtype, const ConvGeom& g, const void* x, const void* dy, float* dw, float* scratch,
+// dw = x^T * dy of every shard, float32 [K][R][S][C]; scratch holds split partial sums
+void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st);
-size_t conv_wgrad_scratch_bytes(const ConvGeom& g);
+// g.N: samples of the largest shard
+size_t conv_wgrad_scratch_bytes(const ConvGeom& g, int p);
 
 // ---- batch norm, bias / ReLU backward --------------------------------------
-// partial: float32 scratch of 2 * kRedRowBlocks * C floats
+// floats the column reductions below take as scratch over the given rows of p shards
+size_t norm_sums_floats(int dtype, int64_t M, int C, int p);
+// save: mean[C], rstd[C] of each shard; running ([2C] or null) follows the first shard; sums.p > 0: partial already
+// holds the sums, cut that way; hw: rows per sample
 void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                       float* save_mean_rstd /*[2C]*/, float* running /*[2C] or null*/, int64_t M, int C,
-                       bool relu, float* partial, int stats_row_blocks /*> 0: partial already holds the sums*/,
-                       hipStream_t st);
-// sums_row_blocks > 0: partial already holds the two backward sums over that many row blocks (left there by
-// the dgrad that produced dy, which is then also masked already)
+                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                       const RowCut& sums, hipStream_t st);
+// sums.p > 0: partial already holds the two backward sums (left there by the dgrad that produced dy, which is then
+// also masked already); coef: 2C floats per shard
 void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy, void* dx, void* dres,
-                        bool dres_accumulate, const float* gamma, const float* save_mean_rstd,
-                        float* dgamma, float* dbeta, int64_t M, int C, bool relu, float* partial, float* coef /*[2C]*/,
-                        int sums_row_blocks, hipStream_t st);
-// dy <- dy * (y > 0) in place if relu; dbias[c] = sum_rows dy (if dbias).
-// sums_row_blocks > 0: dy is masked already and partial holds its column sums over that many row blocks.
-void launch_bias_relu_backward(int dtype, const void* y, void* dy, float* dbias, int64_t M, int C, bool relu,
-                               float* partial, int sums_row_blocks, hipStream_t st);
+                        bool dres_accumulate, const float* gamma, const float* save, GradDst dgamma, GradDst dbeta,
+                        const ShardSet& S, int hw, int C, bool relu, float* partial, float* coef, const RowCut& sums,
+                        hipStream_t st);
+// dy <- dy * (y > 0) in place if relu; dbias[c] = sum_rows dy of each shard (if dbias.g).
+// sums.p > 0: dy is masked already and partial holds its column sums.
+void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
+                               float* partial, const RowCut& sums, hipStream_t st);
 
 // ---- pooling --------------------------------------------------------------
 void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int N, int H, int W, int C, int k,
@@ -129,9 +169,10 @@ void launch_gavgpool_backward(int dtype, const void* dy, void* dx, bool accumula
                               hipStream_t st);
 
 // ---- loss -------------------------------------------------------------------
-// logits float32 [n][C]; dlogits in dtype; loss_out[0] = mean over the n rows
+// logits float32 [samples][C]; dlogits in dtype (of the mean over the sample's shard); loss_out[worker] = mean over
+// the worker's shard
 void launch_softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss,
-                       float* loss_out, int n, int C, hipStream_t st);
+                       float* loss_out, const ShardSet& S, int C, hipStream_t st);
 
 // register-resident MFMA loop (attainable matrix rate); returns the flops the launch issues
 double launch_mfma_rate(int dtype, int blocks, int iters, float* sink, hipStream_t st);

@@ -941,3 +941,43 @@ def test_strided_and_padded_geometries_layerwise():
     geom = dict(H=30, W=26, C=3, classes=10, arch=(8, 1, 1, 1, 0))
     for dtype in ("f32", "bf16"):
         _assert_layerwise(layerwise_parity("resnet50", dtype, 3, verbose=False, **geom), dtype)
+
+
+@pytest.mark.parametrize("model,dtype,kw,cut", [
+    ("mlp", "f32", TINY["mlp"], [5, 0, 7, 1, 11]),                      # scalar loads, empty and one-sample shards
+    ("mlp", "f32", dict(H=1, W=1, C=64, classes=8, arch=(64, 32)), [64, 1, 63, 16]),
+    ("resnet20", "f32", TINY["resnet20"], [1, 9, 2]),                   # shards that end inside a row tile
+    ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), [4, 4, 4, 4, 4, 4, 4, 4]),
+    ("vgg16", "bf16", TINY["vgg16"], [3, 6, 3]),
+    ("resnet50", "bf16", dict(H=64, W=64, C=3, classes=10, arch=(64, 1, 1, 1, 1)), [3, 8, 5]),
+])
+def test_shards_of_one_pass_are_computed_as_each_alone(model, dtype, kw, cut):
+    """The p shards of a mini-batch run together, layer by layer; every worker's gradients and loss are those of its
+    shard run alone (a job of that one shard on the same weights)."""
+    import torch
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    B, N = sum(cut), 2 * sum(cut)
+    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    geom = _cfg_geom(kw)
+    x, y = synth_inputs.dataset(3, N, kw["H"], kw["W"], kw["C"], kw["classes"])
+    dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    job = E.Job(make_config(model, dtype=dtype, N=N, B=B, p_max=len(cut), max_shard=max(cut), **geom), 5)
+    job.bind_dataset(dx, dy)
+    idx, _ = job.shard(B, 1, 0, 1)
+    job.gradients(len(cut), idx, off)
+    losses = job.losses(len(cut))
+    for k, n in enumerate(cut):
+        if n == 0:
+            continue
+        sel = idx[off[k]:off[k + 1]]
+        alone = E.Job(make_config(model, dtype=dtype, N=2 * n, B=n, p_max=1, max_shard=n, **geom), 5)
+        ax, ay = dx[torch.from_numpy(np.tile(sel, 2)).cuda()].contiguous(), dy[torch.from_numpy(np.tile(sel, 2)).cuda()].contiguous()
+        alone.bind_dataset(ax, ay)
+        alone.gradients(1, np.arange(n, dtype=np.int64), np.array([0, n], dtype=np.int64))
+        tol = 1e-5 if dtype == "f32" else 2e-2
+        assert abs(losses[k] - alone.losses(1)[0]) <= tol * abs(losses[k]), (k, losses[k])
+        if dtype == "f32" or model != "resnet50":     # a bf16 residual net's gradient is set by rounding
+            assert relerr(job.grad(k), alone.grad(0)) < tol, k
+        alone.shutdown()
+    job.shutdown()
