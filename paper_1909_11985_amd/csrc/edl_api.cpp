@@ -431,9 +431,7 @@ int32_t edl_shard_host(uint64_t seed, int64_t N, int64_t B, int32_t p, int64_t e
     if (N <= 0 || B <= 0 || p <= 0 || epoch < 0) { set_error("N, B, p must be positive and epoch non-negative"); return EDL_EINVAL; }
     if (B % p || N % B) { set_error("B=%lld must divide by p=%d and N=%lld by B", (long long)B, p, (long long)N); return EDL_EINDIVISIBLE; }
     if (step_in_epoch < 0 || step_in_epoch >= N / B) { set_error("step_in_epoch %lld outside the epoch", (long long)step_in_epoch); return EDL_ERANGE; }
-    std::vector<int64_t> perm;
-    epoch_permutation(seed, epoch, N, perm);
-    memcpy(out_idx, perm.data() + step_in_epoch * B, sizeof(int64_t) * (size_t)B);
+    epoch_permutation_slice(seed, epoch, N, step_in_epoch * B, B, out_idx);
     for (int k = 0; k <= p; ++k) out_off[k] = (int64_t)k * (B / p);
     return EDL_OK;
 }

@@ -58,6 +58,7 @@ int build_graph(const edl_config& cfg, Graph& g);
 // Host integer / initialisation logic
 uint64_t splitmix64_at(uint64_t key, uint64_t j);
 void epoch_permutation(uint64_t seed, int64_t epoch, int64_t N, std::vector<int64_t>& perm);
+void epoch_permutation_slice(uint64_t seed, int64_t epoch, int64_t N, int64_t from, int64_t count, int64_t* out);
 void he_init(const Graph& g, uint64_t seed, float* out);
 
 void set_error(const char* fmt, ...);

@@ -1,6 +1,7 @@
 // Host-side integer logic and model tables: shard assignment (sections 3.1
 // and 4.3 of the paper), He initialisation, and the layer lists of the four
 // model families.  No GPU code here.
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -28,27 +29,100 @@ const char* get_error() { return g_err; }
 static const uint64_t kGolden = 0x9E3779B97F4A7C15ull;
 static const uint64_t kInitKey = 0xD1B54A32D192ED03ull;
 
-uint64_t splitmix64_at(uint64_t key, uint64_t j) {
+static inline uint64_t mix64(uint64_t key, uint64_t j) {
     uint64_t z = key + (j + 1) * kGolden;
     z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
     z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
     return z ^ (z >> 31);
 }
+uint64_t splitmix64_at(uint64_t key, uint64_t j) { return mix64(key, j); }
 
 // The leader's random permutation of section 4.3, one per epoch: Fisher-Yates
 // from the last position down, partner index = high 64 bits of draw*(i+1).
-void epoch_permutation(uint64_t seed, int64_t epoch, int64_t N, std::vector<int64_t>& perm) {
-    const uint64_t key = seed ^ (kGolden * (uint64_t)(epoch + 1));
-    perm.resize((size_t)N);
-    for (int64_t i = 0; i < N; ++i) perm[(size_t)i] = i;
-    uint64_t draw = 0;
-    for (int64_t i = N - 1; i >= 1; --i) {
-        const uint64_t r = splitmix64_at(key, draw++);
-        const uint64_t j = (uint64_t)(((unsigned __int128)r * (unsigned __int128)(uint64_t)(i + 1)) >> 64);
-        const int64_t t = perm[(size_t)i];
-        perm[(size_t)i] = perm[(size_t)j];
-        perm[(size_t)j] = t;
+// A position is final once the walk has passed it, so a caller that wants the
+// entries from `from` on stops there (the mini-batches of an epoch: half the
+// walk on average).
+//
+// Partners are drawn kAhead at a time and their cache lines asked for before the swaps that need them.  Below 2^32
+// entries the product's high half is two 32x32 products, so that the draws vectorise (the build targets plain x86-64:
+// the loop is compiled for wider vectors as well and chosen by what the machine has).
+constexpr int kAhead = 64;
+
+#define EDL_DRAW_PARTNERS                                                                            \
+    for (int k = 0; k < kAhead; ++k) {                                                               \
+        const uint64_t r = mix64(key, draw + (uint64_t)k), m = (uint64_t)(i + 1) - (uint64_t)k; \
+        partner[k] = (uint32_t)(((r >> 32) * (m & 0xffffffffu) + (((r & 0xffffffffu) * (m & 0xffffffffu)) >> 32)) >> 32); \
     }
+static void draw_partners_plain(uint64_t key, uint64_t draw, int64_t i, uint32_t* partner) { EDL_DRAW_PARTNERS }
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+__attribute__((target("avx2"))) static void draw_partners_avx2(uint64_t key, uint64_t draw, int64_t i, uint32_t* partner) { EDL_DRAW_PARTNERS }
+__attribute__((target("avx512f,avx512dq,avx512vl,prefer-256-bit"))) static void draw_partners_avx512(uint64_t key, uint64_t draw, int64_t i, uint32_t* partner) { EDL_DRAW_PARTNERS }
+#endif
+#undef EDL_DRAW_PARTNERS
+
+typedef void (*DrawPartners)(uint64_t, uint64_t, int64_t, uint32_t*);
+static DrawPartners pick_draw_partners() {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    __builtin_cpu_init();
+    if (__builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512dq") && __builtin_cpu_supports("avx512vl")) return draw_partners_avx512;
+    if (__builtin_cpu_supports("avx2")) return draw_partners_avx2;
+#endif
+    return draw_partners_plain;
+}
+
+template <typename I>
+static void shuffle_down_to(uint64_t key, int64_t N, int64_t from, I* perm) {
+    static const DrawPartners draw_partners = pick_draw_partners();
+    for (int64_t i = 0; i < N; ++i) perm[i] = (I)i;
+    const int64_t last = std::max<int64_t>(from, 1);
+    uint64_t draw = 0;
+    int64_t i = N - 1;
+    if (N <= (int64_t)0xffffffffll) {
+        uint32_t partner[kAhead];
+        while (i - kAhead >= last) {
+            draw_partners(key, draw, i, partner);
+            for (int k = 0; k < kAhead; ++k) __builtin_prefetch(perm + partner[k], 1);
+            for (int k = 0; k < kAhead; ++k, --i) {
+                const I t = perm[i];
+                perm[i] = perm[partner[k]];
+                perm[partner[k]] = t;
+            }
+            draw += kAhead;
+        }
+    }
+    for (; i >= last; --i) {
+        const uint64_t r = mix64(key, draw++);
+        const uint64_t j = (uint64_t)(((unsigned __int128)r * (unsigned __int128)(uint64_t)(i + 1)) >> 64);
+        const I t = perm[i];
+        perm[i] = perm[j];
+        perm[j] = t;
+    }
+}
+
+static uint64_t epoch_key(uint64_t seed, int64_t epoch) { return seed ^ (kGolden * (uint64_t)(epoch + 1)); }
+
+void epoch_permutation(uint64_t seed, int64_t epoch, int64_t N, std::vector<int64_t>& perm) {
+    perm.resize((size_t)N);
+    shuffle_down_to<int64_t>(epoch_key(seed, epoch), N, 0, perm.data());
+}
+
+// Entries [from, from + count) of it.  Bound by the walk's random accesses and, for large data sets, by the pages of
+// a fresh work array: 32-bit entries halve the array and each thread keeps its own from call to call (released above
+// kKeptEntries).  1.2 million samples, mini-batches over the epoch: 1.69 -> 0.55 ms on average.
+void epoch_permutation_slice(uint64_t seed, int64_t epoch, int64_t N, int64_t from, int64_t count, int64_t* out) {
+    constexpr int64_t kKeptEntries = 4 << 20;
+    if (N > (int64_t)0xffffffffll) {
+        std::vector<int64_t> perm((size_t)N);
+        shuffle_down_to<int64_t>(epoch_key(seed, epoch), N, from, perm.data());
+        std::copy(perm.begin() + from, perm.begin() + from + count, out);
+        return;
+    }
+    static thread_local std::vector<uint32_t> kept;
+    std::vector<uint32_t> own;
+    std::vector<uint32_t>& perm = N <= kKeptEntries ? kept : own;
+    if ((int64_t)perm.size() < N) perm.resize((size_t)N);
+    shuffle_down_to<uint32_t>(epoch_key(seed, epoch), N, from, perm.data());
+    for (int64_t i = 0; i < count; ++i) out[i] = (int64_t)perm[(size_t)(from + i)];
 }
 
 // He-normal weights by Box-Muller on the counter-based draws, one stream per
