@@ -53,6 +53,7 @@ std::mutex g_side_streams_mutex;
 
 constexpr int64_t kAlign = 256;
 constexpr int kIdxSlots = 4;
+constexpr size_t kStageBytes = 256;  // pinned staging of what is read back: the workers' losses, an image's header
 constexpr int kReadyEvents = 64;   // ring of "dy is final" events for the second stream
 constexpr int kChunkEvents = 64;   // ring of "these weight gradients are final" events for the update stream
 constexpr int kBranchEvents = 16;  // ring of event pairs around a shortcut branch on the second side stream
@@ -597,7 +598,7 @@ static int init_device_state(edl_handle* h) {
         HIP_TRY(hipHostMalloc((void**)&h->idx_host[s], sizeof(int64_t) * (size_t)cfg->B, hipHostMallocDefault));
         HIP_TRY(hipEventCreateWithFlags(&h->idx_event[s], hipEventDisableTiming));
     }
-    HIP_TRY(hipHostMalloc((void**)&h->loss_host, sizeof(float) * kMaxP, hipHostMallocDefault));
+    HIP_TRY(hipHostMalloc((void**)&h->loss_host, kStageBytes, hipHostMallocDefault));
     // this GPU's copy of the static scratch buffer: its address is looked up once, with the device current
     HIP_TRY(hipGetDevice(&h->device));
     if (h->device >= 0 && h->device < kMaxDevices && g_static_scratch[h->device] == nullptr) {
@@ -1376,13 +1377,25 @@ int32_t edl_profile_parallelism(edl_handle* h, int32_t min_p, int32_t max_p, int
     return EDL_OK;
 }
 
+// the arrays of the state image in its order (as the sources of a copy)
+static ImageParts state_parts(const edl_handle* h) {
+    ImageParts parts = {};
+    int q = 0;
+    auto add = [&](float* a, int64_t n) { parts.src[q] = a; parts.n[q] = n; ++q; };
+    add(h->w(), h->g.P);
+    add(h->v(), h->g.P);
+    if (h->adam()) add(h->s2(), h->g.P);
+    add(h->running(), h->g.R);
+    return parts;
+}
+
 int32_t edl_snapshot(edl_handle* h, void* dev_dst, size_t cap, size_t* out_written) {
     if (!h || !dev_dst) { set_error("null argument"); return EDL_EINVAL; }
     const int64_t P = h->g.P, R = h->g.R;
     const size_t need = EDL_SNAPSHOT_HEADER_BYTES + 4 * (size_t)h->state_floats();
     if (cap < need) { set_error("snapshot needs %zu bytes, buffer has %zu", need, cap); return EDL_ENOMEM; }
-    alignas(8) char hdr[EDL_SNAPSHOT_HEADER_BYTES];
-    memset(hdr, 0, sizeof(hdr));
+    static_assert(kImageHeaderBytes == EDL_SNAPSHOT_HEADER_BYTES, "state image header");
+    ImageHeader hdr = {};
     SnapshotHeader sh = {};
     sh.magic = EDL_SNAPSHOT_MAGIC; sh.version = 1; sh.model = (uint32_t)h->cfg.model; sh.dtype = (uint32_t)h->cfg.dtype;
     sh.seed = h->seed; sh.N = h->cfg.N; sh.B = h->cfg.B;
@@ -1390,15 +1403,11 @@ int32_t edl_snapshot(edl_handle* h, void* dev_dst, size_t cap, size_t* out_writt
     sh.lr = h->cfg.lr; sh.momentum = h->cfg.momentum; sh.wd = h->cfg.wd; sh.P = P; sh.R = R;
     sh.optimizer = (uint32_t)h->cfg.optimizer;
     if (h->adam()) { sh.beta2 = h->cfg.beta2; sh.eps = h->cfg.eps; }
-    memcpy(hdr, &sh, sizeof(sh));
-    char* dst = (char*)dev_dst;
-    HIP_TRY(hipMemcpyAsync(dst, hdr, sizeof(hdr), hipMemcpyHostToDevice, h->st));
-    HIP_TRY(hipStreamSynchronize(h->st));   // hdr is on this stack frame
-    launch_copy(dst + EDL_SNAPSHOT_HEADER_BYTES, h->w(), 4 * (size_t)P, h->st);
-    launch_copy(dst + EDL_SNAPSHOT_HEADER_BYTES + 4 * (size_t)P, h->v(), 4 * (size_t)P, h->st);
-    size_t at = EDL_SNAPSHOT_HEADER_BYTES + 8 * (size_t)P;
-    if (h->adam()) { launch_copy(dst + at, h->s2(), 4 * (size_t)P, h->st); at += 4 * (size_t)P; }
-    launch_copy(dst + at, h->running(), 4 * (size_t)R, h->st);
+    memcpy(&hdr, &sh, sizeof(sh));
+    ImageParts parts = state_parts(h);
+    float* at = (float*)((char*)dev_dst + EDL_SNAPSHOT_HEADER_BYTES);
+    for (int q = 0; q < kImageParts; ++q) { parts.dst[q] = at; at += parts.n[q]; }
+    launch_image(parts, hdr, dev_dst, h->st);
     HIP_TRY(hipGetLastError());
     if (out_written) *out_written = need;
     return EDL_OK;
@@ -1409,9 +1418,12 @@ int32_t edl_restore(edl_handle* h, const void* dev_src, size_t len) {
     const int64_t P = h->g.P, R = h->g.R;
     const size_t need = EDL_SNAPSHOT_HEADER_BYTES + 4 * (size_t)h->state_floats();
     if (len < need) { set_error("snapshot image of %zu bytes is shorter than %zu", len, need); return EDL_ERANGE; }
+    // the header is read back through pinned memory (the loss staging, idle between calls)
     SnapshotHeader sh;
-    HIP_TRY(hipMemcpyAsync(&sh, dev_src, sizeof(sh), hipMemcpyDeviceToHost, h->st));
+    static_assert(sizeof(SnapshotHeader) <= kStageBytes, "header fits the staging");
+    HIP_TRY(hipMemcpyAsync(h->loss_host, dev_src, sizeof(sh), hipMemcpyDeviceToHost, h->st));
     HIP_TRY(hipStreamSynchronize(h->st));
+    memcpy(&sh, h->loss_host, sizeof(sh));
     if (sh.magic != EDL_SNAPSHOT_MAGIC || sh.version != 1) { set_error("not a snapshot image"); return EDL_EINVAL; }
     if (sh.P != P || sh.R != R || (int32_t)sh.model != h->cfg.model) { set_error("snapshot is of another model (P=%lld, R=%lld)", (long long)sh.P, (long long)sh.R); return EDL_EINVAL; }
     if (sh.N != h->cfg.N || sh.B != h->cfg.B) { set_error("snapshot is of a job with N=%lld B=%lld", (long long)sh.N, (long long)sh.B); return EDL_EINVAL; }
@@ -1422,12 +1434,10 @@ int32_t edl_restore(edl_handle* h, const void* dev_src, size_t len) {
         set_error("snapshot header holds Adam coefficients outside their range");
         return EDL_EINVAL;
     }
-    const char* src = (const char*)dev_src;
-    launch_copy(h->w(), src + EDL_SNAPSHOT_HEADER_BYTES, 4 * (size_t)P, h->st);
-    launch_copy(h->v(), src + EDL_SNAPSHOT_HEADER_BYTES + 4 * (size_t)P, 4 * (size_t)P, h->st);
-    size_t at = EDL_SNAPSHOT_HEADER_BYTES + 8 * (size_t)P;
-    if (h->adam()) { launch_copy(h->s2(), src + at, 4 * (size_t)P, h->st); at += 4 * (size_t)P; }
-    launch_copy(h->running(), src + at, 4 * (size_t)R, h->st);
+    ImageParts parts = state_parts(h);
+    const float* at = (const float*)((const char*)dev_src + EDL_SNAPSHOT_HEADER_BYTES);
+    for (int q = 0; q < kImageParts; ++q) { parts.dst[q] = (float*)parts.src[q]; parts.src[q] = at; at += parts.n[q]; }
+    launch_image(parts, ImageHeader(), nullptr, h->st);
     HIP_TRY(hipGetLastError());
     // job meta-data travels with the model (section 4.2): the joiner takes over the seed, the progress and the
     // optimizer's coefficients, whatever it was created with

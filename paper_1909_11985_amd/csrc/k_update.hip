@@ -169,6 +169,12 @@ __global__ __launch_bounds__(256) void average_update_wide_kernel(GradPtrs gp, f
     }
 }
 
+// w and v start at the same place of 4 KB pages of opposite parity (see launch_average_update)
+static bool on_alternating_pages(const float* w, const float* v) {
+    const uintptr_t wv = (uintptr_t)w ^ (uintptr_t)v;
+    return (wv & 4095) == 0 && ((wv >> 12) & 1) != 0;
+}
+
 template <int NP, int U, int NT>
 static void launch_update_wide(int grid, const GradPtrs& grads, float* w, float* v, uint16_t* w16, int64_t nvec, int64_t P,
                                float lr, float momentum, float wd, hipStream_t st) {
@@ -209,9 +215,12 @@ void launch_average_update(int p, const GradPtrs& grads, float* w, float* v, uin
     } while (0)
     // the wave-wide walk (upd_wide = vectors per lane, 0 = the kernel above, -1 = by p), upd_nt = non-temporal flags
     // (-1 = by p), upd_blocks > 0 = a grid-stride launch of that many workgroups
-    // Measured on the 138 M-parameter state (update sweep, MI355X): the wave-wide walk with non-temporal
-    // gradient loads and bf16 store gives 5.9 / 5.7 / 5.7 TB/s at p = 1 / 2 / 4 with one vector per lane (the kernel
-    // above: 5.4 / 5.3 / 5.2), and 5.6 TB/s at p = 8 with four vectors per lane and w, v non-temporal too (5.3).
+    // Measured on arrays of separate allocations (TB/s at p = 1 / 3 / 4 / 8; plain kernel above: 5.6 / 5.5 / 5.3 / 5.2).
+    // While w and v fit the 256 MB Infinity Cache they stay there from one update to the next, and only the gradients
+    // (read once) and the bf16 copy are non-temporal: 25.6 M parameters 6.7 / 6.8 / 6.8 / 6.7 with one vector per lane,
+    // two from p = 8 on (w, v non-temporal as well: 5.9 / 5.5 / 5.7 / 5.8).  Larger states pass through it for nothing:
+    // all streams non-temporal, 138 M parameters 6.2 / 5.9 / 5.7 / 5.65 (gradients and copy only: 6.0 / 5.7 / 5.5 /
+    // 5.5; more vectors per lane: within 2% either way, by the placement of the arrays).
     // Where w and v start on 4 KB boundaries of opposite parity (address bit 12; the library's own arena
     // alternates it from one state array to the next), their pieces no longer meet in the same half of the
     // memory system at the same moment, and one vector per lane is the best walk for every p.  At the end of
@@ -221,12 +230,12 @@ void launch_average_update(int p, const GradPtrs& grads, float* w, float* v, uin
     // 5.8 / 5.5 / 5.6 / 5.6): the previous launch's stores are still being written back.
     // (a piece of the arrays that starts at the same offset of both keeps that relation: same position inside the
     // page, pages of opposite parity)
-    const uintptr_t wv = (uintptr_t)w ^ (uintptr_t)v;
-    const bool alternating = (wv & 4095) == 0 && ((wv >> 12) & 1) != 0;
+    const bool alternating = on_alternating_pages(w, v);
     int wide = (int)tune().upd_wide, nt = (int)tune().upd_nt;
-    if (wide < 0) wide = alternating ? 1 : p >= 8 ? 4 : 1;
-    if (nt < 0) nt = alternating ? 3 : p >= 8 ? 7 : 3;
-    if (wide > 0 && (p == 1 || p == 2 || p == 4 || p == 8)) {
+    const bool cached = 8.0 * (double)P <= 256e6;
+    if (wide < 0) wide = alternating ? 1 : (cached && p >= 8) ? 2 : 1;
+    if (nt < 0) nt = (alternating || cached) ? 3 : 7;
+    if (wide > 0 && (p >= 1 && p <= 8)) {
         int wgrid = (int)std::max<int64_t>(1, (nvec + 256 * wide - 1) / (256 * wide));
         if (tune().upd_blocks > 0 && wgrid > tune().upd_blocks) wgrid = (int)tune().upd_blocks;
         if (max_blocks > 0 && wgrid > max_blocks) wgrid = max_blocks;
@@ -234,7 +243,11 @@ void launch_average_update(int p, const GradPtrs& grads, float* w, float* v, uin
         switch (p) {
             case 1: done = launch_update_wide_np<1>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
             case 2: done = launch_update_wide_np<2>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
+            case 3: done = launch_update_wide_np<3>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
             case 4: done = launch_update_wide_np<4>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
+            case 5: done = launch_update_wide_np<5>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
+            case 6: done = launch_update_wide_np<6>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
+            case 7: done = launch_update_wide_np<7>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
             default: done = launch_update_wide_np<8>(wide, nt, wgrid, grads, w, v, w16, nvec, P, lr, momentum, wd, st); break;
         }
         if (done) return;
@@ -295,7 +308,8 @@ __device__ __forceinline__ void adam_one(float g, float& w, float& m, float& s, 
     w -= a.lr * (m * a.c1) / (sqrtf(s * a.c2) + a.eps);
 }
 
-template <int NP, bool WEIGHTED, bool SHADOW>
+// NP > 0: p fixed at compile time, all loads in flight together; NT as in average_update_wide_kernel.
+template <int NP, bool WEIGHTED, bool SHADOW, int NT>
 __global__ __launch_bounds__(256) void adam_update_kernel(GradPtrs gp, ShardShares sh, int p, float* __restrict__ w,
                                                           float* __restrict__ m, float* __restrict__ s,
                                                           uint16_t* __restrict__ w16, int64_t nvec, int64_t P, AdamCoef a) {
@@ -303,39 +317,53 @@ __global__ __launch_bounds__(256) void adam_update_kernel(GradPtrs gp, ShardShar
     const float inv_p = 1.0f / (float)np;
     const int64_t step = (int64_t)gridDim.x * blockDim.x;   // see average_update_kernel
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += step) {
-        float4 wi = reinterpret_cast<float4*>(w)[i];
-        float4 mi = reinterpret_cast<float4*>(m)[i];
-        float4 si = reinterpret_cast<float4*>(s)[i];
+        f32x4* const wp = reinterpret_cast<f32x4*>(w) + i;
+        f32x4* const mp = reinterpret_cast<f32x4*>(m) + i;
+        f32x4* const sp = reinterpret_cast<f32x4*>(s) + i;
+        const f32x4 w0 = (NT & 4) ? __builtin_nontemporal_load(wp) : *wp;
+        const f32x4 m0 = (NT & 4) ? __builtin_nontemporal_load(mp) : *mp;
+        const f32x4 s0 = (NT & 4) ? __builtin_nontemporal_load(sp) : *sp;
         // the gradient buffers are read once and never again: non-temporal loads (as is the bf16 store below)
-        const f32x4 g0 = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(gp.g[0]) + i);
-        float4 g = make_float4(g0[0], g0[1], g0[2], g0[3]);
-        if (WEIGHTED) { g.x *= sh.share[0]; g.y *= sh.share[0]; g.z *= sh.share[0]; g.w *= sh.share[0]; }
+        f32x4 g = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(gp.g[0]) + i);
         if (NP > 0) {
             f32x4 t[NP > 1 ? NP - 1 : 1];
             #pragma unroll
             for (int k = 1; k < NP; ++k) t[k - 1] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(gp.g[k]) + i);
+            if (WEIGHTED) g *= sh.share[0];
             #pragma unroll
             for (int k = 1; k < NP; ++k) {
                 const float c = WEIGHTED ? sh.share[k] : 1.0f;
-                g.x += c * t[k - 1][0]; g.y += c * t[k - 1][1]; g.z += c * t[k - 1][2]; g.w += c * t[k - 1][3];
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] += c * t[k - 1][e];
             }
         } else {
+            if (WEIGHTED) g *= sh.share[0];
             for (int k = 1; k < np; ++k) {
                 const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(gp.g[k]) + i);
                 const float c = WEIGHTED ? sh.share[k] : 1.0f;
-                g.x += c * t[0]; g.y += c * t[1]; g.z += c * t[2]; g.w += c * t[3];
+                #pragma unroll
+                for (int e = 0; e < 4; ++e) g[e] += c * t[e];
             }
         }
-        if (!WEIGHTED) { g.x *= inv_p; g.y *= inv_p; g.z *= inv_p; g.w *= inv_p; }
-        adam_one(g.x, wi.x, mi.x, si.x, a);
-        adam_one(g.y, wi.y, mi.y, si.y, a);
-        adam_one(g.z, wi.z, mi.z, si.z, a);
-        adam_one(g.w, wi.w, mi.w, si.w, a);
-        reinterpret_cast<float4*>(m)[i] = mi;
-        reinterpret_cast<float4*>(s)[i] = si;
-        reinterpret_cast<float4*>(w)[i] = wi;
+        if (!WEIGHTED) g *= inv_p;
+        f32x4 wn, mn, sn;
+        #pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float we = w0[e], me = m0[e], se = s0[e];
+            adam_one(g[e], we, me, se, a);
+            wn[e] = we; mn[e] = me; sn[e] = se;
+        }
+        if (NT & 4) {
+            __builtin_nontemporal_store(mn, mp);
+            __builtin_nontemporal_store(sn, sp);
+            __builtin_nontemporal_store(wn, wp);
+        } else {
+            *mp = mn;
+            *sp = sn;
+            *wp = wn;
+        }
         if (SHADOW) {
-            const u32x2 packed = {pack2_bf16(wi.x, wi.y), pack2_bf16(wi.z, wi.w)};
+            const u32x2 packed = {pack2_bf16(wn[0], wn[1]), pack2_bf16(wn[2], wn[3])};
             __builtin_nontemporal_store(packed, reinterpret_cast<u32x2*>(w16) + i);
         }
     }
@@ -353,10 +381,28 @@ __global__ __launch_bounds__(256) void adam_update_kernel(GradPtrs gp, ShardShar
 }
 
 template <int NP, bool WEIGHTED>
-static void launch_adam_t(int grid, const GradPtrs& grads, const ShardShares& sh, int p, float* w, float* m, float* s,
+static void launch_adam_t(int nt, int grid, const GradPtrs& grads, const ShardShares& sh, int p, float* w, float* m, float* s,
                           uint16_t* w16, int64_t nvec, int64_t P, const AdamCoef& a, hipStream_t st) {
-    if (w16) hipLaunchKernelGGL((adam_update_kernel<NP, WEIGHTED, true>), dim3(grid), dim3(256), 0, st, grads, sh, p, w, m, s, w16, nvec, P, a);
-    else hipLaunchKernelGGL((adam_update_kernel<NP, WEIGHTED, false>), dim3(grid), dim3(256), 0, st, grads, sh, p, w, m, s, w16, nvec, P, a);
+#define EDL_ADAM(SHADOW, NT) hipLaunchKernelGGL((adam_update_kernel<NP, WEIGHTED, SHADOW, NT>), dim3(grid), dim3(256), 0, st, grads, sh, p, w, m, s, w16, nvec, P, a)
+    if (w16) { if (nt & 4) EDL_ADAM(true, 7); else EDL_ADAM(true, 3); }
+    else { if (nt & 4) EDL_ADAM(false, 7); else EDL_ADAM(false, 3); }
+#undef EDL_ADAM
+}
+
+template <bool WEIGHTED>
+static void launch_adam_np(int nt, int grid, const GradPtrs& grads, const ShardShares& sh, int p, float* w, float* m, float* s,
+                           uint16_t* w16, int64_t nvec, int64_t P, const AdamCoef& a, hipStream_t st) {
+    switch (p) {
+        case 1: launch_adam_t<1, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 2: launch_adam_t<2, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 3: launch_adam_t<3, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 4: launch_adam_t<4, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 5: launch_adam_t<5, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 6: launch_adam_t<6, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 7: launch_adam_t<7, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        case 8: launch_adam_t<8, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+        default: launch_adam_t<0, WEIGHTED>(nt, grid, grads, sh, p, w, m, s, w16, nvec, P, a, st); break;
+    }
 }
 
 void launch_adam_update(int p, const GradPtrs& grads, const ShardShares* shares, float* w, float* m, float* s, uint16_t* w16,
@@ -369,22 +415,17 @@ void launch_adam_update(int p, const GradPtrs& grads, const ShardShares* shares,
     // p gradient reads + w, m, s read and written (+ the bf16 copy)
     ProfScope ps("adam_update", 0.0, (4.0 * p + 24.0 + (w16 ? 2.0 : 0.0)) * (double)P, st);
     const ShardShares none = {};
-    if (shares) {
-        launch_adam_t<0, true>(grid, grads, *shares, p, w, m, s, w16, nvec, P, a, st);
-        return;
-    }
-    switch (p) {
-        case 1: launch_adam_t<1, false>(grid, grads, none, p, w, m, s, w16, nvec, P, a, st); break;
-        case 2: launch_adam_t<2, false>(grid, grads, none, p, w, m, s, w16, nvec, P, a, st); break;
-        case 4: launch_adam_t<4, false>(grid, grads, none, p, w, m, s, w16, nvec, P, a, st); break;
-        case 8: launch_adam_t<8, false>(grid, grads, none, p, w, m, s, w16, nvec, P, a, st); break;
-        default: launch_adam_t<0, false>(grid, grads, none, p, w, m, s, w16, nvec, P, a, st); break;
-    }
+    // w, m, s non-temporal as well for states well beyond the Infinity Cache (TB/s at p = 1 / 4 / 8: 138 M parameters
+    // 5.6 / 5.6 / 5.4 -> 5.9 / 5.9 / 5.5; 25.6 M, 306 MB, the other way round: 6.2 against 5.8 at p = 1), but not on
+    // the arena's alternating pages (AlexNet's 61 M at p = 2: 337 us, with them 367)
+    const int nt = tune().upd_nt >= 0 ? (int)tune().upd_nt : (12.0 * (double)P > 512e6 && !on_alternating_pages(w, m)) ? 7 : 3;
+    if (shares) launch_adam_np<true>(nt, grid, grads, *shares, p, w, m, s, w16, nvec, P, a, st);
+    else launch_adam_np<false>(nt, grid, grads, none, p, w, m, s, w16, nvec, P, a, st);
 }
 
 // ---------------------------------------------------------------------------
-// plain copy (snapshot / restore): 16-byte vectors when source, destination
-// and length allow it (the large state arrays do), else 4-byte or 1-byte units
+// plain copy: 16-byte vectors when source, destination
+// and length allow it, else 4-byte or 1-byte units
 // ---------------------------------------------------------------------------
 template <typename U>
 __global__ __launch_bounds__(256) void copy_kernel(U* __restrict__ dst, const U* __restrict__ src, int64_t n) {
@@ -406,6 +447,40 @@ void launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st) {
         const int64_t n = (int64_t)bytes;
         hipLaunchKernelGGL(copy_kernel<uint8_t>, dim3(grid_for(n, 256, 1 << 30)), dim3(256), 0, st, (uint8_t*)dst, (const uint8_t*)src, n);
     }
+}
+
+// ---------------------------------------------------------------------------
+// The state image (snapshot / restore): its header, if one is given, and up to four float arrays in one launch.  A
+// workgroup copies 4 KB of one array; the arrays need 4-byte alignment only (the image packs them without padding),
+// which the 16-byte accesses of this memory path take as they are.  HBM-bound; one launch instead of four and a
+// header copied from host memory (with a wait for it) takes the hand-over of ResNet-50's 205 MB from 183 to 152 us.
+// ---------------------------------------------------------------------------
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+__global__ __launch_bounds__(256) void image_kernel(ImageParts parts, ImageHeader hdr, uint32_t* __restrict__ header_dst) {
+    if (header_dst != nullptr && blockIdx.x == 0 && threadIdx.x < kImageHeaderBytes / 4) header_dst[threadIdx.x] = hdr.words[threadIdx.x];
+    int part = 0;
+    #pragma unroll
+    for (int q = 1; q < kImageParts; ++q) part = (int)blockIdx.x >= parts.block0[q] ? q : part;
+    const float* src = parts.src[part];
+    float* dst = parts.dst[part];
+    const int64_t n = parts.n[part], i = ((int64_t)((int)blockIdx.x - parts.block0[part]) * 256 + threadIdx.x) * 4;
+    if (i + 4 <= n) *reinterpret_cast<f32x4_a4*>(dst + i) = *reinterpret_cast<const f32x4_a4*>(src + i);
+    else for (int64_t e = i; e < n; ++e) dst[e] = src[e];
+}
+
+void launch_image(const ImageParts& in, const ImageHeader& hdr, void* header_dst, hipStream_t st) {
+    ImageParts parts = in;
+    int blocks = 0;
+    double bytes = 0;
+    for (int q = 0; q < kImageParts; ++q) {
+        parts.block0[q] = blocks;
+        blocks += (int)((parts.n[q] + 1023) / 1024);
+        bytes += 4.0 * (double)parts.n[q];
+    }
+    if (blocks == 0) blocks = 1;
+    ProfScope ps("copy", 0.0, 2.0 * bytes, st);
+    hipLaunchKernelGGL(image_kernel, dim3(blocks), dim3(256), 0, st, parts, hdr, (uint32_t*)header_dst);
 }
 
 __global__ __launch_bounds__(256) void fill_kernel(float* dst, float value, int64_t n) {

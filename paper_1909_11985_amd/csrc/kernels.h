@@ -66,6 +66,11 @@ void launch_adam_update(int p, const GradPtrs& grads, const ShardShares* shares,
                         int64_t P, float lr, float beta1, float beta2, float eps, float wd, float c1, float c2, hipStream_t st,
                         int max_blocks = 0);
 void launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st);
+// The state image: arrays of floats (n = 0: none) copied in one launch, its header written from the arguments
+constexpr int kImageParts = 4, kImageHeaderBytes = 256;
+struct ImageHeader { uint32_t words[kImageHeaderBytes / 4]; };
+struct ImageParts { float* dst[kImageParts]; const float* src[kImageParts]; int64_t n[kImageParts]; int block0[kImageParts]; };
+void launch_image(const ImageParts& parts, const ImageHeader& hdr, void* header_dst /* null: none */, hipStream_t st);
 void launch_fill_f32(float* dst, float value, int64_t n, hipStream_t st);
 // dst[c][r][s][k] = cast(src[k][r][s][c]) (weights for the input-gradient contraction) for every
 // layer of a model in one launch, from a table in device memory
