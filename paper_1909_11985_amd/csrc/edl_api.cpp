@@ -155,7 +155,7 @@ int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shard
             if (op.x == 0 && L.cpad != tx.C) dwpad_bytes = std::max<int64_t>(dwpad_bytes, (int64_t)op.K * op.R * op.S * L.cpad * 4 * shards);
             for (int q = 1; q <= shards; ++q)
                 L.wgrad_scratch_bytes = std::max<int64_t>(
-                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(geom_padded(g, op, std::max(1, std::min(c.max_shard, samples / q)), L.cpad), q));
+                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(c.dtype, geom_padded(g, op, std::max(1, std::min(c.max_shard, samples / q)), L.cpad), q));
             // the cut of a forward / dgrad reduction depends on the size of the pass: cover every size up to the largest
             for (int n = 1; n <= samples; n = n < 8 ? n + 1 : n + n / 4)
                 L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,

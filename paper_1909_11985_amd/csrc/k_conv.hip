@@ -1277,7 +1277,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
 // ---------------------------------------------------------------------------
 // host side: tile selection and launch
 // ---------------------------------------------------------------------------
-enum TileCfg { T128x128, T128x64, T128x32, T64x64 };
+enum TileCfg { T128x128, T128x64, T128x32, T64x64, T32x128 };   // T32x128: float32 weight gradients only
 
 #ifndef EDL_PF_BIG
 #define EDL_PF_BIG 1
@@ -1408,6 +1408,10 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<S
             hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK_BIG, true, PF_HALF, SHARDS>), grid, dim3(256), 0, st, a);
             break;
         case T128x32: hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, PF_BIG, SHARDS>), grid, dim3(256), 0, st, a); break;
+        case T32x128:
+            if constexpr (MODE == CONV_WGRAD && sizeof(T) == 4)
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 1, 4, 1, 1, BK, true, 1, SHARDS>), grid, dim3(256), 0, st, a);
+            break;
         default:
             if constexpr (MODE != CONV_WGRAD && sizeof(T) == 2) {
                 // Three stages of a 64x64 tile are 48 KB of LDS: three workgroups per CU, 768 on the chip.  A launch
@@ -1427,6 +1431,7 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<S
 }
 
 static const char* conv_label(int dtype, int mode, TileCfg t) {
+    if (t == T32x128) return "conv_wgrad_f32_32x128";
     static const char* names[2][3][4] = {
         {{"conv_fwd_f32_128x128", "conv_fwd_f32_128x64", "conv_fwd_f32_128x32", "conv_fwd_f32_64x64"},
          {"conv_dgrad_f32_128x128", "conv_dgrad_f32_128x64", "conv_dgrad_f32_128x32", "conv_dgrad_f32_64x64"},
@@ -1724,12 +1729,13 @@ struct WgradPlan {
 // layers whose output already gives enough tiles are split little or not at all.
 // g.N: samples of the largest shard.  shards: how many of them the launch covers; they are as good as cuts for filling
 // the chip and cost no partial tiles (one cut per shard: straight into the worker's gradient).
-static WgradPlan plan_wgrad(const ConvGeom& g, int shards) {
+static WgradPlan plan_wgrad(int dtype, const ConvGeom& g, int shards) {
     WgradPlan p;
     const int M = g.K, Nn = g.R * g.S * g.C, Kred = g.N * g.Ho * g.Wo;
     const int64_t t128 = (int64_t)((M + 127) / 128) * ((Nn + 127) / 128);
     const int64_t t64 = (int64_t)((M + 63) / 64) * ((Nn + 63) / 64);
     if (Nn <= 32) p.t = T128x32;
+    else if (dtype != 1 && M <= 32) p.t = T32x128;      // a 64-row tile would contract rows that are not there
     else if (M <= 64 || Nn <= 64) p.t = (Nn <= 64 && M >= 128) ? T128x64 : T64x64;
     else if (t128 >= 128) p.t = T128x128;
     else if (t64 >= 256 && Kred < 4096) p.t = T64x64;   // long reductions are cut instead (below)
@@ -1738,6 +1744,7 @@ static WgradPlan plan_wgrad(const ConvGeom& g, int shards) {
         case T128x128: p.bm = 128; p.bn = 128; break;
         case T128x64: p.bm = 128; p.bn = 64; break;
         case T128x32: p.bm = 128; p.bn = 32; break;
+        case T32x128: p.bm = 32; p.bn = 128; break;
         default: p.bm = 64; p.bn = 64; break;
     }
     p.tiles = (int64_t)((M + p.bm - 1) / p.bm) * ((Nn + p.bn - 1) / p.bn);
@@ -1754,7 +1761,11 @@ static WgradPlan plan_wgrad(const ConvGeom& g, int shards) {
     // leaves exposed.  Measured on VGG-16: 5.28 -> 5.14 ms per step; three per CU (a second, ragged round
     // of workgroups) is slower again.
     const int long_target = (int)tune().wgrad_long_blocks, long_ks = (int)tune().wgrad_long_ks;
-    const int64_t more = std::min<int64_t>(long_target / tiles, Kred / (long_ks > 0 ? long_ks : 1));
+    int64_t more = std::min<int64_t>(long_target / tiles, Kred / (long_ks > 0 ? long_ks : 1));
+    // float32: a reduction step is sixteen times the matrix work of a bf16 one (no operand latency to hide behind
+    // fewer workgroups), so the chip is filled: three workgroups per CU as long as each keeps 256 elements and the
+    // partial results stay small (4 MB).  ResNet-20, 8 shards of 16: 790 -> 480 us of weight gradients per step.
+    if (dtype != 1) more = std::max(more, std::min<int64_t>(std::min<int64_t>(768 / tiles, Kred / 256), (1 << 20) / ((int64_t)M * Nn * shards)));
     if (more > splits) splits = more;
     const int64_t max_splits = (Kred + 255) / 256;  // at least 4 reduction steps per split
     if (splits > max_splits) splits = max_splits;
@@ -1766,8 +1777,8 @@ static WgradPlan plan_wgrad(const ConvGeom& g, int shards) {
     return p;
 }
 
-size_t conv_wgrad_scratch_bytes(const ConvGeom& g, int shards) {
-    const WgradPlan p = plan_wgrad(g, shards);
+size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int shards) {
+    const WgradPlan p = plan_wgrad(dtype, g, shards);
     if (p.splits <= 1) return 0;
     return (size_t)shards * p.splits * g.K * g.R * g.S * g.C * sizeof(float);
 }
@@ -1777,7 +1788,7 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     const int VEC = dtype == 1 ? 8 : 4;
     ConvGeom one = g;
     one.N = S.largest();
-    WgradPlan p = plan_wgrad(one, S.p);
+    WgradPlan p = plan_wgrad(dtype, one, S.p);
     ConvArgsShards a = base_args(g);
     a.A = dy; a.B = x;
     a.M = g.K; a.Nn = g.R * g.S * g.C; a.Kred = g.N * g.Ho * g.Wo;

@@ -141,7 +141,7 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g);
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st);
 // g.N: samples of the largest shard
-size_t conv_wgrad_scratch_bytes(const ConvGeom& g, int p);
+size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int p);
 
 // ---- batch norm, bias / ReLU backward --------------------------------------
 // floats the column reductions below take as scratch over the given rows of p shards

@@ -18,7 +18,7 @@ struct Tune {
     int64_t bk64_kred = 1024;         // 128x128 tiles take full-length reduction steps from this reduction length on
     int64_t xcd = 1;                  // die-chunked tile order
     int64_t order = -1;               // -1: tile order by operand size; 0 / 1: rows / columns fastest
-    int64_t splitk_tiles = 300;       // forward / dgrad problems of fewer tiles have their reduction cut ...
+    int64_t splitk_tiles = 250;       // forward / dgrad problems of fewer tiles have their reduction cut ...
     int64_t splitk_target = 320;      // ... towards this many workgroups
     int64_t fused_stats = 1;          // batch-norm sums out of the forward convolution's epilogue
     int64_t held_stats = 1;           // ... also for a block's last convolution, held while the shortcut's batch norm runs
