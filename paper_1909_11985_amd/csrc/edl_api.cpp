@@ -1084,7 +1084,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                     }
                     if (launch_maxpool_backward(dt, h->grad(op.y), h->at<uint8_t>(h->L.pool_arg[ii]), h->grad(op.x),
                                                 written[(size_t)sx] != 0, n, tx.H, tx.W, tx.C, op.R, op.stride, op.pad, ty.H,
-                                                ty.W, relu_act, st))
+                                                ty.W, relu_act, h->act(op.y), st))
                         premasked_for = ii - 1;
                     written[(size_t)sx] = 1;
                 }

@@ -81,45 +81,81 @@ __global__ __launch_bounds__(256) void maxpool_bwd_kernel(const T* __restrict__ 
     }
 }
 
-// 16-byte channel vectors per lane (C a multiple of the vector width)
-template <typename T>
+// Work items of the vector kernels below: blocks of 256 channel vectors of one image row, so that only the vector's
+// place within the row is divided per lane (by a shift for the usual channel counts), in 32 bits; the row and image are
+// uniform.  With one flat 64-bit index the divisions took longer than the memory (VGG-16's pools at a shard of 32: 182
+// us backward and 110 us forward per step).
+struct RowItems { int per_row, vecs, cv, cv_shift; };     // blocks per row, vectors per row, vectors per pixel, log2 or -1
+static RowItems row_items(int W, int C, int vec) {
+    RowItems r;
+    r.cv = C / vec;
+    r.vecs = W * r.cv;
+    r.per_row = (r.vecs + 255) / 256;
+    r.cv_shift = -1;
+    for (int k = 0; k < 16; ++k)
+        if (r.cv == 1 << k) r.cv_shift = k;
+    return r;
+}
+// row of the image stack, pixel and first vector of this lane; false for the lanes past the row's end
+__device__ __forceinline__ bool locate_vector(const RowItems& r, int& row, int& pixel, int& cvec) {
+    row = blockIdx.x / r.per_row;
+    const int v = (blockIdx.x - row * r.per_row) * 256 + threadIdx.x;
+    pixel = r.cv_shift >= 0 ? v >> r.cv_shift : v / r.cv;
+    cvec = v - pixel * r.cv;
+    return v < r.vecs;
+}
+
+// 16-byte channel vectors per lane (C a multiple of the vector width); window size and stride known at compile time
+// (KK = 0: not), so that all of a window's loads are in flight together
+template <typename T, int KK>
 __global__ __launch_bounds__(256) void maxpool_fwd_vec_kernel(const T* __restrict__ x, T* __restrict__ y,
-                                                              uint8_t* __restrict__ arg, int N, int H, int W, int C, int k,
+                                                              uint8_t* __restrict__ arg, RowItems items, int H, int W, int C, int kk,
                                                               int stride, int pad, int Ho, int Wo) {
     constexpr int VEC = Elem<T>::VEC;
-    const int cv = C / VEC;
-    const int64_t total = (int64_t)N * Ho * Wo * cv;
-    const int64_t step = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += step) {
-        const int c0 = (int)(i % cv) * VEC;
-        int64_t t = i / cv;
-        const int wo = (int)(t % Wo); t /= Wo;
-        const int ho = (int)(t % Ho);
-        const int n = (int)(t / Ho);
-        float best[VEC];
-        int where[VEC];
+    const int k = KK > 0 ? KK : kk;
+    int row, wo, cvec;
+    if (!locate_vector(items, row, wo, cvec)) return;
+    const int n = row / Ho, ho = row - n * Ho, c0 = cvec * VEC;
+    float best[VEC];
+    int where[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) { best[e] = 0.f; where[e] = 255; }
+    const int h0 = ho * stride - pad, w0 = wo * stride - pad;
+    auto tap = [&](const Vec16<T>& v, int t) {
         #pragma unroll
-        for (int e = 0; e < VEC; ++e) { best[e] = 0.f; where[e] = 255; }
-        for (int r = 0; r < k; ++r) {
-            const int h = ho * stride - pad + r;
-            if (h < 0 || h >= H) continue;
-            for (int s = 0; s < k; ++s) {
-                const int w = wo * stride - pad + s;
-                if (w < 0 || w >= W) continue;
-                const Vec16<T> v = load_vec(x + (((int64_t)n * H + h) * W + w) * C + c0);
-                #pragma unroll
-                for (int e = 0; e < VEC; ++e) {
-                    const float f = Elem<T>::to_f32(v.e[e]);
-                    if (where[e] == 255 || f > best[e]) { best[e] = f; where[e] = r * k + s; }
-                }
-            }
+        for (int e = 0; e < VEC; ++e) {
+            const float f = Elem<T>::to_f32(v.e[e]);
+            if (where[e] == 255 || f > best[e]) { best[e] = f; where[e] = t; }
         }
-        const int64_t o = ((((int64_t)n * Ho + ho) * Wo + wo) * C) + c0;
-        Vec16<T> out;
+    };
+    if (KK > 0) {
+        Vec16<T> v[KK > 0 ? KK * KK : 1];
         #pragma unroll
-        for (int e = 0; e < VEC; ++e) { out.e[e] = Elem<T>::from_f32(best[e]); arg[o + e] = (uint8_t)where[e]; }
-        store_vec(y + o, out);
+        for (int r = 0; r < KK; ++r)
+            #pragma unroll
+            for (int s = 0; s < KK; ++s) {      // a tap outside the image reads the nearest pixel and is ignored
+                const int h = min(max(h0 + r, 0), H - 1), w = min(max(w0 + s, 0), W - 1);
+                v[r * KK + s] = load_vec(x + ((int64_t)(n * H + h) * W + w) * C + c0);
+            }
+        #pragma unroll
+        for (int r = 0; r < KK; ++r)
+            #pragma unroll
+            for (int s = 0; s < KK; ++s)
+                if ((unsigned)(h0 + r) < (unsigned)H && (unsigned)(w0 + s) < (unsigned)W) tap(v[r * KK + s], r * KK + s);
+    } else {
+        for (int r = 0; r < k; ++r)
+            for (int s = 0; s < k; ++s)
+                if ((unsigned)(h0 + r) < (unsigned)H && (unsigned)(w0 + s) < (unsigned)W)
+                    tap(load_vec(x + ((int64_t)(n * H + h0 + r) * W + w0 + s) * C + c0), r * k + s);
     }
+    const int64_t o = ((int64_t)row * Wo + wo) * C + c0;
+    Vec16<T> out;
+    uint8_t am[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) { out.e[e] = Elem<T>::from_f32(best[e]); am[e] = (uint8_t)where[e]; }
+    if (VEC == 8) *reinterpret_cast<uint2*>(arg + o) = *reinterpret_cast<const uint2*>(am);
+    else *reinterpret_cast<uint32_t*>(arg + o) = *reinterpret_cast<const uint32_t*>(am);
+    store_vec(y + o, out);
 }
 
 template <typename T>
@@ -176,27 +212,24 @@ __global__ __launch_bounds__(256) void maxpool_bwd_vec_kernel(const T* __restric
 // NC = ceil(k / stride) per dimension.  All NC*NC loads are issued before the first use (a position outside
 // the output reads a clamped one and is ignored), instead of one load and one wait per tap.
 // MASK: the pooled tensor is the output of a ReLU; the gradient is stored already multiplied by (act > 0),
-// so that the producer's backward need not read its activation again.
+// so that the producer's backward need not read its activation again.  The pixel a window picked holds the window's
+// maximum: where a pixel has one window (NC = 1) the sign comes from the pooled value, a quarter of the bytes of the
+// activation; with several it is one load of the activation.
 template <typename T, int NC, bool MASK>
 __global__ __launch_bounds__(256) void maxpool_bwd_win_kernel(const T* __restrict__ dy, const uint8_t* __restrict__ arg,
-                                                              T* dx, const T* __restrict__ act, int accumulate, int N, int H,
-                                                              int W, int C, int k, int stride, int pad, int Ho, int Wo) {
+                                                              T* dx, const T* __restrict__ act, const T* __restrict__ pooled, int accumulate,
+                                                              RowItems items, int H, int W, int C, int k, int stride, int pad, int Ho, int Wo) {
     constexpr int VEC = Elem<T>::VEC;
-    const int cv = C / VEC;
-    const int64_t total = (int64_t)N * H * W * cv;
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int c0 = (int)(i % cv) * VEC;
-    int64_t t = i / cv;
-    const int w = (int)(t % W); t /= W;
-    const int h = (int)(t % H);
-    const int n = (int)(t / H);
+    int row, w, cvec;
+    if (!locate_vector(items, row, w, cvec)) return;
+    const int n = row / H, h = row - n * H, c0 = cvec * VEC;
     // output rows ho with ho*stride - pad <= h < ho*stride - pad + k: ho in [ho_hi - NC + 1, ho_hi]
     const int ho_hi = (h + pad) / stride, wo_hi = (w + pad) / stride;
     Vec16<T> v[NC][NC];
     uint8_t am[NC][NC][VEC];
     bool ok[NC][NC];
     int tap[NC][NC];
+    Vec16<T> old, sign;
     #pragma unroll
     for (int a = 0; a < NC; ++a) {
         #pragma unroll
@@ -206,17 +239,17 @@ __global__ __launch_bounds__(256) void maxpool_bwd_win_kernel(const T* __restric
             ok[a][b] = ho >= 0 && wo >= 0 && ho < Ho && wo < Wo && r < k && s2 < k;
             tap[a][b] = r * k + s2;
             const int hc = ho < 0 ? 0 : (ho >= Ho ? Ho - 1 : ho), wc = wo < 0 ? 0 : (wo >= Wo ? Wo - 1 : wo);
-            const int64_t o = (((int64_t)n * Ho + hc) * Wo + wc) * C + c0;
+            const int64_t o = ((int64_t)(n * Ho + hc) * Wo + wc) * C + c0;
             v[a][b] = load_vec(dy + o);
             if (VEC == 8) *reinterpret_cast<uint2*>(am[a][b]) = *reinterpret_cast<const uint2*>(arg + o);
             else *reinterpret_cast<uint32_t*>(am[a][b]) = *reinterpret_cast<const uint32_t*>(arg + o);
+            if (MASK && NC == 1) sign = load_vec(pooled + o);
         }
     }
-    const int64_t xo = (((int64_t)n * H + h) * W + w) * C + c0;
-    Vec16<T> old, av;
+    const int64_t xo = ((int64_t)row * W + w) * C + c0;
     old.u = make_uint4(0, 0, 0, 0);
     if (accumulate) old = load_vec(dx + xo);
-    if (MASK) av = load_vec(act + xo);
+    if (MASK && NC > 1) sign = load_vec(act + xo);
     float g[VEC];
     #pragma unroll
     for (int e = 0; e < VEC; ++e) g[e] = 0.f;
@@ -236,7 +269,7 @@ __global__ __launch_bounds__(256) void maxpool_bwd_win_kernel(const T* __restric
     }
     Vec16<T> out;
     #pragma unroll
-    for (int e = 0; e < VEC; ++e) out.e[e] = Elem<T>::from_f32((!MASK || Elem<T>::to_f32(av.e[e]) > 0.f) ? g[e] : 0.f);
+    for (int e = 0; e < VEC; ++e) out.e[e] = Elem<T>::from_f32((!MASK || Elem<T>::to_f32(sign.e[e]) > 0.f) ? g[e] : 0.f);
     store_vec(dx + xo, out);
 }
 
@@ -246,14 +279,15 @@ void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int
     const double esz = dtype == 1 ? 2.0 : 4.0;
     ProfScope ps("maxpool_fwd", 0.0, esz * (double)N * H * W * C + (esz + 1.0) * (double)N * Ho * Wo * C, st);
     const int vec = dtype == 1 ? 8 : 4;
-    if (C % vec == 0) {
-        const int vgrid = ew_grid((int64_t)N * Ho * Wo * (C / vec));
-        if (dtype == 1)
-            hipLaunchKernelGGL(maxpool_fwd_vec_kernel<bf16_t>, dim3(vgrid), dim3(256), 0, st, (const bf16_t*)x, (bf16_t*)y, arg,
-                               N, H, W, C, k, stride, pad, Ho, Wo);
-        else
-            hipLaunchKernelGGL(maxpool_fwd_vec_kernel<float>, dim3(vgrid), dim3(256), 0, st, (const float*)x, (float*)y, arg, N,
-                               H, W, C, k, stride, pad, Ho, Wo);
+    const RowItems items = row_items(Wo, C, vec);
+    if (C % vec == 0 && (double)N * Ho * items.per_row < 2147483648.0) {
+        const dim3 vgrid((unsigned)(N * Ho * items.per_row));
+#define EDL_POOL_FWD(TT, KK)                                                                                             \
+    hipLaunchKernelGGL((maxpool_fwd_vec_kernel<TT, KK>), vgrid, dim3(256), 0, st, (const TT*)x, (TT*)y, arg, items, H, W, C, k, \
+                       stride, pad, Ho, Wo)
+        if (dtype == 1) { if (k == 2) EDL_POOL_FWD(bf16_t, 2); else if (k == 3) EDL_POOL_FWD(bf16_t, 3); else EDL_POOL_FWD(bf16_t, 0); }
+        else { if (k == 2) EDL_POOL_FWD(float, 2); else if (k == 3) EDL_POOL_FWD(float, 3); else EDL_POOL_FWD(float, 0); }
+#undef EDL_POOL_FWD
         return;
     }
     if (dtype == 1)
@@ -265,22 +299,23 @@ void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int
 }
 
 bool launch_maxpool_backward(int dtype, const void* dy, const uint8_t* arg, void* dx, bool accumulate, int N, int H,
-                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const void* relu_act, hipStream_t st) {
+                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const void* relu_act, const void* relu_pooled, hipStream_t st) {
     const int grid = ew_grid((int64_t)N * H * W * C);
     const double esz = dtype == 1 ? 2.0 : 4.0;
     const int vec = dtype == 1 ? 8 : 4;
     const int nc = (k + stride - 1) / stride;
-    const int64_t lanes = C % vec == 0 ? (int64_t)N * H * W * (C / vec) : 0;
-    const bool win = C % vec == 0 && nc <= 2 && lanes < (int64_t)1 << 38;
+    const RowItems items = row_items(W, C, vec);
+    const bool win = C % vec == 0 && nc <= 2 && (double)N * H * items.per_row < 2147483648.0;
     const bool masked = win && relu_act != nullptr && !accumulate;
-    ProfScope ps("maxpool_bwd", 0.0, esz * (double)N * H * W * C * ((accumulate ? 2.0 : 1.0) + (masked ? 1.0 : 0.0)) + (esz + 1.0) * (double)N * Ho * Wo * C, st);
+    ProfScope ps("maxpool_bwd", 0.0, esz * (double)N * H * W * C * ((accumulate ? 2.0 : 1.0) + (masked && nc > 1 ? 1.0 : 0.0)) +
+                                       (esz * (masked && nc == 1 ? 2.0 : 1.0) + 1.0) * (double)N * Ho * Wo * C, st);
     if (C % vec == 0) {
         const int vgrid = ew_grid((int64_t)N * H * W * (C / vec));
         if (win) {
-            const dim3 g1((unsigned)((lanes + 255) / 256));
+            const dim3 g1((unsigned)(N * H * items.per_row));
 #define EDL_POOL_BWD(TT, NCC, MM)                                                                                               \
     hipLaunchKernelGGL((maxpool_bwd_win_kernel<TT, NCC, MM>), g1, dim3(256), 0, st, (const TT*)dy, arg, (TT*)dx, (const TT*)relu_act, \
-                       accumulate ? 1 : 0, N, H, W, C, k, stride, pad, Ho, Wo)
+                       (const TT*)relu_pooled, accumulate ? 1 : 0, items, H, W, C, k, stride, pad, Ho, Wo)
             if (dtype == 1) {
                 if (nc == 1) { if (masked) EDL_POOL_BWD(bf16_t, 1, true); else EDL_POOL_BWD(bf16_t, 1, false); }
                 else { if (masked) EDL_POOL_BWD(bf16_t, 2, true); else EDL_POOL_BWD(bf16_t, 2, false); }
