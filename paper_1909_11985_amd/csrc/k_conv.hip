@@ -131,8 +131,18 @@ struct ConvArgs {
 // argument loads that they keep from being hoisted) cost 0.3 to 0.9 us per launch, 2% of a ResNet-50 step at a shard
 // of 32.
 struct ConvArgsShards : ConvArgs { RowCut cut; };
-template <bool SHARDS> struct ArgsOf { typedef ConvArgs type; };
-template <> struct ArgsOf<true> { typedef ConvArgsShards type; };
+// The residue classes of a stride-2 input gradient in one launch.  Their row tiles take turns (a die gets a contiguous
+// run of tiles, and the classes contract one to four taps); what differs between them replaces the fields of ConvArgs of
+// the same names.
+struct ConvClass {
+    int ph, pw, Hc, Wc, r0, s0, nr, ns, M, Kred;
+    unsigned long long magic_hw, magic_w, magic_taps;
+};
+struct ConvArgsClasses : ConvArgs { int classes; ConvClass cls[4]; };
+enum LaunchKind { PLAIN, SHARDED, CLASSES };
+template <int KIND> struct ArgsOf { typedef ConvArgs type; typedef const ConvArgs& use; };
+template <> struct ArgsOf<SHARDED> { typedef ConvArgsShards type; typedef const ConvArgsShards& use; };
+template <> struct ArgsOf<CLASSES> { typedef ConvArgsClasses type; typedef ConvArgs use; };   // a copy, completed by the class
 
 
 __device__ __forceinline__ int fast_div(int n, unsigned long long magic) {
@@ -356,8 +366,10 @@ __device__ __forceinline__ int64_t out_row(const ConvArgs& a, int row) {
 // multiple of a vector, so the kernel has no element-wise paths at all (a
 // run-time choice between the two inside the loop would force a wait after
 // every load).
-template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, bool SHARDS>
-__global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<SHARDS>::type a) {   // at least two waves per SIMD: 256 registers
+template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND>
+__global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND>::type args) {   // at least two waves per SIMD: 256 registers
+    typename ArgsOf<KIND>::use a = args;
+    constexpr bool SHARDS = KIND == SHARDED;
     constexpr bool WG = MODE == CONV_WGRAD;
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr int VEC = Elem<T>::VEC;
@@ -409,6 +421,15 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<SHAR
     const int wm = wave / WN, wn = wave % WN;
     int tile_x, tile_y, tile_z;
     tile_of_block(a, tile_x, tile_y, tile_z);
+    if constexpr (KIND == CLASSES) {
+        const int t = tile_x / args.classes;
+        const ConvClass& k = args.cls[tile_x - t * args.classes];
+        tile_x = t;
+        if (tile_x * BM >= k.M) return;
+        a.ph = k.ph; a.pw = k.pw; a.Hc = k.Hc; a.Wc = k.Wc; a.r0 = k.r0; a.s0 = k.s0; a.nr = k.nr; a.ns = k.ns;
+        a.M = k.M; a.Kred = k.Kred; a.ksplit = k.Kred;
+        a.magic_hw = k.magic_hw; a.magic_w = k.magic_w; a.magic_taps = k.magic_taps;
+    }
     const int n0 = tile_y * BN;
     int m0 = tile_x * BM, m_end = a.M;       // rows [m0, m_end) of the output
     int kbeg = tile_z * a.ksplit, kend = kbeg + a.ksplit;
@@ -1352,10 +1373,10 @@ static bool magic_fits(double n_max, int d) {
     return n_max * (double)d < 1.0e12 && n_max * (double)magic_of(d) < 9.0e18;
 }
 
-template <typename T, int MODE, bool SHARDS>
-static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<SHARDS>::type& a_in, hipStream_t st) {
+template <typename T, int MODE, int KIND>
+static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<KIND>::type& a_in, hipStream_t st) {
     constexpr int BK = kConvBK<T>;
-    typename ArgsOf<SHARDS>::type a = a_in;
+    typename ArgsOf<KIND>::type a = a_in;
     a.gx = (int)tiles.x; a.gy = (int)tiles.y; a.gz = (int)tiles.z;
     const double total = (double)a.gx * a.gy * a.gz;
     const bool mg = magic_fits(total, a.gx) && magic_fits(total, a.gy);
@@ -1377,7 +1398,8 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<S
     constexpr int PF_DEEP = MODE == CONV_WGRAD ? EDL_PF_WG_DEEP : PF_BIG;
     const bool deep = MODE == CONV_WGRAD && total <= (double)tune().wgrad_deep_max;
     if (!fast) {   // element-wise kernel: one tile shape only
-        hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, false, 1, SHARDS>), grid, dim3(256), 0, st, a);
+        if constexpr (KIND != CLASSES)
+            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, false, 1, KIND>), grid, dim3(256), 0, st, a);
         return;
     }
     switch (t) {
@@ -1388,29 +1410,29 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<S
             const int full_steps_from = (int)tune().bk64_kred;
             if constexpr (MODE == CONV_WGRAD && sizeof(T) == 2) {
                 if (deep) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_DEEP, SHARDS>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_DEEP, KIND>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
             if (BK_BIG != BK && a.Kred >= full_steps_from)
-                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_BIG, SHARDS>), grid, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, PF_BIG, KIND>), grid, dim3(256), 0, st, a);
             else
-                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK_BIG, true, PF_HALF, SHARDS>), grid, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK_BIG, true, PF_HALF, KIND>), grid, dim3(256), 0, st, a);
             break;
         }
         case T128x64:
             if constexpr (MODE == CONV_WGRAD && sizeof(T) == 2) {
                 if (deep) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK, true, PF_DEEP, SHARDS>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK, true, PF_DEEP, KIND>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
-            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK_BIG, true, PF_HALF, SHARDS>), grid, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK_BIG, true, PF_HALF, KIND>), grid, dim3(256), 0, st, a);
             break;
-        case T128x32: hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, PF_BIG, SHARDS>), grid, dim3(256), 0, st, a); break;
+        case T128x32: hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, PF_BIG, KIND>), grid, dim3(256), 0, st, a); break;
         case T32x128:
             if constexpr (MODE == CONV_WGRAD && sizeof(T) == 4)
-                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 1, 4, 1, 1, BK, true, 1, SHARDS>), grid, dim3(256), 0, st, a);
+                hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 1, 4, 1, 1, BK, true, 1, KIND>), grid, dim3(256), 0, st, a);
             break;
         default:
             if constexpr (MODE != CONV_WGRAD && sizeof(T) == 2) {
@@ -1421,11 +1443,11 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<S
                 // 22.1 -> 18.2 us and 25.9 -> 22.2 us for the 3x3 layers at 28x28, 0.490 -> 0.422 ms per ResNet-50
                 // step over all launches of that size.
                 if (total > (double)tune().small_tail_from && total <= (double)tune().small_tail_to) {
-                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, EDL_PF_SMALL_TAIL, SHARDS>), grid, dim3(256), 0, st, a);
+                    hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, EDL_PF_SMALL_TAIL, KIND>), grid, dim3(256), 0, st, a);
                     break;
                 }
             }
-            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, PF_SMALL, SHARDS>), grid, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK_SMALL, true, PF_SMALL, KIND>), grid, dim3(256), 0, st, a);
             break;
     }
 }
@@ -1459,7 +1481,7 @@ static bool conv_magic_ok(int mode, const ConvArgs& a) {
 }
 
 template <int MODE>
-static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a_in, hipStream_t st) {
+static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a_in, hipStream_t st, ConvArgsClasses* classes = nullptr) {
     ConvArgsShards a = a_in;
     a.shards = a.cut.p;
     if (MODE == CONV_FWD) { a.magic_inner = magic_of(a.C); a.magic_taps = magic_of(a.S); }
@@ -1484,7 +1506,7 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a
     else a.n_fastest = (double)a.M * (MODE == CONV_FWD ? a.C : a.K) >= (double)a.Nn * a.Kred;
     // algorithmic work: 2*M*N*K flops; operands and result touched once
     const double esz = dtype == 1 ? 2.0 : 4.0;
-    const double flops = 2.0 * (double)a.M * a.Nn * a.Kred;
+    double flops = 2.0 * (double)a.M * a.Nn * a.Kred;
     double bytes;
     if (MODE == CONV_FWD) bytes = esz * ((double)a.N * a.H * a.W * a.C + (double)a.Nn * a.Kred) + (a.out_fp32 ? 4.0 : esz) * (double)a.M * a.Nn;
     else if (MODE == CONV_DGRAD) {
@@ -1505,13 +1527,32 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a
         if (!found) { names.emplace_back(buf); found = names.back().c_str(); }
         label = found;
     }
+    if (MODE == CONV_DGRAD && classes != nullptr) {
+        flops = 0;
+        bytes = esz * ((double)a.N * a.Ho * a.Wo * a.K + (double)a.Nn * a.ldb + (a.accumulate ? 2.0 : 1.0) * (double)a.N * a.H * a.W * a.Nn);
+        for (int c = 0; c < classes->classes; ++c) flops += 2.0 * (double)classes->cls[c].M * a.Nn * classes->cls[c].Kred;
+    }
     ProfScope ps(label, flops, bytes, st);
+    if (MODE == CONV_DGRAD && classes != nullptr) {
+        static_cast<ConvArgs&>(*classes) = a;
+        for (int c = 0; c < classes->classes; ++c) {
+            ConvClass& k = classes->cls[c];
+            k.magic_hw = magic_of(k.Hc * k.Wc);
+            k.magic_w = magic_of(k.Wc);
+            k.magic_taps = magic_of(k.ns);
+        }
+        if constexpr (MODE == CONV_DGRAD) {
+            if (dtype == 1) launch_cfg<bf16_t, MODE, CLASSES>(t, true, grid, *classes, st);
+            else launch_cfg<float, MODE, CLASSES>(t, true, grid, *classes, st);
+        }
+        return;
+    }
     if (a.shards > 1) {
-        if (dtype == 1) launch_cfg<bf16_t, MODE, true>(t, fast, grid, a, st);
-        else launch_cfg<float, MODE, true>(t, fast, grid, a, st);
+        if (dtype == 1) launch_cfg<bf16_t, MODE, SHARDED>(t, fast, grid, a, st);
+        else launch_cfg<float, MODE, SHARDED>(t, fast, grid, a, st);
     } else {
-        if (dtype == 1) launch_cfg<bf16_t, MODE, false>(t, fast, grid, a, st);
-        else launch_cfg<float, MODE, false>(t, fast, grid, a, st);
+        if (dtype == 1) launch_cfg<bf16_t, MODE, PLAIN>(t, fast, grid, a, st);
+        else launch_cfg<float, MODE, PLAIN>(t, fast, grid, a, st);
     }
 }
 
@@ -1662,6 +1703,43 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
     a.vecA = (g.K % VEC == 0) && bA < 2147483648.0 && stride_pow2; a.vecB = (a.ldb % VEC == 0) && bB < 2147483648.0;
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
     const bool want_mask = tune().fused_mask != 0 && mask != nullptr && mask->act != nullptr && g.stride == 1;
+    // Stride 2: the four residue classes of the input pixel modulo the stride in one launch (each alone is a quarter of
+    // the pixels, three of a 1x1 convolution's only zeros: 24 launches fewer in ResNet-50's chain)
+    if (g.stride == 2 && conv_fast(dtype, CONV_DGRAD, a)) {
+        ConvArgsClasses cls = {};
+        int64_t work = 0;
+        int longest = 0;
+        bool ok = true;
+        for (int c = 0; c < 4; ++c) {
+            const int ph = c >> 1, pw = c & 1;
+            if (ph >= g.H || pw >= g.W) continue;
+            ConvClass k = {};
+            k.ph = ph; k.pw = pw;
+            k.Hc = (g.H - ph + 1) / 2; k.Wc = (g.W - pw + 1) / 2;
+            k.r0 = (ph + g.pad) % 2; k.s0 = (pw + g.pad) % 2;
+            k.nr = k.r0 < g.R ? (g.R - k.r0 + 1) / 2 : 0;
+            k.ns = k.s0 < g.S ? (g.S - k.s0 + 1) / 2 : 0;
+            k.M = g.N * k.Hc * k.Wc;
+            k.Kred = k.nr * k.ns * g.K;
+            if (k.Kred == 0 && accumulate) continue;      // nothing reaches these pixels
+            ConvArgs probe = a;
+            probe.Hc = k.Hc; probe.Wc = k.Wc; probe.ns = k.ns; probe.M = k.M; probe.Kred = k.Kred;
+            ok = ok && conv_magic_ok(CONV_DGRAD, probe);
+            if (k.Kred > 0) work = std::max(work, (int64_t)S.plan * k.Hc * k.Wc);
+            longest = std::max(longest, k.Kred);
+            cls.cls[cls.classes++] = k;
+        }
+        if (ok && cls.classes > 0) {
+            int bm, bn, tiles = 0;
+            const TileCfg t = pick_tile((int)work, a.Nn, longest, &bm, &bn);
+            for (int c = 0; c < cls.classes; ++c) tiles = std::max(tiles, (cls.cls[c].M + bm - 1) / bm);
+            tiles *= cls.classes;
+            const ConvClass& k = cls.cls[0];
+            a.ph = k.ph; a.pw = k.pw; a.Hc = k.Hc; a.Wc = k.Wc; a.r0 = k.r0; a.s0 = k.s0; a.nr = k.nr; a.ns = k.ns; a.M = k.M; a.Kred = k.Kred;
+            launch_mode<CONV_DGRAD>(dtype, t, dim3(tiles, (a.Nn + bn - 1) / bn, 1), a, st, &cls);
+            return left;
+        }
+    }
     // one launch per residue class of the input pixel modulo the stride
     for (int ph = 0; ph < g.stride && ph < g.H; ++ph) {
         for (int pw = 0; pw < g.stride && pw < g.W; ++pw) {
