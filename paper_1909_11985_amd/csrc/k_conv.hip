@@ -101,7 +101,10 @@ struct ConvArgs {
     // gradient is stored already masked, and its column sums over the tile's rows go to msum (the layout of
     // stats above): kind 0 = sum of the masked gradient; kind 1 = sum of masked gradient * (xin - mean) * rstd
     // if xin (the producing batch norm's input) and mean_rstd ([mean[Nn], rstd[Nn]]) are given, else unused.
+    // mask_sign (bf16, may be null): the activation's sign, one bit per element, eight channels to a byte, which is
+    // then read instead of the activation.
     const void* mask_act;
+    const unsigned char* mask_sign;
     const void* xin;
     const float* mean_rstd;     // of shard s at 2 * Nn * s
     float* msum;
@@ -969,6 +972,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     const bool add_old = MODE == CONV_DGRAD && a.accumulate && !to_partial;
     const bool masked = MODE == CONV_DGRAD && a.mask_act != nullptr && !to_partial;
     const bool with_xhat = masked && a.xin != nullptr;
+    const bool by_sign = !OUT_F32 && masked && a.mask_sign != nullptr;
     float mu[OVEC], rs[OVEC];      // of this lane's columns
     #pragma unroll
     for (int e = 0; e < OVEC; ++e) { mu[e] = 0.f; rs[e] = 0.f; }
@@ -995,8 +999,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 oldv[k] = *reinterpret_cast<const uint4*>(src);
             }
         }
-        // the activation (and the batch norm's input) at the positions this lane stores, fetched the same way
+        // the activation or its sign bits (and the batch norm's input) at the positions this lane stores, fetched the
+        // same way
         uint4 actv[NV], xinv[NV];
+        unsigned signv[NV];
         if (masked) {
             #pragma unroll
             for (int k = 0; k < NV; ++k) {
@@ -1004,7 +1010,8 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 const int row = m0 + pass * STAGE_ROWS + rl, col = n0 + cv * OVEC;
                 const bool inside = v < STAGE_ROWS * CV && row < m_end && col < a.Nn;
                 const int64_t at = inside ? ((int64_t)row * a.Nn + col) * OSZ : 0;
-                actv[k] = *reinterpret_cast<const uint4*>((const unsigned char*)a.mask_act + at);
+                if (by_sign) signv[k] = a.mask_sign[at / 16];
+                else actv[k] = *reinterpret_cast<const uint4*>((const unsigned char*)a.mask_act + at);
                 if (with_xhat) xinv[k] = *reinterpret_cast<const uint4*>((const unsigned char*)a.xin + at);
             }
         }
@@ -1078,7 +1085,12 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                         o1.x += __uint_as_float(old.z << 16); o1.y += __uint_as_float(old.z & 0xffff0000u);
                         o1.z += __uint_as_float(old.w << 16); o1.w += __uint_as_float(old.w & 0xffff0000u);
                     }
-                    if (masked) {   // activation > 0: a positive bf16 (sign clear, not zero)
+                    if (by_sign) {
+                        float* const ov[8] = {&o0.x, &o0.y, &o0.z, &o0.w, &o1.x, &o1.y, &o1.z, &o1.w};
+                        #pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (!(signv[k] & (1u << e))) *ov[e] = 0.f;
+                    } else if (masked) {   // activation > 0: a positive bf16 (sign clear, not zero)
                         const uint32_t aw[4] = {actv[k].x, actv[k].y, actv[k].z, actv[k].w};
                         float* const ov[8] = {&o0.x, &o0.y, &o0.z, &o0.w, &o1.x, &o1.y, &o1.z, &o1.w};
                         #pragma unroll
@@ -1512,7 +1524,7 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a
     else if (MODE == CONV_DGRAD) {
         // dy, weights, dx; plus what a fused epilogue reads at every output position: the gradient already
         // there, the activation that masks it, the batch norm's input for the second sum
-        const double extra = (a.accumulate ? 1.0 : 0.0) + (a.mask_act ? 1.0 : 0.0) + (a.xin ? 1.0 : 0.0);
+        const double extra = (a.accumulate ? 1.0 : 0.0) + (a.mask_act ? (a.mask_sign ? 1.0 / 16 : 1.0) : 0.0) + (a.xin ? 1.0 : 0.0);
         bytes = esz * ((double)a.N * a.Ho * a.Wo * a.K + (double)a.Nn * a.Kred + (1.0 + extra) * (double)a.M * a.Nn);
     } else bytes = esz * ((double)a.Kred * a.K + (double)a.N * a.H * a.W * a.C) + 4.0 * (double)a.M * a.Nn;
     const char* label = conv_label(dtype, MODE, t);
@@ -1777,6 +1789,7 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
             const int row_tiles = a.cut.blk0[a.cut.p];
             const bool fuse = want && per_shard && mask->sums.floats >= (size_t)2 * a.Nn * row_tiles;
             a.mask_act = fuse ? mask->act : nullptr;
+            a.mask_sign = fuse && dtype == 1 && a.Nn % 8 == 0 ? mask->sign : nullptr;
             a.xin = fuse ? mask->xin : nullptr;
             a.mean_rstd = fuse ? mask->mean_rstd : nullptr;
             a.msum = fuse ? mask->sums.buf : nullptr;

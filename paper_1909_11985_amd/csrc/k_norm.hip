@@ -282,7 +282,7 @@ template <typename T, int VEC, int U, bool RES, bool NT>
 __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x, const T* __restrict__ res,
                                                        T* __restrict__ y, const float* __restrict__ gamma,
                                                        const float* __restrict__ beta, const float* __restrict__ mean_rstd,
-                                                       RowCut shards, int C, int cvecs, int relu) {
+                                                       RowCut shards, int C, int cvecs, int relu, unsigned char* __restrict__ sign) {
     const int sh = blockIdx.y, row0 = shards.row0[sh];
     const int64_t total = (int64_t)(shards.row0[sh + 1] - row0) * cvecs;
     const int64_t i0 = (int64_t)blockIdx.x * (256 * U) + threadIdx.x;
@@ -311,6 +311,12 @@ __global__ __launch_bounds__(256) void bn_apply_kernel(const T* __restrict__ x, 
             if (relu) out[e] = out[e] > 0.f ? out[e] : 0.f;
         }
         store_row<T, VEC>(y, base + i0 + u * 256, VEC, 0, out);
+        if (VEC == 8 && sign != nullptr) {
+            unsigned bits = 0;      // of the stored values
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) bits |= (Elem<T>::to_f32(Elem<T>::from_f32(out[e])) > 0.f ? 1u : 0u) << e;
+            sign[base + i0 + u * 256] = (unsigned char)bits;
+        }
     }
 }
 
@@ -392,7 +398,7 @@ static int vectors_per_lane(const ShardSet& S, int hw, int cvecs) {
 
 template <typename T, int VEC>
 static void bn_forward_t(const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                         float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                         float* save, float* running, const ShardSet& S, int hw, int C, bool relu, unsigned char* sign, float* partial,
                          const RowCut& sums, hipStream_t st) {
     const int64_t M = (int64_t)S.samples() * hw;
     const RedShape s = red_shape((int64_t)S.plan * hw, C, VEC);
@@ -408,13 +414,13 @@ static void bn_forward_t(const void* x, const void* res, void* y, const float* g
         ProfScope ps("bn_stats_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
         EDL_FINALIZE(bn_stats_finalize_kernel, cut, C, save, running);
     }
-    ProfScope ps(prof_shape_label("bn_apply", M, C), 0.0, tb * (res ? 3.0 : 2.0), st);
+    ProfScope ps(prof_shape_label("bn_apply", M, C), 0.0, tb * ((res ? 3.0 : 2.0) + (sign ? 1.0 / 16 : 0.0)), st);
     const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
     const int u = vectors_per_lane(S, hw, s.cvecs);
     const dim3 grid = ew_grid(S, hw, s.cvecs, u);
 #define EDL_BN_APPLY(U, RES, NT)                                                                                       \
     hipLaunchKernelGGL((bn_apply_kernel<T, VEC, U, RES, NT>), grid, dim3(256), 0, st, (const T*)x, (const T*)res, (T*)y, gamma, beta, \
-                       save, cut, C, s.cvecs, relu ? 1 : 0)
+                       save, cut, C, s.cvecs, relu ? 1 : 0, sign)
 #define EDL_BN_APPLY_U(U)                                                                                              \
     do {                                                                                                               \
         if (res) { if (nt) EDL_BN_APPLY(U, true, true); else EDL_BN_APPLY(U, true, false); }                           \
@@ -426,14 +432,14 @@ static void bn_forward_t(const void* x, const void* res, void* y, const float* g
 }
 
 void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, unsigned char* sign, float* partial,
                        const RowCut& sums, hipStream_t st) {
     if (dtype == 1) {
-        if (C % 8 == 0) bn_forward_t<bf16_t, 8>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
-        else bn_forward_t<bf16_t, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
+        if (C % 8 == 0) bn_forward_t<bf16_t, 8>(x, res, y, gamma, beta, save, running, S, hw, C, relu, sign, partial, sums, st);
+        else bn_forward_t<bf16_t, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, sign, partial, sums, st);
     } else {
-        if (C % 4 == 0) bn_forward_t<float, 4>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
-        else bn_forward_t<float, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, partial, sums, st);
+        if (C % 4 == 0) bn_forward_t<float, 4>(x, res, y, gamma, beta, save, running, S, hw, C, relu, sign, partial, sums, st);
+        else bn_forward_t<float, 1>(x, res, y, gamma, beta, save, running, S, hw, C, relu, sign, partial, sums, st);
     }
 }
 
@@ -522,6 +528,20 @@ void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias
         if (C % 4 == 0) bias_relu_backward_t<float, 4>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
         else bias_relu_backward_t<float, 1>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
     }
+}
+
+__global__ __launch_bounds__(256) void signs_kernel(const bf16_t* __restrict__ act, unsigned char* __restrict__ sign, int64_t vecs) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= vecs) return;
+    const Vec16<bf16_t> v = load_vec(act + i * 8);
+    unsigned bits = 0;
+    #pragma unroll
+    for (int e = 0; e < 8; ++e) bits |= (bf16_to_f32(v.e[e]) > 0.f ? 1u : 0u) << e;
+    sign[i] = (unsigned char)bits;
+}
+
+void launch_signs(const void* act_bf16, unsigned char* sign, int64_t n, hipStream_t st) {
+    hipLaunchKernelGGL(signs_kernel, dim3((unsigned)((n / 8 + 255) / 256)), dim3(256), 0, st, (const bf16_t*)act_bf16, sign, n / 8);
 }
 
 }  // namespace edl

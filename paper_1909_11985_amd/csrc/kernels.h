@@ -123,6 +123,7 @@ size_t conv_sums_floats(const ConvGeom& g, int p);
 // given: a batch norm's backward sums).
 struct DgradMask {
     const void* act;          // the producer's output (= this convolution's input), dtype elements
+    const unsigned char* sign;    // (act > 0), one bit per element, eight channels to a byte; null if not kept
     const void* xin;          // the producing batch norm's input, or null
     const float* mean_rstd;   // with xin: mean[C], rstd[C] of each shard
     SumsBuf sums;
@@ -147,10 +148,13 @@ size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int p);
 // floats the column reductions below take as scratch over the given rows of p shards
 size_t norm_sums_floats(int dtype, int64_t M, int C, int p);
 // save: mean[C], rstd[C] of each shard; running ([2C] or null) follows the first shard; sums.p > 0: partial already
-// holds the sums, cut that way; hw: rows per sample
+// holds the sums, cut that way; hw: rows per sample.  sign (bf16 with C a multiple of 8, else null): receives the bits
+// (y > 0), a sixteenth of y's bytes, for the backward passes that need no more of it
 void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const float* gamma, const float* beta,
-                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, float* partial,
+                       float* save, float* running, const ShardSet& S, int hw, int C, bool relu, unsigned char* sign, float* partial,
                        const RowCut& sums, hipStream_t st);
+// sign[i] = bits (act[8i + e] > 0) of n elements (a multiple of 8)
+void launch_signs(const void* act_bf16, unsigned char* sign, int64_t n, hipStream_t st);
 // sums.p > 0: partial already holds the two backward sums (left there by the dgrad that produced dy, which is then
 // also masked already); coef: 2C floats per shard
 void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy, void* dx, void* dres,
