@@ -128,6 +128,7 @@ struct ConvArgs {
     // one piece per shard straight to the shard's gradient (zdirect: out + worker * zstride).
     int shards, splits, zdirect;
     long long zstride;
+    int strip;      // forward / dgrad of 3x3, stride 1: the kernel whose steps are a kernel row's three taps (takes_strips)
 };
 
 // The tables of a launch over several shards.  One shard takes kernels without them: the table look-ups (and the
@@ -369,7 +370,14 @@ __device__ __forceinline__ int64_t out_row(const ConvArgs& a, int row) {
 // multiple of a vector, so the kernel has no element-wise paths at all (a
 // run-time choice between the two inside the loop would force a wait after
 // every load).
-template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND>
+// TAPS = 3: 3x3 convolutions of stride 1 (forward and dgrad).  A reduction step is BK channels of the three taps of one
+// kernel row: the pixels that the three taps of BM consecutive output pixels read are BM + 2 consecutive pixels, which are
+// staged once (a strip) instead of three times, and each tap's fragments are read from the strip one row further on.
+// Pixels above and below the image come in as zeros; where a row's neighbour to the left or right is outside the
+// image its fragment is read from a row of zeros behind the strip.  What this saves is operand delivery (a 128x64 step
+// of 96 elements loads 21 KB instead of 37 KB) and two of three barriers: VGG-16's 64-channel layers at 224x224, shard
+// of 32: 278 -> 238 us forward, 362 -> 277 us dgrad (two launches each).
+template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND, int TAPS = 1>
 __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND>::type args) {   // at least two waves per SIMD: 256 registers
     typename ArgsOf<KIND>::use a = args;
     constexpr bool SHARDS = KIND == SHARDED;
@@ -383,7 +391,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     constexpr int RVA = BM / VEC, RVB = BN / VEC;   // wgrad: channel vectors per pixel
     constexpr int TOT_A = WG ? KD * RVA : BM * KV;  // work items per tile (wgrad: KPD vectors each)
     constexpr int TOT_B = WG ? KD * RVB : BN * KV;
-    constexpr int ITER_A = (TOT_A + 255) / 256, ITER_B = (TOT_B + 255) / 256;
+    constexpr bool STRIP = TAPS > 1;
+    constexpr int STRIP_ROWS = BM + 16;             // BM + TAPS - 1 rounded up to the 16 rows that a wave's load fills
+    constexpr int ITER_A = STRIP ? (STRIP_ROWS + 63) / 64 : (TOT_A + 255) / 256;
+    constexpr int ITER_B = STRIP ? (TAPS * BN + 63) / 64 : (TOT_B + 255) / 256;
     constexpr int NRA = WG ? ITER_A * KPD : ITER_A, NRB = WG ? ITER_B * KPD : ITER_B;
     // wgrad in bf16 keeps its tiles as they are in memory, [pixel][channel], and transposes on the way out of
     // LDS (ds_read_tr16_b64, see tr_frag); float32 wgrad keeps words [pixel][channel] read one by one
@@ -393,7 +404,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     // instruction fills 64 consecutive 16-byte slots (whole rows), and the slot of chunk c of row r is
     // c ^ ((r / RPL) % KV) with RPL = rows per 256 bytes, which keeps the fragment reads conflict-free.
     constexpr int RB = BK * (int)sizeof(T), RPL = RB > 256 ? 1 : 256 / RB;
-    constexpr bool DIRECT = EDL_DIRECT_LDS != 0 && FAST && !WG && TOT_A % 256 == 0 && TOT_B % 256 == 0 &&
+    constexpr bool DIRECT = EDL_DIRECT_LDS != 0 && FAST && !WG && (STRIP || (TOT_A % 256 == 0 && TOT_B % 256 == 0)) &&
                             (RB == 64 || RB == 128);
     // The bf16 weight gradient the same way: its tiles are rows of pixels as they are in memory, so a
     // wave's load fills whole pixel rows; item v is the 16-byte slot v % RV of pixel v / RV.
@@ -403,8 +414,9 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     constexpr bool DMA = DIRECT || DIRECT_WG;
     constexpr int NST = DMA ? PF + 1 : 2;            // LDS stages
     constexpr int LDK = DIRECT ? BK : BK + VEC;
-    constexpr int A_STAGE = WGT ? BK * BM * 2 : WG ? KD * LDPA * 4 : BM * LDK * (int)sizeof(T);   // bytes per LDS stage
-    constexpr int B_STAGE = WGT ? BK * BN * 2 : WG ? KD * LDPB * 4 : BN * LDK * (int)sizeof(T);
+    static_assert(!STRIP || (DIRECT && RB == 64 && TAPS == 3), "strips are loaded straight into LDS");
+    constexpr int A_STAGE = STRIP ? STRIP_ROWS * RB : WGT ? BK * BM * 2 : WG ? KD * LDPA * 4 : BM * LDK * (int)sizeof(T);   // bytes per LDS stage
+    constexpr int B_STAGE = STRIP ? TAPS * BN * RB : WGT ? BK * BN * 2 : WG ? KD * LDPB * 4 : BN * LDK * (int)sizeof(T);
     // epilogue staging: the rows of one wave row, as float32
     constexpr int STAGE_ROWS = TM * 32, STAGE_LD = BN + 4;
     constexpr int TILE_BYTES = NST * (A_STAGE + B_STAGE);
@@ -450,7 +462,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         }
         if (kend > last) kend = last;        // a short shard's last pieces may be empty: they store zeros
     }
-    const int nk = (kend - kbeg + BK - 1) / BK;
+    const int nk = (kend - kbeg + TAPS * BK - 1) / (TAPS * BK);
 
     Vec16<T> ra[PF][NRA], rb[PF][NRB];   // PF register sets: the loads of the next PF tiles are in flight
     const __amdgpu_buffer_rsrc_t rsrcA = make_rsrc(a.A, a.bytesA), rsrcB = make_rsrc(a.B, a.bytesB);
@@ -473,7 +485,53 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     int wg_r = 0, wg_s = 0, wg_c = 0;  // wgrad: tap and channel of this thread's B rows
     bool wg_j_ok = true;
     int dn = 0, dho = 0, dwo = 0;    // wgrad: BK pixels as (images, rows, columns)
-    if (!WG) {
+    // strips: byte offsets of this lane's vectors of A and B at kernel row 0, the kernel rows at which the vector of A is
+    // inside the image (a bit each), kernel row and channel of the next step
+    constexpr int SIA = STRIP ? ITER_A : 1, SIB = STRIP ? ITER_B : 1;
+    int strip_a[SIA], strip_b[SIB], strip_in[SIA];
+    int strip_r = 0, strip_c = 0;
+    int strip_frag[STRIP ? TM : 1][TAPS];   // byte offset of this lane's fragment in the strip, by column shift
+    if (STRIP) {
+        const int inner = MODE == CONV_FWD ? a.C : a.K;
+        const int step = kbeg / (TAPS * BK), per_row = inner / BK;
+        strip_r = step / per_row;
+        strip_c = (step - strip_r * per_row) * BK;
+        const int slot = tid % KV;
+        const int hw = MODE == CONV_FWD ? a.Ho * a.Wo : a.Hc * a.Wc, wd = a.W;
+        #pragma unroll
+        for (int it = 0; it < ITER_A; ++it) {
+            const int row = (tid + it * 256) / KV, pix = m0 - 1 + row;
+            const int chunk = slot ^ ((row / RPL) % KV);
+            const int n = fast_div(pix, a.magic_hw), h = fast_div(pix - n * hw, a.magic_w);
+            const bool ok = row < BM + TAPS - 1 && pix >= 0 && pix < m_end;
+            int in = 0;
+            #pragma unroll
+            for (int r = 0; r < 3; ++r) {
+                const int q = MODE == CONV_FWD ? h + r - 1 : h + 1 - r;
+                in |= (ok && q >= 0 && q < a.H) ? 1 << r : 0;
+            }
+            strip_in[it] = in;
+            strip_a[it] = ((pix + (MODE == CONV_FWD ? -wd : wd)) * inner + chunk * VEC) * (int)sizeof(T);
+        }
+        #pragma unroll
+        for (int it = 0; it < ITER_B; ++it) {
+            const int row = (tid + it * 256) / KV, tap = row / BN, j = n0 + row - tap * BN;
+            const int chunk = slot ^ ((row / RPL) % KV);
+            strip_b[it] = (j < a.Nn && tap < TAPS) ? (int)((j * a.ldb + tap * inner + chunk * VEC) * (int)sizeof(T)) : (int)kOutOfRange;
+        }
+        #pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int row = (wm * TM + i) * 32 + (lane & 31), pix = m0 + row;
+            const int n = fast_div(pix, a.magic_hw), rem = pix - n * hw;
+            const int w = rem - fast_div(rem, a.magic_w) * wd;
+            #pragma unroll
+            for (int d = 0; d < TAPS; ++d) {
+                const int q = w + d - 1;
+                const int sr = (q >= 0 && q < wd) ? row + d : BM + 8;   // a row past the strip is all zeros
+                strip_frag[i][d] = sr * RB + (((lane >> 5) ^ ((sr / RPL) % KV)) * 16);
+            }
+        }
+    } else if (!WG) {
         const int inner = MODE == CONV_FWD ? a.C : a.K;
         // DIRECT: the lane fills slot tid % KV of its rows, which holds chunk slot ^ ((row / RPL) % KV); a lane's
         // rows are 256 / KV apart, so this is the same chunk for all of them
@@ -552,7 +610,26 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     }
 
     auto load_tiles = [&](int set) {
-        if (DIRECT) {
+        if (STRIP) {
+            const int inner = MODE == CONV_FWD ? a.C : a.K;
+            const int addA = ((MODE == CONV_FWD ? strip_r : -strip_r) * a.W * inner + strip_c) * (int)sizeof(T);
+            const int addB = (strip_r * TAPS * inner + strip_c) * (int)sizeof(T);
+            #pragma unroll
+            for (int it = 0; it < ITER_A; ++it) {
+                const unsigned off = (unsigned)(strip_a[it] + addA) | (((strip_in[it] >> strip_r) & 1) ? 0u : kOutOfRange);
+                if ((it + 1) * 64 <= STRIP_ROWS || __builtin_amdgcn_readfirstlane(wave) < (STRIP_ROWS - it * 64) / 16)
+                    buffer_load16_to_lds(wordsA, ldsA_wave + set * A_STAGE + it * 4096, off);
+            }
+            #pragma unroll
+            for (int it = 0; it < ITER_B; ++it) {
+                if ((it + 1) * 64 <= TAPS * BN || __builtin_amdgcn_readfirstlane(wave) < (TAPS * BN - it * 64) / 16)
+                    buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096, (unsigned)strip_b[it] + (unsigned)addB);
+            }
+            strip_c += BK;
+            const bool next = strip_c == inner;
+            strip_c = next ? 0 : strip_c;
+            strip_r += next ? 1 : 0;
+        } else if (DIRECT) {
             // `set` is the LDS stage
             const bool in_k = kcur < kend;
             #pragma unroll
@@ -818,9 +895,20 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     // flight at every wait is then a compile-time constant.
     // contraction of the tile in LDS stage `buf`
     auto contract = [&](int buf) {
-        constexpr int NG = WG ? 4 : BK / (2 * VEC);   // fragment groups per tile
+        constexpr int NG = WG ? 4 : TAPS * BK / (2 * VEC);   // fragment groups per tile
         auto read_frags = [&](int g, uint4 (&fa)[TM], uint4 (&fb)[TN]) {
-            if (!WG) {
+            if (STRIP) {
+                constexpr int NT = NG / TAPS;
+                static_assert(!STRIP || NT == 2, "two groups per tap");
+                const int tap = g / NT, flip = (g - tap * NT) * 32, d = MODE == CONV_FWD ? tap : TAPS - 1 - tap;
+                #pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    fa[i] = *reinterpret_cast<const uint4*>(As + buf * A_STAGE + (strip_frag[STRIP ? i : 0][STRIP ? d : 0] ^ flip));
+                const int slot = (lane >> 5) ^ (((lane & 31) / RPL) % KV);
+                #pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    fb[j] = *reinterpret_cast<const uint4*>(Bs + buf * B_STAGE + tap * BN * RB + ((((wn * TN + j) * 32 + (lane & 31)) * RB + slot * 16) ^ flip));
+            } else if (!WG) {
                 const T* const Ab = reinterpret_cast<const T*>(As + buf * A_STAGE);
                 const T* const Bb = reinterpret_cast<const T*>(Bs + buf * B_STAGE);
                 // chunk of the row this lane reads, and the slot the tile keeps it in
@@ -877,7 +965,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         // barrier (every wave's part of tile k is in LDS and every wave is done reading tile k-1), then
         // refill the stage tile k-1 was in.  Loads past the end of the reduction write zeros into a stage
         // nobody reads; all of them have landed before the epilogue reuses the memory.
-        constexpr int PER_TILE = DIRECT_WG ? DA + DB : ITER_A + ITER_B;
+        constexpr int PER_TILE = STRIP ? STRIP_ROWS / 64 + TAPS * BN / 64 : DIRECT_WG ? DA + DB : ITER_A + ITER_B;
         #pragma unroll
         for (int u = 0; u < NST - 1; ++u) load_tiles(u);
         for (int kt = 0; kt < nk; kt += NST) {
@@ -1414,6 +1502,19 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<K
             hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, false, 1, KIND>), grid, dim3(256), 0, st, a);
         return;
     }
+    if constexpr (MODE != CONV_WGRAD && KIND != CLASSES) {
+        if (a.strip) {
+            constexpr int BS = 64 / (int)sizeof(T);
+            if constexpr (MODE == CONV_DGRAD) {
+                // 64x64: a third stage as without strips (53 KB, three workgroups per CU either way)
+                if (t == T128x128) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BS, true, 1, KIND, 3>), grid, dim3(256), 0, st, a);
+                if (t == T64x64) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BS, true, 2, KIND, 3>), grid, dim3(256), 0, st, a);
+            }
+            if (t == T128x64) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BS, true, 1, KIND, 3>), grid, dim3(256), 0, st, a);
+            if (t == T128x32) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BS, true, 1, KIND, 3>), grid, dim3(256), 0, st, a);
+            return;
+        }
+    }
     switch (t) {
         case T128x128: {
             // Long reductions (VGG-16's 3x3 layers: 1,152 to 4,608 elements) run faster on full-length reduction
@@ -1466,6 +1567,7 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<K
 
 static const char* conv_label(int dtype, int mode, TileCfg t) {
     if (t == T32x128) return "conv_wgrad_f32_32x128";
+
     static const char* names[2][3][4] = {
         {{"conv_fwd_f32_128x128", "conv_fwd_f32_128x64", "conv_fwd_f32_128x32", "conv_fwd_f32_64x64"},
          {"conv_dgrad_f32_128x128", "conv_dgrad_f32_128x64", "conv_dgrad_f32_128x32", "conv_dgrad_f32_64x64"},
@@ -1596,14 +1698,25 @@ static RowCut tile_cut(const ShardSet& S, int rows_per_sample, int bm, bool want
     return cut_rows(all, rows_per_sample, bm);
 }
 
+// Convolutions whose reduction steps are strips: 3x3, stride 1, one pixel of padding, and a number of channels that is a
+// multiple of the 64 bytes a strip's rows hold.  Every input-gradient launch of that kind gains (64x64 tiles 2 to 3%,
+// 128x128 6%, 128x64 up to 23%), and so do forward launches of narrow outputs (128x64 up to 14%, float32 128x32 8%);
+// forward 128x128 tiles lose 2% (full-length steps have fewer barriers than strips there), 64x64 tiles gain nothing.
+static bool takes_strips(int dtype, int mode, const ConvGeom& g, TileCfg t) {
+    const int inner = mode == CONV_FWD ? g.C : g.K, row = dtype == 1 ? 32 : 16;
+    return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && inner % row == 0 &&
+           (mode == CONV_DGRAD || t == T128x64 || t == T128x32);
+}
+
 // Cut of the reduction for forward / dgrad problems that give too few tiles to
 // fill the chip but have a long reduction (late stages at small batch, fully
 // connected layers): returns the number of splits (1 = none).  The target is little more than one
 // workgroup per CU: every further cut costs the finishing kernel more partial sums than the fuller chip
 // gains (measured on ResNet-50 at a shard of 32: 768 -> 320 workgroups, 4.73 -> 4.69 ms per step;
 // VGG-16 5.20 -> 5.14 ms).
-static int plan_splitk(int dtype, int M, int Nn, int Kred, int bm, int bn, int* ksplit) {
+static int plan_splitk(int dtype, int M, int Nn, int Kred, int bm, int bn, int* ksplit, bool strip) {
     const int BK = dtype == 1 ? 64 : 32;
+    const int unit = strip ? BK / 2 * 3 : BK;      // a cut holds whole steps
     const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((Nn + bn - 1) / bn);
     const int nk = (Kred + BK - 1) / BK;
     int splits = 1;
@@ -1614,7 +1727,7 @@ static int plan_splitk(int dtype, int M, int Nn, int Kred, int bm, int bn, int* 
         if (splits > 8) splits = 8;
         if (splits < 1) splits = 1;
     }
-    int ks = (nk + splits - 1) / splits * BK;
+    const int units = (Kred + unit - 1) / unit, ks = (units + splits - 1) / splits * unit;
     *ksplit = ks;
     return (Kred + ks - 1) / ks;
 }
@@ -1654,8 +1767,8 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g) {
         const int Nn = mode == 0 ? g.K : g.C;
         const int Kred = mode == 0 ? g.R * g.S * g.C : g.R * g.S * g.K;
         int bm, bn, ks;
-        pick_tile(M, Nn, Kred, &bm, &bn, mode == 0 && Kred <= 128);
-        const int splits = plan_splitk(dtype, M, Nn, Kred, bm, bn, &ks);
+        const TileCfg t = pick_tile(M, Nn, Kred, &bm, &bn, mode == 0 && Kred <= 128);
+        const int splits = plan_splitk(dtype, M, Nn, Kred, bm, bn, &ks, takes_strips(dtype, mode, g, t));
         if (splits > 1) need = std::max(need, (size_t)splits * M * Nn * sizeof(float));
     }
     return need;
@@ -1679,8 +1792,9 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     const TileCfg t = pick_tile(Mplan, a.Nn, a.Kred, &bm, &bn, a.Kred <= 128);
     const bool fast = conv_fast(dtype, CONV_FWD, a);
     int splits = 1, ks = a.Kred;
+    a.strip = fast && conv_magic_ok(CONV_FWD, a) && takes_strips(dtype, CONV_FWD, g, t);
     if (fast) {
-        splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks);
+        splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks, a.strip);
         if (splits > 1 && (scratch == nullptr || scratch_bytes < (size_t)splits * a.M * a.Nn * sizeof(float))) splits = 1;
     }
     if (splits > 1) { a.ksplit = ks; a.partial = scratch; }
@@ -1776,8 +1890,9 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
             const TileCfg t = pick_tile(Mplan, a.Nn, a.Kred, &bm, &bn, heavy);
             const bool fast = conv_fast(dtype, CONV_DGRAD, a);
             int splits = 1, ks = a.ksplit;
+            a.strip = fast && conv_magic_ok(CONV_DGRAD, a) && takes_strips(dtype, CONV_DGRAD, g, t);
             if (g.stride == 1 && fast) {
-                splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks);
+                splits = plan_splitk(dtype, Mplan, a.Nn, a.Kred, bm, bn, &ks, a.strip);
                 if (splits > 1 && (scratch == nullptr || scratch_bytes < (size_t)splits * a.M * a.Nn * sizeof(float))) splits = 1;
             }
             if (splits > 1) { a.ksplit = ks; a.partial = scratch; }

@@ -280,6 +280,14 @@ def test_layerwise_under_every_tile_shape(tile):
     assert E.edl_get_option("force_tile") == -1
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("H,W,n", [(1, 1, 40), (4, 2, 70), (9, 5, 7), (6, 131, 2), (33, 20, 3)])
+def test_layerwise_3x3_convolutions_at_image_borders(H, W, n, dtype):
+    """3x3 convolutions of stride 1 read the three taps of a kernel row from one run of pixels: images narrower than a
+    tile row and wider than a tile, runs that start or end at an image's border, a single pixel."""
+    _assert_layerwise(layerwise_parity("resnet20", dtype, n, H=H, W=W, verbose=False), dtype)
+
+
 def test_layerwise_vgg16_bf16_at_full_size():
     """Every layer of VGG-16 at 224x224 (reductions up to 25088 long, 200704-row outputs), four samples."""
     r = layerwise_parity("vgg16", "bf16", 4, verbose=False)
