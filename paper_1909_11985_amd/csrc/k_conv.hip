@@ -503,7 +503,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
             const int row = (tid + it * 256) / KV, pix = m0 - 1 + row;
             const int chunk = slot ^ ((row / RPL) % KV);
             const int n = fast_div(pix, a.magic_hw), h = fast_div(pix - n * hw, a.magic_w);
-            const bool ok = row < BM + TAPS - 1 && pix >= 0 && pix < m_end;
+            const bool ok = row < BM + TAPS - 1 && pix >= 0 && pix < a.M;     // (m_end is the tile's own end)
             int in = 0;
             #pragma unroll
             for (int r = 0; r < 3; ++r) {

@@ -989,3 +989,15 @@ def test_shards_of_one_pass_are_computed_as_each_alone(model, dtype, kw, cut):
             assert relerr(job.grad(k), alone.grad(0)) < tol, k
         alone.shutdown()
     job.shutdown()
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 3])
+@pytest.mark.parametrize("model,kw,cut", [
+    ("resnet20", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), [4, 4, 3, 4]),
+    ("resnet50", dict(H=64, W=64, C=3, classes=10, arch=(64, 1, 1, 1, 1)), [3, 8, 5]),
+])
+def test_row_tiles_inside_a_shard_read_their_neighbours(model, kw, cut, tile):
+    """Row tiles that end inside an image of a shard read the first pixel past them (3x3 taps), on every tile shape."""
+    import paper_1909_11985_amd as E
+    with E.options(force_tile=tile):
+        test_shards_of_one_pass_are_computed_as_each_alone(model, "f32", kw, cut)
