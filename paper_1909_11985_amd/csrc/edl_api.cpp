@@ -280,7 +280,9 @@ void plan_layout(const edl_config& c, const Graph& g, Layout& L) {
         const Op& op = g.ops[i];
         if (op.kind == OP_CONV) {
             const Tensor& tx = g.tensors[(size_t)op.x];
-            if (storage_of(g, op.x) != 0) L.wT[i] = take((int64_t)op.K * op.R * op.S * tx.C * esz);
+            // fully connected layers: none, the input gradient reads the bf16 weights themselves
+            const bool in_place = conv_dgrad_reads_weights(c.dtype, geom_of(g, op, 1), op.w_off);
+            if (storage_of(g, op.x) != 0 && !in_place) L.wT[i] = take((int64_t)op.K * op.R * op.S * tx.C * esz);
             else if (op.x == 0 && L.cpad != tx.C) L.wpad[i] = take((int64_t)op.K * op.R * op.S * L.cpad * esz);
         } else if (op.kind == OP_BN) {
             L.bn_save[i] = take(4 * 2 * (int64_t)op.K * L.pass_shards);
@@ -848,6 +850,11 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
 
 static int apply_range(edl_handle* h, int32_t p, int64_t lo, int64_t hi, hipStream_t st, int max_blocks = 0);
 
+// What the input gradient of layer i reads: the transposed copy, or the bf16 weights where there is none.
+static const void* dgrad_weights(const edl_handle* h, size_t i) {
+    return h->L.wT[i] >= 0 ? (const void*)(h->arena + h->L.wT[i]) : (const void*)(h->arena + h->L.shadow + 2 * h->g.ops[i].w_off);
+}
+
 // early_p > 0: this is the last backward pass of a step of early_p shards, so gradients that are final may be
 // applied while the pass goes on.
 // held (debugging hook only): tensors whose gradient buffers already hold a contribution the pass adds to.
@@ -936,29 +943,41 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 // Parameters are laid out in layer order, so everything from this layer's weights on now has its
                 // final gradient: the second stream holds the weight gradients, and the event it waited for
                 // covers what the main stream has written (bias and batch-norm gradients of the later layers)
-                // and read (their batch-norm scales).  Nothing of the rest of the pass reads those parameters
-                // (input gradients use the transposed copies), so their update starts now, on a third stream, if
+                // and read (their batch-norm scales, and the weights of those whose input gradient reads them where
+                // they lie).  Nothing of the rest of the pass reads those parameters but this layer's own input
+                // gradient, if it is of that kind: the update then waits for it as well.  Other input gradients use
+                // transposed copies.  So their update starts now, on a third stream, if
                 // the layer is a large one (chunk_min weights or more: the update of a small piece gains less than
                 // its launch beside the input-gradient chain costs).  The piece starts at the layer's first weight
                 // rounded up to 64, so that the vector accesses stay aligned; the few weights below go with the
                 // next piece or with the rest of the update after the pass.
-                const int64_t chunk_min = tune().early_update;
-                if (early_p > 0 && ws == h->side && ws != st && h->upd != nullptr && chunk_min > 0) {
-                    const int64_t lo = (op.w_off + 63) / 64 * 64;
-                    const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
-                    if (lo > 0 && lo < h->applied_from && own >= chunk_min) {
-                        hipEvent_t ev = h->ev_chunk[h->chunk_slot];
-                        h->chunk_slot = (h->chunk_slot + 1) % kChunkEvents;
-                        if (hipEventRecord(ev, h->side) == hipSuccess && hipStreamWaitEvent(h->upd, ev, 0) == hipSuccess) {
-                            // held to few workgroups: a full-width launch would take the CUs from the chain of
-                            // input gradients for as long as it runs
-                            const int early_blocks = (int)tune().early_blocks;
-                            apply_range(h, early_p, lo, h->applied_from, h->upd, early_blocks);
-                            h->applied_from = lo;
-                            used_upd = true;
+                const bool reads_weights = storage_of(g, op.x) != 0 && h->L.wT[ii] < 0;
+                auto wait_for_main = [&]() {
+                    hipEvent_t ev = h->ev_chunk[h->chunk_slot];
+                    h->chunk_slot = (h->chunk_slot + 1) % kChunkEvents;
+                    return hipEventRecord(ev, st) == hipSuccess && hipStreamWaitEvent(h->upd, ev, 0) == hipSuccess;
+                };
+                auto update_early = [&]() {
+                    const int64_t chunk_min = tune().early_update;
+                    if (early_p > 0 && ws == h->side && ws != st && h->upd != nullptr && chunk_min > 0) {
+                        const int64_t lo = (op.w_off + 63) / 64 * 64;
+                        const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
+                        if (lo > 0 && lo < h->applied_from && own >= chunk_min) {
+                            hipEvent_t ev = h->ev_chunk[h->chunk_slot];
+                            h->chunk_slot = (h->chunk_slot + 1) % kChunkEvents;
+                            if (hipEventRecord(ev, h->side) == hipSuccess && hipStreamWaitEvent(h->upd, ev, 0) == hipSuccess &&
+                                (!reads_weights || wait_for_main())) {
+                                // held to few workgroups: a full-width launch would take the CUs from the chain of
+                                // input gradients for as long as it runs
+                                const int early_blocks = (int)tune().early_blocks;
+                                apply_range(h, early_p, lo, h->applied_from, h->upd, early_blocks);
+                                h->applied_from = lo;
+                                used_upd = true;
+                            }
                         }
                     }
-                }
+                };
+                if (!reads_weights) update_early();
                 const int sx = storage_of(g, op.x);
                 if (sx != 0) {
                     // If the layer just before in the list produced this convolution's input and ends in a ReLU, and
@@ -983,13 +1002,14 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                             }
                         }
                     }
-                    const RowCut left = launch_conv_dgrad(dt, q, S, h->grad(op.y), h->arena + h->L.wT[ii], acc, h->grad(op.x),
+                    const RowCut left = launch_conv_dgrad(dt, q, S, h->grad(op.y), dgrad_weights(h, ii), acc, h->grad(op.x),
                                                           h->sc<float>(h->L.splitk_scratch), (size_t)h->L.splitk_scratch_bytes,
-                                                          mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr);
+                                                          mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr, reads_weights);
                     h->grad_alias[(size_t)sx] = nullptr;
                     if (left.p > 0) { fused_for = ii - 1; fused_sums = left; }
                     written[(size_t)sx] = 1;
                 }
+                if (reads_weights) update_early();
                 break;
             }
             case OP_BN: {
@@ -1068,8 +1088,9 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                                               ws == h->side ? (size_t)h->L.wgrad_scratch_bytes : 0, ws);
                             // input gradient, with this stream's own split-reduction scratch; nothing to hand over (the
                             // block's first convolution is the last to add to this gradient)
-                            launch_conv_dgrad(dt, qj, S, h->grad(pj.y), h->arena + h->L.wT[ii - 2], written[(size_t)pj_sx] != 0,
-                                              h->grad(pj.x), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, nullptr, bs);
+                            launch_conv_dgrad(dt, qj, S, h->grad(pj.y), dgrad_weights(h, ii - 2), written[(size_t)pj_sx] != 0,
+                                              h->grad(pj.x), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, nullptr, bs,
+                                              nullptr, h->L.wT[ii - 2] < 0);
                             written[(size_t)pj_sx] = 1;
                             (void)hipEventRecord(dn, bs);
                             done[ii - 1] = done[ii - 2] = 1;

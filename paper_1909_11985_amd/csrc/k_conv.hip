@@ -129,6 +129,7 @@ struct ConvArgs {
     int shards, splits, zdirect;
     long long zstride;
     int strip;      // forward / dgrad of 3x3, stride 1: the kernel whose steps are a kernel row's three taps (takes_strips)
+    int brows;      // dgrad of a fully connected layer: B is the weights as they lie, [K][C] (conv_dgrad_reads_weights)
 };
 
 // The tables of a launch over several shards.  One shard takes kernels without them: the table look-ups (and the
@@ -377,7 +378,10 @@ __device__ __forceinline__ int64_t out_row(const ConvArgs& a, int row) {
 // image its fragment is read from a row of zeros behind the strip.  What this saves is operand delivery (a 128x64 step
 // of 96 elements loads 21 KB instead of 37 KB) and two of three barriers: VGG-16's 64-channel layers at 224x224, shard
 // of 32: 278 -> 238 us forward, 362 -> 277 us dgrad (two launches each).
-template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND, int TAPS = 1>
+// BROWS: dgrad with B = the weights as they lie ([K][C]: the reduction is the slow index), for fully connected layers.
+// B's tile is BK rows of BN channels, loaded and read (transposed on the way out of LDS) like the bf16 weight gradient's;
+// the fragments hold the same elements in the same order as those of a transposed copy, so the bits are the same.
+template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND, int TAPS = 1, bool BROWS = false>
 __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND>::type args) {   // at least two waves per SIMD: 256 registers
     typename ArgsOf<KIND>::use a = args;
     constexpr bool SHARDS = KIND == SHARDED;
@@ -415,6 +419,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     constexpr int NST = DMA ? PF + 1 : 2;            // LDS stages
     constexpr int LDK = DIRECT ? BK : BK + VEC;
     static_assert(!STRIP || (DIRECT && RB == 64 && TAPS == 3), "strips are loaded straight into LDS");
+    static_assert(!BROWS || (DIRECT && !STRIP && MODE == CONV_DGRAD && sizeof(T) == 2), "rows of weights are loaded straight into LDS");
     constexpr int A_STAGE = STRIP ? STRIP_ROWS * RB : WGT ? BK * BM * 2 : WG ? KD * LDPA * 4 : BM * LDK * (int)sizeof(T);   // bytes per LDS stage
     constexpr int B_STAGE = STRIP ? TAPS * BN * RB : WGT ? BK * BN * 2 : WG ? KD * LDPB * 4 : BN * LDK * (int)sizeof(T);
     // epilogue staging: the rows of one wave row, as float32
@@ -478,6 +483,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     bool okB[WG ? 1 : ITER_B];
     int tr = 0, ts = 0, tc = 0, tap_off = 0;   // fwd/dgrad: kernel tap and channel of this thread's vector
     int kcur = 0;                    // reduction index of this thread's vector (fwd/dgrad) or of the tile (wgrad)
+    int brow = 0;                    // BROWS: row of the weights of this thread's first vector of B
     constexpr int NOA = DIRECT_WG ? DA : WG ? ITER_A : 1, NPB = DIRECT_WG ? DB : WG ? ITER_B : 1;
     int64_t offA[NOA];               // wgrad: offset of dy[first pixel of the item][first row of the item]
     int pn[NPB], pho[NPB], pwo[NPB]; // wgrad: first pixel of the item
@@ -551,11 +557,20 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         }
         #pragma unroll
         for (int it = 0; it < ITER_A; ++it) rowA[it] = make_row<MODE, FAST>(a, m0 + (tid + it * 256) / KV, m_end);
-        #pragma unroll
-        for (int it = 0; it < ITER_B; ++it) {
-            const int j = n0 + (tid + it * 256) / KV;
-            okB[it] = j < a.Nn && (tid + it * 256) < TOT_B;
-            offB[it] = (int64_t)j * a.ldb;
+        if (BROWS) {
+            // slots as in the weight gradient below; a lane's rows are 256 / RVB apart, its channels the same in all
+            const int pb = tid % RVB;
+            const int j = n0 + ((((pb >> 1) ^ wg_swizzle<BN>(tid / RVB)) << 4) | ((pb & 1) << 3));
+            brow = kbeg + tid / RVB;
+            okB[0] = j < a.Nn;
+            offB[0] = j;
+        } else {
+            #pragma unroll
+            for (int it = 0; it < ITER_B; ++it) {
+                const int j = n0 + (tid + it * 256) / KV;
+                okB[it] = j < a.Nn && (tid + it * 256) < TOT_B;
+                offB[it] = !FAST && a.brows ? j : (int64_t)j * a.ldb;
+            }
         }
     } else if (DIRECT_WG) {
         // slot p of pixel row x holds the 8 channels starting at (((p >> 1) ^ wg_swizzle(x)) << 4) | ((p & 1) << 3)
@@ -638,10 +653,17 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                                      a_voffset<MODE, T>(a, rowA[it], tr, ts, tc, tap_off, in_k));
             #pragma unroll
             for (int it = 0; it < ITER_B; ++it) {
+                if (BROWS) {
+                    const int row = brow + it * (256 / RVB);
+                    const unsigned off = ((unsigned)row * (unsigned)a.C + (unsigned)offB[0]) * (unsigned)sizeof(T);
+                    buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096, off | ((okB[0] & (row < kend)) ? 0u : kOutOfRange));
+                    continue;
+                }
                 const int boff = MODE == CONV_FWD ? kcur : tap_off;
                 buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096,
                                      (okB[it] && in_k) ? (unsigned)((int)offB[it] + boff) * (unsigned)sizeof(T) : kOutOfRange);
             }
+            brow += BK;
             const int inner = MODE == CONV_FWD ? a.C : a.K;
             kcur += BK;
             const int tap = fast_div(kcur, a.magic_inner);
@@ -714,7 +736,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                             const int tap = (kcur + e) / a.K, ri = a.ns > 0 ? tap / a.ns : 0;
                             boff = ((a.r0 + ri * a.stride) * a.S + a.s0 + (tap - ri * a.ns) * a.stride) * a.K + (kcur + e - tap * a.K);
                         }
-                        if (kcur + e < kend) rb[set][it].e[e] = Bg[offB[it] + boff];
+                        if (kcur + e < kend) rb[set][it].e[e] = Bg[offB[it] + (a.brows ? (int64_t)boff * a.C : boff)];
                     }
                 }
             }
@@ -918,8 +940,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 for (int i = 0; i < TM; ++i)
                     fa[i] = *reinterpret_cast<const uint4*>(&Ab[((wm * TM + i) * 32 + (lane & 31)) * LDK + slot * VEC]);
                 #pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    fb[j] = *reinterpret_cast<const uint4*>(&Bb[((wn * TN + j) * 32 + (lane & 31)) * LDK + slot * VEC]);
+                for (int j = 0; j < TN; ++j) {
+                    if constexpr (BROWS) fb[j] = tr_frag<BN>(Bb, (wn * TN + j) * 32, g * 16, lane);
+                    else fb[j] = *reinterpret_cast<const uint4*>(&Bb[((wn * TN + j) * 32 + (lane & 31)) * LDK + slot * VEC]);
+                }
             } else if (WGT) {
                 const bf16_t* const Ab = reinterpret_cast<const bf16_t*>(As + buf * A_STAGE);
                 const bf16_t* const Bb = reinterpret_cast<const bf16_t*>(Bs + buf * B_STAGE);
@@ -1515,6 +1539,17 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<K
             return;
         }
     }
+    if constexpr (MODE == CONV_DGRAD && KIND != CLASSES && sizeof(T) == 2 && EDL_DIRECT_LDS != 0) {
+        if (a.brows) {      // reduction steps and stages as below (the rows are few: long reductions, full steps for 128x128)
+            const bool tail = total > (double)tune().small_tail_from && total <= (double)tune().small_tail_to;
+            if (t == T128x128) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 2, BK, true, 1, KIND, 1, true>), grid, dim3(256), 0, st, a);
+            else if (t == T128x64) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 2, 1, BK / 2, true, 1, KIND, 1, true>), grid, dim3(256), 0, st, a);
+            else if (t == T128x32) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 4, 1, 1, 1, BK, true, 1, KIND, 1, true>), grid, dim3(256), 0, st, a);
+            else if (tail) hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, true, 1, KIND, 1, true>), grid, dim3(256), 0, st, a);
+            else hipLaunchKernelGGL((conv_igemm_kernel<T, MODE, 2, 2, 1, 1, BK, true, 2, KIND, 1, true>), grid, dim3(256), 0, st, a);
+            return;
+        }
+    }
     switch (t) {
         case T128x128: {
             // Long reductions (VGG-16's 3x3 layers: 1,152 to 4,608 elements) run faster on full-length reduction
@@ -1567,7 +1602,6 @@ static void launch_cfg(TileCfg t, bool fast, dim3 tiles, const typename ArgsOf<K
 
 static const char* conv_label(int dtype, int mode, TileCfg t) {
     if (t == T32x128) return "conv_wgrad_f32_32x128";
-
     static const char* names[2][3][4] = {
         {{"conv_fwd_f32_128x128", "conv_fwd_f32_128x64", "conv_fwd_f32_128x32", "conv_fwd_f32_64x64"},
          {"conv_dgrad_f32_128x128", "conv_dgrad_f32_128x64", "conv_dgrad_f32_128x32", "conv_dgrad_f32_64x64"},
@@ -1609,6 +1643,7 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a
         t = T64x64;
         grid.x = (a.M + 63) / 64;
         grid.y = (a.Nn + 63) / 64;
+        if (a.brows) a.vecB = 0;      // the element-wise kernel's vectors of B are along the reduction
     }
     // Tile order: the reduction cuts are the slowest index, so a die's run of tiles
     // stays within few cuts; inside a cut the tiles that share the larger operand
@@ -1812,8 +1847,18 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     return a.stats ? a.cut : RowCut();
 }
 
+// Fully connected layers (one pixel, one tap) in bf16: there the transposed copy costs more than the input gradient itself
+// (VGG-16, shard of 32: 118 us to copy 124 M weights, 104 us for the three launches that read the copy), which reads every
+// weight once, for few rows.  Convolutions read theirs for thousands of rows and keep the copy.  The vectors of B are
+// eight channels of one row, so rows are to start on 16 bytes.  Step of VGG-16, shard of 32: 4,946 -> 4,822 us; AlexNet,
+// two shards of 64: 1,613 -> 1,578 us.
+bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
+    return EDL_DIRECT_LDS != 0 && dtype == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.H == 1 && g.W == 1 &&
+           g.K % 8 == 0 && g.C % 8 == 0 && w_off % 8 == 0;
+}
+
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
-                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src) {
+                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows) {
     RowCut left;
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
@@ -1828,6 +1873,7 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
     const bool stride_pow2 = g.stride == 1 || g.stride == 2 || g.stride == 4;
     a.vecA = (g.K % VEC == 0) && bA < 2147483648.0 && stride_pow2; a.vecB = (a.ldb % VEC == 0) && bB < 2147483648.0;
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
+    a.brows = w_rows;
     const bool want_mask = tune().fused_mask != 0 && mask != nullptr && mask->act != nullptr && g.stride == 1;
     // Stride 2: the four residue classes of the input pixel modulo the stride in one launch (each alone is a quarter of
     // the pixels, three of a 1x1 convolution's only zeros: 24 launches fewer in ResNet-50's chain)

@@ -1001,3 +1001,19 @@ def test_row_tiles_inside_a_shard_read_their_neighbours(model, kw, cut, tile):
     import paper_1909_11985_amd as E
     with E.options(force_tile=tile):
         test_shards_of_one_pass_are_computed_as_each_alone(model, "f32", kw, cut)
+
+
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("classes,arch,n", [
+    (8, (8, 8), 1),             # less than a tile each way
+    (16, (72, 200), 70),        # rows and columns of the weights that end inside a tile, two row tiles
+    (24, (1032, 1000), 130),    # a reduction that is cut, its last piece short
+    (10, (72, 204), 9),         # rows that do not start on 16 bytes: the transposed copy
+])
+def test_input_gradients_that_read_the_weights_where_they_lie(classes, arch, n, tile):
+    """bf16 fully connected layers have no transposed copy: every tile shape, alone and over several shards."""
+    import paper_1909_11985_amd as E
+    geom = dict(H=1, W=1, C=64, classes=classes, arch=arch)
+    with E.options(force_tile=tile):
+        _assert_layerwise(layerwise_parity("mlp", "bf16", n, verbose=False, **geom), "bf16")
+        test_shards_of_one_pass_are_computed_as_each_alone("mlp", "bf16", geom, [n, 0, 1, n])
