@@ -717,6 +717,16 @@ int32_t edl_shard(const edl_handle* h, int64_t B, int32_t p, int64_t epoch, int6
     return edl_shard_host(h->seed, h->cfg.N, B, p, epoch, step_in_epoch, out_idx, out_off);
 }
 
+// Whether a pass may put work on the side streams: not while kernels are timed one by one, and not on the library's
+// shared pair while the job's stream is being captured into a graph - the capture would take the pair in, and with it
+// what the other jobs of this GPU queue there meanwhile.  (The caller's own streams are the caller's to share.)
+static bool side_streams_usable(const edl_handle* h) {
+    if (prof_enabled()) return false;
+    if (!h->own_streams || h->st == nullptr) return true;      // the default stream cannot be captured
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(h->st, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
+}
+
 // Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
 // op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
 // single layers from the debugging hooks, which then skip the gather)
@@ -752,7 +762,7 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
     // A residual block's projection shortcut (convolution + batch norm on the block's input) runs on the second
     // side stream while the main branch runs here; the block's last batch norm, which adds the two, waits for it.
     // Only when the whole list runs and nothing is being timed kernel by kernel.
-    const bool branch = op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && !prof_enabled() && tune().branch_stream != 0;
+    const bool branch = op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && side_streams_usable(h) && tune().branch_stream != 0;
     std::vector<char>& done = h->op_done;
     std::fill(done.begin(), done.end(), 0);
     int join_tensor = -1;
@@ -880,7 +890,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
         for (int t : *held) written[(size_t)storage_of(g, t)] = 1;
     if (op_hi > g.ops.size()) op_hi = g.ops.size();
     // per-kernel timing wants one kernel at a time
-    const bool overlap = h->side != nullptr && !prof_enabled();
+    const bool overlap = h->side != nullptr && side_streams_usable(h);
     bool used_side = false, used_upd = false;
     // the projection shortcut's backward on the second side stream (see forward_pass)
     const bool branch = overlap && op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && tune().branch_stream != 0;
@@ -1208,7 +1218,7 @@ int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_
     // The transposed copies are first read by the backward pass: they are made on the weight-gradient stream, which
     // is idle during the forward pass, and the first backward pass waits for them.
     h->transposes_pending = false;
-    if (h->side != nullptr && !prof_enabled() && tune().transpose_stream != 0 &&
+    if (h->side != nullptr && side_streams_usable(h) && tune().transpose_stream != 0 &&
         hipEventRecord(h->ev_tr_go, h->st) == hipSuccess && hipStreamWaitEvent(h->side, h->ev_tr_go, 0) == hipSuccess) {
         transpose_weights(h, h->side);
         h->transposes_pending = hipEventRecord(h->ev_tr_done, h->side) == hipSuccess;
