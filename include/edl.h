@@ -283,11 +283,15 @@ int32_t edl_apply(edl_handle* h, int32_t p);
  * (p divides B, p <= p_max, B/p <= max_shard), from the largest down to the
  * smallest, `steps` mini-batches each.  These are ordinary training steps: the
  * model and the progress move on exactly as by `steps` calls of edl_step per p.
+ * (Where edl_step would run several shards together, the workers' passes that
+ * are timed are run beside the step's own, so the call takes both times.)
  * Reported per p, timed with HIP events on the job's stream:
- *   ms_per_step, samples_per_s    one mini-batch of B samples on this GPU (all
- *                                 p shards back to back, then the update);
+ *   ms_per_step, samples_per_s    one mini-batch of B samples worker by worker on
+ *                                 this GPU (all p shards back to back, each in
+ *                                 passes of its own, then the update; edl_step
+ *                                 runs the shards together and takes less);
  *   worker_samples_per_s  t(p)    what one worker sustains on its shard of B/p
- *                                 samples: B / (time of the p gradient passes);
+ *                                 samples: B / (time of those p gradient passes);
  *   efficiency            t(p) / max over the profiled p of t(p) (the paper's
  *                         GPU efficiency, with one GPU standing in for each
  *                         worker and no gradient exchange).

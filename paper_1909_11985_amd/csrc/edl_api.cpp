@@ -1167,7 +1167,9 @@ static int check_p(const edl_handle* h, int32_t p) {
     return EDL_OK;
 }
 
-int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* off, float* out_loss) {
+// The gradient passes of one mini-batch.  alone: every shard in a pass of its own, as the worker that holds only this
+// shard would run it, and without touching the running statistics (a measurement; the buffers cannot be applied).
+static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* off, float* out_loss, bool alone) {
     if (!h) { set_error("null handle"); return EDL_EINVAL; }
     if (!h->data_x) { set_error("no data set bound"); return EDL_EINVAL; }
     if ((idx == nullptr) != (off == nullptr)) { set_error("idx and off must both be given or both be NULL"); return EDL_EINVAL; }
@@ -1235,16 +1237,16 @@ int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_
     // consecutive shards in passes of as many as the workspace holds
     for (int k = 0; k <= last_k;) {
         ShardSet S = {};
-        S.plan = equal ? shards_per_pass(h, sizes[0], p) * (int)sizes[0] : 0;
+        S.plan = equal && !alone ? shards_per_pass(h, sizes[0], p) * (int)sizes[0] : 0;
         for (; k <= last_k; ++k) {
             if (sizes[k] == 0) continue;
-            if (S.p > 0 && (S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
+            if (S.p > 0 && (alone || S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
             S.k[S.p] = k;
             S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
             S.p += 1;
         }
-        if (!equal) S.plan = S.samples();
-        forward_pass(h, S, dev_idx + at, dev_losses, first);
+        if (S.plan == 0) S.plan = S.samples();
+        forward_pass(h, S, dev_idx + at, dev_losses, first && !alone);
         backward_pass(h, S, 0, (size_t)-1, k > last_k ? h->early_p : 0);
         first = false;
         at += S.samples();
@@ -1263,8 +1265,12 @@ int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_
         }
         *out_loss = (float)s;
     }
-    h->grads_pending = true;
+    h->grads_pending = !alone;
     return EDL_OK;
+}
+
+int32_t edl_gradients(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* off, float* out_loss) {
+    return gradient_passes(h, p, idx, off, out_loss, false);
 }
 
 // bias corrections of update number t, formed in double
@@ -1376,42 +1382,55 @@ int32_t edl_profile_parallelism(edl_handle* h, int32_t min_p, int32_t max_p, int
         if (h->cfg.B % p == 0 && h->cfg.B / p <= h->cfg.max_shard) ps.push_back(p);
     if (ps.empty()) { set_error("no parallelism in [%d, %d] fits B=%lld, p_max=%d, max_shard=%d", min_p, max_p, (long long)h->cfg.B, h->cfg.p_max, h->cfg.max_shard); return EDL_EINVAL; }
     if ((size_t)cap < ps.size()) { set_error("%zu entries needed", ps.size()); return EDL_ENOMEM; }
-    std::vector<hipEvent_t> ev((size_t)steps * 2 + 1);
-    for (hipEvent_t& e : ev) HIP_TRY(hipEventCreate(&e));
+    // A step runs the shards of a mini-batch together, which no worker with a shard of its own does: what the workers
+    // sustain is timed on passes of one shard each.  The step that moves the model runs as ever (where it would run
+    // the same passes, those are the timed ones).
+    std::vector<hipEvent_t> ev((size_t)steps * 4, nullptr);
     int rc = EDL_OK;
+    for (hipEvent_t& e : ev)
+        if (rc == EDL_OK && hipEventCreate(&e) != hipSuccess) { set_error("hipEventCreate failed"); rc = EDL_EHIP; }
+    auto mark = [&](int t, int which) -> int {
+        if (hipEventRecord(ev[(size_t)4 * t + which], h->st) == hipSuccess) return EDL_OK;
+        set_error("hipEventRecord failed");
+        return EDL_EHIP;
+    };
     for (size_t i = 0; i < ps.size() && rc == EDL_OK; ++i) {
         const int32_t p = ps[i];
-        // ev[2t]: before the gradient passes of step t; ev[2t+1]: after them, before the update; ev[2*steps]: end
+        const bool together = shards_per_pass(h, h->cfg.B / p, p) > 1;
+        // per step: before the workers' passes, after them, before the update, after it
         for (int t = 0; t < steps && rc == EDL_OK; ++t) {
-            if (hipEventRecord(ev[(size_t)2 * t], h->st) != hipSuccess) { set_error("hipEventRecord failed"); rc = EDL_EHIP; break; }
-            rc = edl_gradients(h, p, nullptr, nullptr, nullptr);
-            if (rc) break;
-            if (hipEventRecord(ev[(size_t)2 * t + 1], h->st) != hipSuccess) { set_error("hipEventRecord failed"); rc = EDL_EHIP; break; }
-            rc = edl_apply(h, p);
+            rc = mark(t, 0);
+            if (!rc) rc = gradient_passes(h, p, nullptr, nullptr, nullptr, together);
+            if (!rc) rc = mark(t, 1);
+            if (!rc && together) rc = edl_gradients(h, p, nullptr, nullptr, nullptr);
+            if (!rc) rc = mark(t, 2);
+            if (!rc) rc = edl_apply(h, p);
+            if (!rc) rc = mark(t, 3);
         }
         if (rc) break;
-        if (hipEventRecord(ev[(size_t)2 * steps], h->st) != hipSuccess || hipEventSynchronize(ev[(size_t)2 * steps]) != hipSuccess) {
+        if (hipEventSynchronize(ev.back()) != hipSuccess) {
             set_error("timing events failed");
             rc = EDL_EHIP;
             break;
         }
-        float total_ms = 0.f;
-        double grad_ms = 0.0;
-        (void)hipEventElapsedTime(&total_ms, ev[0], ev[(size_t)2 * steps]);
+        double grad_ms = 0.0, total_ms = 0.0;
         for (int t = 0; t < steps; ++t) {
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, ev[(size_t)2 * t], ev[(size_t)2 * t + 1]);
-            grad_ms += ms;
+            float grad = 0.f, update = 0.f;
+            (void)hipEventElapsedTime(&grad, ev[(size_t)4 * t], ev[(size_t)4 * t + 1]);
+            (void)hipEventElapsedTime(&update, ev[(size_t)4 * t + 2], ev[(size_t)4 * t + 3]);
+            grad_ms += grad;
+            total_ms += (double)grad + update;
         }
         edl_parallelism_point& o = out[i];
         o.p = p;
         o.shard = (int32_t)(h->cfg.B / p);
-        o.ms_per_step = (double)total_ms / steps;
+        o.ms_per_step = total_ms / steps;
         o.samples_per_s = (double)h->cfg.B / (o.ms_per_step * 1e-3);
         o.worker_samples_per_s = (double)h->cfg.B / (grad_ms / steps * 1e-3);
         o.efficiency = 0.0;
     }
-    for (hipEvent_t e : ev) (void)hipEventDestroy(e);
+    for (hipEvent_t e : ev)
+        if (e) (void)hipEventDestroy(e);
     if (rc) return rc;
     double best = 0.0;
     for (size_t i = 0; i < ps.size(); ++i) best = std::max(best, out[i].worker_samples_per_s);

@@ -531,6 +531,34 @@ def test_profile_parallelism_scales_in_and_trains_like_the_same_steps():
         job.profile_parallelism(1, 4, 0)
 
 
+def test_profile_reports_what_a_worker_alone_sustains():
+    """t(p) is that of a worker with only its shard of B/p (here of a job of that shard alone, 8 times the smaller), not
+    of the pass that runs the shards together, which takes about a fifth of the time; and the model moves exactly as by
+    edl_step."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    B, p = 128, 8
+    x, y = synth_inputs.dataset(1, 2 * B, 32, 32, 3, 10)
+    dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+
+    def job(b, p_max, n):
+        j = E.Job(make_config("resnet20", N=n, B=b, p_max=p_max, max_shard=B // p), 1)
+        j.bind_dataset(dx[:n].contiguous(), dy[:n].contiguous())
+        return j
+    whole, twin, alone = job(B, p, 2 * B), job(B, p, 2 * B), job(B // p, 1, B)
+    whole.profile_parallelism(p, p, 3)
+    alone.profile_parallelism(1, 1, 3)
+    t, t1 = whole.profile_parallelism(p, p, 20)[0], alone.profile_parallelism(1, 1, 20)[0]
+    assert t["shard"] == t1["shard"] == B // p
+    assert t["worker_samples_per_s"] < 2 * t1["worker_samples_per_s"], (t, t1)
+    for _ in range(23):
+        twin.step(p)
+    assert whole.progress() == twin.progress()
+    assert np.array_equal(whole.params(), twin.params()) and np.array_equal(whole.momentum(), twin.momentum())
+    assert np.array_equal(whole.running(), twin.running())
+
+
 # ---------------------------------------------------------------- shards of unequal size
 @pytest.mark.parametrize("model,dtype", [("mlp", "f32"), ("resnet20", "f32"), ("resnet50", "bf16")])
 def test_unequal_shards_weigh_in_with_their_share(model, dtype):
