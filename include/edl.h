@@ -372,6 +372,10 @@ int32_t edl_debug_backward_range(edl_handle* h, int32_t op_lo, int32_t op_hi, in
 int32_t edl_debug_backward_range_from(edl_handle* h, int32_t op_lo, int32_t op_hi, int32_t n, int32_t k,
                                       const int32_t* held, int32_t n_held);
 int32_t edl_debug_set_labels(edl_handle* h, const int32_t* labels, int32_t n);
+/* Bytes of partial results that the weight gradients of one pass over p shards of the given sizes (host int64[p])
+ * are cut into, and the bytes that the arena's plan has for them.  Host only.  EDL_ERANGE if the shards do not run
+ * in one pass. */
+int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t* sizes, int64_t* out_needed, int64_t* out_there);
 
 int32_t edl_shutdown(edl_handle* h);
 

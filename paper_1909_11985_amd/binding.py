@@ -100,6 +100,7 @@ _SIGS = {
     "edl_debug_backward_range": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32],
     "edl_debug_backward_range_from": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_int32],
     "edl_debug_set_labels": [C.c_void_p, C.POINTER(C.c_int32), C.c_int32],
+    "edl_debug_wgrad_scratch": [C.POINTER(Config), C.c_int32, _i64p, _i64p, _i64p],
     "edl_set_side_streams": [C.c_void_p, C.c_void_p, C.c_void_p],
     "edl_set_option": [C.c_char_p, C.c_int64],
     "edl_get_option": [C.c_char_p, _i64p],
@@ -160,6 +161,14 @@ def edl_query(cfg):
     s = Sizes()
     _check(lib.edl_query(C.byref(cfg), C.byref(s)))
     return s
+
+
+def edl_debug_wgrad_scratch(cfg, sizes):
+    """(bytes needed, bytes there) for the cut weight gradients of one pass over shards of these sizes."""
+    sizes = np.ascontiguousarray(sizes, dtype=np.int64)
+    need, there = C.c_int64(), C.c_int64()
+    _check(lib.edl_debug_wgrad_scratch(C.byref(cfg), len(sizes), sizes.ctypes.data_as(_i64p), C.byref(need), C.byref(there)))
+    return need.value, there.value
 
 
 def edl_tensor_table(cfg):

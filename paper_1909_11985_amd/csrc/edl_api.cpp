@@ -154,9 +154,10 @@ int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shard
             const Tensor& tx = g.tensors[(size_t)op.x];
             const Tensor& ty = g.tensors[(size_t)op.y];
             if (op.x == 0 && L.cpad != tx.C) dwpad_bytes = std::max<int64_t>(dwpad_bytes, (int64_t)op.K * op.R * op.S * L.cpad * 4 * shards);
-            for (int q = 1; q <= shards; ++q)
+            // a weight gradient is cut for the largest of the pass's q shards, which may hold all but one sample of each other
+            for (int q = 1; q <= shards && q <= samples; ++q)
                 L.wgrad_scratch_bytes = std::max<int64_t>(
-                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(c.dtype, geom_padded(g, op, std::max(1, std::min(c.max_shard, samples / q)), L.cpad), q));
+                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(c.dtype, geom_padded(g, op, std::min(c.max_shard, samples - (q - 1)), L.cpad), q));
             // the cut of a forward / dgrad reduction depends on the size of the pass: cover every size up to the largest
             for (int n = 1; n <= samples; n = n < 8 ? n + 1 : n + n / 4)
                 L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
@@ -403,6 +404,32 @@ int32_t edl_query(const edl_config* cfg, edl_sizes* out) {
     out->second_off = L.second;
     out->shadow_off = L.shadow;
     out->scratch_bytes = L.scratch_hi - L.scratch_lo;
+    return EDL_OK;
+}
+
+int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t* sizes, int64_t* out_needed, int64_t* out_there) {
+    if (!cfg || !sizes || !out_needed || !out_there) { set_error("null argument"); return EDL_EINVAL; }
+    int rc = validate(*cfg);
+    if (rc) return rc;
+    if (p <= 0 || p > cfg->p_max) { set_error("p=%d outside [1, p_max=%d]", p, cfg->p_max); return EDL_EINVAL; }
+    Graph g;
+    rc = build_graph(*cfg, g);
+    if (rc) return rc;
+    Layout L;
+    plan_layout(*cfg, g, L);
+    ShardSet S = {};
+    for (int k = 0; k < p; ++k) {
+        if (sizes[k] <= 0 || sizes[k] > cfg->max_shard) { set_error("shard %d outside [1, max_shard]", k); return EDL_EINVAL; }
+        S.off[k + 1] = S.off[k] + (int)sizes[k];
+        S.k[k] = k;
+    }
+    S.p = p;
+    if (p > L.pass_shards || S.samples() > L.pass_samples) { set_error("these shards do not run in one pass"); return EDL_ERANGE; }
+    *out_needed = 0;
+    *out_there = L.wgrad_scratch_bytes;
+    for (const Op& op : g.ops)
+        if (op.kind == OP_CONV)
+            *out_needed = std::max(*out_needed, (int64_t)conv_wgrad_needs(cfg->dtype, geom_padded(g, op, S.samples(), L.cpad), S));
     return EDL_OK;
 }
 

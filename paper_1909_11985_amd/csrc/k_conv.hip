@@ -1972,6 +1972,7 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
 struct WgradPlan {
     TileCfg t;
     int bm, bn, splits, ksplit;
+    int most;         // splits before the cut's length was rounded: no less for a larger shard
     int64_t tiles;
 };
 
@@ -2022,6 +2023,7 @@ static WgradPlan plan_wgrad(int dtype, const ConvGeom& g, int shards) {
     const int64_t max_splits = (Kred + 255) / 256;  // at least 4 reduction steps per split
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;
+    p.most = (int)splits;
     int64_t ks = (Kred + splits - 1) / splits;
     ks = (ks + 63) / 64 * 64;
     p.ksplit = (int)ks;
@@ -2029,10 +2031,18 @@ static WgradPlan plan_wgrad(int dtype, const ConvGeom& g, int shards) {
     return p;
 }
 
+static size_t wgrad_partial_bytes(const ConvGeom& g, int shards, int splits) {
+    return splits <= 1 ? 0 : (size_t)shards * splits * g.K * g.R * g.S * g.C * sizeof(float);
+}
+
 size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int shards) {
-    const WgradPlan p = plan_wgrad(dtype, g, shards);
-    if (p.splits <= 1) return 0;
-    return (size_t)shards * p.splits * g.K * g.R * g.S * g.C * sizeof(float);
+    return wgrad_partial_bytes(g, shards, plan_wgrad(dtype, g, shards).most);
+}
+
+size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
+    ConvGeom one = g;
+    one.N = S.largest();
+    return wgrad_partial_bytes(g, S.p, plan_wgrad(dtype, one, S.p).splits);
 }
 
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
@@ -2049,7 +2059,7 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     a.vecA = (g.K % VEC == 0) && bA < 2147483648.0; a.vecB = (g.C % VEC == 0) && bB < 2147483648.0;
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
     const int64_t n = (int64_t)a.M * a.Nn;
-    const bool direct = p.splits <= 1 || scratch == nullptr || scratch_bytes < (size_t)S.p * p.splits * n * sizeof(float);
+    const bool direct = p.splits <= 1 || scratch == nullptr || scratch_bytes < wgrad_partial_bytes(g, S.p, p.splits);
     if (direct) {
         p.splits = 1;
         p.ksplit = one.N * g.Ho * g.Wo;

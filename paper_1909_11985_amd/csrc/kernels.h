@@ -144,8 +144,9 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g);
 // dw = x^T * dy of every shard, float32 [K][R][S][C]; scratch holds split partial sums
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st);
-// g.N: samples of the largest shard
+// what any p shards need of which the largest has up to g.N samples; and what those of one pass do
 size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int p);
+size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S);
 
 // ---- batch norm, bias / ReLU backward --------------------------------------
 // floats the column reductions below take as scratch over the given rows of p shards

@@ -205,3 +205,28 @@ def test_options_are_named_set_and_read_back(E):
         assert ei.value.code == -1
         with pytest.raises(E.EdlError):
             E.edl_get_option(bad)
+
+
+@pytest.mark.parametrize("model,dtype,kw", [("resnet20", "f32", {}), ("resnet20", "f32", dict(H=25, W=25)), ("resnet50", "bf16", {}),
+                                            ("resnet50", "bf16", dict(H=161, W=161)), ("alexnet", "bf16", {}), ("vgg16", "f32", dict(H=64, W=64))])
+def test_the_arena_holds_the_cut_weight_gradients_of_any_shards(E, model, dtype, kw):
+    """A weight gradient is cut as its launch plans it, for the largest of a pass's shards: the arena has to hold the
+    partial results for near-equal and for very unequal cuts, or the launch falls back to one cut per shard."""
+    import random
+    from paper_1909_11985_amd.binding import edl_debug_wgrad_scratch, make_config
+    rng = random.Random(5)
+    checked, cuts = 0, [[22, 21, 21], [17, 16, 16], [32, 32, 32, 32, 1], [64] + [1] * 7, [58, 2, 2, 2], [1], [7, 1], [1] * 16]
+    for _ in range(60):
+        p = rng.randint(1, 16)
+        cuts.append([1 + int(rng.random() ** 3 * 36) for _ in range(p)])
+    for cut in cuts:
+        for max_shard in (max(cut), sum(cut)):
+            cfg = make_config(model, dtype=dtype, N=sum(cut), B=sum(cut), p_max=len(cut), max_shard=max_shard, **kw)
+            try:
+                need, there = edl_debug_wgrad_scratch(cfg, cut)
+            except E.EdlError as e:
+                assert e.code == -4               # more than one pass: its parts are cuts like the others
+                continue
+            checked += 1
+            assert need <= there, (cut, max_shard)
+    assert checked > len(cuts)
