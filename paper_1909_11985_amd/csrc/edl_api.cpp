@@ -202,8 +202,9 @@ int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shard
 // one launch instead of p, with p times the workgroups (ResNet-50 bf16, aggregate batch 256 as 8 shards of 32:
 // 34.5 -> 23.4 ms per step; ResNet-20 float32, 8 shards of 16: 10.3 -> 1.84 ms; MLP, 4 shards of 16: 0.48 -> 0.17 ms).  Limits, none of which cuts a single shard:
 // 32 GB of activations and gradients (a pass of some 250 images of 224x224 gains nothing more from more of them),
-// 2 GiB per tensor (the vector kernels' 32-bit offsets), and the static scratch buffer where one shard at a time
-// fits it (the two entry points run the same passes).
+// 2 GiB per tensor (the vector kernels' 32-bit offsets), what every convolution's vector kernel takes (VGG-16 on
+// 320x320 images: 95 samples), and the static scratch buffer where one shard at a time fits it (the two entry points
+// run the same passes).
 void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
     const int64_t esz = c.dtype == EDL_DTYPE_BF16 ? 2 : 4;
     int64_t per_sample = 1, widest = 1;
@@ -214,7 +215,11 @@ void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
         widest = std::max(widest, bytes);
     }
     int64_t samples = std::min<int64_t>(c.B, std::min<int64_t>(32000000000ll / per_sample, 2147483647ll / widest));
-    samples = std::max<int64_t>(std::min<int64_t>(samples, 65535), c.max_shard);
+    samples = std::min<int64_t>(samples, 65535);
+    for (const Op& op : g.ops)
+        if (op.kind == OP_CONV)
+            samples = std::min<int64_t>(samples, conv_vector_samples(geom_padded(g, op, 1, L.cpad), storage_of(g, op.x) != 0));
+    samples = std::max<int64_t>(samples, c.max_shard);
     int shards = c.p_max;
     if (plan_scratch(c, g, c.max_shard, 1, 0, L) <= (int64_t)EDL_STATIC_SCRATCH_BYTES)
         while (shards > 1 && plan_scratch(c, g, (int)samples, shards, 0, L) > (int64_t)EDL_STATIC_SCRATCH_BYTES) {

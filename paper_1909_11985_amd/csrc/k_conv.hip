@@ -1714,6 +1714,25 @@ static ConvArgsShards base_args(const ConvGeom& g) {
     return a;
 }
 
+int conv_vector_samples(const ConvGeom& g, bool dgrad) {
+    constexpr int kMost = 65535;
+    const auto ok = [&](int n) {
+        ConvArgs f = base_args(g), d = base_args(g);
+        // (of a strided input gradient the largest residue class)
+        d.Hc = (g.H + g.stride - 1) / g.stride; d.Wc = (g.W + g.stride - 1) / g.stride;
+        d.ns = (g.S + g.stride - 1) / g.stride;
+        const int64_t fm = (int64_t)n * g.Ho * g.Wo, dm = (int64_t)n * d.Hc * d.Wc;
+        if (std::max(fm, dm) >= (1ll << 31)) return false;
+        f.M = (int)fm; f.Kred = g.R * g.S * g.C;
+        d.M = (int)dm; d.Kred = g.R * g.S * g.K;
+        return conv_magic_ok(CONV_FWD, f) && (!dgrad || conv_magic_ok(CONV_DGRAD, d));
+    };
+    if (!ok(1) || ok(kMost)) return kMost;      // never on the vector path, or always
+    int lo = 1, hi = kMost;
+    while (hi - lo > 1) (ok((lo + hi) / 2) ? lo : hi) = (lo + hi) / 2;
+    return lo;
+}
+
 size_t conv_sums_floats(const ConvGeom& g, int p) {
     // the narrowest row tile is 64 rows; the finishing kernel of a cut reduction takes kRedRowBlocks blocks at most
     const auto blocks = [&](int64_t rows) { return std::max<int64_t>(rows / 64, std::min<int64_t>(rows / 16, kRedRowBlocks)) + 1 + p; };

@@ -116,6 +116,9 @@ struct SumsBuf { float* buf; size_t floats; };
 // and returns how they are cut; p == 0 if it left none.
 RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
                        bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st);
+// The most samples (65535 at most) of which a launch, forward and with dgrad also of the input gradient, keeps to the
+// vector kernel: its multiply-shift divisions are exact up to some number of pixels (g.N is ignored).
+int conv_vector_samples(const ConvGeom& g, bool dgrad);
 // floats the sums of this layer's forward and input-gradient epilogues can take over g.N samples of p shards
 size_t conv_sums_floats(const ConvGeom& g, int p);
 // What the layer that produced the convolution's input wants from the gradient dx when it ends in a ReLU:

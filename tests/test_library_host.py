@@ -230,3 +230,17 @@ def test_the_arena_holds_the_cut_weight_gradients_of_any_shards(E, model, dtype,
             checked += 1
             assert need <= there, (cut, max_shard)
     assert checked > len(cuts)
+
+
+@pytest.mark.parametrize("image,together", [(224, 4), (320, 2), (400, 1)])
+def test_shards_run_together_only_as_far_as_the_vector_kernels_reach(E, image, together):
+    """The convolution kernels' multiply-shift divisions are exact while samples * pixels^2 < 1e12: a pass of more
+    shards than that would take the element-wise kernels where each shard alone takes the vector ones."""
+    from paper_1909_11985_amd.binding import edl_debug_wgrad_scratch, make_config
+    cfg = make_config("vgg16", dtype="bf16", N=128, B=128, p_max=4, max_shard=32, H=image, W=image, arch=(32, 64, 1, 1, 1, 1, 1))
+    assert (32 * together * image ** 4 < 1e12) and (together == 4 or 32 * 4 * image ** 4 > 1e12)
+    edl_debug_wgrad_scratch(cfg, [32] * together)
+    if together < 4:
+        with pytest.raises(E.EdlError) as ei:
+            edl_debug_wgrad_scratch(cfg, [32] * 4)
+        assert ei.value.code == -4
