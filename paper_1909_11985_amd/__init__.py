@@ -6,7 +6,7 @@ to allocate device memory and to provide streams.
 """
 from .binding import (  # noqa: F401
     EdlError, Config, Sizes, Job, Pipeline, MODELS, DTYPES,
-    edl_query, edl_shard_host, edl_init_params_host, edl_tensor_table,
+    edl_query, edl_arena_bytes, edl_shard_host, edl_init_params_host, edl_tensor_table,
     edl_adam_update, edl_average_update, edl_copy, edl_mfma_rate, edl_profile, edl_profile_report, lib,
     edl_set_option, edl_get_option, options,
 )

@@ -100,6 +100,7 @@ _SIGS = {
     "edl_debug_backward_range": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32],
     "edl_debug_backward_range_from": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_int32],
     "edl_debug_set_labels": [C.c_void_p, C.POINTER(C.c_int32), C.c_int32],
+    "edl_arena_bytes": [C.POINTER(Config), C.c_int64, _i64p],
     "edl_debug_wgrad_scratch": [C.POINTER(Config), C.c_int32, _i64p, _i64p, _i64p],
     "edl_set_side_streams": [C.c_void_p, C.c_void_p, C.c_void_p],
     "edl_set_option": [C.c_char_p, C.c_int64],
@@ -161,6 +162,13 @@ def edl_query(cfg):
     s = Sizes()
     _check(lib.edl_query(C.byref(cfg), C.byref(s)))
     return s
+
+
+def edl_arena_bytes(cfg, pass_samples=0):
+    """Device memory of a job that runs up to pass_samples samples together (0: one shard at a time, the least)."""
+    n = C.c_int64()
+    _check(lib.edl_arena_bytes(C.byref(cfg), pass_samples, C.byref(n)))
+    return n.value
 
 
 def edl_debug_wgrad_scratch(cfg, sizes):
@@ -329,8 +337,10 @@ class Job:
     """One elastic job on one GPU.  Allocates the arena with torch and hands
     raw pointers to the library."""
 
-    def __init__(self, cfg, seed, device="cuda:0", stream=None, side_streams="library"):
-        """side_streams: "library" (the library's two side streams, unless the option wgrad_stream
+    def __init__(self, cfg, seed, device="cuda:0", stream=None, side_streams="library", arena_bytes=None):
+        """arena_bytes: device memory of the job (None: edl_query's arena_bytes, room for all shards of a
+        mini-batch together; with less, down to edl_arena_bytes(cfg), a step takes them in several passes).
+        side_streams: "library" (the library's two side streams, unless the option wgrad_stream
         is 0), "torch" (two torch.cuda.Stream objects of default priority made here and handed over), or None
         (everything on the job's stream)."""
         import torch
@@ -338,7 +348,7 @@ class Job:
         self.cfg = cfg
         self.sizes = edl_query(cfg)
         self.device = torch.device(device)
-        self.arena = torch.empty(self.sizes.arena_bytes, dtype=torch.uint8, device=self.device)
+        self.arena = torch.empty(self.sizes.arena_bytes if arena_bytes is None else arena_bytes, dtype=torch.uint8, device=self.device)
         self.stream = stream
         sp = stream.cuda_stream if stream is not None else 0
         self._h = C.c_void_p()

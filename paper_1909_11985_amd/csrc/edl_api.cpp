@@ -230,10 +230,9 @@ void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
     L.pass_samples = shards == 1 ? c.max_shard : (int)samples;
 }
 
-void plan_layout(const edl_config& c, const Graph& g, Layout& L) {
+// the arena of a job whose passes run up to L.pass_samples samples in up to L.pass_shards shards
+void plan_arena(const edl_config& c, const Graph& g, Layout& L) {
     const int64_t esz = c.dtype == EDL_DTYPE_BF16 ? 2 : 4;
-    L.cpad = input_pad(c, g);
-    plan_pass(c, g, L);
     int64_t o = 0;
     auto take = [&](int64_t bytes) { const int64_t at = o; o += align_up(bytes); return at; };
     // The arrays the update kernel walks side by side (w, v, the bf16 copy, the p gradient buffers) start on 4 KB
@@ -299,6 +298,27 @@ void plan_layout(const edl_config& c, const Graph& g, Layout& L) {
     o = plan_scratch(c, g, L.pass_samples, L.pass_shards, o, L);
     L.ttable = take((int64_t)sizeof(TransposeEntry) * 2 * std::max<size_t>(no, 1));   // element-wise entries, then vector ones
     L.total = o;
+}
+
+// The arena, for the largest pass of plan_pass or, if that takes more than arena_bytes, the largest that fits: the
+// caller bounds a job's memory by what it gives.  The state arrays lie at the same offsets whatever the pass.  Returns
+// false if not even one shard of max_shard samples at a time fits (L is the plan for that then).
+bool plan_layout(const edl_config& c, const Graph& g, Layout& L, int64_t arena_bytes = INT64_MAX) {
+    L.cpad = input_pad(c, g);
+    plan_pass(c, g, L);
+    plan_arena(c, g, L);
+    if (L.total <= arena_bytes) return true;
+    const int shards = L.pass_shards;
+    int lo = c.max_shard, hi = L.pass_samples;      // lo fits (once tried), hi does not
+    const auto fits = [&](int samples, int p) {
+        L.pass_samples = samples;
+        L.pass_shards = p;
+        plan_arena(c, g, L);
+        return L.total <= arena_bytes;
+    };
+    if (shards == 1 || !fits(lo, shards)) return fits(c.max_shard, 1);
+    while (hi - lo > 1) (fits(lo + (hi - lo) / 2, shards) ? lo : hi) = lo + (hi - lo) / 2;
+    return fits(lo, shards);
 }
 
 }  // namespace
@@ -395,7 +415,7 @@ int32_t edl_query(const edl_config* cfg, edl_sizes* out) {
     rc = build_graph(*cfg, g);
     if (rc) return rc;
     Layout L;
-    plan_layout(*cfg, g, L);
+    plan_layout(*cfg, g, L);       // no limit: all of the mini-batch together if it can be
     out->P = g.P;
     out->R = g.R;
     out->params_off = L.params;
@@ -409,6 +429,28 @@ int32_t edl_query(const edl_config* cfg, edl_sizes* out) {
     out->second_off = L.second;
     out->shadow_off = L.shadow;
     out->scratch_bytes = L.scratch_hi - L.scratch_lo;
+    return EDL_OK;
+}
+
+int32_t edl_arena_bytes(const edl_config* cfg, int64_t pass_samples, int64_t* out_bytes) {
+    if (!cfg || !out_bytes) { set_error("null argument"); return EDL_EINVAL; }
+    if (pass_samples < 0) { set_error("negative pass_samples"); return EDL_EINVAL; }
+    int rc = validate(*cfg);
+    if (rc) return rc;
+    Graph g;
+    rc = build_graph(*cfg, g);
+    if (rc) return rc;
+    Layout L;
+    if (pass_samples == 0) {
+        plan_layout(*cfg, g, L, 0);
+    } else {
+        plan_layout(*cfg, g, L);
+        if (pass_samples < L.pass_samples) {
+            L.pass_samples = (int)std::max<int64_t>(pass_samples, cfg->max_shard);
+            plan_arena(*cfg, g, L);
+        }
+    }
+    *out_bytes = L.total;
     return EDL_OK;
 }
 
@@ -599,8 +641,7 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
     h->seed = seed;
     rc = build_graph(*cfg, h->g);
     if (rc) { delete h; return rc; }
-    plan_layout(*cfg, h->g, h->L);
-    if ((int64_t)arena_bytes < h->L.total) {
+    if (!plan_layout(*cfg, h->g, h->L, (int64_t)std::min<size_t>(arena_bytes, INT64_MAX))) {
         set_error("arena of %zu bytes is smaller than the %lld needed", arena_bytes, (long long)h->L.total);
         delete h;
         return EDL_ENOMEM;

@@ -1045,3 +1045,75 @@ def test_input_gradients_that_read_the_weights_where_they_lie(classes, arch, n, 
     with E.options(force_tile=tile):
         _assert_layerwise(layerwise_parity("mlp", "bf16", n, verbose=False, **geom), "bf16")
         test_shards_of_one_pass_are_computed_as_each_alone("mlp", "bf16", geom, [n, 0, 1, n])
+
+
+def _damped(job):
+    """Scales the last batch norm of every residual block down (they start at zero in large-batch training): a bf16
+    residual net's gradient is then set by its weights and not by rounding."""
+    from paper_1909_11985_amd.binding import edl_tensor_table
+    w = job.params()
+    for name, off, size, _ in edl_tensor_table(job.cfg):
+        if name.endswith((".bn3.g",) if job.cfg.model == 2 else (".bn2.g",)):
+            w[off:off + size] *= 0.01
+    job.set_params(w)
+
+
+def _passes(job, p, idx, off):
+    """How many passes the mini-batch takes: each launches the loss once."""
+    import paper_1909_11985_amd as E
+    E.edl_profile(True)
+    try:
+        job.gradients(p, idx, off)
+        report = E.edl_profile_report()
+    finally:
+        E.edl_profile(False)
+    return sum(r["launches"] for r in report if r["name"] == "softmax_ce")
+
+
+@pytest.mark.parametrize("model,dtype,kw,cut,together,passes", [
+    ("mlp", "f32", TINY["mlp"], [5, 0, 7, 1, 11], 12, 2),
+    ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), [4] * 8, 20, 2),          # 5 + 3 equal shards
+    ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), [6, 6, 0, 5, 5], 12, 2),
+    ("vgg16", "bf16", TINY["vgg16"], [4] * 4, 0, 4),                                                   # one shard at a time
+    ("resnet50", "bf16", dict(H=64, W=64, C=3, classes=10, arch=(64, 1, 1, 1, 1)), [4] * 5, 12, 2),    # 3 + 2
+    ("resnet50", "bf16", dict(H=64, W=64, C=3, classes=10, arch=(64, 1, 1, 1, 1)), [8, 3, 5, 7], 16, 2),
+])
+def test_a_mini_batch_that_takes_several_passes(model, dtype, kw, cut, together, passes):
+    """A job whose arena does not hold the whole mini-batch trains as one whose arena does: every worker's gradient and
+    loss, the running statistics (the first worker's) and the weights after steps (the early update belongs to the last
+    pass)."""
+    import torch
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    B, p = sum(cut), len(cut)
+    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    x, y = synth_inputs.dataset(3, 2 * B, kw["H"], kw["W"], kw["C"], kw["classes"])
+    dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    cfg = make_config(model, dtype=dtype, N=2 * B, B=B, p_max=p, max_shard=max(cut), lr=0.01, **_cfg_geom(kw))
+    with E.options(early_update=1000):
+        whole, parts = E.Job(cfg, 5), E.Job(cfg, 5, arena_bytes=E.edl_arena_bytes(cfg, together))
+        for job in (whole, parts):
+            job.bind_dataset(dx, dy)
+            if model in ("resnet20", "resnet50"):
+                _damped(job)
+        idx, _ = whole.shard(B, 1, 0, 1)
+        assert _passes(whole, p, idx, off) == 1 and _passes(parts, p, idx, off) == passes
+        tol = 1e-5 if dtype == "f32" else 2e-2
+        for job in (whole, parts):
+            job.gradients(p, idx, off)
+        la, lb = whole.losses(p), parts.losses(p)
+        for k in range(p):
+            if cut[k]:
+                assert abs(la[k] - lb[k]) <= tol * abs(la[k]), k
+                assert relerr(parts.grad(k), whole.grad(k)) < tol, k
+        for t in range(2):
+            for job in (whole, parts):
+                job.step(p, idx, off)
+            assert relerr(parts.params(), whole.params()) < tol
+            if whole.R:
+                assert relerr(parts.running(), whole.running()) < tol
+        for job in (whole, parts):
+            job.shutdown()
+    with pytest.raises(E.EdlError) as ei:
+        E.Job(cfg, 5, arena_bytes=E.edl_arena_bytes(cfg) - 256)
+    assert ei.value.code == -3
