@@ -470,7 +470,7 @@ int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t*
         S.off[k + 1] = S.off[k] + (int)sizes[k];
         S.k[k] = k;
     }
-    S.p = p;
+    S.p = S.plan_p = p;
     if (p > L.pass_shards || S.samples() > L.pass_samples) { set_error("these shards do not run in one pass"); return EDL_ERANGE; }
     *out_needed = 0;
     *out_there = L.wgrad_scratch_bytes;
@@ -1310,7 +1310,10 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
     // consecutive shards in passes of as many as the workspace holds
     for (int k = 0; k <= last_k;) {
         ShardSet S = {};
-        S.plan = equal && !alone ? shards_per_pass(h, sizes[0], p) * (int)sizes[0] : 0;
+        if (equal && !alone) {
+            S.plan_p = shards_per_pass(h, sizes[0], p);
+            S.plan = S.plan_p * (int)sizes[0];
+        }
         for (; k <= last_k; ++k) {
             if (sizes[k] == 0) continue;
             if (S.p > 0 && (alone || S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
@@ -1318,7 +1321,7 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
             S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
             S.p += 1;
         }
-        if (S.plan == 0) S.plan = S.samples();
+        if (S.plan == 0) { S.plan = S.samples(); S.plan_p = S.p; }
         forward_pass(h, S, dev_idx + at, dev_losses, first && !alone);
         backward_pass(h, S, 0, (size_t)-1, k > last_k ? h->early_p : 0);
         first = false;
@@ -1653,7 +1656,8 @@ static ShardSet one_shard(const edl_handle* h, int n, int k) {
     ShardSet S = {};
     S.p = 1;
     S.off[1] = n;
-    S.plan = h->cfg.B % n == 0 && h->cfg.B / n <= h->cfg.p_max ? n * shards_per_pass(h, n, (int)(h->cfg.B / n)) : n;
+    S.plan_p = h->cfg.B % n == 0 && h->cfg.B / n <= h->cfg.p_max ? shards_per_pass(h, n, (int)(h->cfg.B / n)) : 1;
+    S.plan = n * S.plan_p;
     S.k[0] = k;
     return S;
 }

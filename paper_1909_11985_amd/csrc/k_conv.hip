@@ -1747,7 +1747,7 @@ static RowCut tile_cut(const ShardSet& S, int rows_per_sample, int bm, bool want
     if (want_sums && S.smallest() * rows_per_sample >= bm) *per_shard = true;
     if (*per_shard) return cut_rows(S, rows_per_sample, bm);
     ShardSet all = {};
-    all.p = 1;
+    all.p = all.plan_p = 1;
     all.off[1] = all.plan = S.samples();
     return cut_rows(all, rows_per_sample, bm);
 }
@@ -2061,7 +2061,7 @@ size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int shards) {
 size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
     ConvGeom one = g;
     one.N = S.largest();
-    return wgrad_partial_bytes(g, S.p, plan_wgrad(dtype, one, S.p).splits);
+    return wgrad_partial_bytes(g, S.p, plan_wgrad(dtype, one, S.plan_p).splits);
 }
 
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
@@ -2069,7 +2069,7 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     const int VEC = dtype == 1 ? 8 : 4;
     ConvGeom one = g;
     one.N = S.largest();
-    WgradPlan p = plan_wgrad(dtype, one, S.p);
+    WgradPlan p = plan_wgrad(dtype, one, S.plan_p);
     ConvArgsShards a = base_args(g);
     a.A = dy; a.B = x;
     a.M = g.K; a.Nn = g.R * g.S * g.C; a.Kred = g.N * g.Ho * g.Wo;

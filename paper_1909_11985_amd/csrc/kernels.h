@@ -21,10 +21,10 @@ struct ShardSet {
     int p;                    // shards in the pass
     int off[kMaxP + 1];       // first sample of each, off[p] = samples of the pass
     int k[kMaxP];             // the worker: which gradient buffer, which loss
-    // Samples that tiles and reduction cuts are chosen for: those of the pass, or of the passes this one stands for (a
-    // step's last pass may hold fewer shards than the others; a debugging hook runs one shard of such a pass).
-    // Sums are then formed in the same order for a shard of a given size whichever pass it is in.
-    int plan;
+    // Samples and shards that tiles and reduction cuts are chosen for: those of the pass, or of the passes this one
+    // stands for (a step's last pass may hold fewer shards than the others; a debugging hook runs one shard of such a
+    // pass).  Sums are then formed in the same order for a shard of a given size whichever pass it is in.
+    int plan, plan_p;
     int samples() const { return off[p]; }
     int largest() const { int m = 0; for (int s = 0; s < p; ++s) if (off[s + 1] - off[s] > m) m = off[s + 1] - off[s]; return m; }
     int smallest() const { int m = off[1]; for (int s = 1; s < p; ++s) if (off[s + 1] - off[s] < m) m = off[s + 1] - off[s]; return m; }

@@ -1117,3 +1117,34 @@ def test_a_mini_batch_that_takes_several_passes(model, dtype, kw, cut, together,
     with pytest.raises(E.EdlError) as ei:
         E.Job(cfg, 5, arena_bytes=E.edl_arena_bytes(cfg) - 256)
     assert ei.value.code == -3
+
+
+@pytest.mark.parametrize("model,dtype,kw,n,p,together", [
+    ("mlp", "f32", TINY["mlp"], 7, 5, 0),
+    ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), 5, 8, 0),
+    ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), 5, 8, 25),        # 5 + 3
+    ("resnet20", "bf16", dict(H=32, W=32, C=3, classes=10, arch=(16, 3, 1)), 8, 8, 0),
+    ("resnet20", "bf16", dict(H=32, W=32, C=3, classes=10, arch=(16, 3, 1)), 8, 8, 40),       # weight gradients of 5, 3 and 1 shards would be cut differently
+    ("alexnet", "bf16", TINY["alexnet"], 6, 3, 12),                                           # 2 + 1
+])
+def test_equal_shards_are_summed_in_the_same_order_wherever_they_run(model, dtype, kw, n, p, together):
+    """Workers with the same samples have the same gradient and loss, bit for bit: whichever place of a pass their shard
+    has, in a full pass and in a step's shorter last one, and in the hooks that run one shard of such a pass."""
+    import torch
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    x, y = synth_inputs.dataset(3, n * p, kw["H"], kw["W"], kw["C"], kw["classes"])
+    cfg = make_config(model, dtype=dtype, N=n * p, B=n * p, p_max=p, max_shard=n, **_cfg_geom(kw))
+    job = E.Job(cfg, 5, arena_bytes=E.edl_arena_bytes(cfg, together) if together else None)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    one = np.arange(n, dtype=np.int64) * p
+    idx, off = np.tile(one, p), np.arange(p + 1, dtype=np.int64) * n
+    assert _passes(job, p, idx, off) == (2 if together else 1)
+    job.gradients(p, idx, off)
+    losses, grads = job.losses(p), [job.grad(k) for k in range(p)]
+    for k in range(1, p):
+        assert losses[k] == losses[0] and np.array_equal(grads[k], grads[0]), k
+    job.debug_forward(one)
+    job.debug_backward(n, 0)
+    assert np.array_equal(job.grad(0), grads[0])
+    job.shutdown()
