@@ -119,8 +119,8 @@ typedef struct edl_sizes {
     int64_t snapshot_bytes; /* EDL_SNAPSHOT_HEADER_BYTES + 4*(2P + R), with Adam 4*(3P + R) */
     double flops_per_sample; /* multiply-add flops of forward + both backward contractions */
     int64_t second_off;     /* float32 s[P]: Adam's second moment; -1 with EDL_OPT_MOMENTUM */
-    int64_t scratch_bytes;  /* the part of the arena that is the kernels' scratch (what edl_step_static_scratch
-                               must fit into EDL_STATIC_SCRATCH_BYTES) */
+    int64_t scratch_bytes;  /* the part of the arena that is the kernels' scratch (edl_step_static_scratch takes a
+                               pass in parts where that is more than EDL_STATIC_SCRATCH_BYTES) */
     int64_t shadow_off;     /* bf16 copy of w[P] that the contractions read; -1 for float32 jobs */
 } edl_sizes;
 
@@ -271,7 +271,7 @@ int32_t edl_step(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* of
  * EDL_STATIC_SCRATCH_BYTES that the library holds once per GPU for the life of the process, instead of in the
  * arena's scratch piece.  The call allocates nothing, neither device nor pinned memory nor through any library;
  * arguments, results and errors are edl_step's, bit for bit the same model.  EDL_ENOMEM if the job's kernels
- * need more scratch than the buffer holds (large models: use edl_step); EDL_EINVAL if another device is current
+ * need more scratch for one shard of max_shard samples than the buffer holds (large models: use edl_step); EDL_EINVAL if another device is current
  * than the one the job was created on.  All jobs on one GPU share the buffer, which keeps the last call's
  * contents: calls of this entry point that overlap on one GPU (other threads, other streams) race; calls that
  * follow each other on one stream, or are separated by a synchronisation, do not.  Nothing in the buffer needs

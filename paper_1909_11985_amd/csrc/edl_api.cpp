@@ -72,22 +72,28 @@ struct SnapshotHeader {
 };
 static_assert(sizeof(SnapshotHeader) == 104, "snapshot header layout");
 
-struct Layout {
-    int64_t params = 0, momentum = 0, second = -1, running = 0, shadow = 0, grads = 0, grad_stride = 0;
-    int64_t idx = 0, labels = 0, row_loss = 0, losses = 0, partial = 0, partial_held = 0, coef = 0, wgrad_scratch = 0;
+// The kernels' scratch (partial results that live inside one pass), in one contiguous piece [scratch_lo, scratch_hi).
+struct Scratch {
+    int scratch_samples = 0, scratch_shards = 0;     // most samples / shards it takes together
+    int64_t row_loss = 0, partial = 0, partial_held = 0, coef = 0, wgrad_scratch = 0;
     int64_t partial_side = 0, coef_side = 0, splitk_side = 0;   // the branch stream's own scratch
     int64_t partial_floats = 0;          // of each of the three partial-sum pieces
-    int pass_samples = 0, pass_shards = 0;   // most samples / shards that one pass runs together
     int64_t wgrad_scratch_bytes = 0;
     int64_t wgrad_scratch2 = 0;          // for the few weight gradients that run on the main stream beside the second one
     // partial sums of forward / dgrad reductions that are cut; apart from the weight-gradient
     // scratch because weight gradients may run on the second stream meanwhile
     int64_t splitk_scratch = 0, splitk_scratch_bytes = 0;
+    int64_t dwpad = 0;                   // float32 gradient of weights on padded images before it is compacted
+    int64_t scratch_lo = 0, scratch_hi = 0;
+};
+
+struct Layout : Scratch {                // the Scratch is the arena's
+    int64_t params = 0, momentum = 0, second = -1, running = 0, shadow = 0, grads = 0, grad_stride = 0;
+    int64_t idx = 0, labels = 0, losses = 0;
+    int pass_samples = 0, pass_shards = 0;   // most samples / shards that one pass runs together
     int64_t ttable = 0;                  // TransposeEntry[] for the one-launch weight transpose
-    int64_t scratch_lo = 0, scratch_hi = 0;   // the kernels' scratch pieces lie in [scratch_lo, scratch_hi)
     int cpad = 0;                        // channels of the stored input images (>= the logical count, see input_pad)
     std::vector<int64_t> wpad;           // per op: zero-padded weight copy of a convolution on padded images (-1 if none)
-    int64_t dwpad = 0;                   // float32 gradient of such weights before it is compacted
     std::vector<int64_t> act, grad;      // per tensor (storage owners only; -1 otherwise)
     std::vector<int64_t> sign;           // per tensor: (activation > 0) as bits, for outputs of a batch norm with ReLU that a stride-1 convolution reads (bf16)
     std::vector<int64_t> wT;             // per op: transposed weight copy (-1 if not needed)
@@ -140,61 +146,59 @@ ConvGeom geom_padded(const Graph& g, const Op& op, int n, int cpad) {
     return q;
 }
 
-// The kernels' scratch (partial results that live inside one pass) for passes of up to `samples` samples in up to
-// `shards` shards, in one contiguous piece from `o` on: a caller without an arena piece for it can run the same pass
-// on the library's static buffer (edl_step_static_scratch).  Returns its end.
-int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shards, int64_t o, Layout& L) {
+// The kernels' scratch from offset `o` on for running up to `samples` samples in up to `shards` shards together, as
+// parts of passes of up to L.pass_samples and L.pass_shards (whose tiles and cuts the parts take).  Returns its end.
+int64_t plan_scratch(const edl_config& c, const Graph& g, const Layout& L, int samples, int shards, int64_t o, Scratch& X) {
     auto take = [&](int64_t bytes) { const int64_t at = o; o += align_up(bytes); return at; };
+    X.scratch_samples = samples;
+    X.scratch_shards = shards;
     int cmax = 1;
     int64_t dwpad_bytes = 16;
-    L.wgrad_scratch_bytes = L.splitk_scratch_bytes = L.partial_floats = 0;
+    X.wgrad_scratch_bytes = X.splitk_scratch_bytes = X.partial_floats = 0;
     for (const Op& op : g.ops) {
         if (op.kind == OP_CONV) {
             cmax = std::max(cmax, op.K);
             const Tensor& tx = g.tensors[(size_t)op.x];
             const Tensor& ty = g.tensors[(size_t)op.y];
             if (op.x == 0 && L.cpad != tx.C) dwpad_bytes = std::max<int64_t>(dwpad_bytes, (int64_t)op.K * op.R * op.S * L.cpad * 4 * shards);
-            // a weight gradient is cut for the largest of the pass's q shards, which may hold all but one sample of each other
+            // a weight gradient is cut for the largest of the pass's shards
             for (int q = 1; q <= shards && q <= samples; ++q)
-                L.wgrad_scratch_bytes = std::max<int64_t>(
-                    L.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(c.dtype, geom_padded(g, op, std::min(c.max_shard, samples - (q - 1)), L.cpad), q));
-            // the cut of a forward / dgrad reduction depends on the size of the pass: cover every size up to the largest
-            for (int n = 1; n <= samples; n = n < 8 ? n + 1 : n + n / 4)
-                L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
-                                                           (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, n)));
-            L.splitk_scratch_bytes = std::max<int64_t>(L.splitk_scratch_bytes,
-                                                       (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, samples)));
-            L.partial_floats = std::max<int64_t>(L.partial_floats, (int64_t)conv_sums_floats(geom_padded(g, op, samples, L.cpad), shards));
-            L.partial_floats = std::max<int64_t>(L.partial_floats,
-                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)samples * ty.H * ty.W, op.K, shards));
+                X.wgrad_scratch_bytes = std::max<int64_t>(
+                    X.wgrad_scratch_bytes, (int64_t)conv_wgrad_scratch_bytes(c.dtype, geom_padded(g, op, c.max_shard, L.cpad), q));
+            X.splitk_scratch_bytes = std::max<int64_t>(X.splitk_scratch_bytes,
+                                                       (int64_t)conv_splitk_scratch_bytes(c.dtype, geom_of(g, op, L.pass_samples), samples));
+            X.partial_floats = std::max<int64_t>(X.partial_floats, (int64_t)conv_sums_floats(geom_padded(g, op, samples, L.cpad), shards));
+            X.partial_floats = std::max<int64_t>(X.partial_floats,
+                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)L.pass_samples * ty.H * ty.W, op.K, L.pass_shards));
         } else if (op.kind == OP_BN) {
             cmax = std::max(cmax, op.K);
             const Tensor& tx = g.tensors[(size_t)op.x];
-            L.partial_floats = std::max<int64_t>(L.partial_floats,
-                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)samples * tx.H * tx.W, op.K, shards));
+            X.partial_floats = std::max<int64_t>(X.partial_floats,
+                                                 (int64_t)norm_sums_floats(c.dtype, (int64_t)L.pass_samples * tx.H * tx.W, op.K, L.pass_shards));
         }
     }
-    // (room for kRedRowBlocks blocks of the widest layer in any case: what a job needs of the static buffer does not
+    // (a column reduction's blocks are planned for the whole pass and may be as many for a part of it;
+    // room for kRedRowBlocks blocks of the widest layer in any case: what a job needs of the static buffer does not
     // depend on how its launches happen to be cut)
-    L.partial_floats = std::max<int64_t>(L.partial_floats, 2 * (int64_t)kRedRowBlocks * cmax);
-    L.scratch_lo = o;
-    L.row_loss = take(4 * (int64_t)samples);
-    L.partial = take(4 * L.partial_floats);
+    X.partial_floats = std::max<int64_t>(X.partial_floats, 2 * (int64_t)kRedRowBlocks * cmax);
+    X.scratch_lo = o;
+    X.row_loss = take(4 * (int64_t)samples);
+    X.partial = take(4 * X.partial_floats);
     // a second one for sums that wait while another batch norm runs (a block's last convolution, whose
     // batch norm comes after the projection shortcut's)
-    L.partial_held = take(4 * L.partial_floats);
-    L.coef = take(4 * 2 * (int64_t)cmax * shards);
+    X.partial_held = take(4 * X.partial_floats);
+    X.coef = take(4 * 2 * (int64_t)cmax * shards);
     // the same pair for the projection shortcut's batch norm while it runs on the branch stream beside the main one
-    L.partial_side = take(4 * L.partial_floats);
-    L.coef_side = take(4 * 2 * (int64_t)cmax * shards);
-    L.wgrad_scratch = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
-    L.wgrad_scratch2 = take(std::max<int64_t>(L.wgrad_scratch_bytes, 16));
-    L.splitk_scratch = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
+    X.partial_side = take(4 * X.partial_floats);
+    X.coef_side = take(4 * 2 * (int64_t)cmax * shards);
+    X.wgrad_scratch = take(std::max<int64_t>(X.wgrad_scratch_bytes, 16));
+    X.wgrad_scratch2 = take(std::max<int64_t>(X.wgrad_scratch_bytes, 16));
+    X.splitk_scratch = take(std::max<int64_t>(X.splitk_scratch_bytes, 16));
     // the branch stream cuts reductions exactly as the main stream would (same results, bit for bit, whichever
     // stream a layer runs on), in a buffer of its own
-    L.splitk_side = take(std::max<int64_t>(L.splitk_scratch_bytes, 16));
-    L.dwpad = take(dwpad_bytes);
-    L.scratch_hi = o;
+    X.splitk_side = take(std::max<int64_t>(X.splitk_scratch_bytes, 16));
+    X.dwpad = take(dwpad_bytes);
+    X.scratch_hi = o;
     return o;
 }
 
@@ -202,9 +206,8 @@ int64_t plan_scratch(const edl_config& c, const Graph& g, int samples, int shard
 // one launch instead of p, with p times the workgroups (ResNet-50 bf16, aggregate batch 256 as 8 shards of 32:
 // 34.5 -> 23.4 ms per step; ResNet-20 float32, 8 shards of 16: 10.3 -> 1.84 ms; MLP, 4 shards of 16: 0.48 -> 0.17 ms).  Limits, none of which cuts a single shard:
 // 32 GB of activations and gradients (a pass of some 250 images of 224x224 gains nothing more from more of them),
-// 2 GiB per tensor (the vector kernels' 32-bit offsets), what every convolution's vector kernel takes (VGG-16 on
-// 320x320 images: 95 samples), and the static scratch buffer where one shard at a time fits it (the two entry points
-// run the same passes).
+// 2 GiB per tensor (the vector kernels' 32-bit offsets), and what every convolution's vector kernel takes (VGG-16 on
+// 320x320 images: 95 samples).
 void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
     const int64_t esz = c.dtype == EDL_DTYPE_BF16 ? 2 : 4;
     int64_t per_sample = 1, widest = 1;
@@ -220,14 +223,8 @@ void plan_pass(const edl_config& c, const Graph& g, Layout& L) {
         if (op.kind == OP_CONV)
             samples = std::min<int64_t>(samples, conv_vector_samples(geom_padded(g, op, 1, L.cpad), storage_of(g, op.x) != 0));
     samples = std::max<int64_t>(samples, c.max_shard);
-    int shards = c.p_max;
-    if (plan_scratch(c, g, c.max_shard, 1, 0, L) <= (int64_t)EDL_STATIC_SCRATCH_BYTES)
-        while (shards > 1 && plan_scratch(c, g, (int)samples, shards, 0, L) > (int64_t)EDL_STATIC_SCRATCH_BYTES) {
-            shards = (shards + 1) / 2;
-            samples = std::max<int64_t>(samples / 2, c.max_shard);
-        }
-    L.pass_shards = shards;
-    L.pass_samples = shards == 1 ? c.max_shard : (int)samples;
+    L.pass_shards = c.p_max;
+    L.pass_samples = c.p_max == 1 ? c.max_shard : (int)samples;
 }
 
 // the arena of a job whose passes run up to L.pass_samples samples in up to L.pass_shards shards
@@ -295,7 +292,7 @@ void plan_arena(const edl_config& c, const Graph& g, Layout& L) {
             L.pool_arg[i] = take(g.tensors[(size_t)op.y].elems() * L.pass_samples);
         }
     }
-    o = plan_scratch(c, g, L.pass_samples, L.pass_shards, o, L);
+    o = plan_scratch(c, g, L, L.pass_samples, L.pass_shards, o, L);
     L.ttable = take((int64_t)sizeof(TransposeEntry) * 2 * std::max<size_t>(no, 1));   // element-wise entries, then vector ones
     L.total = o;
 }
@@ -319,6 +316,18 @@ bool plan_layout(const edl_config& c, const Graph& g, Layout& L, int64_t arena_b
     if (shards == 1 || !fits(lo, shards)) return fits(c.max_shard, 1);
     while (hi - lo > 1) (fits(lo + (hi - lo) / 2, shards) ? lo : hi) = lo + (hi - lo) / 2;
     return fits(lo, shards);
+}
+
+// The scratch of edl_step_static_scratch: a pass in as large parts as the static buffer has room for.  Returns false if
+// it has none for a shard of max_shard samples (X is the plan for that then).
+bool plan_static_scratch(const edl_config& c, const Graph& g, const Layout& L, Scratch& X) {
+    int samples = L.pass_samples, shards = L.pass_shards;
+    while (plan_scratch(c, g, L, samples, shards, 0, X) > (int64_t)EDL_STATIC_SCRATCH_BYTES) {
+        if (shards == 1 && samples == c.max_shard) return false;
+        shards = (shards + 1) / 2;
+        samples = shards == 1 ? c.max_shard : std::max(samples / 2, c.max_shard);
+    }
+    return true;
 }
 
 }  // namespace
@@ -369,9 +378,11 @@ struct edl_handle {
     int early_p = 0;
     int64_t applied_from = 0;
 
-    // where the kernels' scratch lives during the current call: the arena piece (null), or another buffer of
-    // the same layout
+    // where the kernels' scratch lives during the current call: the arena piece (null), or the static buffer, whose
+    // plan L then holds (exchanged with static_plan)
     char* scratch_base = nullptr;
+    Scratch static_plan;
+    bool static_fits = false;
     int device = -1;
     std::vector<char> written;           // backward pass: which gradient buffers hold something (per tensor)
     std::vector<char> op_done;           // a pass: layers already launched out of list order (on the branch stream)
@@ -470,7 +481,8 @@ int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t*
         S.off[k + 1] = S.off[k] + (int)sizes[k];
         S.k[k] = k;
     }
-    S.p = S.plan_p = p;
+    S.p = p;
+    S.plan_itself();
     if (p > L.pass_shards || S.samples() > L.pass_samples) { set_error("these shards do not run in one pass"); return EDL_ERANGE; }
     *out_needed = 0;
     *out_there = L.wgrad_scratch_bytes;
@@ -646,6 +658,7 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
         delete h;
         return EDL_ENOMEM;
     }
+    h->static_fits = plan_static_scratch(*cfg, h->g, h->L, h->static_plan);
     // a conv output feeding a batch norm must have no other consumer (its gradient is written, not added)
     h->arena = (char*)dev_arena;
     h->st = (hipStream_t)hip_stream;
@@ -1310,10 +1323,6 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
     // consecutive shards in passes of as many as the workspace holds
     for (int k = 0; k <= last_k;) {
         ShardSet S = {};
-        if (equal && !alone) {
-            S.plan_p = shards_per_pass(h, sizes[0], p);
-            S.plan = S.plan_p * (int)sizes[0];
-        }
         for (; k <= last_k; ++k) {
             if (sizes[k] == 0) continue;
             if (S.p > 0 && (alone || S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
@@ -1321,11 +1330,23 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
             S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
             S.p += 1;
         }
-        if (S.plan == 0) { S.plan = S.samples(); S.plan_p = S.p; }
-        forward_pass(h, S, dev_idx + at, dev_losses, first && !alone);
-        backward_pass(h, S, 0, (size_t)-1, k > last_k ? h->early_p : 0);
-        first = false;
-        at += S.samples();
+        if (equal && !alone) S.plan_equal((int)sizes[0], shards_per_pass(h, sizes[0], p));
+        else S.plan_itself();
+        // ... and a pass in parts, if its scratch takes no more
+        for (int s = 0; s < S.p;) {
+            ShardSet part = S;
+            for (part.p = 0; s < S.p; ++s) {
+                const int n = S.off[s + 1] - S.off[s];
+                if (part.p > 0 && (part.p == h->L.scratch_shards || part.off[part.p] + n > h->L.scratch_samples)) break;
+                part.k[part.p] = S.k[s];
+                part.off[part.p + 1] = part.off[part.p] + n;
+                part.p += 1;
+            }
+            forward_pass(h, part, dev_idx + at, dev_losses, first && !alone);
+            backward_pass(h, part, 0, (size_t)-1, k > last_k && s == S.p ? h->early_p : 0);
+            first = false;
+            at += part.samples();
+        }
     }
     HIP_TRY(hipGetLastError());
     if (out_loss) {
@@ -1427,10 +1448,9 @@ int32_t edl_step(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* of
 
 int32_t edl_step_static_scratch(edl_handle* h, int32_t p, const int64_t* idx, const int64_t* off, float* out_loss) {
     if (!h) { set_error("null handle"); return EDL_EINVAL; }
-    const int64_t need = h->L.scratch_hi - h->L.scratch_lo;
-    if (need > (int64_t)EDL_STATIC_SCRATCH_BYTES) {
+    if (!h->static_fits) {
         set_error("the kernels of this job need %lld bytes of scratch; the static buffer holds %lld (use edl_step, whose "
-                  "scratch is part of the caller's arena)", (long long)need, (long long)EDL_STATIC_SCRATCH_BYTES);
+                  "scratch is part of the caller's arena)", (long long)h->static_plan.scratch_hi, (long long)EDL_STATIC_SCRATCH_BYTES);
         return EDL_ENOMEM;
     }
     int dev = -1;
@@ -1442,7 +1462,9 @@ int32_t edl_step_static_scratch(edl_handle* h, int32_t p, const int64_t* idx, co
     // nothing in the buffer has to start at zero: every partial result is written by the launch that precedes its
     // reader (the arena's piece is never cleared either)
     h->scratch_base = (char*)g_static_scratch[dev];
+    std::swap(static_cast<Scratch&>(h->L), h->static_plan);
     const int rc = edl_step(h, p, idx, off, out_loss);
+    std::swap(static_cast<Scratch&>(h->L), h->static_plan);
     h->scratch_base = nullptr;
     return rc;
 }
@@ -1656,8 +1678,7 @@ static ShardSet one_shard(const edl_handle* h, int n, int k) {
     ShardSet S = {};
     S.p = 1;
     S.off[1] = n;
-    S.plan_p = h->cfg.B % n == 0 && h->cfg.B / n <= h->cfg.p_max ? shards_per_pass(h, n, (int)(h->cfg.B / n)) : 1;
-    S.plan = n * S.plan_p;
+    S.plan_equal(n, h->cfg.B % n == 0 && h->cfg.B / n <= h->cfg.p_max ? shards_per_pass(h, n, (int)(h->cfg.B / n)) : 1);
     S.k[0] = k;
     return S;
 }

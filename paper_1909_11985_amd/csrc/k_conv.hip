@@ -1743,12 +1743,13 @@ size_t conv_sums_floats(const ConvGeom& g, int p) {
 // How a launch's rows are cut into row tiles of bm: within the shards if it is to leave column sums (and the shards
 // are large enough for that not to leave most of a tile idle), else without regard to them.
 static RowCut tile_cut(const ShardSet& S, int rows_per_sample, int bm, bool want_sums, bool* per_shard) {
-    *per_shard = S.samples() == S.plan && S.p == 1;
-    if (want_sums && S.smallest() * rows_per_sample >= bm) *per_shard = true;
+    *per_shard = S.plan_p == 1;
+    if (want_sums && S.plan_smallest * rows_per_sample >= bm) *per_shard = true;
     if (*per_shard) return cut_rows(S, rows_per_sample, bm);
     ShardSet all = {};
-    all.p = all.plan_p = 1;
-    all.off[1] = all.plan = S.samples();
+    all.p = 1;
+    all.off[1] = S.samples();
+    all.plan_itself();
     return cut_rows(all, rows_per_sample, bm);
 }
 
@@ -1813,17 +1814,23 @@ static RowCut launch_finish(const ConvArgs& a, const ShardSet& S, int rows_per_s
     return stats.buf ? cut : RowCut();
 }
 
-size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g) {
+size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g, int samples) {
     size_t need = 0;
     for (int mode = 0; mode < 2; ++mode) {
         if (mode == 1 && g.stride != 1) continue;
-        const int M = mode == 0 ? g.N * g.Ho * g.Wo : g.N * g.H * g.W;
+        const int hw = mode == 0 ? g.Ho * g.Wo : g.H * g.W;
         const int Nn = mode == 0 ? g.K : g.C;
         const int Kred = mode == 0 ? g.R * g.S * g.C : g.R * g.S * g.K;
-        int bm, bn, ks;
-        const TileCfg t = pick_tile(M, Nn, Kred, &bm, &bn, mode == 0 && Kred <= 128);
-        const int splits = plan_splitk(dtype, M, Nn, Kred, bm, bn, &ks, takes_strips(dtype, mode, g, t));
-        if (splits > 1) need = std::max(need, (size_t)splits * M * Nn * sizeof(float));
+        // the number of cuts does not follow the size of the pass steadily (the tile changes): every size up to those
+        // that are not cut on any tile
+        for (int n = 1; n <= g.N; ++n) {
+            const int M = n * hw;
+            if ((int64_t)((M + 127) / 128) * ((Nn + 127) / 128) >= tune().splitk_tiles) break;
+            int bm, bn, ks;
+            const TileCfg t = pick_tile(M, Nn, Kred, &bm, &bn, mode == 0 && Kred <= 128);
+            const int splits = plan_splitk(dtype, M, Nn, Kred, bm, bn, &ks, takes_strips(dtype, mode, g, t));
+            if (splits > 1) need = std::max(need, (size_t)splits * std::min(n, samples) * hw * Nn * sizeof(float));
+        }
     }
     return need;
 }
@@ -2060,7 +2067,7 @@ size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int shards) {
 
 size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
     ConvGeom one = g;
-    one.N = S.largest();
+    one.N = S.plan_largest;
     return wgrad_partial_bytes(g, S.p, plan_wgrad(dtype, one, S.plan_p).splits);
 }
 
@@ -2068,7 +2075,7 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
                        size_t scratch_bytes, hipStream_t st) {
     const int VEC = dtype == 1 ? 8 : 4;
     ConvGeom one = g;
-    one.N = S.largest();
+    one.N = S.plan_largest;
     WgradPlan p = plan_wgrad(dtype, one, S.plan_p);
     ConvArgsShards a = base_args(g);
     a.A = dy; a.B = x;

@@ -378,9 +378,7 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__
 // a finishing kernel over all channels and shards: four waves per channel where a shard has many row blocks
 #define EDL_FINALIZE(KERNEL, CUT, CH, ...)                                                                                     \
     do {                                                                                                                       \
-        int most = 0;                                                                                                          \
-        for (int s_ = 0; s_ < (CUT).p; ++s_) most = std::max(most, (CUT).blk0[s_ + 1] - (CUT).blk0[s_]);                       \
-        if (most > 512) hipLaunchKernelGGL(KERNEL<4>, dim3(CH, (CUT).p), dim3(256), 0, st, partial, CUT, CH, __VA_ARGS__);     \
+        if ((CUT).most > 512) hipLaunchKernelGGL(KERNEL<4>, dim3(CH, (CUT).p), dim3(256), 0, st, partial, CUT, CH, __VA_ARGS__);     \
         else hipLaunchKernelGGL(KERNEL<1>, dim3(((CH) + 3) / 4, (CUT).p), dim3(256), 0, st, partial, CUT, CH, __VA_ARGS__);    \
     } while (0)
 

@@ -21,10 +21,13 @@ struct ShardSet {
     int p;                    // shards in the pass
     int off[kMaxP + 1];       // first sample of each, off[p] = samples of the pass
     int k[kMaxP];             // the worker: which gradient buffer, which loss
-    // Samples and shards that tiles and reduction cuts are chosen for: those of the pass, or of the passes this one
-    // stands for (a step's last pass may hold fewer shards than the others; a debugging hook runs one shard of such a
-    // pass).  Sums are then formed in the same order for a shard of a given size whichever pass it is in.
-    int plan, plan_p;
+    // What tiles and reduction cuts are chosen for: samples, shards and the largest and smallest shard of the pass, or of
+    // the pass this one stands for (a step's last pass may hold fewer shards than the others; a debugging hook runs one
+    // shard of such a pass; the static scratch buffer may take a pass in parts).  Sums are then formed in the same
+    // order for a shard whichever part it is in.
+    int plan, plan_p, plan_largest, plan_smallest;
+    void plan_itself() { plan = samples(); plan_p = p; plan_largest = largest(); plan_smallest = smallest(); }
+    void plan_equal(int n, int shards) { plan = n * shards; plan_p = shards; plan_largest = plan_smallest = n; }
     int samples() const { return off[p]; }
     int largest() const { int m = 0; for (int s = 0; s < p; ++s) if (off[s + 1] - off[s] > m) m = off[s + 1] - off[s]; return m; }
     int smallest() const { int m = off[1]; for (int s = 1; s < p; ++s) if (off[s + 1] - off[s] < m) m = off[s + 1] - off[s]; return m; }
@@ -37,6 +40,7 @@ struct RowCut {
     int row0[kMaxP + 1] = {};     // first row of each shard
     int blk0[kMaxP + 1] = {};     // first block of each shard, blk0[p] = blocks in all
     int k[kMaxP] = {};            // the shard's worker
+    int most = 0;                 // blocks of the largest shard of the plan
 };
 inline RowCut cut_rows(const ShardSet& S, int rows_per_sample, int rows_per_block) {
     RowCut c;
@@ -47,6 +51,7 @@ inline RowCut cut_rows(const ShardSet& S, int rows_per_sample, int rows_per_bloc
         c.blk0[s + 1] = c.blk0[s] + (c.row0[s + 1] - c.row0[s] + rows_per_block - 1) / rows_per_block;
         c.k[s] = S.k[s];
     }
+    c.most = (S.plan_largest * rows_per_sample + rows_per_block - 1) / rows_per_block;
     return c;
 }
 
@@ -142,8 +147,9 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
                          const void* acc_src = nullptr, bool w_rows = false);
 // whether the input gradient of a layer whose weights start at element w_off reads them where they lie
 bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off);
-// float32 scratch a forward / dgrad launch may use to cut a long reduction of a small problem
-size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g);
+// float32 scratch the forward / dgrad launches of passes of up to `samples` samples may use to cut a long reduction of a
+// small problem, where cuts are planned for passes of up to g.N
+size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g, int samples);
 // dw = x^T * dy of every shard, float32 [K][R][S][C]; scratch holds split partial sums
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st);

@@ -1125,6 +1125,8 @@ def test_a_mini_batch_that_takes_several_passes(model, dtype, kw, cut, together,
     ("resnet20", "f32", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), 5, 8, 25),        # 5 + 3
     ("resnet20", "bf16", dict(H=32, W=32, C=3, classes=10, arch=(16, 3, 1)), 8, 8, 0),
     ("resnet20", "bf16", dict(H=32, W=32, C=3, classes=10, arch=(16, 3, 1)), 8, 8, 40),       # weight gradients of 5, 3 and 1 shards would be cut differently
+    ("resnet50", "bf16", dict(H=96, W=96, C=3, classes=10, arch=(64, 1, 1, 1, 1)), 9, 7, 0),
+    ("resnet50", "bf16", dict(H=96, W=96, C=3, classes=10, arch=(64, 1, 1, 1, 1)), 9, 7, 36), # 4 + 3
     ("alexnet", "bf16", TINY["alexnet"], 6, 3, 12),                                           # 2 + 1
 ])
 def test_equal_shards_are_summed_in_the_same_order_wherever_they_run(model, dtype, kw, n, p, together):

@@ -10,7 +10,7 @@ import synth_inputs
 pytestmark = pytest.mark.gpu
 
 
-def _twin_jobs(model, dtype, N, B, p_max, geom, seed=5, lr=0.05):
+def _twin_jobs(model, dtype, N, B, p_max, geom, seed=5, lr=0.05, max_shard=None):
     import torch
     import paper_1909_11985_amd as E
     from paper_1909_11985_amd.binding import make_config
@@ -19,7 +19,7 @@ def _twin_jobs(model, dtype, N, B, p_max, geom, seed=5, lr=0.05):
     dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
     jobs = []
     for _ in range(2):
-        cfg = make_config(model, dtype=dtype, N=N, B=B, p_max=p_max, max_shard=B, lr=lr, **geom)
+        cfg = make_config(model, dtype=dtype, N=N, B=B, p_max=p_max, max_shard=max_shard or B, lr=lr, **geom)
         job = E.Job(cfg, seed)
         job.bind_dataset(dx, dy)
         jobs.append(job)
@@ -73,3 +73,32 @@ def test_static_scratch_step_refuses_what_does_not_fit():
     assert sta.progress() == (0, 0, 0) and np.array_equal(sta.params(), w0)
     assert sta.step(2) == ref.step(2)
     _same_state(ref, sta, 2)
+
+
+@pytest.mark.parametrize("model,dtype,geom,cuts", [
+    ("resnet50", "bf16", dict(H=64, W=64, C_=3, classes=10, arch=(64, 1, 1, 1, 1)), [[6] * 8, [4, 11, 0, 1, 12, 12, 3, 5], [12, 12, 12, 12]]),
+    ("resnet20", "f32", dict(H=24, W=24, C_=3, classes=10, arch=(64, 3, 1)), [[32] * 8, [48, 1, 0, 48, 39, 48, 24, 48]]),
+])
+def test_a_pass_that_the_static_scratch_takes_in_parts(model, dtype, geom, cuts):
+    """Where the static buffer does not hold the scratch of all shards together, edl_step still runs them together and
+    edl_step_static_scratch takes them in parts, whose tiles and cuts are those of the whole: the same model, bit for
+    bit, for equal and unequal shards."""
+    import paper_1909_11985_amd as E
+    B, p = sum(cuts[0]), len(cuts[0])
+    ref, sta = _twin_jobs(model, dtype, 2 * B, B, p, geom, max_shard=max(max(c) for c in cuts))
+    assert ref.sizes.scratch_bytes > 64 << 20
+    for cut in cuts:
+        idx, _ = ref.shard(B, 1, *ref.progress()[1:])
+        off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+        passes = []
+        for step in (ref.step, sta.step_static_scratch):
+            E.edl_profile(True)
+            try:
+                step(len(cut), idx, off)
+                passes.append(sum(r["launches"] for r in E.edl_profile_report() if r["name"] == "softmax_ce"))
+            finally:
+                E.edl_profile(False)
+        assert passes[0] == 1 and passes[1] > 1, passes
+        _same_state(ref, sta, len(cut))
+        assert ref.step(len(cut), idx, off) == sta.step_static_scratch(len(cut), idx, off)
+        _same_state(ref, sta, len(cut))
