@@ -28,8 +28,8 @@
  *     host staging buffers (the mini-batch's indices, the workers' losses),
  *     HIP events, and - unless the caller brings them, see
  *     edl_set_side_streams - uses two non-blocking streams of default priority
- *     that the jobs of a GPU share (created with the first, destroyed with the
- *     last of them).
+ *     that the jobs on one stream share (created with the first, destroyed
+ *     with the last of them).
  *   - device work is queued on the hipStream_t given to edl_init (NULL = the
  *     default stream).  A training pass also uses the two side streams (weight
  *     gradients; the update of layers whose gradients are final), ordered
@@ -382,6 +382,8 @@ int32_t edl_debug_backward_range(edl_handle* h, int32_t op_lo, int32_t op_hi, in
 int32_t edl_debug_backward_range_from(edl_handle* h, int32_t op_lo, int32_t op_hi, int32_t n, int32_t k,
                                       const int32_t* held, int32_t n_held);
 int32_t edl_debug_set_labels(edl_handle* h, const int32_t* labels, int32_t n);
+/* The side streams in use (NULL, NULL: none). */
+int32_t edl_debug_side_streams(const edl_handle* h, void** wgrad_stream, void** update_stream);
 /* Bytes of partial results that the weight gradients of one pass over p shards of the given sizes (host int64[p])
  * are cut into, and the bytes that the arena's plan has for them.  Host only.  EDL_ERANGE if the shards do not run
  * in one pass. */

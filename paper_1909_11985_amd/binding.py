@@ -100,6 +100,7 @@ _SIGS = {
     "edl_debug_backward_range": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32],
     "edl_debug_backward_range_from": [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_int32],
     "edl_debug_set_labels": [C.c_void_p, C.POINTER(C.c_int32), C.c_int32],
+    "edl_debug_side_streams": [C.c_void_p, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p)],
     "edl_arena_bytes": [C.POINTER(Config), C.c_int64, _i64p],
     "edl_debug_wgrad_scratch": [C.POINTER(Config), C.c_int32, _i64p, _i64p, _i64p],
     "edl_set_side_streams": [C.c_void_p, C.c_void_p, C.c_void_p],
@@ -460,6 +461,11 @@ class Job:
             _check(lib.edl_debug_tensor_shape(self._h, t, C.byref(H), C.byref(W), C.byref(Cc), C.byref(al)))
             out.append((H.value, W.value, Cc.value, al.value))
         return out
+
+    def debug_side_streams(self):
+        a, b = C.c_void_p(), C.c_void_p()
+        _check(lib.edl_debug_side_streams(self._h, C.byref(a), C.byref(b)))
+        return a.value, b.value
 
     def debug_forward(self, idx):
         idx = np.ascontiguousarray(idx, dtype=np.int64)

@@ -37,18 +37,19 @@ namespace {
 constexpr int kMaxDevices = 64;
 void* g_static_scratch[kMaxDevices] = {};     // per device: address of that device's copy of `scratch`
 
-// The library's own pair of side streams is one per GPU, shared by the jobs on it and destroyed with the last of
-// them.  A process has few hardware queues (four by default) and streams are dealt to them in turn: with a pair of
-// its own, the third job's side streams shared a queue with the jobs' main stream and with each other, and its
-// weight gradients ran in line with the pass they should run beside (ResNet-50, shard of 32: 4.40 ms per step for
-// the first two jobs, 5.75 for the third; three jobs in turn 4.92 -> 4.40 with one pair).  Every wait a job queues on
-// a shared stream is for an event recorded before it, so jobs on several threads and streams only queue up behind
-// one another there.
+// The library's own pair of side streams is one per job stream, shared by the jobs on that stream and destroyed with
+// the last of them.  A process has few hardware queues (four by default) and streams are dealt to them in turn: with
+// a pair of its own, the third job's side streams shared a queue with the jobs' main stream and with each other, and
+// its weight gradients ran in line with the pass they should run beside (ResNet-50, shard of 32: 4.40 ms per step for
+// the first two jobs, 5.75 for the third; three jobs in turn 4.92 -> 4.40 with one pair).  Jobs on one stream follow
+// one another there anyway, so sharing orders nothing that was free: a job whose stream is held up, or under capture
+// into a graph, holds up or captures the side work of the jobs on that stream only.
 struct SharedStreams {
-    hipStream_t side = nullptr, upd = nullptr;
-    int users = 0;
+    int device;
+    hipStream_t main, side, upd;
+    int users;
 };
-SharedStreams g_side_streams[kMaxDevices];
+std::vector<SharedStreams> g_side_streams;      // as many as there are job streams in use
 std::mutex g_side_streams_mutex;
 
 constexpr int64_t kAlign = 256;
@@ -362,7 +363,7 @@ struct edl_handle {
     bool shards_equal = true;
     bool grads_pending = false;          // edl_gradients has run and edl_apply has not consumed its buffers yet
     // second stream for the weight gradients (null: everything on st); own_streams: the library's (shared by the
-    // jobs of this GPU), not the caller's
+    // jobs on this stream), not the caller's
     hipStream_t side = nullptr;
     bool own_streams = false;
     hipEvent_t ev_ready[kReadyEvents] = {};
@@ -462,6 +463,13 @@ int32_t edl_arena_bytes(const edl_config* cfg, int64_t pass_samples, int64_t* ou
         }
     }
     *out_bytes = L.total;
+    return EDL_OK;
+}
+
+int32_t edl_debug_side_streams(const edl_handle* h, void** wgrad_stream, void** update_stream) {
+    if (!h || !wgrad_stream || !update_stream) { set_error("null argument"); return EDL_EINVAL; }
+    *wgrad_stream = (void*)h->side;
+    *update_stream = (void*)h->upd;
     return EDL_OK;
 }
 
@@ -579,23 +587,26 @@ static int create_side_events(edl_handle* h) {
     return EDL_OK;
 }
 
-// takes the library's pair of side streams for this GPU into use (created by the first job)
+// takes the library's pair of side streams for the job's stream into use (created by the first job there)
 static int acquire_side_streams(edl_handle* h) {
-    if (h->device < 0 || h->device >= kMaxDevices) return EDL_OK;       // everything on the job's stream
     std::lock_guard<std::mutex> lock(g_side_streams_mutex);
-    SharedStreams& s = g_side_streams[h->device];
-    if (s.users == 0) {
-        HIP_TRY(hipStreamCreateWithFlags(&s.side, hipStreamNonBlocking));
-        const hipError_t e = hipStreamCreateWithFlags(&s.upd, hipStreamNonBlocking);
+    SharedStreams* s = nullptr;
+    for (SharedStreams& q : g_side_streams)
+        if (q.device == h->device && q.main == h->st) s = &q;
+    if (s == nullptr) {
+        SharedStreams q = {h->device, h->st, nullptr, nullptr, 0};
+        HIP_TRY(hipStreamCreateWithFlags(&q.side, hipStreamNonBlocking));
+        const hipError_t e = hipStreamCreateWithFlags(&q.upd, hipStreamNonBlocking);
         if (e != hipSuccess) {
-            (void)hipStreamDestroy(s.side);
-            s = SharedStreams();
+            (void)hipStreamDestroy(q.side);
             HIP_TRY(e);
         }
+        g_side_streams.push_back(q);
+        s = &g_side_streams.back();
     }
-    s.users += 1;
-    h->side = s.side;
-    h->upd = s.upd;
+    s->users += 1;
+    h->side = s->side;
+    h->upd = s->upd;
     h->own_streams = true;
     return EDL_OK;
 }
@@ -606,11 +617,12 @@ static void release_side_streams(edl_handle* h) {
     if (h->upd) (void)hipStreamSynchronize(h->upd);
     if (h->own_streams) {
         std::lock_guard<std::mutex> lock(g_side_streams_mutex);
-        SharedStreams& s = g_side_streams[h->device];
-        if (--s.users == 0) {
-            (void)hipStreamDestroy(s.side);
-            (void)hipStreamDestroy(s.upd);
-            s = SharedStreams();
+        for (size_t i = 0; i < g_side_streams.size(); ++i) {
+            if (g_side_streams[i].side != h->side || --g_side_streams[i].users > 0) continue;
+            (void)hipStreamDestroy(h->side);
+            (void)hipStreamDestroy(h->upd);
+            g_side_streams.erase(g_side_streams.begin() + (long)i);
+            break;
         }
     }
     h->side = nullptr;
@@ -803,16 +815,6 @@ int32_t edl_shard(const edl_handle* h, int64_t B, int32_t p, int64_t epoch, int6
     return edl_shard_host(h->seed, h->cfg.N, B, p, epoch, step_in_epoch, out_idx, out_off);
 }
 
-// Whether a pass may put work on the side streams: not while kernels are timed one by one, and not on the library's
-// shared pair while the job's stream is being captured into a graph - the capture would take the pair in, and with it
-// what the other jobs of this GPU queue there meanwhile.  (The caller's own streams are the caller's to share.)
-static bool side_streams_usable(const edl_handle* h) {
-    if (prof_enabled()) return false;
-    if (!h->own_streams || h->st == nullptr) return true;      // the default stream cannot be captured
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(h->st, &status) == hipSuccess && status == hipStreamCaptureStatusNone;
-}
-
 // Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
 // op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
 // single layers from the debugging hooks, which then skip the gather)
@@ -848,7 +850,7 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
     // A residual block's projection shortcut (convolution + batch norm on the block's input) runs on the second
     // side stream while the main branch runs here; the block's last batch norm, which adds the two, waits for it.
     // Only when the whole list runs and nothing is being timed kernel by kernel.
-    const bool branch = op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && side_streams_usable(h) && tune().branch_stream != 0;
+    const bool branch = op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && !prof_enabled() && tune().branch_stream != 0;
     std::vector<char>& done = h->op_done;
     std::fill(done.begin(), done.end(), 0);
     int join_tensor = -1;
@@ -976,7 +978,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
         for (int t : *held) written[(size_t)storage_of(g, t)] = 1;
     if (op_hi > g.ops.size()) op_hi = g.ops.size();
     // per-kernel timing wants one kernel at a time
-    const bool overlap = h->side != nullptr && side_streams_usable(h);
+    const bool overlap = h->side != nullptr && !prof_enabled();
     bool used_side = false, used_upd = false;
     // the projection shortcut's backward on the second side stream (see forward_pass)
     const bool branch = overlap && op_lo == 0 && op_hi == g.ops.size() && h->upd != nullptr && tune().branch_stream != 0;
@@ -1306,7 +1308,7 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
     // The transposed copies are first read by the backward pass: they are made on the weight-gradient stream, which
     // is idle during the forward pass, and the first backward pass waits for them.
     h->transposes_pending = false;
-    if (h->side != nullptr && side_streams_usable(h) && tune().transpose_stream != 0 &&
+    if (h->side != nullptr && !prof_enabled() && tune().transpose_stream != 0 &&
         hipEventRecord(h->ev_tr_go, h->st) == hipSuccess && hipStreamWaitEvent(h->side, h->ev_tr_go, 0) == hipSuccess) {
         transpose_weights(h, h->side);
         h->transposes_pending = hipEventRecord(h->ev_tr_done, h->side) == hipSuccess;

@@ -1150,3 +1150,95 @@ def test_equal_shards_are_summed_in_the_same_order_wherever_they_run(model, dtyp
     job.debug_backward(n, 0)
     assert np.array_equal(job.grad(0), grads[0])
     job.shutdown()
+
+
+# ---------------------------------------------------------------- jobs beside one another
+def _resnet_job(seed, stream=None, dtype="bf16", B=24, p=3):
+    import torch
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    geom = dict(H=48, W=48, C=3, classes=10, arch=(32, 1, 2, 1, 1))
+    x, y = synth_inputs.dataset(seed, 2 * B, geom["H"], geom["W"], geom["C"], geom["classes"])
+    job = E.Job(make_config("resnet50", dtype=dtype, N=2 * B, B=B, p_max=p, max_shard=B, lr=0.01, **_cfg_geom(geom)), seed, stream=stream)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    torch.cuda.synchronize()
+    return job
+
+
+def test_jobs_share_side_streams_with_those_on_their_own_stream_only():
+    """The jobs on one stream share a pair; a job on another stream has another, so that what holds one stream up holds
+    up nobody else's side work.  Jobs end in any order, and jobs stepped from two threads on two streams train as
+    each does alone, bit for bit."""
+    import threading
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    with E.options(early_update=1):
+        alone = {}
+        for seed in (1, 2, 3):
+            job = _resnet_job(seed)
+            for _ in range(12):
+                job.step(3)
+            alone[seed] = (job.params(), job.momentum(), job.running())
+            job.shutdown()
+        first, second = _resnet_job(9), _resnet_job(3)
+        a, b = _resnet_job(1, s1), _resnet_job(2, s2)
+        gone = _resnet_job(8, s1)
+        pairs = [j.debug_side_streams() for j in (first, second, a, b, gone)]
+        assert pairs[0] == pairs[1] and pairs[2] == pairs[4]
+        assert len({s for pair in pairs for s in pair}) == 6 and None not in pairs[0]
+        first.step(3)
+        first.shutdown()                       # the pair's first user goes before the others
+        errors = []
+
+        def train(job):
+            try:
+                for _ in range(12):
+                    job.step(3, want_loss=False)
+            except Exception as e:             # shown by the main thread
+                errors.append(e)
+        threads = [threading.Thread(target=train, args=(j,)) for j in (a, b)]
+        for t in threads:
+            t.start()
+        for _ in range(12):
+            second.step(3, want_loss=False)
+        for t in threads:
+            t.join()
+        assert not errors, errors
+        gone.shutdown()
+        for seed, job in ((1, a), (2, b), (3, second)):
+            for got, want in zip((job.params(), job.momentum(), job.running()), alone[seed]):
+                assert np.array_equal(got, want), seed
+            job.shutdown()
+        again = _resnet_job(4, s1)             # the pool starts anew
+        again.step(3)
+        again.shutdown()
+
+
+def test_a_captured_step_takes_in_its_own_streams_only():
+    """A step captured into a graph, side streams and all, while a job on another stream goes on: replayed it trains as
+    the same steps queued one by one, and the other job's steps are its own."""
+    torch = _torch()
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    a, other = _resnet_job(1, s1), _resnet_job(2, s2)
+    twin, other_twin = _resnet_job(1), _resnet_job(2)
+    idx, off = a.shard(24, 3, 0, 1)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s1, capture_error_mode="relaxed"):
+        a.step_static_scratch(3, idx, off, want_loss=False)
+        other.step(3, want_loss=False)
+    other_twin.step(3)
+    other.sync()
+    assert np.array_equal(other.params(), other_twin.params())
+    for _ in range(3):
+        with torch.cuda.stream(s1):
+            graph.replay()
+        other.step(3)
+        other_twin.step(3)
+        twin.step_static_scratch(3, idx, off)
+        torch.cuda.synchronize()
+        assert np.array_equal(a.params(), twin.params()) and np.array_equal(a.momentum(), twin.momentum())
+        assert np.array_equal(a.running(), twin.running())
+        assert np.array_equal(other.params(), other_twin.params())
+    for job in (a, other, twin, other_twin):
+        job.shutdown()
