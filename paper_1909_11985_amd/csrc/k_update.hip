@@ -452,13 +452,14 @@ void launch_copy(void* dst, const void* src, size_t bytes, hipStream_t st) {
 // ---------------------------------------------------------------------------
 // The state image (snapshot / restore): its header, if one is given, and up to four float arrays in one launch.  A
 // workgroup copies 4 KB of one array; the arrays need 4-byte alignment only (the image packs them without padding),
-// which the 16-byte accesses of this memory path take as they are.  HBM-bound; one launch instead of four and a
+// which the 16-byte accesses of this memory path take as they are.  An image at an odd address is copied array by array.  HBM-bound; one launch instead of four and a
 // header copied from host memory (with a wait for it) takes the hand-over of ResNet-50's 205 MB from 183 to 152 us.
 // ---------------------------------------------------------------------------
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
-__global__ __launch_bounds__(256) void image_kernel(ImageParts parts, ImageHeader hdr, uint32_t* __restrict__ header_dst) {
-    if (header_dst != nullptr && blockIdx.x == 0 && threadIdx.x < kImageHeaderBytes / 4) header_dst[threadIdx.x] = hdr.words[threadIdx.x];
+__global__ __launch_bounds__(256) void image_kernel(ImageParts parts, ImageHeader hdr, unsigned char* __restrict__ header_dst) {
+    static_assert(kImageHeaderBytes == 256, "a byte per lane");
+    if (header_dst != nullptr && blockIdx.x == 0) header_dst[threadIdx.x] = (unsigned char)(hdr.words[threadIdx.x / 4] >> threadIdx.x % 4 * 8);
     int part = 0;
     #pragma unroll
     for (int q = 1; q < kImageParts; ++q) part = (int)blockIdx.x >= parts.block0[q] ? q : part;
@@ -471,6 +472,16 @@ __global__ __launch_bounds__(256) void image_kernel(ImageParts parts, ImageHeade
 
 void launch_image(const ImageParts& in, const ImageHeader& hdr, void* header_dst, hipStream_t st) {
     ImageParts parts = in;
+    uintptr_t bits = 0;
+    for (int q = 0; q < kImageParts; ++q)
+        if (parts.n[q] > 0) bits |= (uintptr_t)parts.dst[q] | (uintptr_t)parts.src[q];
+    if (bits & 3) {
+        for (int q = 0; q < kImageParts; ++q) {
+            if (parts.n[q] > 0) launch_copy(parts.dst[q], parts.src[q], 4 * (size_t)parts.n[q], st);
+            parts.n[q] = 0;
+        }
+        if (header_dst == nullptr) return;
+    }
     int blocks = 0;
     double bytes = 0;
     for (int q = 0; q < kImageParts; ++q) {
@@ -480,7 +491,7 @@ void launch_image(const ImageParts& in, const ImageHeader& hdr, void* header_dst
     }
     if (blocks == 0) blocks = 1;
     ProfScope ps("copy", 0.0, 2.0 * bytes, st);
-    hipLaunchKernelGGL(image_kernel, dim3(blocks), dim3(256), 0, st, parts, hdr, (uint32_t*)header_dst);
+    hipLaunchKernelGGL(image_kernel, dim3(blocks), dim3(256), 0, st, parts, hdr, (unsigned char*)header_dst);
 }
 
 __global__ __launch_bounds__(256) void fill_kernel(float* dst, float value, int64_t n) {

@@ -825,6 +825,28 @@ def test_snapshot_bytes_and_resume():
     assert np.array_equal(job.running(), joiner.running())
 
 
+@pytest.mark.parametrize("optimizer", ["momentum", "adam"])
+@pytest.mark.parametrize("shift", [1, 2, 4, 8, 255])
+def test_a_state_image_may_start_at_any_address(optimizer, shift):
+    """Snapshot and restore take images at any byte address; nothing beside the image is written."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    cfg = make_config("resnet20", N=32, B=16, p_max=2, max_shard=16, optimizer=optimizer, **_cfg_geom(TINY["resnet20"]))
+    job, joiner = E.Job(cfg, 3), E.Job(cfg, 4)
+    want = job.snapshot().clone()
+    n = job.sizes.snapshot_bytes
+    buf = torch.zeros(n + 512, dtype=torch.uint8, device="cuda")
+    job.snapshot(buf[shift:shift + n])
+    joiner.restore(buf[shift:shift + n])
+    torch.cuda.synchronize()
+    assert torch.equal(buf[shift:shift + n], want)
+    assert int(buf[:shift].sum()) == 0 and int(buf[shift + n:].sum()) == 0
+    assert torch.equal(joiner.snapshot(), want)
+    for j in (job, joiner):
+        j.shutdown()
+
+
 def test_step_is_deterministic():
     a = run_parity("resnet50", "bf16", N=48, B=24, schedule=[2, 3], verbose=False, **TINY["resnet50"])
     b = run_parity("resnet50", "bf16", N=48, B=24, schedule=[2, 3], verbose=False, **TINY["resnet50"])
