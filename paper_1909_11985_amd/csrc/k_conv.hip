@@ -494,7 +494,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     // strips: byte offsets of this lane's vectors of A and B at kernel row 0, the kernel rows at which the vector of A is
     // inside the image (a bit each), kernel row and channel of the next step
     constexpr int SIA = STRIP ? ITER_A : 1, SIB = STRIP ? ITER_B : 1;
-    int strip_a[SIA], strip_b[SIB], strip_in[SIA];
+    // (unsigned: in the last image row of a tensor of nearly 2 GiB the offset at row 0 is past it until the row's term, modulo
+    // 2^32, brings it back)
+    unsigned strip_a[SIA], strip_b[SIB];
+    int strip_in[SIA];
     int strip_r = 0, strip_c = 0;
     int strip_frag[STRIP ? TM : 1][TAPS];   // byte offset of this lane's fragment in the strip, by column shift
     if (STRIP) {
@@ -517,13 +520,13 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 in |= (ok && q >= 0 && q < a.H) ? 1 << r : 0;
             }
             strip_in[it] = in;
-            strip_a[it] = ((pix + (MODE == CONV_FWD ? -wd : wd)) * inner + chunk * VEC) * (int)sizeof(T);
+            strip_a[it] = ((unsigned)(pix + (MODE == CONV_FWD ? -wd : wd)) * (unsigned)inner + (unsigned)(chunk * VEC)) * (unsigned)sizeof(T);
         }
         #pragma unroll
         for (int it = 0; it < ITER_B; ++it) {
             const int row = (tid + it * 256) / KV, tap = row / BN, j = n0 + row - tap * BN;
             const int chunk = slot ^ ((row / RPL) % KV);
-            strip_b[it] = (j < a.Nn && tap < TAPS) ? (int)((j * a.ldb + tap * inner + chunk * VEC) * (int)sizeof(T)) : (int)kOutOfRange;
+            strip_b[it] = (j < a.Nn && tap < TAPS) ? (unsigned)(j * a.ldb + tap * inner + chunk * VEC) * (unsigned)sizeof(T) : kOutOfRange;
         }
         #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -627,18 +630,18 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     auto load_tiles = [&](int set) {
         if (STRIP) {
             const int inner = MODE == CONV_FWD ? a.C : a.K;
-            const int addA = ((MODE == CONV_FWD ? strip_r : -strip_r) * a.W * inner + strip_c) * (int)sizeof(T);
-            const int addB = (strip_r * TAPS * inner + strip_c) * (int)sizeof(T);
+            const unsigned addA = (unsigned)((MODE == CONV_FWD ? strip_r : -strip_r) * a.W * inner + strip_c) * (unsigned)sizeof(T);
+            const unsigned addB = (unsigned)(strip_r * TAPS * inner + strip_c) * (unsigned)sizeof(T);
             #pragma unroll
             for (int it = 0; it < ITER_A; ++it) {
-                const unsigned off = (unsigned)(strip_a[it] + addA) | (((strip_in[it] >> strip_r) & 1) ? 0u : kOutOfRange);
+                const unsigned off = (strip_a[it] + addA) | (((strip_in[it] >> strip_r) & 1) ? 0u : kOutOfRange);
                 if ((it + 1) * 64 <= STRIP_ROWS || __builtin_amdgcn_readfirstlane(wave) < (STRIP_ROWS - it * 64) / 16)
                     buffer_load16_to_lds(wordsA, ldsA_wave + set * A_STAGE + it * 4096, off);
             }
             #pragma unroll
             for (int it = 0; it < ITER_B; ++it) {
                 if ((it + 1) * 64 <= TAPS * BN || __builtin_amdgcn_readfirstlane(wave) < (TAPS * BN - it * 64) / 16)
-                    buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096, (unsigned)strip_b[it] + (unsigned)addB);
+                    buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096, strip_b[it] + addB);
             }
             strip_c += BK;
             const bool next = strip_c == inner;
