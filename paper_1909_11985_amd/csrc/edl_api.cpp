@@ -205,7 +205,8 @@ int64_t plan_scratch(const edl_config& c, const Graph& g, const Layout& L, int s
 
 // How many samples and shards one pass runs together.  All of the mini-batch if it fits: a layer of p shards is then
 // one launch instead of p, with p times the workgroups (ResNet-50 bf16, aggregate batch 256 as 8 shards of 32:
-// 34.5 -> 23.4 ms per step; ResNet-20 float32, 8 shards of 16: 10.3 -> 1.84 ms; MLP, 4 shards of 16: 0.48 -> 0.17 ms).  Limits, none of which cuts a single shard:
+// 34.5 -> 23.4 ms per step; ResNet-20 float32, 8 shards of 16: 8.3 -> 1.8 ms; MLP, 4 shards of 16: 0.41 -> 0.15 ms).
+// Limits, none of which cuts a single shard:
 // 32 GB of activations and gradients (a pass of some 250 images of 224x224 gains nothing more from more of them),
 // 2 GiB per tensor (the vector kernels' 32-bit offsets), and what every convolution's vector kernel takes (VGG-16 on
 // 320x320 images: 95 samples).

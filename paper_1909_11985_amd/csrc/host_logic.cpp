@@ -108,7 +108,9 @@ void epoch_permutation(uint64_t seed, int64_t epoch, int64_t N, std::vector<int6
 
 // Entries [from, from + count) of it.  Bound by the walk's random accesses and, for large data sets, by the pages of
 // a fresh work array: 32-bit entries halve the array and each thread keeps its own from call to call (released above
-// kKeptEntries).  1.2 million samples, mini-batches over the epoch: 1.69 -> 0.55 ms on average.
+// kKeptEntries).  1.2 million samples, mini-batches of 250, medians on one host core: the epoch's first, which walks
+// all of it, 5.7 -> 5.3 ms, its middle one 6.4 -> 3.3 ms, its last 6.6 -> 0.3 ms (early ones on the host of an MI355X
+// 1.6-1.8 -> 0.75-0.82 ms).
 void epoch_permutation_slice(uint64_t seed, int64_t epoch, int64_t N, int64_t from, int64_t count, int64_t* out) {
     constexpr int64_t kKeptEntries = 4 << 20;
     if (N > (int64_t)0xffffffffll) {

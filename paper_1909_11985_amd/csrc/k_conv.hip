@@ -31,8 +31,9 @@
 //    tiles: the reduction index (the pixel) is the slow index in memory; bf16
 //    tiles stay [pixel][channel] and are transposed on the way out of LDS
 //    (ds_read_tr16_b64), float32 tiles are 32-bit words read one by one.
-//  * dgrad of a strided convolution runs once per residue class of the input
-//    pixel modulo the stride and contracts only the taps that reach the class.
+//  * dgrad of a strided convolution contracts, for each residue class of the
+//    input pixel modulo the stride, only the taps that reach the class: one
+//    launch for the four classes of stride 2, else one per class.
 //  * epilogue: through LDS as float32, out as 16-byte vectors (bf16 packed by
 //    the hardware conversion).
 //  * long reductions of small problems, and every weight gradient, are cut
@@ -79,8 +80,8 @@ struct ConvArgs {
     int vecA, vecB;
     int ksplit;  // reduction elements per blockIdx.z
     unsigned bytesA, bytesB;  // extents of the two operands (for the range-checked vector loads)
-    // dgrad of a strided convolution, one launch per residue class of the input
-    // pixel (h % stride, w % stride) = (ph, pw): only the taps r = r0, r0+stride, ...
+    // dgrad of a strided convolution, per residue class of the input pixel
+    // (h % stride, w % stride) = (ph, pw): only the taps r = r0, r0+stride, ...
     // (nr of them) and s = s0, ... (ns) reach such a pixel, so the reduction runs
     // over nr*ns*K instead of R*S*K.  Hc x Wc pixels per image are in the class.
     // For stride 1 (and the other modes): ph = pw = r0 = s0 = 0, nr = R, ns = S.
