@@ -6,7 +6,7 @@ import pytest
 import synth_inputs
 from oracle import oracle as O
 from parity_util import (TIGHT, TOL, conv_bn_pair_parity, forced_parity, layerwise_ok, layerwise_parity, relerr,
-                         relu_producer_pair_parity, run_parity, stepwise_parity)
+                         per_tensor_relerr, relu_producer_pair_parity, run_parity, stepwise_parity)
 
 pytestmark = pytest.mark.gpu
 
@@ -102,6 +102,78 @@ def test_adam_update_matches_oracle(p, shares, P, shadow):
     if shadow:
         want = O.round_bf16(gw).astype(np.float32)
         np.testing.assert_array_equal(d16.float().cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+@pytest.mark.parametrize("p", [5, 6, 7, 9])
+@pytest.mark.parametrize("shadow", [False, True])
+def test_updates_at_the_other_worker_counts_match_oracle(p, shadow):
+    """p has its own instantiation up to 8 and a loop beyond."""
+    n = np.arange(p) + 2.0
+    test_average_update_matches_oracle(p, 100003, shadow)
+    test_adam_update_matches_oracle(p, None, 100003, shadow)
+    test_adam_update_matches_oracle(p, tuple(n / n.sum()), 100003, shadow)
+
+
+@pytest.mark.parametrize("p", [1, 3, 8])
+@pytest.mark.parametrize("pages", [0, 1])
+@pytest.mark.parametrize("P", [32000000, 32000007, 42666671])
+def test_updates_of_states_around_the_infinity_cache(P, pages, p):
+    """32,000,000 parameters are the last whose momentum update keeps w and v cached, and Adam's limit is 42,666,666; beyond
+    them all streams are non-temporal, unless the state arrays start on 4 KB pages of opposite parity (pages=1).  Two
+    updates against the same formulas in float64, every element, and against the plain kernel bit for bit."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    rng = torch.Generator(device="cuda").manual_seed(P + p)
+    pitch = (-(-4 * P // 8192) * 8192 + 4096 * pages) // 4                  # floats from one state array to the next
+    room = torch.empty(3 * pitch + 2048, device="cuda")
+    room = room[(-room.data_ptr() // 4) % 2048:]
+    w, v, s = (room[i * pitch:i * pitch + P] for i in range(3))
+    assert (w.data_ptr() ^ v.data_ptr()) & 8191 == 4096 * pages
+    w16 = torch.empty(P, dtype=torch.bfloat16, device="cuda")
+    g = [torch.randn(P, device="cuda", generator=rng).mul_(1e-2) for _ in range(p)]
+    w0, v0 = torch.randn(P, device="cuda", generator=rng).mul_(0.05), torch.randn(P, device="cuda", generator=rng).mul_(0.05)
+    s0 = torch.rand(P, device="cuda", generator=rng).add_(0.5).mul_(1e-4)
+    lr, mom, wd, b2, eps = F32(0.01), F32(0.9), F32(5e-4), F32(0.999), F32(1e-8)
+
+    def near(got, want, atol=1e-7):         # the bar of the small updates above
+        bad = (got.double() - want).abs_().sub_(want.abs().mul_(2e-6)).max()
+        assert float(bad) <= atol, float(bad)
+
+    def reset():
+        w.copy_(w0), v.copy_(v0), s.copy_(s0), w16.zero_()
+
+    def mean():
+        return torch.stack([gk.double() for gk in g]).mean(0) if p < 8 else sum(gk.double() for gk in g) / p
+
+    # momentum
+    reset()
+    for _ in range(2):
+        E.edl_average_update(g, w, v, w16, lr, mom, wd)
+    W, V, m = w0.double(), v0.double(), mean()
+    for _ in range(2):
+        V = mom * V + (m + wd * W)
+        W = W - lr * V
+    near(w, W), near(v, V)
+    assert torch.equal(w16, w.bfloat16())
+    wide = w.clone(), v.clone()
+    with E.options(upd_wide=0):
+        reset()
+        for _ in range(2):
+            E.edl_average_update(g, w, v, w16, lr, mom, wd)
+    assert torch.equal(w, wide[0]) and torch.equal(v, wide[1])
+    del wide, V, W
+    # Adam
+    reset()
+    for t in (10, 11):
+        E.edl_adam_update(g, w, v, s, w16, lr, mom, b2, eps, wd, t)
+    W, M, S = w0.double(), v0.double(), s0.double()
+    for t in (10, 11):
+        G = m + wd * W
+        M = mom * M + (1 - mom) * G
+        S = b2 * S + (1 - b2) * G * G
+        W = W - lr * (M / (1 - mom ** t)) / ((S / (1 - b2 ** t)).sqrt() + eps)
+    near(w, W), near(v, M), near(s, S, 1e-12)
+    assert torch.equal(w16, w.bfloat16())
 
 
 def test_adam_update_rejects_bad_arguments():
@@ -1051,6 +1123,49 @@ def test_row_tiles_inside_a_shard_read_their_neighbours(model, kw, cut, tile):
     import paper_1909_11985_amd as E
     with E.options(force_tile=tile):
         test_shards_of_one_pass_are_computed_as_each_alone(model, "f32", kw, cut)
+
+
+@pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
+@pytest.mark.parametrize("model,kw,cut", [
+    ("resnet20", dict(H=16, W=16, C=3, classes=10, arch=(16, 3, 1)), [4, 1, 9, 4]),
+    ("resnet50", dict(H=64, W=64, C=3, classes=10, arch=(64, 1, 1, 1, 1)), [3, 8, 5]),
+    ("resnet50", dict(H=50, W=42, C=3, classes=10, arch=(64, 1, 2, 1, 1)), [7, 7, 6]),       # odd images, identity shortcuts
+])
+def test_bf16_gradients_of_residual_shards_are_those_of_each_alone(model, kw, cut, tile):
+    """The bf16 epilogues of a pass over several shards (masks from sign bits, batch statistics per shard, strips that end
+    with a shard) on nets whose gradients are not set by rounding (_damped).  Both sides round the same tensors to bf16; a
+    sum formed in another order moves a rounding now and then.  A rounding is 2^-9 / sqrt(3) = 1.1e-3 of a value in the mean;
+    some 30 tensors on the way, each rounded on either side, are sqrt(60) * 1.1e-3 = 9e-3 if no two roundings agree: 1e-2
+    for the gradient as one vector (measured 2e-3), the bf16 bar for each contraction's weights.  Not for a single batch
+    norm's shift and scale: their terms cancel, so that what is left is no larger than the terms' roundings (stem.bn.b
+    2.4e-2)."""
+    import torch
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import edl_tensor_table, make_config
+    B, geom = sum(cut), _cfg_geom(kw)
+    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    x, y = synth_inputs.dataset(3, 2 * B, kw["H"], kw["W"], kw["C"], kw["classes"])
+    dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    with E.options(force_tile=tile):
+        job = E.Job(make_config(model, dtype="bf16", N=2 * B, B=B, p_max=len(cut), max_shard=max(cut), **geom), 5)
+        job.bind_dataset(dx, dy)
+        _damped(job)
+        idx, _ = job.shard(B, 1, 0, 1)
+        job.gradients(len(cut), idx, off)
+        losses = job.losses(len(cut))
+        weights = [t for t in edl_tensor_table(job.cfg) if "bn" not in t[0]]
+        for k, n in enumerate(cut):
+            alone = E.Job(make_config(model, dtype="bf16", N=n, B=n, p_max=1, max_shard=n, **geom), 5)
+            sel = torch.from_numpy(idx[off[k]:off[k + 1]]).cuda()
+            alone.bind_dataset(dx[sel].contiguous(), dy[sel].contiguous())
+            _damped(alone)
+            alone.gradients(1, np.arange(n, dtype=np.int64), np.array([0, n], dtype=np.int64))
+            worst, where, whole = per_tensor_relerr(weights, job.grad(k), alone.grad(0))
+            print("shard %d of %s: worst %.2e (%s) whole %.2e" % (k, cut, worst, where, whole), flush=True)
+            assert abs(losses[k] - alone.losses(1)[0]) <= 2e-2 * abs(losses[k]), k
+            assert whole < 1e-2 and worst < 2e-2, (k, worst, where, whole)
+            alone.shutdown()
+        job.shutdown()
 
 
 @pytest.mark.parametrize("tile", [-1, 0, 1, 2, 3])
