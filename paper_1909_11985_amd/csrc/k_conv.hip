@@ -79,6 +79,7 @@ struct ConvArgs {
     int relu, out_fp32, accumulate;
     int vecA, vecB;
     int ksplit;  // reduction elements per blockIdx.z
+    int fold;    // FOLDED weight gradients and float32: most reduction elements that are summed in one chain
     unsigned bytesA, bytesB;  // extents of the two operands (for the range-checked vector loads)
     // dgrad of a strided convolution, per residue class of the input pixel
     // (h % stride, w % stride) = (ph, pw): only the taps r = r0, r0+stride, ...
@@ -145,9 +146,13 @@ struct ConvClass {
     unsigned long long magic_hw, magic_w, magic_taps;
 };
 struct ConvArgsClasses : ConvArgs { int classes; ConvClass cls[4]; };
-enum LaunchKind { PLAIN, SHARDED, CLASSES };
+// FOLDED: a weight gradient over shards (or one of them) whose pieces are summed in shorter chains (ConvArgs::fold); a kernel
+// of its own because the second set of sums costs the 128x128 tile 64 registers and with them the place of a wave beside it
+// (on all weight gradients: VGG-16 1.3%, AlexNet 2.7% slower).
+enum LaunchKind { PLAIN, SHARDED, CLASSES, FOLDED };
 template <int KIND> struct ArgsOf { typedef ConvArgs type; typedef const ConvArgs& use; };
 template <> struct ArgsOf<SHARDED> { typedef ConvArgsShards type; typedef const ConvArgsShards& use; };
+template <> struct ArgsOf<FOLDED> { typedef ConvArgsShards type; typedef const ConvArgsShards& use; };
 template <> struct ArgsOf<CLASSES> { typedef ConvArgsClasses type; typedef ConvArgs use; };   // a copy, completed by the class
 
 
@@ -385,7 +390,7 @@ __device__ __forceinline__ int64_t out_row(const ConvArgs& a, int row) {
 template <typename T, int MODE, int WM, int WN, int TM, int TN, int BK, bool FAST, int PF, int KIND, int TAPS = 1, bool BROWS = false>
 __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND>::type args) {   // at least two waves per SIMD: 256 registers
     typename ArgsOf<KIND>::use a = args;
-    constexpr bool SHARDS = KIND == SHARDED;
+    constexpr bool SHARDS = KIND == SHARDED || KIND == FOLDED;
     constexpr bool WG = MODE == CONV_WGRAD;
     constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
     constexpr int VEC = Elem<T>::VEC;
@@ -910,6 +915,35 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         for (int j = 0; j < TN; ++j)
             #pragma unroll
             for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+    // Two levels of sums: after at most a.fold elements the accumulators are added to `folded` and start again.  The
+    // rounding error of a chain grows with its length, and a pass over several shards cuts each shard's reduction into
+    // fewer, longer pieces than the shard alone.  Relative error of a shard's weight gradient against float64, alone / in a
+    // pass in one chain / folded: ResNet-50's stem, 8 shards of 32, 4.9e-7 / 1.35e-6 / 4.6e-7; VGG-16's conv2, 4 of 16,
+    // 5.3e-7 / 1.17e-6 / 5.1e-7; ResNet-20 in float32, 8 of 64, its 8x8 layers 2.2e-7 / 4.5e-7 / 2.0e-7, their outputs
+    // 1.6e-7 / 2.9e-7 / 1.4e-7.  It costs the step of 8 shards of 32 0.2%, AlexNet's of 2 of 64 1.4%.
+    constexpr bool FOLDS = KIND == FOLDED || (!WG && sizeof(T) == 4);
+    floatx16 folded[FOLDS ? TM : 1][FOLDS ? TN : 1];
+    if constexpr (FOLDS)
+        #pragma unroll
+        for (int i = 0; i < TM; ++i)
+            #pragma unroll
+            for (int j = 0; j < TN; ++j)
+                #pragma unroll
+                for (int q = 0; q < 16; ++q) folded[i][j][q] = 0.f;
+    auto fold = [&]() {
+        if constexpr (FOLDS)
+            #pragma unroll
+            for (int i = 0; i < TM; ++i)
+                #pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    folded[i][j] += acc[i][j];
+                    #pragma unroll
+                    for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+                }
+    };
+    // tiles between folds: whole rounds of the LDS stages / register sets
+    constexpr int ROUND = DMA ? NST : PF;
+    const int chain = FOLDS ? (a.fold / (TAPS * BK) > ROUND ? a.fold / (TAPS * BK) / ROUND * ROUND : ROUND) : 0;
 
     // Software pipeline: two LDS stages and PF register sets.  While tile k is
     // contracted from LDS stage k%2, the global loads of tiles k+1 .. k+PF are in
@@ -996,15 +1030,20 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         constexpr int PER_TILE = STRIP ? STRIP_ROWS / 64 + TAPS * BN / 64 : DIRECT_WG ? DA + DB : ITER_A + ITER_B;
         #pragma unroll
         for (int u = 0; u < NST - 1; ++u) load_tiles(u);
-        for (int kt = 0; kt < nk; kt += NST) {
-            #pragma unroll
-            for (int u = 0; u < NST; ++u) {
-                if (kt + u >= nk) break;
-                wait_vmcnt<(NST - 2) * PER_TILE>();
-                __syncthreads();
-                load_tiles((u + NST - 1) % NST);
-                contract(u);
+        for (int kt = 0;;) {
+            const int stop = FOLDS && nk - kt > chain ? kt + chain : nk;
+            for (; kt < stop; kt += NST) {
+                #pragma unroll
+                for (int u = 0; u < NST; ++u) {
+                    if (kt + u >= nk) break;
+                    wait_vmcnt<(NST - 2) * PER_TILE>();
+                    __syncthreads();
+                    load_tiles((u + NST - 1) % NST);
+                    contract(u);
+                }
             }
+            if (!FOLDS || kt >= nk) break;
+            fold();
         }
         wait_vmcnt<0>();
         __syncthreads();
@@ -1013,19 +1052,29 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         for (int u = 0; u < PF; ++u) load_tiles(u);
         store_tiles(0, 0);
         __syncthreads();
-        for (int kt = 0; kt < nk; kt += PF) {
-            #pragma unroll
-            for (int u = 0; u < PF; ++u) {
-                const int k = kt + u;
-                if (k >= nk) break;
-                const int buf = PF == 1 ? (k & 1) : (u & 1);
-                load_tiles(u);
-                contract(buf);
-                store_tiles((u + 1) % PF, buf ^ 1);
-                __syncthreads();
+        for (int kt = 0;;) {
+            const int stop = FOLDS && nk - kt > chain ? kt + chain : nk;
+            for (; kt < stop; kt += PF) {
+                #pragma unroll
+                for (int u = 0; u < PF; ++u) {
+                    const int k = kt + u;
+                    if (k >= nk) break;
+                    const int buf = PF == 1 ? (k & 1) : (u & 1);
+                    load_tiles(u);
+                    contract(buf);
+                    store_tiles((u + 1) % PF, buf ^ 1);
+                    __syncthreads();
+                }
             }
+            if (!FOLDS || kt >= nk) break;
+            fold();
         }
     }
+    if constexpr (FOLDS)
+        #pragma unroll
+        for (int i = 0; i < TM; ++i)
+            #pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] += folded[i][j];
 
     // ---- epilogue: lane holds column lane%32, rows (q/4)*8 + (lane/32)*4 + q%4 of each 32x32 tile ----
     constexpr bool OUT_F32 = WG || sizeof(T) == 4;       // element type of the vector-path output
@@ -1700,7 +1749,12 @@ static void launch_mode(int dtype, TileCfg t, dim3 grid, const ConvArgsShards& a
         }
         return;
     }
-    if (a.shards > 1) {
+    if (MODE == CONV_WGRAD && a.ksplit > a.fold) {
+        if constexpr (MODE == CONV_WGRAD) {
+            if (dtype == 1) launch_cfg<bf16_t, MODE, FOLDED>(t, fast, grid, a, st);
+            else launch_cfg<float, MODE, FOLDED>(t, fast, grid, a, st);
+        }
+    } else if (a.shards > 1) {
         if (dtype == 1) launch_cfg<bf16_t, MODE, SHARDED>(t, fast, grid, a, st);
         else launch_cfg<float, MODE, SHARDED>(t, fast, grid, a, st);
     } else {
@@ -1715,6 +1769,7 @@ static ConvArgsShards base_args(const ConvGeom& g) {
     a.stride = g.stride; a.pad = g.pad; a.Ho = g.Ho; a.Wo = g.Wo;
     a.ph = a.pw = a.r0 = a.s0 = 0; a.nr = g.R; a.ns = g.S; a.Hc = g.H; a.Wc = g.W;
     a.cut.p = 1;
+    a.fold = 128;       // forward and input gradients in float32: about what a cut reduction's shortest pieces are
     return a;
 }
 
@@ -2096,9 +2151,11 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     }
     a.ksplit = p.ksplit;
     a.splits = p.splits;
+    a.fold = plan_wgrad(dtype, one, 1).ksplit;       // no longer chains than those of the shard alone
     a.cut = cut_rows(S, g.Ho * g.Wo, p.ksplit);
     a.zdirect = direct;
-    a.out = direct ? (S.p == 1 ? dw.g + S.k[0] * dw.stride : dw.g) : scratch;
+    // (a kernel with the table of shards finds the worker's gradient itself)
+    a.out = direct ? (S.p == 1 && a.ksplit <= a.fold ? dw.g + S.k[0] * dw.stride : dw.g) : scratch;
     a.zstride = direct ? dw.stride : n;
     const dim3 grid((a.M + p.bm - 1) / p.bm, (a.Nn + p.bn - 1) / p.bn, S.p * p.splits);
     launch_mode<CONV_WGRAD>(dtype, p.t, grid, a, st);

@@ -150,22 +150,41 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
                 }
             }
         };
+        // Sums of 16 rows are added to fa, fb, and the lanes below in float64: a lane's rows grow with the shards of the pass
+        // (ResNet-50's stem, 8 shards of 32: 12 -> 98), and with them the rounding error of one chain (16 layers' scale
+        // gradients against float64: alone 9.4e-8, in a pass in one chain 1.23e-7, so 8.5e-8, alone 7.1e-8).
+        float fa[VEC], fb[VEC];
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) { fa[e] = 0.f; fb[e] = 0.f; }
         int64_t r = r0 + ty;
-        for (; r + TY < r1; r += 2 * (int64_t)TY) rows(r, std::integral_constant<int, 2>());
+        for (int trip = 1; r + TY < r1; r += 2 * (int64_t)TY, ++trip) {
+            rows(r, std::integral_constant<int, 2>());
+            if ((trip & 7) == 0) {
+                #pragma unroll
+                for (int e = 0; e < VEC; ++e) { fa[e] += a[e]; fb[e] += b[e]; a[e] = 0.f; b[e] = 0.f; }
+            }
+        }
         if (r < r1) rows(r, std::integral_constant<int, 1>());
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) { a[e] += fa[e]; b[e] += fb[e]; }
     }
     const int lane = ty * TX + tx;
     #pragma unroll
     for (int e = 0; e < VEC; ++e) { red[0][lane * VEC + e] = a[e]; red[1][lane * VEC + e] = b[e]; }
     __syncthreads();
     if (ty == 0 && active) {
+        double da[VEC], db[VEC];
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) { da[e] = (double)a[e]; db[e] = (double)b[e]; }
         for (int j = 1; j < TY; ++j) {
             #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-                a[e] += red[0][(j * TX + tx) * VEC + e];
-                b[e] += red[1][(j * TX + tx) * VEC + e];
+                da[e] += (double)red[0][(j * TX + tx) * VEC + e];
+                db[e] += (double)red[1][(j * TX + tx) * VEC + e];
             }
         }
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) { a[e] = (float)da[e]; b[e] = (float)db[e]; }
         // partial[sum kind][channel][row block]: a channel's partial sums are contiguous for the finishing kernel
         #pragma unroll
         for (int e = 0; e < VEC; ++e) {

@@ -5,8 +5,8 @@ import pytest
 
 import synth_inputs
 from oracle import oracle as O
-from parity_util import (TIGHT, TOL, conv_bn_pair_parity, forced_parity, layerwise_ok, layerwise_parity, relerr,
-                         per_tensor_relerr, relu_producer_pair_parity, run_parity, stepwise_parity)
+from parity_util import (TIGHT, TOL, Case, conv_bn_pair_parity, forced_parity, layerwise_ok, layerwise_parity, relerr,
+                         per_tensor_relerr, relu_producer_pair_parity, run_parity, stepwise_parity, tid)
 
 pytestmark = pytest.mark.gpu
 
@@ -1287,6 +1287,39 @@ def test_equal_shards_are_summed_in_the_same_order_wherever_they_run(model, dtyp
     job.debug_backward(n, 0)
     assert np.array_equal(job.grad(0), grads[0])
     job.shutdown()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_weight_gradients_of_a_pass_are_as_precise_as_alone(dtype):
+    """A pass over several shards cuts a shard's weight gradient into fewer pieces than the shard alone (here 8 times), but
+    sums it in no longer chains: its error against float64 on the same inputs may not grow.  The errors are norms over 432
+    and 2,304 sums of as many independent roundings each, known to a few percent: a quarter more is growth (one chain
+    for each of the longer pieces: 1.3 and 1.7 times the error)."""
+    n, errs = 8, {}
+    for p in (1, 8):
+        case = Case("resnet20", dtype, n, N=n * p, B=n * p, p_max=p, H=64, W=64, C=3, classes=10, arch=(16, 1, 1))
+        cast = O.round_bf16 if dtype == "bf16" else lambda a: a.astype(np.float64)
+        case.job.debug_forward(np.arange(n, dtype=np.int64))
+        errs[p] = {}
+        for i, op in enumerate(o for o in case.oracle(False).graph.ops if o["kind"] != "flatten"):
+            if op["kind"] != "conv" or op["R"] != 3:
+                continue
+            rng = np.random.default_rng(i)
+            h, w, c, _ = case.tensors[tid(op["x"])]
+            x = case.x[:n] if tid(op["x"]) == 0 else np.maximum(rng.standard_normal((n, h, w, c), dtype=np.float32), 0)
+            dy = rng.standard_normal((n, h, w, op["K"]), dtype=np.float32)
+            if tid(op["x"]) != 0:
+                case.job.debug_set(tid(op["x"]), x)
+            case.job.debug_set(tid(op["y"]), dy, which=1)
+            case.job.debug_backward_op(i, n, 0)
+            xp, d = np.pad(cast(x), ((0, 0), (1, 1), (1, 1), (0, 0))), cast(dy).reshape(-1, op["K"])
+            want = np.stack([d.T @ xp[:, r:r + h, s:s + w].reshape(-1, c) for r in range(3) for s in range(3)], 1)
+            errs[p][op["name"]] = relerr(case.job.grad_slice(0, op["w_off"], want.size).reshape(want.shape), want)
+        case.close()
+    print(errs, flush=True)
+    assert len(errs[1]) == 3
+    for name, e in errs[1].items():
+        assert errs[8][name] < 1.25 * e, (name, errs)
 
 
 # ---------------------------------------------------------------- jobs beside one another
