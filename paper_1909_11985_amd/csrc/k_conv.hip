@@ -2151,7 +2151,9 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     }
     a.ksplit = p.ksplit;
     a.splits = p.splits;
-    a.fold = plan_wgrad(dtype, one, 1).ksplit;       // no longer chains than those of the shard alone
+    ConvGeom small = g;
+    small.N = S.plan_smallest;
+    a.fold = plan_wgrad(dtype, small, 1).ksplit;     // no longer chains than those of the smallest shard alone
     a.cut = cut_rows(S, g.Ho * g.Wo, p.ksplit);
     a.zdirect = direct;
     // (a kernel with the table of shards finds the worker's gradient itself)

@@ -95,7 +95,8 @@ __device__ __forceinline__ void store_row(T* base, int64_t r, int C, int c0, con
 // KIND 0: a = x, b = x^2                       (batch-norm statistics)
 // KIND 1: a = dy', b = dy' * xhat              (batch-norm backward sums), dy' = dy * (y>0) if relu
 // KIND 2: a = dy' (written back in place), b=0 (bias gradient / ReLU mask)
-template <typename T, int VEC, int KIND>
+// LONG: in two levels (see long_blocks)
+template <typename T, int VEC, int KIND, bool LONG>
 __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x, const T* __restrict__ y, T* dy,
                                                         const float* __restrict__ mean_rstd, RowCut cut, int C,
                                                         int relu, float* __restrict__ partial) {
@@ -150,41 +151,40 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
                 }
             }
         };
-        // Sums of 16 rows are added to fa, fb, and the lanes below in float64: a lane's rows grow with the shards of the pass
-        // (ResNet-50's stem, 8 shards of 32: 12 -> 98), and with them the rounding error of one chain (16 layers' scale
-        // gradients against float64: alone 9.4e-8, in a pass in one chain 1.23e-7, so 8.5e-8, alone 7.1e-8).
-        float fa[VEC], fb[VEC];
+        float fa[VEC], fb[VEC];      // LONG: sums of 16 rows are added up here
         #pragma unroll
         for (int e = 0; e < VEC; ++e) { fa[e] = 0.f; fb[e] = 0.f; }
         int64_t r = r0 + ty;
         for (int trip = 1; r + TY < r1; r += 2 * (int64_t)TY, ++trip) {
             rows(r, std::integral_constant<int, 2>());
-            if ((trip & 7) == 0) {
+            if (LONG && (trip & 7) == 0) {
                 #pragma unroll
                 for (int e = 0; e < VEC; ++e) { fa[e] += a[e]; fb[e] += b[e]; a[e] = 0.f; b[e] = 0.f; }
             }
         }
         if (r < r1) rows(r, std::integral_constant<int, 1>());
-        #pragma unroll
-        for (int e = 0; e < VEC; ++e) { a[e] += fa[e]; b[e] += fb[e]; }
+        if (LONG)
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) { a[e] += fa[e]; b[e] += fb[e]; }
     }
     const int lane = ty * TX + tx;
     #pragma unroll
     for (int e = 0; e < VEC; ++e) { red[0][lane * VEC + e] = a[e]; red[1][lane * VEC + e] = b[e]; }
     __syncthreads();
     if (ty == 0 && active) {
-        double da[VEC], db[VEC];
+        using Sum = std::conditional_t<LONG, double, float>;
+        Sum sa[VEC], sb[VEC];
         #pragma unroll
-        for (int e = 0; e < VEC; ++e) { da[e] = (double)a[e]; db[e] = (double)b[e]; }
+        for (int e = 0; e < VEC; ++e) { sa[e] = a[e]; sb[e] = b[e]; }
         for (int j = 1; j < TY; ++j) {
             #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-                da[e] += (double)red[0][(j * TX + tx) * VEC + e];
-                db[e] += (double)red[1][(j * TX + tx) * VEC + e];
+                sa[e] += red[0][(j * TX + tx) * VEC + e];
+                sb[e] += red[1][(j * TX + tx) * VEC + e];
             }
         }
         #pragma unroll
-        for (int e = 0; e < VEC; ++e) { a[e] = (float)da[e]; b[e] = (float)db[e]; }
+        for (int e = 0; e < VEC; ++e) { a[e] = (float)sa[e]; b[e] = (float)sb[e]; }
         // partial[sum kind][channel][row block]: a channel's partial sums are contiguous for the finishing kernel
         #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -413,6 +413,21 @@ static int vectors_per_lane(const ShardSet& S, int hw, int cvecs) {
     return groups >= 4 * 768 ? 4 : groups >= 2 * 768 ? 2 : 1;
 }
 
+// Whether the row blocks of a pass are longer than those of its smallest shard alone.  A lane's rows grow with the shards of
+// the pass (ResNet-50's stem, 8 shards of 32: 12 -> 98), and with them the rounding error of one float32 chain: those are
+// summed in chains of 16 rows, the lanes' sums in float64 (16 layers' scale gradients against float64: alone 9.4e-8, in a
+// pass in one chain 1.23e-7, in two levels 8.5e-8; no measurable time).  A shard alone keeps one chain.
+static bool long_blocks(const ShardSet& S, int hw, int C, int VEC, const RedShape& pass) {
+    return pass.rows_per_block > red_shape((int64_t)S.plan_smallest * hw, C, VEC).rows_per_block;
+}
+template <typename T, int VEC, int KIND>
+static void launch_colreduce(const RedShape& s, bool two_levels, const T* x, const T* y, T* dy, const float* mean_rstd, const RowCut& cut,
+                             int C, int relu, float* partial, hipStream_t st) {
+    const dim3 grid(s.col_blocks, cut.blk0[cut.p]);
+    if (two_levels) hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, true>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial);
+    else hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, false>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial);
+}
+
 template <typename T, int VEC>
 static void bn_forward_t(const void* x, const void* res, void* y, const float* gamma, const float* beta,
                          float* save, float* running, const ShardSet& S, int hw, int C, bool relu, unsigned char* sign, float* partial,
@@ -424,8 +439,7 @@ static void bn_forward_t(const void* x, const void* res, void* y, const float* g
     if (cut.p == 0) {   // else the producer of x left the partial sums
         ProfScope ps(prof_shape_label("bn_stats", M, C), 0.0, tb, st);
         cut = cut_rows(S, hw, s.rows_per_block);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 0>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)x, (const T*)nullptr,
-                           (T*)nullptr, (const float*)nullptr, cut, C, 0, partial);
+        launch_colreduce<T, VEC, 0>(s, long_blocks(S, hw, C, VEC, s), (const T*)x, (const T*)nullptr, (T*)nullptr, (const float*)nullptr, cut, C, 0, partial, st);
     }
     {
         ProfScope ps("bn_stats_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
@@ -472,8 +486,7 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
     if (!fused) {   // else the dgrad that produced dy left the sums
         ProfScope ps(prof_shape_label("bn_bwd_reduce", M, C), 0.0, tb * (relu ? 3.0 : 2.0), st);
         cut = cut_rows(S, hw, s.rows_per_block);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 1>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)x,
-                           (const T*)(relu ? y : x), (T*)dy, save, cut, C, relu ? 1 : 0, partial);
+        launch_colreduce<T, VEC, 1>(s, long_blocks(S, hw, C, VEC, s), (const T*)x, (const T*)(relu ? y : x), (T*)dy, save, cut, C, relu ? 1 : 0, partial, st);
     }
     {
         ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
@@ -526,8 +539,7 @@ static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const S
     if (cut.p == 0) {   // else dy is masked already and its column sums are in partial
         ProfScope ps("bias_relu_bwd", 0.0, tb * (relu ? 3.0 : 1.0), st);
         cut = cut_rows(S, hw, s.rows_per_block);
-        hipLaunchKernelGGL((colreduce_kernel<T, VEC, 2>), dim3(s.col_blocks, cut.blk0[cut.p]), s.block, 0, st, (const T*)nullptr,
-                           (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial);
+        launch_colreduce<T, VEC, 2>(s, long_blocks(S, hw, C, VEC, s), (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st);
     }
     if (dbias.g) {
         ProfScope ps("bias_finalize", 0.0, 4.0 * (double)cut.blk0[cut.p] * C, st);
