@@ -575,19 +575,24 @@ static void transpose_weights(edl_handle* h, hipStream_t tst) {
 
 static int init_device_state(edl_handle* h);
 
-// events that order the side streams against the job's stream (created once, whoever owns the streams)
+// Events that order the side streams against the job's stream (created once, whoever owns the streams).  They order work on
+// one GPU only, for which the agent-scope release at the end of every kernel is enough: the write-back to system scope that
+// recording does otherwise is left out.  Measured on a chain of 8 us kernels with a record after each: 10.9 -> 9.1 us per
+// kernel (a backward pass of ResNet-50 records 70 on the chain of its input gradients).  What the host reads is ordered by
+// stream synchronisation or by events of the full kind.
+constexpr unsigned kOrderOnly = hipEventDisableTiming | hipEventDisableSystemFence;
 static int create_side_events(edl_handle* h) {
     for (int e = 0; e < kReadyEvents; ++e)
-        if (!h->ev_ready[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_ready[e], hipEventDisableTiming));
-    if (!h->ev_side_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_side_done, hipEventDisableTiming));
+        if (!h->ev_ready[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_ready[e], kOrderOnly));
+    if (!h->ev_side_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_side_done, kOrderOnly));
     for (int e = 0; e < kChunkEvents; ++e)
-        if (!h->ev_chunk[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_chunk[e], hipEventDisableTiming));
-    if (!h->ev_upd_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_upd_done, hipEventDisableTiming));
-    if (!h->ev_tr_go) HIP_TRY(hipEventCreateWithFlags(&h->ev_tr_go, hipEventDisableTiming));
-    if (!h->ev_tr_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_tr_done, hipEventDisableTiming));
+        if (!h->ev_chunk[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_chunk[e], kOrderOnly));
+    if (!h->ev_upd_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_upd_done, kOrderOnly));
+    if (!h->ev_tr_go) HIP_TRY(hipEventCreateWithFlags(&h->ev_tr_go, kOrderOnly));
+    if (!h->ev_tr_done) HIP_TRY(hipEventCreateWithFlags(&h->ev_tr_done, kOrderOnly));
     for (int e = 0; e < kBranchEvents; ++e) {
-        if (!h->ev_branch_go[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_branch_go[e], hipEventDisableTiming));
-        if (!h->ev_branch_done[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_branch_done[e], hipEventDisableTiming));
+        if (!h->ev_branch_go[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_branch_go[e], kOrderOnly));
+        if (!h->ev_branch_done[e]) HIP_TRY(hipEventCreateWithFlags(&h->ev_branch_done[e], kOrderOnly));
     }
     return EDL_OK;
 }
