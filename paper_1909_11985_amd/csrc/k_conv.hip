@@ -45,6 +45,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "pointwise.h"
 #include "profiler.h"
 #include "tune.h"
 
@@ -1911,6 +1912,14 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     const int Mplan = S.plan * g.Ho * g.Wo;
     const TileCfg t = pick_tile(Mplan, a.Nn, a.Kred, &bm, &bn, a.Kred <= 128);
     const bool fast = conv_fast(dtype, CONV_FWD, a);
+    if (fast && bias == nullptr && !relu && !out_fp32 && tune().force_tile < 0 && pointwise_takes(dtype, g, S.plan, a.Kred, a.Nn)) {
+        PointwiseTask t = {};
+        t.K = a.Kred; t.N = a.Nn;
+        t.A = x; t.B = w; t.out = y;
+        if (tune().fused_stats != 0) t.sums = stats;
+        RowCut left;
+        if (launch_pointwise(g, S, t, &left, st)) return left;
+    }
     int splits = 1, ks = a.Kred;
     a.strip = fast && conv_magic_ok(CONV_FWD, a) && takes_strips(dtype, CONV_FWD, g, t);
     if (fast) {
@@ -1960,6 +1969,18 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
     a.bytesA = a.vecA ? (unsigned)bA : 0; a.bytesB = a.vecB ? (unsigned)bB : 0;
     a.brows = w_rows;
     const bool want_mask = tune().fused_mask != 0 && mask != nullptr && mask->act != nullptr && g.stride == 1;
+    // A residual join: the gradient is added to the shortcut's, masked and summed
+    if (want_mask && accumulate && tune().fused_mask_join != 0 && mask->sign != nullptr && mask->xin != nullptr && tune().force_tile < 0 &&
+        conv_fast(dtype, CONV_DGRAD, a) && pointwise_takes(dtype, g, S.plan, g.K, g.C)) {
+        PointwiseTask t = {};
+        t.K = g.K; t.N = g.C;
+        t.A = dy; t.B = wT; t.out = dx;
+        t.join = true;
+        t.old = a.acc_src != nullptr ? a.acc_src : dx;
+        t.sign = mask->sign; t.xin = mask->xin; t.mean_rstd = mask->mean_rstd;
+        t.sums = mask->sums;
+        if (launch_pointwise(g, S, t, &left, st)) return left;
+    }
     // Stride 2: the four residue classes of the input pixel modulo the stride in one launch (each alone is a quarter of
     // the pixels, three of a 1x1 convolution's only zeros: 24 launches fewer in ResNet-50's chain)
     if (g.stride == 2 && conv_fast(dtype, CONV_DGRAD, a)) {

@@ -50,6 +50,8 @@ const Entry kEntries[] = {
     {"alias_shortcut", &Tune::alias_shortcut},
     {"bn_nt", &Tune::bn_nt},
     {"bn_nt_bytes", &Tune::bn_nt_bytes},
+    {"pointwise_rows", &Tune::pointwise_rows},
+    {"pointwise_blocks", &Tune::pointwise_blocks},
     {"spare0", &Tune::spare0},
     {"spare1", &Tune::spare1},
 };

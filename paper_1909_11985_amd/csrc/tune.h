@@ -45,6 +45,8 @@ struct Tune {
     int64_t alias_shortcut = 1;       // an identity shortcut's gradient is read from the block output's gradient instead of being copied
     int64_t bn_nt = 1;                // the batch-norm element-wise passes load what they read once (the convolution's output; the activation for the mask) non-temporally ...
     int64_t bn_nt_bytes = 8000000;    // ... for tensors of at least this many bytes
+    int64_t pointwise_rows = 32768;   // 1x1 convolutions with a short reduction stream from this many rows of 256 columns on ...
+    int64_t pointwise_blocks = 256;   // ... with this many workgroups of eight waves
     int64_t spare0 = 0, spare1 = 0;   // free slots for experiments (EDL_TUNE_SPARE0 / 1)
 };
 

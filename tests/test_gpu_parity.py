@@ -316,6 +316,33 @@ def test_input_gradient_pass_hands_masked_gradient_and_sums_to_its_producer(mode
     _assert_layerwise(r, dtype)
 
 
+@pytest.mark.parametrize("blocks", [1, 3, 256])
+@pytest.mark.parametrize("n,kw", [
+    (5, dict(H=50, W=42, C=3, classes=10, arch=(64, 2, 2, 2, 2))),       # odd images: the last tile of a run is ragged
+    (1, dict(H=33, W=33, C=3, classes=10, arch=(64, 1, 1, 1, 1))),       # fewer rows than a tile
+])
+def test_streaming_pointwise_convolutions(n, kw, blocks):
+    """The streaming kernel of 1x1 convolutions (reductions of 64, 128, 256 and 512 channels, forward and residual joins) at
+    sizes far below those it is chosen for: runs of one tile, of many tiles, and of rows that end inside a tile."""
+    import paper_1909_11985_amd as E
+    with E.options(pointwise_rows=0, pointwise_blocks=blocks):
+        _assert_layerwise(conv_bn_pair_parity("resnet50", "bf16", n, **kw), "bf16")
+        r = relu_producer_pair_parity("resnet50", "bf16", n, only_joins=True, **kw)
+        assert r["plain"]["join_pairs"] > 0
+        _assert_layerwise(r, "bf16")
+
+
+@pytest.mark.parametrize("together", [0, 36])
+@pytest.mark.parametrize("blocks", [3, 256])
+def test_streaming_pointwise_convolutions_keep_to_their_shard(blocks, together):
+    """Runs of rows end with a shard, whose sums are its own: the same bits wherever the shard lies, and in the hooks that
+    run it alone (whose layers the test above compares with the oracle's)."""
+    import paper_1909_11985_amd as E
+    kw = dict(H=50, W=42, C=3, classes=10, arch=(64, 1, 2, 1, 2))
+    with E.options(pointwise_rows=0, pointwise_blocks=blocks):
+        test_equal_shards_are_summed_in_the_same_order_wherever_they_run("resnet50", "bf16", kw, 9, 7, together)
+
+
 def test_residual_join_epilogue_at_the_benchmark_shape():
     """The 15 residual joins of ResNet-50 at 224x224 with the shard of 32: the first convolution of a block runs
     its input-gradient pass on top of the shortcut's part already in the buffer (the oracle's), masks the total
