@@ -391,6 +391,7 @@ struct edl_handle {
     bool static_fits = false;
     int device = -1;
     std::vector<char> written;           // backward pass: which gradient buffers hold something (per tensor)
+    std::vector<size_t> wgrad_waiting;   // a backward pass: layers whose weight gradient is yet to be launched
     std::vector<char> op_done;           // a pass: layers already launched out of list order (on the branch stream)
     // backward pass, per tensor: where the gradient "already there" is to be read from if not from the tensor's
     // own gradient buffer (an identity shortcut's part is the masked gradient of the block's output itself)
@@ -687,6 +688,7 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
     h->readers.assign(h->g.tensors.size(), 0);
     h->written.assign(h->g.tensors.size(), 0);
     h->op_done.assign(h->g.ops.size(), 0);
+    h->wgrad_waiting.reserve(h->g.ops.size());
     h->grad_alias.assign(h->g.tensors.size(), nullptr);
     h->shard_n.reserve(kMaxP);
     h->perm.reserve((size_t)cfg->N);
@@ -963,6 +965,14 @@ static const void* dgrad_weights(const edl_handle* h, size_t i) {
     return h->L.wT[i] >= 0 ? (const void*)(h->arena + h->L.wT[i]) : (const void*)(h->arena + h->L.shadow + 2 * h->g.ops[i].w_off);
 }
 
+// About how long a layer's weight gradient takes: its launches, and the longer of its contraction (250 and 25 TFLOP/s, what
+// such short launches reach) and of its bytes at 4 TB/s.  Only for the choice of what is handed over to the second stream together.
+static double weight_gradient_us(int dt, const ConvGeom& q, int shards) {
+    const double esz = dt == EDL_DTYPE_BF16 ? 2.0 : 4.0, weights = (double)q.K * q.R * q.S * q.C, rows = (double)q.N * q.Ho * q.Wo;
+    const double bytes = 4.0 * shards * weights + esz * (rows * q.K + (double)q.N * q.H * q.W * q.C);
+    return 4.0 + std::max(2.0 * weights * rows / (dt == EDL_DTYPE_BF16 ? 250e6 : 25e6), bytes / 4e6);
+}
+
 // early_p > 0: this is the last backward pass of a step of early_p shards, so gradients that are final may be
 // applied while the pass goes on.
 // held (debugging hook only): tensors whose gradient buffers already hold a contribution the pass adds to.
@@ -1000,6 +1010,35 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
     RowCut fused_sums;
     const SumsBuf sums_buf = {partial, (size_t)h->L.partial_floats};
     size_t premasked_for = (size_t)-1;   // the layer whose gradient the max pool after it left masked by its ReLU
+    auto weight_gradient = [&](size_t ii, hipStream_t ws, float* scratch) {
+        const Op& op = g.ops[ii];
+        const ConvGeom q = geom_padded(g, op, n, h->L.cpad);
+        if (h->L.wpad[ii] >= 0) {
+            // the shards' gradients of the padded weights side by side, then compacted into the flat vectors
+            const int64_t rows = (int64_t)op.K * op.R * op.S;
+            ShardSet slots = S;
+            for (int k = 0; k < S.p; ++k) slots.k[k] = k;
+            launch_conv_wgrad(dt, q, slots, h->act(op.x), h->grad(op.y), GradDst{h->sc<float>(h->L.dwpad), rows * h->L.cpad},
+                              scratch, (size_t)h->L.wgrad_scratch_bytes, ws);
+            launch_unpad_rows(h->sc<float>(h->L.dwpad), grads_at(op.w_off), S, rows, g.tensors[0].C, h->L.cpad, ws);
+        } else {
+            launch_conv_wgrad(dt, q, S, h->act(op.x), h->grad(op.y), grads_at(op.w_off), scratch, (size_t)h->L.wgrad_scratch_bytes, ws);
+        }
+    };
+    // weight gradients that wait to be handed over to the second stream
+    std::vector<size_t>& waiting = h->wgrad_waiting;
+    waiting.clear();
+    double waiting_us = 0;
+    auto hand_over = [&]() {
+        hipEvent_t ev = h->ev_ready[h->ev_slot];
+        h->ev_slot = (h->ev_slot + 1) % kReadyEvents;
+        const bool ok = hipEventRecord(ev, st) == hipSuccess && hipStreamWaitEvent(h->side, ev, 0) == hipSuccess;
+        for (size_t j : waiting) weight_gradient(j, ok ? h->side : st, h->sc<float>(ok ? h->L.wgrad_scratch : h->L.wgrad_scratch2));
+        used_side = used_side || ok;
+        waiting.clear();
+        waiting_us = 0;
+        return ok;
+    };
     for (size_t ii = op_hi; ii-- > op_lo;) {
         const Op& op = g.ops[ii];
         if (done[ii]) continue;
@@ -1014,39 +1053,31 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 break;
             case OP_CONV: {
                 const ConvGeom q = geom_padded(g, op, n, h->L.cpad);
-                const bool padded = h->L.wpad[ii] >= 0;
                 launch_bias_relu_backward(dt, h->act(op.y), h->grad(op.y), op.bias ? grads_at(op.b_off) : no_grads, S, q.Ho * q.Wo, op.K,
                                           op.relu && premasked_for != ii, partial, fused_for == ii ? fused_sums : RowCut(), st);
                 // The weight gradient needs only dy (final from here on) and the layer's input, and nothing
                 // before the update reads it: it runs on the second stream, beside the chain of input
-                // gradients, whose short kernels leave part of the chip idle.
-                hipStream_t ws = st;
+                // gradients, whose short kernels leave part of the chip idle.  Handing work over costs an event (1 us on
+                // this chain, some 18 us of host time), so small layers' gradients are handed over together.
                 // The first layers' weight gradients are the last of the pass: by then the main stream has nothing
                 // else to do, so they stay on it (with a scratch of their own) and run beside the second stream's backlog.
-                const int tail_main = (int)tune().wgrad_tail_main;
                 int conv_ordinal = 0;
                 for (size_t j = 0; j < ii; ++j) conv_ordinal += g.ops[j].kind == OP_CONV;
-                const bool on_main = overlap && conv_ordinal < tail_main;
-                float* const wscratch = h->sc<float>(on_main ? h->L.wgrad_scratch2 : h->L.wgrad_scratch);
-                if (overlap && !on_main) {
-                    hipEvent_t ev = h->ev_ready[h->ev_slot];
-                    h->ev_slot = (h->ev_slot + 1) % kReadyEvents;
-                    if (hipEventRecord(ev, st) == hipSuccess && hipStreamWaitEvent(h->side, ev, 0) == hipSuccess) {
-                        ws = h->side;
-                        used_side = true;
-                    }
-                }
-                if (padded) {
-                    // the shards' gradients of the padded weights side by side, then compacted into the flat vectors
-                    const int64_t rows = (int64_t)op.K * op.R * op.S;
-                    ShardSet slots = S;
-                    for (int k = 0; k < S.p; ++k) slots.k[k] = k;
-                    launch_conv_wgrad(dt, q, slots, h->act(op.x), h->grad(op.y), GradDst{h->sc<float>(h->L.dwpad), rows * h->L.cpad},
-                                      wscratch, (size_t)h->L.wgrad_scratch_bytes, ws);
-                    launch_unpad_rows(h->sc<float>(h->L.dwpad), grads_at(op.w_off), S, rows, g.tensors[0].C, h->L.cpad, ws);
+                const bool on_main = !overlap || conv_ordinal < (int)tune().wgrad_tail_main;
+                const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
+                const bool early = early_p > 0 && overlap && !on_main && h->upd != nullptr && tune().early_update > 0 && own >= tune().early_update;
+                bool handed_over = false;
+                if (on_main) {
+                    weight_gradient(ii, st, h->sc<float>(overlap ? h->L.wgrad_scratch2 : h->L.wgrad_scratch));
                 } else {
-                    launch_conv_wgrad(dt, q, S, h->act(op.x), h->grad(op.y), grads_at(op.w_off), wscratch,
-                                      (size_t)h->L.wgrad_scratch_bytes, ws);
+                    waiting.push_back(ii);
+                    // From 15 us of work on, and a layer of 10 us at once.  us per step, each layer by itself / 10 / 15 / 25:
+                    // MLP 4 x 16 137 / 77 / 77 / 78, ResNet-20 1 x 8 1,200 / 1,080 / 990 / 1,040, ResNet-50 of 112x112 1 x 8
+                    // 2,600 / 2,450 / 2,320 / 2,300, VGG-16 of 64x64 1 x 4 705 / 650 / 654 / 664, 2 x 8 932 / 933 / 965 / 946
+                    // (its layers take 10 to 14 us each); larger jobs are the same within 1%.
+                    const double us = weight_gradient_us(dt, q, S.p), batch = (double)tune().wgrad_batch_us;
+                    waiting_us += us;
+                    if (early || waiting_us >= batch || us >= batch * 2 / 3) handed_over = hand_over();
                 }
                 // Parameters are laid out in layer order, so everything from this layer's weights on now has its
                 // final gradient: the second stream holds the weight gradients, and the event it waited for
@@ -1066,11 +1097,9 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                     return hipEventRecord(ev, st) == hipSuccess && hipStreamWaitEvent(h->upd, ev, 0) == hipSuccess;
                 };
                 auto update_early = [&]() {
-                    const int64_t chunk_min = tune().early_update;
-                    if (early_p > 0 && ws == h->side && ws != st && h->upd != nullptr && chunk_min > 0) {
+                    if (early && handed_over) {
                         const int64_t lo = (op.w_off + 63) / 64 * 64;
-                        const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
-                        if (lo > 0 && lo < h->applied_from && own >= chunk_min) {
+                        if (lo > 0 && lo < h->applied_from) {
                             hipEvent_t ev = h->ev_chunk[h->chunk_slot];
                             h->chunk_slot = (h->chunk_slot + 1) % kChunkEvents;
                             if (hipEventRecord(ev, h->side) == hipSuccess && hipStreamWaitEvent(h->upd, ev, 0) == hipSuccess &&
@@ -1242,6 +1271,9 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
             }
         }
     }
+    // too little to hand over: behind the chain (a pass whose weight gradients are all small takes no event at all)
+    for (size_t j : waiting) weight_gradient(j, st, h->sc<float>(h->L.wgrad_scratch2));
+    waiting.clear();
     // the next forward pass overwrites the activations the weight gradients read, and the update reads G
     if (used_side) {
         (void)hipEventRecord(h->ev_side_done, h->side);

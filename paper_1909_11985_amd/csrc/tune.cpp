@@ -38,6 +38,7 @@ const Entry kEntries[] = {
     {"wgrad_long_ks", &Tune::wgrad_long_ks},
     {"wgrad_deep_max", &Tune::wgrad_deep_max},
     {"wgrad_stream", &Tune::wgrad_stream},
+    {"wgrad_batch_us", &Tune::wgrad_batch_us},
     {"wgrad_tail_main", &Tune::wgrad_tail_main},
     {"early_update", &Tune::early_update},
     {"early_blocks", &Tune::early_blocks},

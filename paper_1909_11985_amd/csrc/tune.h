@@ -33,6 +33,7 @@ struct Tune {
     int64_t wgrad_long_ks = 3072;     // least reduction elements per cut of a long reduction
     int64_t wgrad_deep_max = 256;     // weight gradients of at most this many workgroups keep one more tile in flight (0: none do)
     int64_t wgrad_stream = 1;         // weight gradients on a second stream (read when a job is created)
+    int64_t wgrad_batch_us = 15;      // about how many microseconds of weight gradients are handed over to that stream together
     int64_t wgrad_tail_main = 1;      // the first this-many convolutions keep their weight gradient on the main stream
     int64_t early_update = 16000000;  // layers of at least this many weights start their update during the backward pass (0: none)
     int64_t early_blocks = 256;       // workgroups of such a background update
