@@ -1133,6 +1133,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                             mask.act = h->act(op.x);
                             if (prod.kind == OP_BN) mask.sign = h->sign(op.x);
                             mask.sums = sums_buf;
+                            if (prod.kind == OP_CONV && prod.bias) mask.dbias = grads_at(prod.b_off);
                             if (prod.kind == OP_BN) {
                                 mask.xin = h->act(prod.x);
                                 mask.mean_rstd = h->at<float>(h->L.bn_save[ii - 1]);

@@ -47,6 +47,7 @@
 #include "kernels.h"
 #include "pointwise.h"
 #include "profiler.h"
+#include "thin.h"
 #include "tune.h"
 
 // 1: LDS fragment reads run one fragment group ahead of the MFMAs (tiles of more than one MFMA per group;
@@ -1366,7 +1367,7 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
                                                             int64_t M, int Nn, int splits, int relu, int out_fp32, int accumulate,
                                                             RowCut cut, float* __restrict__ stats,
                                                             const T* __restrict__ mask_act, const T* __restrict__ xin,
-                                                            const float* __restrict__ mean_rstd, const void* acc_src) {
+                                                            const float* __restrict__ mean_rstd, const void* acc_src, GradDst dbias) {
     if (acc_src == nullptr) acc_src = out;      // where the gradient that is added to is read (see ConvArgs)
     // a workgroup owns 64 columns of one block of rows: 16 lanes across (4 columns each), 16 rows at a time
     int r0, r1;
@@ -1468,7 +1469,11 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
             float t = 0.f;
             #pragma unroll
             for (int j = 0; j < 16; ++j) t += red[kind][j][c];
-            stats[(int64_t)(kind * Nn + cg) * gridDim.y + blockIdx.y] = t;
+            if (MASKED && dbias.g != nullptr) {     // a block is a shard: the sums are the producer's bias gradient
+                if (kind == 0) dbias.g[(int64_t)cut.k[shard] * dbias.stride + cg] = t;
+            } else {
+                stats[(int64_t)(kind * Nn + cg) * gridDim.y + blockIdx.y] = t;
+            }
         }
     }
 }
@@ -1859,18 +1864,19 @@ static RowCut launch_finish(const ConvArgs& a, const ShardSet& S, int rows_per_s
     if (rb > max_rb) rb = max_rb;
     if (rb > kRedRowBlocks) rb = kRedRowBlocks;
     if (rb < 1) rb = 1;
-    const RowCut cut = cut_rows(S, rows_per_sample, (int)((M + rb - 1) / rb));
+    RowCut cut = cut_rows(S, rows_per_sample, (int)((M + rb - 1) / rb));
     const int row_blocks = cut.blk0[cut.p];
+    cut.stored = mask != nullptr && mask->xin == nullptr && mask->dbias.g != nullptr && cut.block_per_shard();
     if (stats.buf != nullptr && stats.floats < (size_t)2 * a.Nn * row_blocks) stats.buf = nullptr;   // cannot happen: sized for it
     ProfScope ps("splitk_finish", 0.0, 4.0 * (double)a.M * a.Nn * splits + (a.out_fp32 ? 4.0 : (double)sizeof(T)) * (double)a.M * a.Nn, st);
     if (mask != nullptr && stats.buf != nullptr)
         hipLaunchKernelGGL((splitk_finish_kernel<T, true>), dim3(col_blocks, row_blocks), dim3(256), 0, st, a.partial, a.out, a.bias,
                            (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, cut, stats.buf,
-                           (const T*)mask->act, (const T*)mask->xin, mask->mean_rstd, a.acc_src);
+                           (const T*)mask->act, (const T*)mask->xin, mask->mean_rstd, a.acc_src, cut.stored ? mask->dbias : GradDst{nullptr, 0});
     else
         hipLaunchKernelGGL((splitk_finish_kernel<T, false>), dim3(col_blocks, row_blocks), dim3(256), 0, st, a.partial, a.out, a.bias,
                            (int64_t)a.M, a.Nn, splits, a.relu, a.out_fp32, a.accumulate, cut, mask != nullptr ? nullptr : stats.buf,
-                           (const T*)nullptr, (const T*)nullptr, (const float*)nullptr, a.acc_src);
+                           (const T*)nullptr, (const T*)nullptr, (const float*)nullptr, a.acc_src, GradDst{nullptr, 0});
     return stats.buf ? cut : RowCut();
 }
 
@@ -1897,6 +1903,10 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g, int samples) {
 
 RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
                        bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st) {
+    if (thin_takes(dtype, g)) {
+        launch_thin_fwd(dtype, g, x, w, bias, relu, out_fp32, y, st);
+        return RowCut();
+    }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
     a.A = x; a.B = w; a.out = y; a.bias = bias;
@@ -1954,6 +1964,9 @@ bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
                          float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows) {
     RowCut left;
+    if (thin_takes(dtype, g) && !w_rows)
+        return launch_thin_dgrad(dtype, g, S, dy, wT, accumulate ? (acc_src != nullptr ? acc_src : dx) : nullptr, dx,
+                                 tune().fused_mask != 0 && (!accumulate || tune().fused_mask_join != 0) ? mask : nullptr, st);
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
     a.A = dy; a.B = wT; a.out = dx;
@@ -2097,6 +2110,10 @@ static WgradPlan plan_wgrad(int dtype, const ConvGeom& g, int shards) {
     else if (dtype != 1 && M <= 32) p.t = T32x128;      // a 64-row tile would contract rows that are not there
     else if (M <= 64 || Nn <= 64) p.t = (Nn <= 64 && M >= 128) ? T128x64 : T64x64;
     else if (t128 >= 128) p.t = T128x128;
+    // Few rows that no cut makes enough workgroups of (fully connected layers): four times as many of a quarter of the size
+    // (MLP, four shards of 16, 784 -> 256: 56 workgroups 9.4 us, 208 5.5 us).  Not by the number of shards: a pass in parts
+    // would then be cut otherwise than the whole.
+    else if (t128 * std::max(1, Kred / 256) < 64) p.t = T64x64;
     else if (t64 >= 256 && Kred < 4096) p.t = T64x64;   // long reductions are cut instead (below)
     else p.t = T128x128;
     switch (p.t) {
@@ -2153,6 +2170,10 @@ size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
 
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st) {
+    if (thin_takes(dtype, g) && thin_takes_shard(S.plan_largest)) {
+        launch_thin_wgrad(dtype, g, S, x, dy, dw, st);
+        return;
+    }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvGeom one = g;
     one.N = S.plan_largest;

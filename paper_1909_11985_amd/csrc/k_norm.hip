@@ -99,7 +99,7 @@ __device__ __forceinline__ void store_row(T* base, int64_t r, int C, int c0, con
 template <typename T, int VEC, int KIND, bool LONG>
 __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x, const T* __restrict__ y, T* dy,
                                                         const float* __restrict__ mean_rstd, RowCut cut, int C,
-                                                        int relu, float* __restrict__ partial) {
+                                                        int relu, float* __restrict__ partial, GradDst dbias) {
     __shared__ float red[2][256 * VEC];
     int r0, r1;
     const int sh = locate_block(cut, blockIdx.y, r0, r1);
@@ -185,6 +185,12 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
         }
         #pragma unroll
         for (int e = 0; e < VEC; ++e) { a[e] = (float)sa[e]; b[e] = (float)sb[e]; }
+        if (KIND == 2 && dbias.g != nullptr) {      // a block is a shard: the sums need no finishing kernel
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e)
+                if (c0 + e < C) dbias.g[(int64_t)cut.k[sh] * dbias.stride + c0 + e] = a[e];
+            return;
+        }
         // partial[sum kind][channel][row block]: a channel's partial sums are contiguous for the finishing kernel
         #pragma unroll
         for (int e = 0; e < VEC; ++e) {
@@ -422,10 +428,10 @@ static bool long_blocks(const ShardSet& S, int hw, int C, int VEC, const RedShap
 }
 template <typename T, int VEC, int KIND>
 static void launch_colreduce(const RedShape& s, bool two_levels, const T* x, const T* y, T* dy, const float* mean_rstd, const RowCut& cut,
-                             int C, int relu, float* partial, hipStream_t st) {
+                             int C, int relu, float* partial, hipStream_t st, GradDst dbias = GradDst{nullptr, 0}) {
     const dim3 grid(s.col_blocks, cut.blk0[cut.p]);
-    if (two_levels) hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, true>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial);
-    else hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, false>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial);
+    if (two_levels) hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, true>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial, dbias);
+    else hipLaunchKernelGGL((colreduce_kernel<T, VEC, KIND, false>), grid, s.block, 0, st, x, y, dy, mean_rstd, cut, C, relu, partial, dbias);
 }
 
 template <typename T, int VEC>
@@ -539,9 +545,12 @@ static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const S
     if (cut.p == 0) {   // else dy is masked already and its column sums are in partial
         ProfScope ps("bias_relu_bwd", 0.0, tb * (relu ? 3.0 : 1.0), st);
         cut = cut_rows(S, hw, s.rows_per_block);
-        launch_colreduce<T, VEC, 2>(s, long_blocks(S, hw, C, VEC, s), (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st);
+        // Where a block is a whole shard (few rows: fully connected layers) its sums are the bias gradient: one launch less.
+        cut.stored = dbias.g != nullptr && cut.block_per_shard();
+        launch_colreduce<T, VEC, 2>(s, long_blocks(S, hw, C, VEC, s), (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st,
+                                    cut.stored ? dbias : GradDst{nullptr, 0});
     }
-    if (dbias.g) {
+    if (dbias.g && !cut.stored) {
         ProfScope ps("bias_finalize", 0.0, 4.0 * (double)cut.blk0[cut.p] * C, st);
         EDL_FINALIZE(bias_finalize_kernel, cut, C, dbias.g, dbias.stride);
     }

@@ -1,0 +1,180 @@
+// Fully connected layers with few outputs whose number is no multiple of a vector (a classifier of 10 classes): the three
+// contractions of such a layer.  What bounds them is latency: a few hundred thousand multiplications.  The tiled kernel took
+// its element-wise path for them (one workgroup of 64x64 outputs, a wait after every load): MLP of 64 samples 12.1 / 10.8 /
+// 5.7 us forward / input gradient / weight gradient, here 3.1 / 3.6 / 3.3; a chain of 20 launches of 3 to 8 us each.
+//
+//   forward           y[m][k]  = sum_c x[m][c] w[k][c] + b[k]       a wave per output, lanes along c
+//   input gradient    dx[m][c] = sum_k dy[m][k] wT[c][k]            a lane per column c and four rows
+//   weight gradient   dw[k][c] = sum_m dy[m][k] x[m][c]             a lane per column c and every 16th row of the shard
+//
+// All sums in float32, in chains no longer than the tiled kernel's.
+#include <algorithm>
+
+#include "dev_common.h"
+#include "kernels.h"
+#include "profiler.h"
+#include "thin.h"
+
+namespace edl {
+
+constexpr int kThinOutputs = 128;      // more than that fills tiles
+constexpr int kThinShard = 1024;       // rows of a shard: a chain of 64 in the weight gradient
+constexpr int kThinRows = 16;          // rows of a workgroup of the input gradient
+
+template <typename T, int VEC>
+__global__ __launch_bounds__(256) void thin_fwd_kernel(const T* __restrict__ x, const T* __restrict__ w, const float* __restrict__ bias,
+                                                       void* __restrict__ y, int M, int K, int C, int relu, int out_fp32) {
+    const int lane = threadIdx.x & 63, o = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (o >= M * K) return;
+    const int m = o / K, k = o - m * K;
+    const T* const xr = x + (size_t)m * C;
+    const T* const wr = w + (size_t)k * C;
+    float s = 0.f;
+    for (int c = lane * VEC; c < C; c += 64 * VEC) {
+        if (VEC > 1) {
+            const Vec16<T> a = load_vec(xr + c), b = load_vec(wr + c);
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) s += Elem<T>::to_f32(a.e[e]) * Elem<T>::to_f32(b.e[e]);
+        } else {
+            s += Elem<T>::to_f32(xr[c]) * Elem<T>::to_f32(wr[c]);
+        }
+    }
+    for (int d = 32; d > 0; d >>= 1) s += __shfl_xor(s, d, 64);
+    if (lane != 0) return;
+    if (bias != nullptr) s += bias[k];
+    if (relu) s = fmaxf(s, 0.f);
+    if (out_fp32) ((float*)y)[o] = s;
+    else ((T*)y)[o] = Elem<T>::from_f32(s);
+}
+
+// grid: (64 columns, blocks of rows within a shard).  Masked and summed as a bias layer with ReLU wants it (DgradMask with no
+// xin); with one block per shard the sums are that layer's bias gradients.
+template <typename T>
+__global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ dy, const T* __restrict__ wT, const T* old, T* dx,
+                                                         const T* __restrict__ mask_act, float* __restrict__ sums, GradDst dbias,
+                                                         RowCut cut, int K, int C) {
+    __shared__ float red[4][64];
+    int r0, r1;
+    const int shard = locate_block(cut, blockIdx.y, r0, r1);
+    const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane;
+    const bool active = c < C;
+    constexpr int R = kThinRows / 4, KC = 16;
+    float acc[R];
+    #pragma unroll
+    for (int i = 0; i < R; ++i) acc[i] = 0.f;
+    for (int k0 = 0; k0 < K; k0 += KC) {
+        float wk[KC];
+        #pragma unroll
+        for (int e = 0; e < KC; ++e) wk[e] = active && k0 + e < K ? Elem<T>::to_f32(wT[(size_t)c * K + k0 + e]) : 0.f;
+        #pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int r = min(r0 + sub + 4 * i, r1 - 1);     // (a row past the end is computed and not used)
+            #pragma unroll
+            for (int e = 0; e < KC; ++e) acc[i] += Elem<T>::to_f32(dy[(size_t)r * K + min(k0 + e, K - 1)]) * wk[e];
+        }
+    }
+    float s = 0.f;
+    #pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int r = r0 + sub + 4 * i;
+        if (r >= r1 || !active) continue;
+        const size_t at = (size_t)r * C + c;
+        float v = acc[i];
+        if (old != nullptr) v += Elem<T>::to_f32(old[at]);
+        if (mask_act != nullptr && !(Elem<T>::to_f32(mask_act[at]) > 0.f)) v = 0.f;
+        const T o = Elem<T>::from_f32(v);
+        dx[at] = o;
+        s += Elem<T>::to_f32(o);
+    }
+    if (sums == nullptr) return;
+    red[sub][lane] = s;
+    __syncthreads();
+    if (sub != 0 || !active) return;
+    s = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+    if (dbias.g != nullptr) dbias.g[(int64_t)cut.k[shard] * dbias.stride + c] = s;
+    else {
+        sums[(size_t)c * gridDim.y + blockIdx.y] = s;
+        sums[(size_t)(C + c) * gridDim.y + blockIdx.y] = 0.f;
+    }
+}
+
+// grid: (64 columns, outputs / 8, shards); a wave takes every 16th row of the shard (with every fourth, a shard of 512 rows
+// was 128 dependent trips, 20 us)
+template <typename T>
+__global__ __launch_bounds__(1024) void thin_wgrad_kernel(const T* __restrict__ dy, const T* __restrict__ x, GradDst dw, ShardSet S, int K, int C) {
+    constexpr int KC = 8, NW = 16;
+    __shared__ float red[NW][KC][64];
+    const int lane = threadIdx.x & 63, sub = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane, k0 = blockIdx.y * KC, sh = blockIdx.z;
+    const int r0 = S.off[sh], r1 = S.off[sh + 1];
+    const bool active = c < C;
+    float acc[KC];
+    #pragma unroll
+    for (int e = 0; e < KC; ++e) acc[e] = 0.f;
+    #pragma unroll 4
+    for (int r = r0 + sub; r < r1; r += NW) {
+        const float xv = active ? Elem<T>::to_f32(x[(size_t)r * C + c]) : 0.f;
+        #pragma unroll
+        for (int e = 0; e < KC; ++e) acc[e] += Elem<T>::to_f32(dy[(size_t)r * K + min(k0 + e, K - 1)]) * xv;
+    }
+    #pragma unroll
+    for (int e = 0; e < KC; ++e) red[sub][e][lane] = acc[e];
+    __syncthreads();
+    if (sub >= KC || !active || k0 + sub >= K) return;
+    float s = 0.f;
+    #pragma unroll
+    for (int q = 0; q < NW; ++q) s += red[q][sub][lane];
+    dw.g[(int64_t)S.k[sh] * dw.stride + (size_t)(k0 + sub) * C + c] = s;
+}
+
+bool thin_takes(int dtype, const ConvGeom& g) {
+    return g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.K % (dtype == 1 ? 8 : 4) != 0 && g.K <= kThinOutputs &&
+           (int64_t)g.N * std::max(g.K, g.C) < (1ll << 31);
+}
+bool thin_takes_shard(int largest) { return largest <= kThinShard; }
+
+template <typename T>
+static void fwd(const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu, bool out_fp32, void* y, hipStream_t st) {
+    const dim3 grid((g.N * g.K + 3) / 4);
+    if (g.C % Elem<T>::VEC == 0 && (((uintptr_t)x | (uintptr_t)w) & 15) == 0)     // (parameters lie at any element)
+        hipLaunchKernelGGL((thin_fwd_kernel<T, Elem<T>::VEC>), grid, dim3(256), 0, st, (const T*)x, (const T*)w, bias, y, g.N, g.K, g.C, relu, out_fp32);
+    else
+        hipLaunchKernelGGL((thin_fwd_kernel<T, 1>), grid, dim3(256), 0, st, (const T*)x, (const T*)w, bias, y, g.N, g.K, g.C, relu, out_fp32);
+}
+
+void launch_thin_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu, bool out_fp32, void* y, hipStream_t st) {
+    ProfScope ps(prof_shape_label("thin_fwd", g.N, g.C), 2.0 * g.N * g.K * g.C, (dtype == 1 ? 2.0 : 4.0) * ((double)(g.N + g.K) * g.C + (double)g.N * g.K), st);
+    if (dtype == 1) fwd<bf16_t>(g, x, w, bias, relu, out_fp32, y, st);
+    else fwd<float>(g, x, w, bias, relu, out_fp32, y, st);
+}
+
+RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, const void* old, void* dx,
+                         const DgradMask* mask, hipStream_t st) {
+    RowCut cut = cut_rows(S, 1, kThinRows);
+    const int blocks = cut.blk0[cut.p];
+    const bool fuse = mask != nullptr && mask->act != nullptr && mask->xin == nullptr && mask->sums.buf != nullptr &&
+                      mask->sums.floats >= (size_t)2 * g.C * blocks;
+    cut.stored = fuse && mask->dbias.g != nullptr && cut.block_per_shard();
+    const void* const act = fuse ? mask->act : nullptr;
+    float* const sums = fuse ? mask->sums.buf : nullptr;
+    const GradDst dbias = cut.stored ? mask->dbias : GradDst{nullptr, 0};
+    ProfScope ps(prof_shape_label("thin_dgrad", g.N, g.C), 2.0 * g.N * g.K * g.C, (dtype == 1 ? 2.0 : 4.0) * ((double)(g.N + g.K) * g.C + (double)g.N * g.K), st);
+    const dim3 grid((g.C + 63) / 64, blocks);
+    if (dtype == 1)
+        hipLaunchKernelGGL(thin_dgrad_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)dy, (const bf16_t*)wT, (const bf16_t*)old, (bf16_t*)dx,
+                           (const bf16_t*)act, sums, dbias, cut, g.K, g.C);
+    else
+        hipLaunchKernelGGL(thin_dgrad_kernel<float>, grid, dim3(256), 0, st, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx,
+                           (const float*)act, sums, dbias, cut, g.K, g.C);
+    return fuse ? cut : RowCut();
+}
+
+void launch_thin_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, hipStream_t st) {
+    ProfScope ps(prof_shape_label("thin_wgrad", g.N, g.C), 2.0 * g.N * g.K * g.C, (dtype == 1 ? 2.0 : 4.0) * ((double)g.N * (g.C + g.K)) + 4.0 * S.p * g.K * g.C, st);
+    const dim3 grid((g.C + 63) / 64, (g.K + 7) / 8, S.p);
+    if (dtype == 1) hipLaunchKernelGGL(thin_wgrad_kernel<bf16_t>, grid, dim3(1024), 0, st, (const bf16_t*)dy, (const bf16_t*)x, dw, S, g.K, g.C);
+    else hipLaunchKernelGGL(thin_wgrad_kernel<float>, grid, dim3(1024), 0, st, (const float*)dy, (const float*)x, dw, S, g.K, g.C);
+}
+
+}  // namespace edl

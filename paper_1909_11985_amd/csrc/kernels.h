@@ -41,6 +41,8 @@ struct RowCut {
     int blk0[kMaxP + 1] = {};     // first block of each shard, blk0[p] = blocks in all
     int k[kMaxP] = {};            // the shard's worker
     int most = 0;                 // blocks of the largest shard of the plan
+    bool stored = false;          // column sums: each shard is one block, and its sums are already where they go (DgradMask::dbias)
+    bool block_per_shard() const { return p > 0 && blk0[p] == p; }
 };
 inline RowCut cut_rows(const ShardSet& S, int rows_per_sample, int rows_per_block) {
     RowCut c;
@@ -135,6 +137,8 @@ struct DgradMask {
     const void* xin;          // the producing batch norm's input, or null
     const float* mean_rstd;   // with xin: mean[C], rstd[C] of each shard
     SumsBuf sums;
+    GradDst dbias;            // without xin: the workers' bias gradients, which are these sums; a launch whose row blocks are whole
+                              // shards may store them there itself (RowCut::stored).  g may be null
 };
 // dx (+)= conv^T(dy, wT); wT is the [C][R][S][K] copy.  mask (may be null): if the launch can (stride 1, one
 // launch over all pixels, writing), dx is stored already masked and the sums are left in mask->sums; returns

@@ -1100,6 +1100,23 @@ def test_strided_and_padded_geometries_layerwise():
         _assert_layerwise(layerwise_parity("resnet50", dtype, 3, verbose=False, **geom), dtype)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes,arch,n", [
+    (10, (64, 256), 40), (3, (30, 70), 5), (17, (65, 9), 1), (127, (64, 64), 130), (129, (64, 64), 33), (6, (128, 1024), 1030),
+])
+def test_fully_connected_layers_with_few_ragged_outputs(classes, arch, n, dtype):
+    """Output counts that are no multiple of a vector, up to and beyond those the small-layer kernels take, rows and columns
+    that end inside a workgroup, a shard of more rows than their weight gradient takes."""
+    _assert_layerwise(layerwise_parity("mlp", dtype, n, verbose=False, H=1, W=1, C=24, classes=classes, arch=arch), dtype)
+    _assert_layerwise(relu_producer_pair_parity("mlp", dtype, n, H=1, W=1, C=24, classes=classes, arch=arch), dtype)
+
+
+@pytest.mark.parametrize("cut", [[16, 16, 16, 16], [16, 3, 1, 40], [17, 15]])
+def test_small_shards_leave_their_bias_gradients(cut):
+    """Shards of one row block (their sums are stored as bias gradients where they are formed) and of several, together."""
+    test_shards_of_one_pass_are_computed_as_each_alone("mlp", "f32", dict(H=1, W=1, C=48, classes=10, arch=(64, 256)), cut)
+
+
 @pytest.mark.parametrize("model,dtype,kw,cut", [
     ("mlp", "f32", TINY["mlp"], [5, 0, 7, 1, 11]),                      # scalar loads, empty and one-sample shards
     ("mlp", "f32", dict(H=1, W=1, C=64, classes=8, arch=(64, 32)), [64, 1, 63, 16]),
