@@ -425,6 +425,10 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     static_assert(!DIRECT_WG || (BK * RVA % 256 == 0 && BK * RVB % 256 == 0), "whole waves of slots");
     constexpr bool DMA = DIRECT || DIRECT_WG;
     constexpr int NST = DMA ? PF + 1 : 2;            // LDS stages
+    // Weight gradients with three stages (few workgroups, one per CU) issue a tile's loads between their MFMAs instead of all
+    // at once before them: nobody else's MFMAs hide the address arithmetic there (128x128, ResNet-50 at a shard of 32: 27.1
+    // -> 24.3 us).  Two stages lose 8 to 13% that way (the loads have one step to land), 128x64 tiles 6%.
+    constexpr bool SPREAD = DIRECT_WG && NST >= 3 && TM == TN;
     constexpr int LDK = DIRECT ? BK : BK + VEC;
     static_assert(!STRIP || (DIRECT && RB == 64 && TAPS == 3), "strips are loaded straight into LDS");
     static_assert(!BROWS || (DIRECT && !STRIP && MODE == CONV_DGRAD && sizeof(T) == 2), "rows of weights are loaded straight into LDS");
@@ -635,22 +639,29 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         kcur = kbeg;
     }
 
-    auto load_tiles = [&](int set) {
+    // Part `part` of `parts` of a tile's loads (the direct kernels); the last one advances to the next tile.
+    auto load_part = [&](int set, int part, int parts) {
+        constexpr int NA = STRIP || DIRECT ? ITER_A : DA, NB = STRIP || DIRECT ? ITER_B : DB;
+        const auto mine = [&](int item) { return item * parts / (NA + NB) == part; };
+        const bool last = part == parts - 1;
         if (STRIP) {
             const int inner = MODE == CONV_FWD ? a.C : a.K;
             const unsigned addA = (unsigned)((MODE == CONV_FWD ? strip_r : -strip_r) * a.W * inner + strip_c) * (unsigned)sizeof(T);
             const unsigned addB = (unsigned)(strip_r * TAPS * inner + strip_c) * (unsigned)sizeof(T);
             #pragma unroll
             for (int it = 0; it < ITER_A; ++it) {
+                if (!mine(it)) continue;
                 const unsigned off = (strip_a[it] + addA) | (((strip_in[it] >> strip_r) & 1) ? 0u : kOutOfRange);
                 if ((it + 1) * 64 <= STRIP_ROWS || __builtin_amdgcn_readfirstlane(wave) < (STRIP_ROWS - it * 64) / 16)
                     buffer_load16_to_lds(wordsA, ldsA_wave + set * A_STAGE + it * 4096, off);
             }
             #pragma unroll
             for (int it = 0; it < ITER_B; ++it) {
+                if (!mine(NA + it)) continue;
                 if ((it + 1) * 64 <= TAPS * BN || __builtin_amdgcn_readfirstlane(wave) < (TAPS * BN - it * 64) / 16)
                     buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096, strip_b[it] + addB);
             }
+            if (!last) return;
             strip_c += BK;
             const bool next = strip_c == inner;
             strip_c = next ? 0 : strip_c;
@@ -659,11 +670,14 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
             // `set` is the LDS stage
             const bool in_k = kcur < kend;
             #pragma unroll
-            for (int it = 0; it < ITER_A; ++it)
+            for (int it = 0; it < ITER_A; ++it) {
+                if (!mine(it)) continue;
                 buffer_load16_to_lds(wordsA, ldsA_wave + set * A_STAGE + it * 4096,
                                      a_voffset<MODE, T>(a, rowA[it], tr, ts, tc, tap_off, in_k));
+            }
             #pragma unroll
             for (int it = 0; it < ITER_B; ++it) {
+                if (!mine(NA + it)) continue;
                 if (BROWS) {
                     const int row = brow + it * (256 / RVB);
                     const unsigned off = ((unsigned)row * (unsigned)a.C + (unsigned)offB[0]) * (unsigned)sizeof(T);
@@ -674,6 +688,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 buffer_load16_to_lds(wordsB, ldsB_wave + set * B_STAGE + it * 4096,
                                      (okB[it] && in_k) ? (unsigned)((int)offB[it] + boff) * (unsigned)sizeof(T) : kOutOfRange);
             }
+            if (!last) return;
             brow += BK;
             const int inner = MODE == CONV_FWD ? a.C : a.K;
             kcur += BK;
@@ -693,6 +708,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
             // `set` is the LDS stage; pixel rows past the end of the reduction come in as zeros
             #pragma unroll
             for (int it = 0; it < DA; ++it) {
+                if (!mine(it)) continue;
                 const bool ok = rowA_ok & (kcur + (tid + it * 256) / RVA < kend);
                 buffer_load16_to_lds(wordsA, ldsA_wave + set * A_STAGE + it * 4096,
                                      ((unsigned)(int)offA[it] * (unsigned)sizeof(T)) | (ok ? 0u : kOutOfRange));
@@ -700,6 +716,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
             }
             #pragma unroll
             for (int it = 0; it < DB; ++it) {
+                if (!mine(NA + it)) continue;
                 const int h = pho[it] * a.stride - a.pad + wg_r, w = pwo[it] * a.stride - a.pad + wg_s;
                 const bool ok = wg_j_ok & (kcur + (tid + it * 256) / RVB < kend) & ((unsigned)h < (unsigned)a.H) &
                                 ((unsigned)w < (unsigned)a.W);
@@ -715,7 +732,12 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                 qn += chh ? 1 : 0;
                 pwo[it] = qw; pho[it] = qh; pn[it] = qn;
             }
-            kcur += BK;
+            if (last) kcur += BK;
+        }
+    };
+    auto load_tiles = [&](int set) {
+        if (DMA) {
+            load_part(set, 0, 1);
         } else if (!WG) {
             const bool in_k = kcur < kend;
             #pragma unroll
@@ -956,7 +978,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
     // range, so they touch no memory and return zeros, and the number of loads in
     // flight at every wait is then a compile-time constant.
     // contraction of the tile in LDS stage `buf`
-    auto contract = [&](int buf) {
+    auto contract = [&](int buf, auto&& between) {
         constexpr int NG = WG ? 4 : TAPS * BK / (2 * VEC);   // fragment groups per tile
         auto read_frags = [&](int g, uint4 (&fa)[TM], uint4 (&fb)[TN]) {
             if (STRIP) {
@@ -1015,6 +1037,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
         for (int g = 0; g < NG; ++g) {
             if (g + 1 < NG) read_frags(g + 1, fa[(g + 1) & 1], fb[(g + 1) & 1]);
             if (FRAG_AHEAD) __builtin_amdgcn_sched_barrier(0);
+            between(g, NG);
             #pragma unroll
             for (int i = 0; i < TM; ++i)
                 #pragma unroll
@@ -1040,8 +1063,8 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                     if (kt + u >= nk) break;
                     wait_vmcnt<(NST - 2) * PER_TILE>();
                     __syncthreads();
-                    load_tiles((u + NST - 1) % NST);
-                    contract(u);
+                    if (!SPREAD) load_tiles((u + NST - 1) % NST);
+                    contract(u, [&](int g, int groups) { if (SPREAD) load_part((u + NST - 1) % NST, g, groups); });
                 }
             }
             if (!FOLDS || kt >= nk) break;
@@ -1063,7 +1086,7 @@ __global__ __launch_bounds__(256, 2) void conv_igemm_kernel(typename ArgsOf<KIND
                     if (k >= nk) break;
                     const int buf = PF == 1 ? (k & 1) : (u & 1);
                     load_tiles(u);
-                    contract(buf);
+                    contract(buf, [](int, int) {});
                     store_tiles((u + 1) % PF, buf ^ 1);
                     __syncthreads();
                 }
