@@ -40,6 +40,19 @@ def test_shard_assignment_is_bit_exact(E, seed, N, B):
                 assert idx.dtype == np.int64 and np.array_equal(idx, io) and np.array_equal(off, oo)
 
 
+@pytest.mark.parametrize("N,B", [(4096, 1), (65536, 16), (100000, 250), (262144, 512), (1 << 20, 64)])
+def test_shard_assignment_by_followed_entries(E, N, B):
+    """Mini-batches that are a small part of a large data set are not walked to but followed back: every part of the epoch,
+    its first and last mini-batch, against the whole permutation."""
+    steps = N // B
+    for epoch in (0, 3):
+        perm, _ = E.edl_shard_host(11, N, N, 1, epoch, 0)
+        assert np.array_equal(np.sort(perm), np.arange(N))
+        for t in sorted({0, 1, steps // 7, steps // 2, steps - steps // 50 - 1, steps - 2, steps - 1}):
+            idx, _ = E.edl_shard_host(11, N, B, 1, epoch, t)
+            assert np.array_equal(idx, perm[t * B:(t + 1) * B]), (epoch, t)
+
+
 def test_shard_errors(E):
     for args, code in [((0, 64, 8, 3, 0, 0), -2), ((0, 60, 8, 2, 0, 0), -2), ((0, 64, 8, 2, 0, 8), -4),
                        ((0, 64, 8, 0, 0, 0), -1), ((0, 64, 8, 2, -1, 0), -1)]:
