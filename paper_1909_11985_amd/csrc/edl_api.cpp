@@ -289,7 +289,7 @@ void plan_arena(const edl_config& c, const Graph& g, Layout& L) {
         if (op.kind == OP_CONV) {
             const Tensor& tx = g.tensors[(size_t)op.x];
             // fully connected layers: none, the input gradient reads the bf16 weights themselves
-            const bool in_place = conv_dgrad_reads_weights(c.dtype, geom_of(g, op, 1), op.w_off);
+            const bool in_place = conv_dgrad_reads_weights(c.dtype, geom_of(g, op, L.pass_samples), op.w_off);
             if (storage_of(g, op.x) != 0 && !in_place) L.wT[i] = take((int64_t)op.K * op.R * op.S * tx.C * esz);
             else if (op.x == 0 && L.cpad != tx.C) L.wpad[i] = take((int64_t)op.K * op.R * op.S * L.cpad * esz);
         } else if (op.kind == OP_BN) {
@@ -960,8 +960,9 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
 
 static int apply_range(edl_handle* h, int32_t p, int64_t lo, int64_t hi, hipStream_t st, int max_blocks = 0);
 
-// What the input gradient of layer i reads: the transposed copy, or the bf16 weights where there is none.
+// What the input gradient of layer i reads: the transposed copy, or the weights (bf16: their copy) where there is none.
 static const void* dgrad_weights(const edl_handle* h, size_t i) {
+    if (h->L.wT[i] < 0 && h->cfg.dtype != EDL_DTYPE_BF16) return h->w() + h->g.ops[i].w_off;
     return h->L.wT[i] >= 0 ? (const void*)(h->arena + h->L.wT[i]) : (const void*)(h->arena + h->L.shadow + 2 * h->g.ops[i].w_off);
 }
 

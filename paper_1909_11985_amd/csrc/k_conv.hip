@@ -1930,6 +1930,10 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
         launch_thin_fwd(dtype, g, x, w, bias, relu, out_fp32, y, st);
         return RowCut();
     }
+    if (small_fc_takes(dtype, g, g.C, g.K, S.plan) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && tune().force_tile < 0) {
+        launch_small_fc_fwd(g, (const float*)x, (const float*)w, bias, relu, (float*)y, st);
+        return RowCut();
+    }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
     a.A = x; a.B = w; a.out = y; a.bias = bias;
@@ -1979,7 +1983,9 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
 // weight once, for few rows.  Convolutions read theirs for thousands of rows and keep the copy.  The vectors of B are
 // eight channels of one row, so rows are to start on 16 bytes.  Step of VGG-16, shard of 32: 4,946 -> 4,822 us; AlexNet,
 // two shards of 64: 1,613 -> 1,578 us.
+// Small layers (k_thin.hip) read them so in either type.
 bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
+    if (thin_takes(dtype, g) || small_fc_takes(dtype, g, g.K, g.C, g.N)) return true;
     return EDL_DIRECT_LDS != 0 && dtype == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.H == 1 && g.W == 1 &&
            g.K % 8 == 0 && g.C % 8 == 0 && w_off % 8 == 0;
 }
@@ -1987,9 +1993,12 @@ bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
                          float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows) {
     RowCut left;
-    if (thin_takes(dtype, g) && !w_rows)
-        return launch_thin_dgrad(dtype, g, S, dy, wT, accumulate ? (acc_src != nullptr ? acc_src : dx) : nullptr, dx,
-                                 tune().fused_mask != 0 && (!accumulate || tune().fused_mask_join != 0) ? mask : nullptr, st);
+    if (w_rows && (dtype != 1 || thin_takes(dtype, g))) {
+        const void* const old = accumulate ? (acc_src != nullptr ? acc_src : dx) : nullptr;
+        const DgradMask* const m = tune().fused_mask != 0 && (!accumulate || tune().fused_mask_join != 0) ? mask : nullptr;
+        if (thin_takes(dtype, g)) return launch_thin_dgrad(dtype, g, S, dy, wT, old, dx, m, st);
+        return launch_small_fc_dgrad(g, S, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx, m, st);
+    }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
     a.A = dy; a.B = wT; a.out = dx;

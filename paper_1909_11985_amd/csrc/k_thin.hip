@@ -1,13 +1,15 @@
-// Fully connected layers with few outputs whose number is no multiple of a vector (a classifier of 10 classes): the three
-// contractions of such a layer.  What bounds them is latency: a few hundred thousand multiplications.  The tiled kernel took
+// Small fully connected layers.  First, those with few outputs whose number is no multiple of a vector (a classifier of 10
+// classes): the three contractions of such a layer.  What bounds them is latency: a few hundred thousand multiplications.  The tiled kernel took
 // its element-wise path for them (one workgroup of 64x64 outputs, a wait after every load): MLP of 64 samples 12.1 / 10.8 /
 // 5.7 us forward / input gradient / weight gradient, here 3.1 / 3.6 / 3.3; a chain of 20 launches of 3 to 8 us each.
 //
 //   forward           y[m][k]  = sum_c x[m][c] w[k][c] + b[k]       a wave per output, lanes along c
-//   input gradient    dx[m][c] = sum_k dy[m][k] wT[c][k]            a lane per column c and four rows
+//   input gradient    dx[m][c] = sum_k dy[m][k] w[k][c]             a lane per column c and four rows
 //   weight gradient   dw[k][c] = sum_m dy[m][k] x[m][c]             a lane per column c and every 16th row of the shard
 //
 // All sums in float32, in chains no longer than the tiled kernel's.
+//
+// Second (small_fc_kernel), forward and input gradient of float32 layers that give the chip less than a workgroup per CU: below.
 #include <algorithm>
 
 #include "dev_common.h"
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(256) void thin_fwd_kernel(const T* __restrict__ x, 
 // grid: (64 columns, blocks of rows within a shard).  Masked and summed as a bias layer with ReLU wants it (DgradMask with no
 // xin); with one block per shard the sums are that layer's bias gradients.
 template <typename T>
-__global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ dy, const T* __restrict__ wT, const T* old, T* dx,
+__global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ dy, const T* __restrict__ w, const T* old, T* dx,
                                                          const T* __restrict__ mask_act, float* __restrict__ sums, GradDst dbias,
                                                          RowCut cut, int K, int C) {
     __shared__ float red[4][64];
@@ -66,7 +68,7 @@ __global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ d
     for (int k0 = 0; k0 < K; k0 += KC) {
         float wk[KC];
         #pragma unroll
-        for (int e = 0; e < KC; ++e) wk[e] = active && k0 + e < K ? Elem<T>::to_f32(wT[(size_t)c * K + k0 + e]) : 0.f;
+        for (int e = 0; e < KC; ++e) wk[e] = active && k0 + e < K ? Elem<T>::to_f32(w[(size_t)(k0 + e) * C + c]) : 0.f;
         #pragma unroll
         for (int i = 0; i < R; ++i) {
             const int r = min(r0 + sub + 4 * i, r1 - 1);     // (a row past the end is computed and not used)
@@ -149,7 +151,7 @@ void launch_thin_fwd(int dtype, const ConvGeom& g, const void* x, const void* w,
     else fwd<float>(g, x, w, bias, relu, out_fp32, y, st);
 }
 
-RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, const void* old, void* dx,
+RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* w, const void* old, void* dx,
                          const DgradMask* mask, hipStream_t st) {
     RowCut cut = cut_rows(S, 1, kThinRows);
     const int blocks = cut.blk0[cut.p];
@@ -162,10 +164,10 @@ RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
     ProfScope ps(prof_shape_label("thin_dgrad", g.N, g.C), 2.0 * g.N * g.K * g.C, (dtype == 1 ? 2.0 : 4.0) * ((double)(g.N + g.K) * g.C + (double)g.N * g.K), st);
     const dim3 grid((g.C + 63) / 64, blocks);
     if (dtype == 1)
-        hipLaunchKernelGGL(thin_dgrad_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)dy, (const bf16_t*)wT, (const bf16_t*)old, (bf16_t*)dx,
+        hipLaunchKernelGGL(thin_dgrad_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)dy, (const bf16_t*)w, (const bf16_t*)old, (bf16_t*)dx,
                            (const bf16_t*)act, sums, dbias, cut, g.K, g.C);
     else
-        hipLaunchKernelGGL(thin_dgrad_kernel<float>, grid, dim3(256), 0, st, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx,
+        hipLaunchKernelGGL(thin_dgrad_kernel<float>, grid, dim3(256), 0, st, (const float*)dy, (const float*)w, (const float*)old, (float*)dx,
                            (const float*)act, sums, dbias, cut, g.K, g.C);
     return fuse ? cut : RowCut();
 }
@@ -175,6 +177,129 @@ void launch_thin_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     const dim3 grid((g.C + 63) / 64, (g.K + 7) / 8, S.p);
     if (dtype == 1) hipLaunchKernelGGL(thin_wgrad_kernel<bf16_t>, grid, dim3(1024), 0, st, (const bf16_t*)dy, (const bf16_t*)x, dw, S, g.K, g.C);
     else hipLaunchKernelGGL(thin_wgrad_kernel<float>, grid, dim3(1024), 0, st, (const float*)dy, (const float*)x, dw, S, g.K, g.C);
+}
+
+// ---------------------------------------------------------------------------------------------------------------------
+// Float32 layers of few tiles (an MLP of 64 samples and 256 wide): latency again.  The tiled kernel cut their reduction over
+// workgroups to fill some of the chip, with a launch more to add the pieces (784 -> 256: 7.4 + 4.2 us).  Here a workgroup owns
+// 32x32 outputs, its sixteen waves a piece of the reduction each (with two sets of sums), which meet in LDS: no pieces
+// in memory, no second launch; operands go from global memory into registers, and the input gradient reads the weights as they
+// lie, so that these layers need no transposed copy either (3.8 us of the chain).  784 -> 256, 64 rows: 7 us in one launch.
+// ---------------------------------------------------------------------------------------------------------------------
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+constexpr int kSmallTiles = 256, kSmallReduction = 2048, kSmallWaves = 16;     // (chains of 64 products at most)
+
+struct SmallArgs {
+    const float *A, *B;          // [M][K]; forward [N][K], input gradient [K][N]
+    float* out;                  // [M][N]
+    const float *bias, *old, *act;
+    float* sums;                 // input gradient, with act: column sums per block (see launch_thin_dgrad)
+    GradDst dbias;
+    int K, N, relu;
+    RowCut cut;
+};
+
+template <bool DGRAD>
+__global__ __launch_bounds__(64 * kSmallWaves) void small_fc_kernel(SmallArgs a) {
+    __shared__ float red[kSmallWaves][32][33];
+    int r0, r1;
+    const int shard = locate_block(a.cut, blockIdx.y, r0, r1);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, half = lane >> 5;
+    const int row = min(r0 + (lane & 31), r1 - 1), col = blockIdx.x * 32 + (lane & 31), colc = min(col, a.N - 1);
+    const float* const Ar = a.A + (size_t)row * a.K;
+    const float* const Br = DGRAD ? a.B + colc : a.B + (size_t)colc * a.K;
+    floatx16 acc[2];
+    #pragma unroll
+    for (int q = 0; q < 16; ++q) acc[0][q] = acc[1][q] = 0.f;
+    const int steps = (a.K + 7) / 8;
+    // (reads past the end of the reduction take its last vector and count as zeros; rows and columns past theirs are not stored)
+    auto step = [&](int s, floatx16& c) {
+        const int k = s * 8 + half * 4, kc = min(k, a.K - 4);
+        float4 x = *reinterpret_cast<const float4*>(Ar + kc), w;
+        if (DGRAD) w = make_float4(Br[(size_t)kc * a.N], Br[(size_t)(kc + 1) * a.N], Br[(size_t)(kc + 2) * a.N], Br[(size_t)(kc + 3) * a.N]);
+        else w = *reinterpret_cast<const float4*>(Br + kc);
+        if (k >= a.K) { x = make_float4(0.f, 0.f, 0.f, 0.f); w = x; }
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.x, w.x, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.y, w.y, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.z, w.z, c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(x.w, w.w, c, 0, 0, 0);
+    };
+    // neighbouring steps share their cache lines; with four waves (and 32 KB in flight per workgroup) 784 -> 256 took 14 us
+    const int piece = (steps + kSmallWaves - 1) / kSmallWaves, end = min((wave + 1) * piece, steps);
+    #pragma unroll 4
+    for (int s = wave * piece; s < end; s += 2) {
+        step(s, acc[0]);
+        step(s + 1 < end ? s + 1 : steps, acc[1]);      // (step `steps` is all zeros)
+    }
+    #pragma unroll
+    for (int q = 0; q < 16; ++q) red[wave][(q >> 2) * 8 + half * 4 + (q & 3)][lane & 31] = acc[0][q] + acc[1][q];
+    __syncthreads();
+    const int rl = threadIdx.x >> 5, cl = threadIdx.x & 31, r = r0 + rl, c = blockIdx.x * 32 + cl;
+    const bool live = r < r1 && c < a.N;
+    float v = 0.f;
+    #pragma unroll
+    for (int w = 0; w < kSmallWaves; w += 4) v += (red[w][rl][cl] + red[w + 1][rl][cl]) + (red[w + 2][rl][cl] + red[w + 3][rl][cl]);
+    if (live) {
+        const size_t at = (size_t)r * a.N + c;
+        if (!DGRAD && a.bias != nullptr) v += a.bias[c];
+        if (!DGRAD && a.relu) v = fmaxf(v, 0.f);
+        if (DGRAD && a.old != nullptr) v += a.old[at];
+        if (DGRAD && a.act != nullptr && !(a.act[at] > 0.f)) v = 0.f;
+        a.out[at] = v;
+    }
+    if (!DGRAD || a.sums == nullptr) return;
+    __syncthreads();
+    red[0][rl][cl] = live ? v : 0.f;
+    __syncthreads();
+    if (threadIdx.x >= 32 || blockIdx.x * 32 + (int)threadIdx.x >= a.N) return;
+    float p[4] = {0.f, 0.f, 0.f, 0.f};
+    #pragma unroll
+    for (int i = 0; i < 32; ++i) p[i & 3] += red[0][i][threadIdx.x];
+    const float t = (p[0] + p[1]) + (p[2] + p[3]);
+    const int cg = blockIdx.x * 32 + threadIdx.x;
+    if (a.dbias.g != nullptr) a.dbias.g[(int64_t)a.cut.k[shard] * a.dbias.stride + cg] = t;
+    else {
+        a.sums[(size_t)cg * gridDim.y + blockIdx.y] = t;
+        a.sums[(size_t)(a.N + cg) * gridDim.y + blockIdx.y] = 0.f;
+    }
+}
+
+bool small_fc_takes(int dtype, const ConvGeom& g, int K, int N, int samples) {
+    return dtype != 1 && g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && K % 4 == 0 &&
+           K <= kSmallReduction && (int64_t)((samples + 31) / 32) * ((N + 31) / 32) <= kSmallTiles;
+}
+
+void launch_small_fc_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, bool relu, float* y, hipStream_t st) {
+    ShardSet all = {};
+    all.p = 1;
+    all.off[1] = g.N;
+    all.plan_itself();
+    SmallArgs a = {};
+    a.A = x; a.B = w; a.out = y; a.bias = bias; a.relu = relu;
+    a.K = g.C; a.N = g.K;
+    a.cut = cut_rows(all, 1, 32);
+    ProfScope ps(prof_shape_label("small_fc_fwd", g.N, g.K), 2.0 * g.N * g.K * g.C, 4.0 * ((double)g.N * (g.C + g.K) + (double)g.K * g.C), st);
+    hipLaunchKernelGGL(small_fc_kernel<false>, dim3((a.N + 31) / 32, a.cut.blk0[a.cut.p]), dim3(64 * kSmallWaves), 0, st, a);
+}
+
+RowCut launch_small_fc_dgrad(const ConvGeom& g, const ShardSet& S, const float* dy, const float* w, const float* old, float* dx,
+                             const DgradMask* mask, hipStream_t st) {
+    SmallArgs a = {};
+    a.A = dy; a.B = w; a.out = dx; a.old = old;
+    a.K = g.K; a.N = g.C;
+    a.cut = cut_rows(S, 1, 32);
+    const int blocks = a.cut.blk0[a.cut.p];
+    const bool fuse = mask != nullptr && mask->act != nullptr && mask->xin == nullptr && mask->sums.buf != nullptr &&
+                      mask->sums.floats >= (size_t)2 * g.C * blocks;
+    a.cut.stored = fuse && mask->dbias.g != nullptr && a.cut.block_per_shard();
+    if (fuse) {
+        a.act = (const float*)mask->act;
+        a.sums = mask->sums.buf;
+        if (a.cut.stored) a.dbias = mask->dbias;
+    }
+    ProfScope ps(prof_shape_label("small_fc_dgrad", g.N, g.C), 2.0 * g.N * g.K * g.C, 4.0 * ((double)g.N * (g.C + g.K) + (double)g.K * g.C), st);
+    hipLaunchKernelGGL(small_fc_kernel<true>, dim3((a.N + 31) / 32, blocks), dim3(64 * kSmallWaves), 0, st, a);
+    return fuse ? a.cut : RowCut();
 }
 
 }  // namespace edl

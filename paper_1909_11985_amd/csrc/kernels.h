@@ -145,11 +145,12 @@ struct DgradMask {
 // how they are cut (what the producer's backward takes), else p == 0 and dx is the plain gradient.
 // acc_src (stride 1 with accumulate only; may be null): the gradient that is added to is read from this tensor of
 // dx's shape instead of from dx itself (dx is then written, not read).
-// w_rows (only where conv_dgrad_reads_weights): wT is not a copy but the bf16 weights as they lie, [K][C].
+// w_rows (only where conv_dgrad_reads_weights): wT is not a copy but the weights (bf16: their copy) as they lie, [K][C].
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
                          float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st,
                          const void* acc_src = nullptr, bool w_rows = false);
-// whether the input gradient of a layer whose weights start at element w_off reads them where they lie
+// whether the input gradient of a layer whose weights start at element w_off reads them where they lie, in passes of up to
+// g.N samples
 bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off);
 // float32 scratch the forward / dgrad launches of passes of up to `samples` samples may use to cut a long reduction of a
 // small problem, where cuts are planned for passes of up to g.N

@@ -1,16 +1,24 @@
-// Fully connected layers with few, ragged outputs (k_thin.hip), behind launch_conv_fwd, launch_conv_dgrad and launch_conv_wgrad.
+// Small fully connected layers (k_thin.hip), behind launch_conv_fwd, launch_conv_dgrad and launch_conv_wgrad.  Input gradients
+// read the weights as they lie, [K][C] (conv_dgrad_reads_weights).
 #pragma once
 #include "kernels.h"
 
 namespace edl {
 
+// few, ragged outputs
 bool thin_takes(int dtype, const ConvGeom& g);
 // ... and, for the weight gradient, shards of this many samples at most
 bool thin_takes_shard(int largest);
 void launch_thin_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu, bool out_fp32, void* y, hipStream_t st);
 // old (may be null, may be dx): the gradient that is added to.  Returns how the sums of mask are cut, p == 0 if it left none.
-RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, const void* old, void* dx,
+RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* w, const void* old, void* dx,
                          const DgradMask* mask, hipStream_t st);
 void launch_thin_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, hipStream_t st);
+// float32, few tiles of 32x32 outputs: the forward or input-gradient contraction of K products for N outputs, over a pass
+// planned for `samples`
+bool small_fc_takes(int dtype, const ConvGeom& g, int K, int N, int samples);
+void launch_small_fc_fwd(const ConvGeom& g, const float* x, const float* w, const float* bias, bool relu, float* y, hipStream_t st);
+RowCut launch_small_fc_dgrad(const ConvGeom& g, const ShardSet& S, const float* dy, const float* w, const float* old, float* dx,
+                             const DgradMask* mask, hipStream_t st);
 
 }  // namespace edl

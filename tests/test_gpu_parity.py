@@ -1111,6 +1111,16 @@ def test_fully_connected_layers_with_few_ragged_outputs(classes, arch, n, dtype)
     _assert_layerwise(relu_producer_pair_parity("mlp", dtype, n, H=1, W=1, C=24, classes=classes, arch=arch), dtype)
 
 
+@pytest.mark.parametrize("C,arch,n", [
+    (784, (256, 256), 64), (8, (4, 36), 1), (1024, (32, 100), 33), (1028, (64, 1024), 40), (12, (2048, 2052), 128), (520, (512, 512), 513),
+])
+def test_small_float32_fully_connected_layers(C, arch, n):
+    """Layers of few 32x32 tiles, up to the number of tiles and the length of the reduction at which tiled launches take over:
+    ragged rows and columns, reductions that end inside a step and that give some of the four waves nothing."""
+    _assert_layerwise(layerwise_parity("mlp", "f32", n, verbose=False, H=1, W=1, C=C, classes=12, arch=arch), "f32")
+    _assert_layerwise(relu_producer_pair_parity("mlp", "f32", n, H=1, W=1, C=C, classes=12, arch=arch), "f32")
+
+
 @pytest.mark.parametrize("cut", [[16, 16, 16, 16], [16, 3, 1, 40], [17, 15]])
 def test_small_shards_leave_their_bias_gradients(cut):
     """Shards of one row block (their sums are stored as bias gradients where they are formed) and of several, together."""
