@@ -392,6 +392,8 @@ struct edl_handle {
     int device = -1;
     std::vector<char> written;           // backward pass: which gradient buffers hold something (per tensor)
     std::vector<size_t> wgrad_waiting;   // a backward pass: layers whose weight gradient is yet to be launched
+    std::vector<char> bias_waiting;      // ... of them, those whose bias gradient goes with it (2: from the pool after the layer)
+    bool has_bn = false;
     std::vector<char> op_done;           // a pass: layers already launched out of list order (on the branch stream)
     // backward pass, per tensor: where the gradient "already there" is to be read from if not from the tensor's
     // own gradient buffer (an identity shortcut's part is the masked gradient of the block's output itself)
@@ -689,6 +691,8 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
     h->written.assign(h->g.tensors.size(), 0);
     h->op_done.assign(h->g.ops.size(), 0);
     h->wgrad_waiting.reserve(h->g.ops.size());
+    h->bias_waiting.assign(h->g.ops.size(), 0);
+    for (const Op& op : h->g.ops) h->has_bn = h->has_bn || op.kind == OP_BN;
     h->grad_alias.assign(h->g.tensors.size(), nullptr);
     h->shard_n.reserve(kMaxP);
     h->perm.reserve((size_t)cfg->N);
@@ -1011,9 +1015,25 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
     RowCut fused_sums;
     const SumsBuf sums_buf = {partial, (size_t)h->L.partial_floats};
     size_t premasked_for = (size_t)-1;   // the layer whose gradient the max pool after it left masked by its ReLU
+    auto bias_gradient = [&](size_t ii, bool premasked, const RowCut& sums, float* part, hipStream_t bs) {
+        const Op& op = g.ops[ii];
+        const GradDst dst = op.bias ? grads_at(op.b_off) : no_grads;
+        if (premasked && sums.p == 0 && op.bias) {       // its sum is that of the pool's gradient where the pooled value is positive
+            const int py = g.ops[ii + 1].y;
+            const Tensor& tp = g.tensors[(size_t)py];
+            launch_pooled_bias_backward(dt, h->act(py), h->grad(py), dst, S, tp.H * tp.W, op.K, part, bs);
+            return;
+        }
+        const Tensor& ty = g.tensors[(size_t)op.y];
+        launch_bias_relu_backward(dt, h->act(op.y), h->grad(op.y), dst, S, ty.H * ty.W, op.K, op.relu && !premasked, part, sums, bs);
+    };
     auto weight_gradient = [&](size_t ii, hipStream_t ws, float* scratch) {
         const Op& op = g.ops[ii];
         const ConvGeom q = geom_padded(g, op, n, h->L.cpad);
+        if (h->bias_waiting[ii] != 0) {
+            bias_gradient(ii, h->bias_waiting[ii] == 2, RowCut(), ws == h->side ? h->sc<float>(h->L.partial_side) : h->sc<float>(h->L.partial_held), ws);
+            h->bias_waiting[ii] = 0;
+        }
         if (h->L.wpad[ii] >= 0) {
             // the shards' gradients of the padded weights side by side, then compacted into the flat vectors
             const int64_t rows = (int64_t)op.K * op.R * op.S;
@@ -1054,8 +1074,6 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 break;
             case OP_CONV: {
                 const ConvGeom q = geom_padded(g, op, n, h->L.cpad);
-                launch_bias_relu_backward(dt, h->act(op.y), h->grad(op.y), op.bias ? grads_at(op.b_off) : no_grads, S, q.Ho * q.Wo, op.K,
-                                          op.relu && premasked_for != ii, partial, fused_for == ii ? fused_sums : RowCut(), st);
                 // The weight gradient needs only dy (final from here on) and the layer's input, and nothing
                 // before the update reads it: it runs on the second stream, beside the chain of input
                 // gradients, whose short kernels leave part of the chip idle.  Handing work over costs an event (1 us on
@@ -1065,6 +1083,12 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 int conv_ordinal = 0;
                 for (size_t j = 0; j < ii; ++j) conv_ordinal += g.ops[j].kind == OP_CONV;
                 const bool on_main = !overlap || conv_ordinal < (int)tune().wgrad_tail_main;
+                // Bias and ReLU mask come first, except where the chain needs nothing of them: with the gradient masked by the
+                // pool after the layer, or without a ReLU, what is left is the bias gradient's sum, which goes with the weight
+                // gradient (VGG-16, shard of 32: 21 us a layer on the chain; jobs with batch norms use the second
+                // buffer of partial sums on their branch stream).
+                const bool aside = op.bias && !on_main && !h->has_bn && fused_for != ii && (premasked_for == ii || !op.relu);
+                if (!aside) bias_gradient(ii, premasked_for == ii, fused_for == ii ? fused_sums : RowCut(), partial, st);
                 const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
                 const bool early = early_p > 0 && overlap && !on_main && h->upd != nullptr && tune().early_update > 0 && own >= tune().early_update;
                 bool handed_over = false;
@@ -1072,6 +1096,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                     weight_gradient(ii, st, h->sc<float>(overlap ? h->L.wgrad_scratch2 : h->L.wgrad_scratch));
                 } else {
                     waiting.push_back(ii);
+                    if (aside) h->bias_waiting[ii] = premasked_for == ii ? 2 : 1;
                     // From 15 us of work on, and a layer of 10 us at once.  us per step, each layer by itself / 10 / 15 / 25:
                     // MLP 4 x 16 137 / 77 / 77 / 78, ResNet-20 1 x 8 1,200 / 1,080 / 990 / 1,040, ResNet-50 of 112x112 1 x 8
                     // 2,600 / 2,450 / 2,320 / 2,300, VGG-16 of 64x64 1 x 4 705 / 650 / 654 / 664, 2 x 8 932 / 933 / 965 / 946

@@ -95,6 +95,7 @@ __device__ __forceinline__ void store_row(T* base, int64_t r, int C, int c0, con
 // KIND 0: a = x, b = x^2                       (batch-norm statistics)
 // KIND 1: a = dy', b = dy' * xhat              (batch-norm backward sums), dy' = dy * (y>0) if relu
 // KIND 2: a = dy' (written back in place), b=0 (bias gradient / ReLU mask)
+// KIND 3: a = dy', b=0, nothing written back
 // LONG: in two levels (see long_blocks)
 template <typename T, int VEC, int KIND, bool LONG>
 __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x, const T* __restrict__ y, T* dy,
@@ -144,7 +145,7 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
                         #pragma unroll
                         for (int e = 0; e < VEC; ++e) { a[e] += g[u][e]; b[e] += g[u][e] * ((xv[u][e] - mu[e]) * rs[e]); }
                     } else {
-                        if (relu) store_row<T, VEC>(dy, r + (int64_t)u * TY, C, c0, g[u]);
+                        if (KIND == 2 && relu) store_row<T, VEC>(dy, r + (int64_t)u * TY, C, c0, g[u]);
                         #pragma unroll
                         for (int e = 0; e < VEC; ++e) a[e] += g[u][e];
                     }
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(256) void colreduce_kernel(const T* __restrict__ x,
         }
         #pragma unroll
         for (int e = 0; e < VEC; ++e) { a[e] = (float)sa[e]; b[e] = (float)sb[e]; }
-        if (KIND == 2 && dbias.g != nullptr) {      // a block is a shard: the sums need no finishing kernel
+        if (KIND >= 2 && dbias.g != nullptr) {      // a block is a shard: the sums need no finishing kernel
             #pragma unroll
             for (int e = 0; e < VEC; ++e)
                 if (c0 + e < C) dbias.g[(int64_t)cut.k[sh] * dbias.stride + c0 + e] = a[e];
@@ -535,20 +536,23 @@ void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy,
     }
 }
 
+// store: the masked gradient is written back (dy <- dy')
 template <typename T, int VEC>
-static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu, float* partial,
+static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu, bool store, float* partial,
                                  const RowCut& sums, hipStream_t st) {
     const int64_t M = (int64_t)S.samples() * hw;
     const RedShape s = red_shape((int64_t)S.plan * hw, C, VEC);
     const double tb = (double)sizeof(T) * (double)M * C;
     RowCut cut = sums;
     if (cut.p == 0) {   // else dy is masked already and its column sums are in partial
-        ProfScope ps("bias_relu_bwd", 0.0, tb * (relu ? 3.0 : 1.0), st);
+        ProfScope ps("bias_relu_bwd", 0.0, tb * (relu ? (store ? 3.0 : 2.0) : 1.0), st);
         cut = cut_rows(S, hw, s.rows_per_block);
         // Where a block is a whole shard (few rows: fully connected layers) its sums are the bias gradient: one launch less.
         cut.stored = dbias.g != nullptr && cut.block_per_shard();
-        launch_colreduce<T, VEC, 2>(s, long_blocks(S, hw, C, VEC, s), (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st,
-                                    cut.stored ? dbias : GradDst{nullptr, 0});
+        const GradDst direct = cut.stored ? dbias : GradDst{nullptr, 0};
+        const bool two = long_blocks(S, hw, C, VEC, s);
+        if (store) launch_colreduce<T, VEC, 2>(s, two, (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st, direct);
+        else launch_colreduce<T, VEC, 3>(s, two, (const T*)nullptr, (const T*)(relu ? y : dy), (T*)dy, (const float*)nullptr, cut, C, relu ? 1 : 0, partial, st, direct);
     }
     if (dbias.g && !cut.stored) {
         ProfScope ps("bias_finalize", 0.0, 4.0 * (double)cut.blk0[cut.p] * C, st);
@@ -556,16 +560,26 @@ static void bias_relu_backward_t(const void* y, void* dy, GradDst dbias, const S
     }
 }
 
+static void bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu, bool store,
+                               float* partial, const RowCut& sums, hipStream_t st) {
+    if (dtype == 1) {
+        if (C % 8 == 0) bias_relu_backward_t<bf16_t, 8>(y, dy, dbias, S, hw, C, relu, store, partial, sums, st);
+        else bias_relu_backward_t<bf16_t, 1>(y, dy, dbias, S, hw, C, relu, store, partial, sums, st);
+    } else {
+        if (C % 4 == 0) bias_relu_backward_t<float, 4>(y, dy, dbias, S, hw, C, relu, store, partial, sums, st);
+        else bias_relu_backward_t<float, 1>(y, dy, dbias, S, hw, C, relu, store, partial, sums, st);
+    }
+}
+
 void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
                                float* partial, const RowCut& sums, hipStream_t st) {
     if (!relu && !dbias.g) return;
-    if (dtype == 1) {
-        if (C % 8 == 0) bias_relu_backward_t<bf16_t, 8>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
-        else bias_relu_backward_t<bf16_t, 1>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
-    } else {
-        if (C % 4 == 0) bias_relu_backward_t<float, 4>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
-        else bias_relu_backward_t<float, 1>(y, dy, dbias, S, hw, C, relu, partial, sums, st);
-    }
+    bias_relu_backward(dtype, y, dy, dbias, S, hw, C, relu, true, partial, sums, st);
+}
+
+void launch_pooled_bias_backward(int dtype, const void* pooled, const void* dpooled, GradDst dbias, const ShardSet& S, int hw, int C,
+                                 float* partial, hipStream_t st) {
+    if (dbias.g) bias_relu_backward(dtype, pooled, const_cast<void*>(dpooled), dbias, S, hw, C, true, false, partial, RowCut(), st);
 }
 
 __global__ __launch_bounds__(256) void signs_kernel(const bf16_t* __restrict__ act, unsigned char* __restrict__ sign, int64_t vecs) {

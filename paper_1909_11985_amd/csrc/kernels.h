@@ -183,6 +183,11 @@ void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy,
 // sums.p > 0: dy is masked already and partial holds its column sums.
 void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
                                float* partial, const RowCut& sums, hipStream_t st);
+// The same bias gradient of a ReLU layer whose output only a max pool reads, from the pool's output and its gradient: the pool
+// hands each of its gradients to one element, whose activation is the pooled value, so that the sum over the layer's masked
+// gradient is that of dpooled * (pooled > 0), of fewer elements.  hw: pooled pixels per sample.
+void launch_pooled_bias_backward(int dtype, const void* pooled, const void* dpooled, GradDst dbias, const ShardSet& S, int hw, int C,
+                                 float* partial, hipStream_t st);
 
 // ---- pooling --------------------------------------------------------------
 void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int N, int H, int W, int C, int k,
