@@ -488,10 +488,52 @@ __global__ void loss_mean_kernel(const float* __restrict__ row_loss, ShardSet S,
     if (threadIdx.x == 0) out[S.k[blockIdx.x]] = s / (float)(hi - lo);
 }
 
+// The same for small shards and few classes, the means included: a workgroup per shard, a wave per row, a lane per class.  As two
+// launches (a block per row, then the means) it took 8 us of an MLP's 64 us chain, so 4.
+constexpr int kSmallClasses = 64, kSmallLossRows = 64;
+template <typename T>
+__global__ __launch_bounds__(1024) void softmax_ce_small_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
+                                                                T* __restrict__ dlogits, float* __restrict__ row_loss, ShardSet S, int C,
+                                                                float* __restrict__ out) {
+    __shared__ float loss[kSmallLossRows];
+    const int lo = S.off[blockIdx.x], n = S.off[blockIdx.x + 1] - lo;
+    const int lane = threadIdx.x & 63;
+    const bool live = lane < C;
+    const float invn = 1.f / (float)n;
+    for (int r = threadIdx.x >> 6; r < n; r += 16) {
+        const int i = lo + r;
+        const float z = live ? logits[(int64_t)i * C + lane] : -INFINITY;
+        const int label = labels[i];
+        float mx = z;
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 64));
+        const float e = live ? expf(z - mx) : 0.f;
+        float s = e;
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        const float inv = 1.f / s;
+        if (live) dlogits[(int64_t)i * C + lane] = Elem<T>::from_f32((e * inv - (lane == label ? 1.f : 0.f)) * invn);
+        const float zl = __shfl(z, label, 64);
+        if (lane == 0) {
+            const float l = logf(s) - (zl - mx);
+            row_loss[i] = l;
+            loss[r] = l;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    float s = lane < n ? loss[lane] : 0.f;      // as in loss_mean_kernel
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (lane == 0) out[S.k[blockIdx.x]] = s / (float)n;
+}
+
 void launch_softmax_ce(int dtype, const float* logits, const int32_t* labels, void* dlogits, float* row_loss,
                        float* loss_out, const ShardSet& S, int C, hipStream_t st) {
     const int n = S.samples();
     ProfScope ps("softmax_ce", 0.0, (4.0 + (dtype == 1 ? 2.0 : 4.0)) * (double)n * C, st);
+    if (C <= kSmallClasses && S.largest() <= kSmallLossRows) {
+        if (dtype == 1) hipLaunchKernelGGL(softmax_ce_small_kernel<bf16_t>, dim3(S.p), dim3(1024), 0, st, logits, labels, (bf16_t*)dlogits, row_loss, S, C, loss_out);
+        else hipLaunchKernelGGL(softmax_ce_small_kernel<float>, dim3(S.p), dim3(1024), 0, st, logits, labels, (float*)dlogits, row_loss, S, C, loss_out);
+        return;
+    }
     const RowCut shards = cut_rows(S, 1, 1);
     if (dtype == 1)
         hipLaunchKernelGGL(softmax_ce_kernel<bf16_t>, dim3(n), dim3(256), 0, st, logits, labels, (bf16_t*)dlogits, row_loss, shards, C);
