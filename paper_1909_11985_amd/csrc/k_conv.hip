@@ -1926,11 +1926,12 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g, int samples) {
 
 RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
                        bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st) {
-    if (thin_takes(dtype, g)) {
+    const bool small = small_fc_takes(dtype, g, g.C, g.K, S.plan) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && tune().force_tile < 0;
+    if (thin_fwd_takes(dtype, g, S.plan, small)) {
         launch_thin_fwd(dtype, g, x, w, bias, relu, out_fp32, y, st);
         return RowCut();
     }
-    if (small_fc_takes(dtype, g, g.C, g.K, S.plan) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && tune().force_tile < 0) {
+    if (small) {
         launch_small_fc_fwd(g, (const float*)x, (const float*)w, bias, relu, (float*)y, st);
         return RowCut();
     }
@@ -1985,7 +1986,7 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
 // two shards of 64: 1,613 -> 1,578 us.
 // Small layers (k_thin.hip) read them so in either type.
 bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
-    if (thin_takes(dtype, g) || small_fc_takes(dtype, g, g.K, g.C, g.N)) return true;
+    if (thin_dgrad_takes(dtype, g) || small_fc_takes(dtype, g, g.K, g.C, g.N)) return true;
     return EDL_DIRECT_LDS != 0 && dtype == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.H == 1 && g.W == 1 &&
            g.K % 8 == 0 && g.C % 8 == 0 && w_off % 8 == 0;
 }
@@ -1993,10 +1994,11 @@ bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
                          float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows) {
     RowCut left;
-    if (w_rows && (dtype != 1 || thin_takes(dtype, g))) {
+    const bool ragged = g.K % (dtype == 1 ? 8 : 4) != 0;
+    if (w_rows && (dtype != 1 || ragged)) {
         const void* const old = accumulate ? (acc_src != nullptr ? acc_src : dx) : nullptr;
         const DgradMask* const m = tune().fused_mask != 0 && (!accumulate || tune().fused_mask_join != 0) ? mask : nullptr;
-        if (thin_takes(dtype, g)) return launch_thin_dgrad(dtype, g, S, dy, wT, old, dx, m, st);
+        if (ragged) return launch_thin_dgrad(dtype, g, S, dy, wT, old, dx, m, st);
         return launch_small_fc_dgrad(g, S, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx, m, st);
     }
     const int VEC = dtype == 1 ? 8 : 4;
@@ -2202,7 +2204,7 @@ size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
 
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st) {
-    if (thin_takes(dtype, g) && thin_takes_shard(S.plan_largest)) {
+    if (thin_wgrad_takes(dtype, g, S)) {
         launch_thin_wgrad(dtype, g, S, x, dy, dw, st);
         return;
     }

@@ -1,6 +1,6 @@
 // Small fully connected layers.  First, those with few outputs whose number is no multiple of a vector (a classifier of 10
-// classes): the three contractions of such a layer.  What bounds them is latency: a few hundred thousand multiplications.  The tiled kernel took
-// its element-wise path for them (one workgroup of 64x64 outputs, a wait after every load): MLP of 64 samples 12.1 / 10.8 /
+// classes): the three contractions of such a layer.  Where they are small (thin_fwd_takes and its like say how small) latency bounds them.  The
+// tiled kernel took its element-wise path for them (one workgroup of 64x64 outputs, a wait after every load): MLP of 64 samples 12.1 / 10.8 /
 // 5.7 us forward / input gradient / weight gradient, here 3.1 / 3.6 / 3.3; a chain of 20 launches of 3 to 8 us each.
 //
 //   forward           y[m][k]  = sum_c x[m][c] w[k][c] + b[k]       a wave per output, lanes along c
@@ -19,7 +19,7 @@
 
 namespace edl {
 
-constexpr int kThinOutputs = 128;      // more than that fills tiles
+constexpr int kThinOutputs = 128;      // as far as the rules below were measured
 constexpr int kThinShard = 1024;       // rows of a shard: a chain of 64 in the weight gradient
 constexpr int kThinRows = 16;          // rows of a workgroup of the input gradient
 
@@ -130,11 +130,48 @@ __global__ __launch_bounds__(1024) void thin_wgrad_kernel(const T* __restrict__ 
     dw.g[(int64_t)S.k[sh] * dw.stride + (size_t)(k0 + sub) * C + c] = s;
 }
 
-bool thin_takes(int dtype, const ConvGeom& g) {
-    return g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.K % (dtype == 1 ? 8 : 4) != 0 && g.K <= kThinOutputs &&
-           (int64_t)g.N * std::max(g.K, g.C) < (1ll << 31);
+static bool thin_shape(int dtype, const ConvGeom& g) {
+    return g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && g.K % (dtype == 1 ? 8 : 4) != 0 && g.K <= kThinOutputs;
 }
-bool thin_takes_shard(int largest) { return largest <= kThinShard; }
+
+// Float32 rows that are no whole vectors: the tiled kernel reads everything element by element then, and takes up to three times as
+// long (bf16 as well, but so does the thin one there).
+static bool odd_rows(int dtype, const ConvGeom& g) { return dtype != 1 && g.C % 4 != 0; }
+
+// The rules, from launches of 64 to 32,768 rows (M), 63 to 4,096 columns (C) and 10 to 127 outputs (K).  Times are us between events
+// around a launch, 5 to 6 of them the events', float32 / bf16 where both are given.
+//
+// Forward: a wave per output costs 0.14 ns + 0.05 per further 64 vectors of the row, whatever the tiled kernel reuses; that one's time is
+// its reduction's, in few workgroups.  Thin against tiled, M x K:
+//    65,024 C =   512   15.1 against 15.9 (bf16)                33,280 C = 64      9.7 / 10.1 against 6.5 / 10.9
+//   135,168 C =   512   32.4 / 27.6 against 11.6 / 17.7      4,161,536 C = 64      578 / 627 against 16.3 / 15.1
+//    65,024 C = 4,096   66.5 / 39.8 against 114 / 114          520,192 C = 4,096   466 / 269 against 116 / 111
+//   odd rows: 65,024 C = 511 29.4 / 28.9 against 53.6 / 44.5, 135,168 C = 2,047 180 / 180 against 190 / 141
+// and against small_fc_kernel (float32): 5,120 C = 64 6.3 against 6.2, 8,128 C = 512 6.2 against 8.7, 16,896 C = 64 7.8 against 6.2,
+// 33,280 C = 512 11.7 against 9.4, 520,192 C = 512 106 against 22.9.
+bool thin_fwd_takes(int dtype, const ConvGeom& g, int samples, bool small) {
+    const int64_t most = small ? 12288 : 32768 + (odd_rows(dtype, g) ? 110 : 64) * std::min(g.C, 1024);
+    return thin_shape(dtype, g) && (int64_t)samples * g.K <= most;
+}
+
+// Input gradient: thin against tiled and the launches that come with it (the ReLU's mask and sums, the transposed weights), M x K x C:
+//   8.5e6 to 1.7e7   11 to 15 against 34 to 38         1.3e8 to 1.4e8 (K = 65, 127)   29 to 38 against 36 to 49
+//   2.7e8 (K = 127)  47 / 57 against 43 to 50          5.5e8 (K = 33)   139 / 181 against 131 / 137    2.1e9 (K = 127)   313 / 425 against 194 / 181
+//   odd rows: 2.7e8 (K = 127) 50 against 48 to 53, 2.8e8 (K = 33) 76 against 88 to 90, 1.1e9 167 against 123
+// Up to 16 outputs it is one pass over what it reads and writes, at any size: 32,768 x 10 x 512 55 / 66 against 69 / 113.
+// (Blocks of 16 rows stay below 65,536.)
+bool thin_dgrad_takes(int dtype, const ConvGeom& g) {
+    return thin_shape(dtype, g) && (g.K <= 16 ? g.N <= 1000000 : (int64_t)g.N * g.K * g.C <= (odd_rows(dtype, g) ? 400000000 : 200000000));
+}
+
+// Weight gradient: thin against tiled and the sum of its pieces, M x K x C:
+//   4.2e6 to 1.7e7   13 to 20 against 17 to 25         6.9e7   21 / 23 to 24 against 24 to 25 / 21 to 23
+//   1.4e8            30 / 32 against 27 / 22           5.5e8   86 / 97 against 36 / 27
+//   odd rows: 1.3e8 24 against 33, 2.8e8 49 against 41
+bool thin_wgrad_takes(int dtype, const ConvGeom& g, const ShardSet& S) {
+    const int64_t most = odd_rows(dtype, g) ? 200000000 : dtype == 1 ? 70000000 : 100000000;
+    return thin_shape(dtype, g) && S.plan_largest <= kThinShard && (int64_t)S.plan * g.K * g.C <= most;
+}
 
 template <typename T>
 static void fwd(const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu, bool out_fp32, void* y, hipStream_t st) {

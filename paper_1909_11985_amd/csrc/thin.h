@@ -5,10 +5,11 @@
 
 namespace edl {
 
-// few, ragged outputs
-bool thin_takes(int dtype, const ConvGeom& g);
-// ... and, for the weight gradient, shards of this many samples at most
-bool thin_takes_shard(int largest);
+// few, ragged outputs: the forward contraction of a pass planned for `samples` (small: if not, launch_small_fc_fwd takes it), the
+// input gradient of passes of up to g.N, the weight gradient of a pass planned as S is
+bool thin_fwd_takes(int dtype, const ConvGeom& g, int samples, bool small);
+bool thin_dgrad_takes(int dtype, const ConvGeom& g);
+bool thin_wgrad_takes(int dtype, const ConvGeom& g, const ShardSet& S);
 void launch_thin_fwd(int dtype, const ConvGeom& g, const void* x, const void* w, const float* bias, bool relu, bool out_fp32, void* y, hipStream_t st);
 // old (may be null, may be dx): the gradient that is added to.  Returns how the sums of mask are cut, p == 0 if it left none.
 RowCut launch_thin_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* w, const void* old, void* dx,

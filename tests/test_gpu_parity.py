@@ -1111,6 +1111,77 @@ def test_fully_connected_layers_with_few_ragged_outputs(classes, arch, n, dtype)
     _assert_layerwise(relu_producer_pair_parity("mlp", dtype, n, H=1, W=1, C=24, classes=classes, arch=arch), dtype)
 
 
+def _launches(job, p):
+    """Launches per label of one mini-batch's gradients."""
+    import paper_1909_11985_amd as E
+    E.edl_profile(True)
+    try:
+        job.gradients(p)
+        return {r["name"]: r["launches"] for r in E.edl_profile_report()}
+    finally:
+        E.edl_profile(False)
+
+
+@pytest.mark.parametrize("dtype,classes,C,n,p,taken", [
+    ("f32", 10, 64, 64, 4, "fwd dgrad wgrad"),
+    ("bf16", 127, 512, 64, 1, "fwd dgrad wgrad"),
+    ("f32", 12, 64, 64, 1, ""),                       # outputs that are whole vectors
+    ("bf16", 129, 64, 33, 1, ""),                     # more outputs than the rules were measured over
+    # the ends of the forward rule: 12,288 outputs beside the float32 kernel of few tiles, 32,768 + 64 columns beside tiled launches
+    ("f32", 3, 64, 4096, 4, "fwd dgrad wgrad"), ("f32", 3, 64, 4100, 5, "small dgrad wgrad"),
+    ("bf16", 36, 64, 1024, 1, "fwd dgrad wgrad"), ("bf16", 36, 64, 1025, 1, "dgrad"),
+    # of the input gradient's: 200 million products
+    ("bf16", 100, 1000, 2000, 2, "dgrad"), ("bf16", 100, 1000, 2002, 2, ""),
+    # of the weight gradient's: 70 (bf16) and 100 million (float32) products
+    ("bf16", 10, 1000, 7000, 7, "fwd dgrad wgrad"), ("bf16", 10, 1000, 7007, 7, "fwd dgrad"),
+    ("f32", 10, 1000, 10000, 10, "dgrad wgrad"), ("f32", 10, 1000, 10010, 10, "dgrad"),
+])
+def test_which_layers_the_kernels_of_few_outputs_take(dtype, classes, C, n, p, taken):
+    """The rules of the kernels for few ragged outputs, at both sides of each of their ends."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=p, max_shard=n // p, H=1, W=1, C_=8, arch=(8, C), classes=classes), 2)
+    x, y = synth_inputs.dataset(1, n, 1, 1, 8, classes)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    got = _launches(job, p)
+    expected = {"thin_" + t: 1 for t in taken.split() if t != "small"}
+    assert {k: v for k, v in got.items() if k.startswith("thin_")} == expected, got
+    if "small" in taken:
+        assert got["small_fc_fwd"] == 2, got      # the first layer and the last; the second has 258 tiles
+    job.shutdown()
+
+
+@pytest.mark.parametrize("dtype,bound", [("f32", 1e-4), ("bf16", 2e-2)])
+def test_a_classifier_over_very_many_rows(dtype, bound):
+    """560,000 rows of 127 outputs: 71 million outputs, more than a launch of a wave each can have (2^32 lanes), against torch
+    in float64.  Float32 sums of 560,000 terms in any order differ by 2^-24 times the square root of their number (4.5e-5)."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    M, K, C0, C1, C2 = 560000, 127, 8, 16, 32
+    rng = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.randn(M, 1, 1, C0, device="cuda", generator=rng)
+    y = torch.randint(0, K, (M,), device="cuda", dtype=torch.int32, generator=rng)
+    job = E.Job(make_config("mlp", dtype=dtype, N=M, B=M, p_max=1, max_shard=M, H=1, W=1, C_=C0, arch=(C1, C2), classes=K), 0)
+    job.bind_dataset(x, y)
+    loss = job.gradients(1)
+    got = job.grad(0)
+    w = torch.from_numpy(job.params()).cuda().double()
+    table = {name: (off, size) for name, off, size, _ in E.edl_tensor_table(job.cfg)}
+    leaves = {name: w[off:off + size].clone().requires_grad_(True) for name, (off, size) in table.items()}
+    h = x.reshape(M, C0).double()
+    for i, (outs, ins) in enumerate([(C1, C0), (C2, C1), (K, C2)]):
+        h = h @ leaves["fc%d.w" % (i + 1)].reshape(outs, ins).T + leaves["fc%d.b" % (i + 1)]
+        h = h.relu() if i < 2 else h
+    expected = torch.nn.functional.cross_entropy(h, y.long())
+    expected.backward()
+    assert abs(loss - expected.item()) < bound * expected.item(), (loss, expected.item())
+    for name, (off, size) in table.items():
+        assert relerr(got[off:off + size], leaves[name].grad.cpu().numpy()) < bound, name
+    job.shutdown()
+
+
 @pytest.mark.parametrize("C,arch,n", [
     (784, (256, 256), 64), (8, (4, 36), 1), (1024, (32, 100), 33), (1028, (64, 1024), 40), (12, (2048, 2052), 128), (520, (512, 512), 513),
 ])
