@@ -73,7 +73,10 @@ __global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ d
         for (int i = 0; i < R; ++i) {
             const int r = min(r0 + sub + 4 * i, r1 - 1);     // (a row past the end is computed and not used)
             #pragma unroll
-            for (int e = 0; e < KC; ++e) acc[i] += Elem<T>::to_f32(dy[(size_t)r * K + min(k0 + e, K - 1)]) * wk[e];
+            for (int e = 0; e < KC; ++e) {
+                const float d = Elem<T>::to_f32(dy[(size_t)r * K + min(k0 + e, K - 1)]);
+                acc[i] += (k0 + e < K ? d : 0.f) * wk[e];      // (an infinite last gradient times the zeros of wk would be NaN)
+            }
         }
     }
     float s = 0.f;

@@ -1182,6 +1182,25 @@ def test_a_classifier_over_very_many_rows(dtype, bound):
     job.shutdown()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes", [10, 12, 16, 17, 31])
+def test_an_infinite_gradient_stays_infinite(classes, dtype):
+    """Reductions that end inside a step of the input gradient's kernels: what lies past their end adds nothing, also where the
+    last gradient is infinite (a gradient that overflowed shows as such, not as NaN)."""
+    case = Case("mlp", dtype, 5, H=1, W=1, C=8, classes=classes, arch=(16, 72))
+    logits, hidden = len(case.tensors) - 1, len(case.tensors) - 2
+    dy = np.full((5, 1, 1, classes), 0.25, np.float32)
+    dy[2, 0, 0, classes - 1] = np.inf
+    case.job.debug_forward(np.arange(5))
+    case.job.debug_set(logits, dy, which=1)
+    case.job.debug_backward_op(case.job.debug_op_count() - 2, 5)
+    w = case.job.params()[-(72 * classes + classes):-classes].reshape(classes, 72)
+    dx = case.job.debug_get(hidden, 5, which=1).reshape(5, 72)
+    assert np.array_equal(dx[2], np.inf * np.sign(w[-1])), dx[2]
+    assert np.isfinite(np.delete(dx, 2, axis=0)).all()
+    case.close()
+
+
 @pytest.mark.parametrize("C,arch,n", [
     (784, (256, 256), 64), (8, (4, 36), 1), (1024, (32, 100), 33), (1028, (64, 1024), 40), (12, (2048, 2052), 128), (520, (512, 512), 513),
 ])
