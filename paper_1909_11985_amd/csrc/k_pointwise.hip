@@ -58,6 +58,15 @@ __device__ __forceinline__ uint4 rows_load(__amdgpu_buffer_rsrc_t r, unsigned at
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
+// What lanes of a wave have written to the wave's part of LDS is there for its other lanes, and what they have read may be
+// overwritten.  The hardware keeps a wave's LDS accesses in order; the fence keeps the compiler from moving one across this
+// point (a wave barrier alone says nothing about memory).  It orders LDS only: one over all memory, or two of them, cost the
+// joins at K = 128 3%.
+__device__ __forceinline__ void wave_lds_handover() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
 template <int K, int NW, int SUB, bool JOIN>
 __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) {
     constexpr int NT = 64 * NW, TN = 8 / NW;                                  // lanes; MFMA tiles of 32 columns per wave
@@ -150,7 +159,9 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
     put_rows(0, next);
     int buf = 0;
     for (int mt = 0; mt < (int)rows; mt += TROWS, buf ^= 1) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // this wave's part of the tile is in LDS ...
+        // This wave's part of the tile is in LDS ...  (Not redundant: the compiler leaves its own wait out here, where the writes come
+        // round the loop, in every one of these kernels; without this line other waves read rows that are not written yet.)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __syncthreads();      // ... every wave's is, and every wave is done with the tile before
         load_rows(mt + TROWS, next);
         #pragma unroll
@@ -171,7 +182,7 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
                     acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[j][g]), __builtin_bit_cast(bf16x8, x), acc[j], 0, 0, 0);
             }
             // lane: pixel lane % 32, channels j * 32 + (q / 4) * 8 + (lane / 32) * 4 + q % 4
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_handover();
             #pragma unroll
             for (int j = 0; j < TN; ++j)
                 #pragma unroll
@@ -181,7 +192,7 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
                     if (JOIN) *reinterpret_cast<float4*>(p + ch * 4) = make_float4(acc[j][q], acc[j][q + 1], acc[j][q + 2], acc[j][q + 3]);
                     else *reinterpret_cast<uint2*>(p + ch * 2) = make_uint2(pack2_bf16(acc[j][q], acc[j][q + 1]), pack2_bf16(acc[j][q + 2], acc[j][q + 3]));
                 }
-            __builtin_amdgcn_wave_barrier();     // (a wave's LDS accesses complete in order)
+            wave_lds_handover();
             float t1[8], t2[8];
             #pragma unroll
             for (int e = 0; e < 8; ++e) t1[e] = t2[e] = 0.f;

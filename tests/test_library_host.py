@@ -275,3 +275,27 @@ def test_a_job_can_be_held_to_the_memory_of_one_shard(E, model, dtype, kw):
         assert one.arena_bytes < full.arena_bytes / 2
     with pytest.raises(E.EdlError):
         E.edl_arena_bytes(cfg, -1)
+
+
+# ---------------------------------------------------------------- device code of the streaming 1x1 convolutions
+def _device_code(*flags):
+    """k_pointwise.hip as the library is built of it, in text."""
+    import subprocess
+    from paper_1909_11985_amd import build
+    cmd = ["hipcc", "-x", "hip", "-S", "--cuda-device-only", os.path.join(build.CSRC, "k_pointwise.hip"), "-o", "-"] + build.FLAGS
+    return subprocess.run(cmd + list(flags), check=True, capture_output=True, text=True).stdout
+
+
+def test_streaming_kernels_order_their_lds_accesses():
+    """A wave's outputs pass between its lanes through LDS behind a fence (before they are written, before they are read), and
+    every barrier is reached with the wave's LDS writes done."""
+    kernels = re.findall(r"^define [^\n]*pointwise_kernel[^\n]*\n(.*?)^}", _device_code("-emit-llvm"), flags=re.S | re.M)
+    assert len(kernels) == 8
+    for body in kernels:
+        assert len(re.findall(r'fence syncscope\("wavefront"\) acq_rel', body)) >= 2
+    code = [line.split(";")[0].strip() for line in _device_code().splitlines()]
+    code = [line for line in code if line and not line.startswith(".")]
+    barriers = [i for i, line in enumerate(code) if line == "s_barrier"]
+    assert len(barriers) == 8
+    for i in barriers:
+        assert code[i - 1] == "s_waitcnt lgkmcnt(0)", code[i - 3:i + 1]
