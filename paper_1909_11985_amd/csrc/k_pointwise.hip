@@ -1,23 +1,26 @@
 // 1x1 convolutions of stride 1 with a short reduction and a wide output (the expanding layers of a residual block and
 // the input gradients that end at its join), bf16, over many pixels:
 //
-//   out[m][n] = sum_k A[m][k] * B[n][k]      K = 64, 128 or 256;  N a multiple of 256;  M pixels
+//   out[m][n] = sum_k A[m][k] * B[n][k]      K = 64, 128, 256 or 512;  N a multiple of 256;  M pixels
 //
 // What bounds them is memory: at K = 64 and N = 256 a row is 128 bytes in and 512 out (a join reads another 1,056), and
 // the tiled kernel of k_conv.hip spent its time between a tile's loads and its stores instead (set-up, one or two reduction
 // steps, an epilogue, per workgroup of 128x64 outputs: 3.0 TB/s, a join 3.9).  Here a workgroup walks a run of rows:
-//   * its four or eight waves own 64 or 32 of 256 columns each; their weights stay in registers for the whole run (64 or 128
-//     of them per lane), so LDS holds only the rows, read once for 256 columns;
+//   * its waves, four at K = 64 and eight above, own 64 or 32 of 256 columns each; their weights stay in registers for the
+//     whole run (32 of them per lane at K = 64 and 128, 64 at 256, 128 at 512), so LDS holds only the rows, read once for
+//     256 columns;
 //   * the next rows, and what the epilogue of the next 32 reads, are on their way into registers while the present ones are
 //     contracted and stored (joins without that: 5 to 15% slower; forward at K = 64 with 32 rows in flight per workgroup
-//     instead of 64: 148 us for 116 at one workgroup per CU);
+//     instead of 64, both at one workgroup per CU: 148 us for 116; with two it is 102);
 //   * the weights are the first operand of the MFMA, so that a lane gets four consecutive channels of one pixel; the wave
 //     turns its 32 pixels into rows through LDS of its own, which takes no barrier (one per tile of rows is left);
 //   * the column sums a batch norm wants (of the stored values, see ConvArgs::stats and ::msum) are kept in float64 per lane
 //     from one tile to the next: one partial sum per channel and run of rows.
 // The contraction runs over k in the same order as in the tiled kernel: the outputs are the same bits.
-// Measured: 5.0 TB/s at M = 802,816, N = 256, K = 64, a join 5.2 TB/s (pointwise_takes has the times).
-// The variants are those without spills: registers in scratch cost up to a factor of two here.
+// Measured: 5.0 TB/s at M = 802,816, N = 256, K = 64, a join 5.1 TB/s (pointwise_takes has the times).
+// The variants are those without spills.  At K = 512 that takes an instruction more per LDS read: with the read addresses kept
+// in registers the join had 23 others in scratch (M = 12,544, N = 2,048: 82 us for 61) and the forward launch fewer loads
+// under way (M = 200,704, N = 256: 94 for 77).
 #include <algorithm>
 
 #include "dev_common.h"
@@ -76,8 +79,8 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
     constexpr int G = K / 16;
     constexpr bool AHEAD = JOIN && K <= 256;      // (K = 512: no registers left)
     constexpr int TILE = TROWS * RB;
-    // a wave's outputs on their way to rows: float32 where the epilogue adds to them, else bf16; rows of 68 words or 34
-    // words, so that neither the writes of 32 pixels nor the reads of rows meet in a bank
+    // a wave's outputs on their way to rows: float32 where the epilogue adds to them, else bf16; rows of 68 (36) words or 34
+    // (18), so that neither the writes of 32 pixels nor the reads of rows meet in a bank
     constexpr int LDS_ROW = JOIN ? (32 * TN + 4) * 4 : (16 * TN + 2) * 4;
     constexpr int STAGE = kRows * LDS_ROW;
     __shared__ __attribute__((aligned(16))) unsigned char smem[2 * TILE + NW * STAGE];
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
     const int n0 = by * kCols + wave * (32 * TN);
     unsigned char* const stage = smem + 2 * TILE + wave * STAGE;
 
-    // the weights of this wave's 64 columns, as MFMA operands
+    // the weights of this wave's columns, as MFMA operands
     uint4 wf[TN][G];
     #pragma unroll
     for (int j = 0; j < TN; ++j)
@@ -173,10 +176,13 @@ __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) 
             for (int j = 0; j < TN; ++j)
                 #pragma unroll
                 for (int q = 0; q < 16; ++q) acc[j][q] = 0.f;
+            const int row = sub * kRows + (lane & 31);
+            int turn = (row / RPL) % KV;
+            // (K = 512: the compiler would compute the 32 addresses once, ahead of the loop, into 32 registers that are not there)
+            if (K == 512) asm volatile("" : "+v"(turn));
             #pragma unroll
             for (int g = 0; g < G; ++g) {
-                const int row = sub * kRows + (lane & 31);
-                const uint4 x = *reinterpret_cast<const uint4*>(smem + buf * TILE + row * RB + (((2 * g + (lane >> 5)) ^ ((row / RPL) % KV)) * 16));
+                const uint4 x = *reinterpret_cast<const uint4*>(smem + buf * TILE + row * RB + (((2 * g + (lane >> 5)) ^ turn) * 16));
                 #pragma unroll
                 for (int j = 0; j < TN; ++j)
                     acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wf[j][g]), __builtin_bit_cast(bf16x8, x), acc[j], 0, 0, 0);
@@ -276,12 +282,18 @@ static int rows_per_run(int64_t M, int K, int N) {
 }
 
 // From 32,768 rows of 256 columns on (four tiles of 32 per workgroup).  Below, a workgroup has too few tiles to pay for the
-// weights that it loads: us, tiled / streaming, forward and join, of ResNet-50 at 32 samples
-//   M = 100,352 N = 256   23.7 / 19.1 and 48.4 / 39.0        M = 25,088 N = 512   19.0 / 17.5 and 31.7 / 25.8
-//   M = 6,272 N = 1,024   15.7 / 16.8 and 23.9 / 23.9        M = 1,568 N = 2,048  14.5 / 18.5 and 18.9 / 26.2
-// and at 256 samples
-//   M = 802,816 N = 256   169 / 103 and 360 / 270            M = 200,704 N = 512  94.6 / 69.7 and 210 / 138
-//   M = 50,176 N = 1,024  60.0 / 48.9 and 135 / 90           M = 12,544 N = 2,048 47.6 / 40.8 and 94.8 / 84
+// weights that it loads.  us between events, tiled / streaming, forward and join (a first block's join and its projection
+// have other K than the rest of their stage), of ResNet-50 at 256 samples
+//   M = 802,816 N = 256    K =  64 167 / 102 and 344 / 265     K = 128 join 389 / 282
+//   M = 200,704 N = 512    K = 128 95 / 68 and 199 / 133       K = 256 join 237 / 151      N = 256 K = 512 forward 104 / 77
+//   M = 50,176  N = 1,024  K = 256 59 / 48 and 128 / 79        K = 512 join 164 / 104
+//   M = 12,544  N = 2,048  K = 512 48 / 41 and 93 / 61
+// at 32 samples
+//   M = 100,352 N = 256    K =  64 24.2 / 19.3 and 47.1 / 35.1    K = 128 join 55.0 / 38.5
+//   M = 25,088  N = 512    K = 128 19.7 / 17.3 and 30.8 / 24.5    K = 256 join 36.6 / 29.0
+// and there below the line
+//   M = 6,272   N = 1,024  K = 256 15.8 / 16.6    joins of K = 256 and 512 together 24.3 / 22.6
+//   M = 1,568   N = 2,048  K = 512 15.0 / 18.8 and 19.8 / 21.3    M = 25,088 N = 256 K = 512 forward 22.9 / 23.8
 bool pointwise_takes(int dtype, const ConvGeom& g, int plan_samples, int K, int N) {
     const int64_t M = (int64_t)plan_samples * g.H * g.W;
     return dtype == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && (K == 64 || K == 128 || K == 256 || K == 512) &&

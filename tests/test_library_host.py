@@ -299,3 +299,11 @@ def test_streaming_kernels_order_their_lds_accesses():
     assert len(barriers) == 8
     for i in barriers:
         assert code[i - 1] == "s_waitcnt lgkmcnt(0)", code[i - 3:i + 1]
+
+
+def test_streaming_kernels_keep_everything_in_registers():
+    """Every variant that the dispatch reaches: registers in scratch cost a third of its speed."""
+    code = _device_code()
+    spills = dict(zip(re.findall(r"\.name: +(\S*pointwise_kernel\S*)", code), re.findall(r"\.vgpr_spill_count: +(\d+)", code)))
+    assert len(spills) == 8 and set(spills.values()) == {"0"}, spills
+    assert set(re.findall(r"\.private_segment_fixed_size: +(\d+)", code)) == {"0"}
