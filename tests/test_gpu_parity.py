@@ -952,19 +952,20 @@ def test_step_is_deterministic():
     assert np.array_equal(a["job"].params(), b["job"].params())
 
 
-def _digest_after_steps(options, side_streams="library", optimizers=("momentum",), unequal=False):
-    """sha256 of the model state after a few ResNet-50 steps (64x64 images, bf16) under the given options."""
+def _digest_after_steps(options, side_streams="library", optimizers=("momentum",), unequal=False, model="resnet50", dtype="bf16", **geom):
+    """sha256 of the model state after a few steps (ResNet-50 on 64x64 images in bf16 unless said) under the given options."""
     import hashlib
     torch = _torch()
     import paper_1909_11985_amd as E
     from paper_1909_11985_amd.binding import make_config
     N, B = 96, 24
-    x, y = synth_inputs.dataset(1, N, 64, 64, 3, 1000)
+    geom = dict(dict(H=64, W=64, C_=3, classes=1000), **geom)
+    x, y = synth_inputs.dataset(1, N, geom["H"], geom["W"], geom["C_"], geom["classes"])
     dx, dy = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
     h = hashlib.sha256()
     with E.options(**options):
         for optimizer in optimizers:
-            cfg = make_config("resnet50", dtype="bf16", N=N, B=B, p_max=4, max_shard=B, lr=0.002, H=64, W=64, optimizer=optimizer)
+            cfg = make_config(model, dtype=dtype, N=N, B=B, p_max=4, max_shard=B, lr=0.002, optimizer=optimizer, **geom)
             job = E.Job(cfg, 0, side_streams=side_streams)
             job.bind_dataset(dx, dy)
             for p in (1, 2, 4, 1):
@@ -973,7 +974,7 @@ def _digest_after_steps(options, side_streams="library", optimizers=("momentum",
                 idx, _ = job.shard(B, 1, 1, 0)
                 job.step(3, idx, np.array([0, 10, 10, 24], dtype=np.int64))      # unequal shards, an empty one in the middle
                 job.step(2, idx, np.array([0, 24, 24], dtype=np.int64))          # the last shard is empty
-            h.update(job.params().tobytes() + job.momentum().tobytes() + job.running().tobytes())
+            h.update(job.params().tobytes() + job.momentum().tobytes() + (job.running().tobytes() if job.R else b""))
             if optimizer == "adam":
                 h.update(job.second_moment().tobytes())
             job.shutdown()
@@ -999,6 +1000,27 @@ def test_the_second_stream_does_not_change_the_result():
     assert _digest_after_steps({"bn_nt_bytes": 0}) == base
     assert _digest_after_steps({}, side_streams="torch") == base          # the caller's streams
     assert _digest_after_steps({}, side_streams=None) == base             # none: edl_set_side_streams(NULL, NULL)
+
+
+@pytest.mark.parametrize("model,dtype,geom", [
+    ("resnet50", "bf16", {}),
+    ("vgg16", "bf16", dict(arch=(64, 256, 2, 2, 3, 3, 3))), ("vgg16", "f32", dict(H=32, W=32, arch=(16, 64, 2, 2, 3, 3, 3))),
+    ("alexnet", "bf16", dict(H=96, W=96, arch=(64, 256))), ("alexnet", "f32", dict(H=96, W=96, arch=(16, 64))),
+    ("resnet20", "f32", dict(H=32, W=32, classes=10)), ("mlp", "f32", dict(H=1, W=1, C_=784, classes=10, arch=(256, 256))),
+])
+def test_how_weight_gradients_are_handed_over_does_not_change_the_result(model, dtype, geom):
+    """Weight gradients, and the bias gradients that go with them (before a max pool, without a ReLU), each by itself on the
+    second stream, several together, all behind the chain of input gradients, or everything on one stream: bit for bit the same
+    model, over equal and unequal shards."""
+    kw = dict(model=model, dtype=dtype, unequal=True, **geom)
+    base = _digest_after_steps({}, **kw)
+    for batch in (0, 1, 40, 1000000):
+        assert _digest_after_steps({"wgrad_batch_us": batch}, **kw) == base, batch
+    for batch in (0, 1000000):
+        assert _digest_after_steps({"wgrad_batch_us": batch, "wgrad_tail_main": 0}, **kw) == base, batch
+    assert _digest_after_steps({"wgrad_batch_us": 1000000, "early_update": 1}, **kw) == base
+    assert _digest_after_steps({"wgrad_stream": 0}, **kw) == base
+    assert _digest_after_steps({"wgrad_batch_us": 1000000}, side_streams="torch", **kw) == base
 
 
 def test_the_update_started_during_the_backward_pass_does_not_change_the_result():
