@@ -49,6 +49,16 @@ __global__ __launch_bounds__(256) void thin_fwd_kernel(const T* __restrict__ x, 
     else ((T*)y)[o] = Elem<T>::from_f32(s);
 }
 
+// An element through a buffer descriptor: what lies past its end is read as zero.
+constexpr unsigned kPastEnd = 0x80000000u;      // (the rules below keep the gradients under that many bytes)
+template <typename T> __device__ __forceinline__ float load_or_zero(__amdgpu_buffer_rsrc_t r, unsigned at);
+template <> __device__ __forceinline__ float load_or_zero<float>(__amdgpu_buffer_rsrc_t r, unsigned at) {
+    return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, at, 0, 0));
+}
+template <> __device__ __forceinline__ float load_or_zero<bf16_t>(__amdgpu_buffer_rsrc_t r, unsigned at) {
+    return bf16_to_f32(__builtin_amdgcn_raw_buffer_load_b16(r, at, 0, 0));
+}
+
 // grid: (64 columns, blocks of rows within a shard).  Masked and summed as a bias layer with ReLU wants it (DgradMask with no
 // xin); with one block per shard the sums are that layer's bias gradients.
 template <typename T>
@@ -62,6 +72,8 @@ __global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ d
     const int c = blockIdx.x * 64 + lane;
     const bool active = c < C;
     constexpr int R = kThinRows / 4, KC = 16;
+    const __amdgpu_buffer_rsrc_t rdy =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(dy), 0, (unsigned)cut.row0[cut.p] * (unsigned)K * (unsigned)sizeof(T), 0x00020000);
     float acc[R];
     #pragma unroll
     for (int i = 0; i < R; ++i) acc[i] = 0.f;
@@ -71,11 +83,13 @@ __global__ __launch_bounds__(256) void thin_dgrad_kernel(const T* __restrict__ d
         for (int e = 0; e < KC; ++e) wk[e] = active && k0 + e < K ? Elem<T>::to_f32(w[(size_t)(k0 + e) * C + c]) : 0.f;
         #pragma unroll
         for (int i = 0; i < R; ++i) {
-            const int r = min(r0 + sub + 4 * i, r1 - 1);     // (a row past the end is computed and not used)
+            // (a row past the end is computed and not used)
+            const unsigned row = (unsigned)min(r0 + sub + 4 * i, r1 - 1) * (unsigned)K * (unsigned)sizeof(T);
             #pragma unroll
             for (int e = 0; e < KC; ++e) {
-                const float d = Elem<T>::to_f32(dy[(size_t)r * K + min(k0 + e, K - 1)]);
-                acc[i] += (k0 + e < K ? d : 0.f) * wk[e];      // (an infinite last gradient times the zeros of wk would be NaN)
+                // an output past the last one is read as zero, and not as the last times a zero weight: that may be infinite
+                const unsigned col = (unsigned)(k0 + e) * (unsigned)sizeof(T) + (k0 + e < K ? 0u : kPastEnd);
+                acc[i] += load_or_zero<T>(rdy, row + col) * wk[e];
             }
         }
     }
