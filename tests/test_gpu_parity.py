@@ -332,6 +332,28 @@ def test_streaming_pointwise_convolutions(n, kw, blocks):
         _assert_layerwise(r, "bf16")
 
 
+@pytest.mark.parametrize("rows,blocks", [(0, 1), (0, 256), (1 << 40, 256)])
+@pytest.mark.parametrize("n,kw", [
+    (5, dict(H=50, W=42, C=3, classes=10, arch=(64, 2, 2, 2, 2))), (1, dict(H=33, W=33, C=3, classes=10, arch=(64, 1, 1, 1, 1))),
+])
+def test_which_convolutions_stream(n, kw, rows, blocks):
+    """The layers that the tests above and below mean to run on the streaming kernel do: every 1x1 convolution of stride 1 from 64 to
+    512 channels into a multiple of 256, and the input gradient at every residual join; none with the line far away."""
+    import paper_1909_11985_amd as E
+    case = Case("resnet50", "bf16", n, **kw)
+    with E.options(pointwise_rows=rows, pointwise_blocks=blocks):
+        got = _launches(case.job, 1)
+    ops, blocks_in_all = case.oracle(False).graph.ops, sum(kw["arch"][1:])
+    channels = {op["y"]: op["C" if op["kind"] == "bn" else "K"] for op in ops if op["kind"] in ("bn", "conv")}
+    channels.update({op["y"]: channels[op["x"]] for op in ops if op["kind"] == "maxpool"})
+    forward = [op for op in ops if op["kind"] == "conv" and (op["R"], op["stride"], op["pad"]) == (1, 1, 0) and op["K"] % 256 == 0 and
+               channels.get(op["x"]) in (64, 128, 256, 512)]
+    assert len(forward) > blocks_in_all
+    expected = {"pointwise_fwd": len(forward), "pointwise_join": blocks_in_all - 1} if rows == 0 else {}
+    assert {k: v for k, v in got.items() if k.startswith("pointwise_")} == expected, got
+    case.close()
+
+
 @pytest.mark.parametrize("together", [0, 36])
 @pytest.mark.parametrize("blocks", [3, 256])
 def test_streaming_pointwise_convolutions_keep_to_their_shard(blocks, together):
@@ -1023,6 +1045,45 @@ def test_how_weight_gradients_are_handed_over_does_not_change_the_result(model, 
     assert _digest_after_steps({"wgrad_batch_us": 1000000}, side_streams="torch", **kw) == base
 
 
+@pytest.mark.parametrize("options", [{}, {"wgrad_batch_us": 0}, {"wgrad_batch_us": 1000000}, {"wgrad_stream": 0}])
+@pytest.mark.parametrize("model,dtype,n,kw", [
+    ("vgg16", "bf16", 3, dict(H=32, W=32, C=3, classes=10, arch=(16, 32, 2, 2, 3, 3, 3))),         # windows side by side
+    ("alexnet", "bf16", 3, dict(H=103, W=83, C=3, classes=10, arch=(16, 32))),                     # windows that overlap
+    ("alexnet", "f32", 2, dict(H=96, W=96, C=3, classes=10, arch=(8, 32))),
+])
+def test_bias_gradients_before_a_pool(model, dtype, n, kw, options):
+    """Every convolution with the pool behind it, backward together as in a step: the bias gradient, which is summed over the
+    pool's gradient, tensor by tensor against float64.  A channel's sum runs in float32 chains of at most some 256 terms: 256 times
+    2^-24 of the sum of their sizes."""
+    import paper_1909_11985_amd as E
+    rng = np.random.default_rng(5)
+    with E.options(**options):
+        case = Case(model, dtype, n, perturb=0.05, **kw)
+        job = case.job
+        job.debug_forward(np.arange(n))
+        graph = case.oracle(False).graph
+        ops = [op for op in graph.ops if op["kind"] != "flatten"]
+        pairs = 0
+        for gi in range(len(ops) - 1):
+            conv, pool = ops[gi], ops[gi + 1]
+            if conv["kind"] != "conv" or pool["kind"] != "maxpool":
+                continue
+            act = job.debug_get(tid(conv["y"]), n).astype(np.float64)
+            pooled, arg = O.maxpool_forward(np.ascontiguousarray(act), pool["k"], pool["stride"], pool["pad"])
+            assert np.array_equal(job.debug_get(tid(pool["y"]), n), pooled)
+            dpool = O.round_bf16(rng.standard_normal(pooled.shape))
+            job.debug_set(tid(pool["y"]), dpool, which=1)
+            job.debug_backward_range(gi, gi + 2, n)
+            terms = (dpool * (pooled > 0)).reshape(-1, conv["K"])
+            got = job.grad_slice(0, conv["b_off"], conv["K"])
+            assert (np.abs(got - terms.sum(0)) <= 256 * 2.0 ** -24 * np.abs(terms).sum(0)).all(), conv["name"]
+            dy = O.maxpool_backward(np.ascontiguousarray(dpool), arg, act.shape) * (act > 0)
+            assert relerr(job.debug_get(tid(conv["y"]), n, which=1), dy) < (1e-6 if dtype == "f32" else 4e-3), conv["name"]
+            pairs += 1
+        assert pairs == (5 if model == "vgg16" else 3)
+        case.close()
+
+
 def test_the_update_started_during_the_backward_pass_does_not_change_the_result():
     """The update of layers whose gradients are final starts during the last backward pass of a step, in pieces on
     a third stream (by default only from layers of 16 M weights on; here from every layer, and with the
@@ -1228,9 +1289,49 @@ def test_an_infinite_gradient_stays_infinite(classes, dtype):
 ])
 def test_small_float32_fully_connected_layers(C, arch, n):
     """Layers of few 32x32 tiles, up to the number of tiles and the length of the reduction at which tiled launches take over:
-    ragged rows and columns, reductions that end inside a step and that give some of the four waves nothing."""
+    ragged rows and columns, reductions that end inside a step and that give some of the sixteen waves nothing."""
     _assert_layerwise(layerwise_parity("mlp", "f32", n, verbose=False, H=1, W=1, C=C, classes=12, arch=arch), "f32")
     _assert_layerwise(relu_producer_pair_parity("mlp", "f32", n, H=1, W=1, C=C, classes=12, arch=arch), "f32")
+
+
+@pytest.mark.parametrize("dtype,C0,n,fwd,dgrad", [
+    ("f32", 8, 64, 3, 2), ("bf16", 8, 64, 0, 0),
+    ("f32", 6, 64, 2, 2),                                 # a reduction that is no whole vectors
+    ("f32", 2048, 64, 3, 2), ("f32", 2052, 64, 2, 2),     # the longest reduction, one that is too long
+    ("f32", 8, 4096, 3, 2), ("f32", 8, 4097, 1, 0),       # 256 tiles, and 258: only the classifier's forward contraction is left
+])
+def test_which_layers_the_float32_kernel_of_few_tiles_takes(dtype, C0, n, fwd, dgrad):
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=1, max_shard=n, H=1, W=1, C_=C0, arch=(64, 64), classes=16), 2)
+    x, y = synth_inputs.dataset(1, n, 1, 1, C0, 16)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    got = _launches(job, 1)
+    assert (got.get("small_fc_fwd", 0), got.get("small_fc_dgrad", 0)) == (fwd, dgrad), got
+    job.shutdown()
+
+
+@pytest.mark.parametrize("dtype,bound", [("f32", 1e-5), ("bf16", 4e-3)])
+@pytest.mark.parametrize("classes", [10, 16, 100])
+def test_input_gradients_of_small_layers_add_to_what_is_there(classes, dtype, bound):
+    """A gradient that another reader has left in the buffer is added to (few ragged outputs, few tiles, the tiled kernel in bf16).
+    bf16: one rounding, 2^-8 of the value at most."""
+    n, C = 21, 72
+    case = Case("mlp", dtype, n, H=1, W=1, C=8, classes=classes, arch=(16, C))
+    job = case.job
+    logits, hidden = len(case.tensors) - 1, len(case.tensors) - 2
+    rng = np.random.default_rng(3)
+    dy, there = O.round_bf16(rng.standard_normal((n, classes))), O.round_bf16(rng.standard_normal((n, C)))
+    job.debug_forward(np.arange(n))
+    job.debug_set(logits, dy.reshape(n, 1, 1, classes), which=1)
+    job.debug_set(hidden, there.reshape(n, 1, 1, C), which=1)
+    last = job.debug_op_count() - 2
+    job.debug_backward_range_from(last, last + 1, n, [hidden])
+    w = job.params()[-(C * classes + classes):-classes].reshape(classes, C).astype(np.float64)
+    w = O.round_bf16(w) if dtype == "bf16" else w
+    assert relerr(job.debug_get(hidden, n, which=1).reshape(n, C), there + dy @ w) < bound
+    case.close()
 
 
 @pytest.mark.parametrize("cut", [[16, 16, 16, 16], [16, 3, 1, 40], [17, 15]])
