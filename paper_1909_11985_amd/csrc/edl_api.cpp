@@ -1097,18 +1097,22 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 } else {
                     waiting.push_back(ii);
                     if (aside) h->bias_waiting[ii] = premasked_for == ii ? 2 : 1;
-                    // From 15 us of work on, and a layer of 8 us at once.  us per step: each layer by itself / from 15 with 10 at
+                    // From 15 us of work on, and a layer of 8 or 10 us at once.  us per step: each layer by itself / from 15 with 10 at
                     // once / 15 and 8 / 20 and 8 / 25 and 8 (MLP, 4 x 16: 116 / 61 to 70 whichever)
-                    //   ResNet-20 1 x 8 1,228 / 1,079 / 1,039 / 1,003 / 999   ResNet-50 of 112x112 1 x 8 2,928 / 2,382 / 2,388 / 2,305 / 2,262
                     //   VGG-16 of 64x64 1 x 4 761 / 782 / 771 / 770 / 770     1 x 8 794 / 805 / 793 / 807 / 806
                     //   2 x 8 924 / 943 / 925 / 924 / 925                     1 x 32 1,015 / 1,029 / 1,015 / 1,015 / 1,015
                     //   of 112x112 1 x 4 890 / 897 / 893 / 900 / 906
                     //   AlexNet of 96x96 1 x 16 425 / 450 / 427 / 431 / 431   of 224x224 1 x 16 749 / 764 / 754 / 750 / 755
-                    // A layer of 8 to 10 us that waits for the next leaves the second stream idle for as long as its event costs;
-                    // larger jobs are the same within 1%.
+                    //   ResNet-20 1 x 8 1,228 / 1,079 / 1,039 / 1,003 / 999   3 x 8 1,339 / 1,126 / 1,280
+                    //   ResNet-50 of 112x112 1 x 8 2,928 / 2,382 / 2,388 / 2,305 / 2,262
+                    // A layer of 8 to 10 us that waits for the next leaves the second stream idle for longer than its event costs on
+                    // the chain.  Not so where the event's host time counts (nets with batch norms launch three times as much per layer:
+                    // ResNet-20, 3 x 8), or where nothing but the first layer is left to run beside it and the wait at the end of the
+                    // pass is for that layer alone (MLP 784-100-300-10, 8 x 256: 104 behind the chain, 114 handed over).
                     const double us = weight_gradient_us(dt, q, S.p), batch = (double)tune().wgrad_batch_us;
                     waiting_us += us;
-                    if (early || waiting_us >= batch || us >= batch * 8 / 15) handed_over = hand_over();
+                    const double at_once = batch * (!h->has_bn && (used_side || conv_ordinal > 1) ? 8 : 10) / 15;
+                    if (early || waiting_us >= batch || us >= at_once) handed_over = hand_over();
                 }
                 // Parameters are laid out in layer order, so everything from this layer's weights on now has its
                 // final gradient: the second stream holds the weight gradients, and the event it waited for
