@@ -288,7 +288,8 @@ void plan_arena(const edl_config& c, const Graph& g, Layout& L) {
         const Op& op = g.ops[i];
         if (op.kind == OP_CONV) {
             const Tensor& tx = g.tensors[(size_t)op.x];
-            // fully connected layers: none, the input gradient reads the bf16 weights themselves
+            // none where the input gradient reads the weights themselves: fully connected layers, of whole vectors in bf16, small
+            // ones (for passes of this many samples) in either type
             const bool in_place = conv_dgrad_reads_weights(c.dtype, geom_of(g, op, L.pass_samples), op.w_off);
             if (storage_of(g, op.x) != 0 && !in_place) L.wT[i] = take((int64_t)op.K * op.R * op.S * tx.C * esz);
             else if (op.x == 0 && L.cpad != tx.C) L.wpad[i] = take((int64_t)op.K * op.R * op.S * L.cpad * esz);

@@ -318,6 +318,11 @@ __global__ __launch_bounds__(64 * kSmallWaves) void small_fc_kernel(SmallArgs a)
     }
 }
 
+// Up to 256 tiles (one per CU) and a reduction of 2,048 (the longest that keeps the chains at 64).  Steps of a job of two such layers of
+// equal width, this kernel / tiled, us:
+//   width 256, 16 tiles 68 / 90, 256 tiles 105 / 127          1,024, 64 tiles 97 / 106, 256 tiles 120 / 139
+//   2,048, 64 tiles 142 / 144, 128 tiles 153 / 153, 256 tiles 173 / 190
+// Past the line the short reductions still gain and the long ones lose: 512 tiles 124 / 144, 156 / 171, 239 / 241, and 524 / 487 at 4,096.
 bool small_fc_takes(int dtype, const ConvGeom& g, int K, int N, int samples) {
     return dtype != 1 && g.H == 1 && g.W == 1 && g.R == 1 && g.S == 1 && g.stride == 1 && g.pad == 0 && K % 4 == 0 &&
            K <= kSmallReduction && (int64_t)((samples + 31) / 32) * ((N + 31) / 32) <= kSmallTiles;
