@@ -40,7 +40,7 @@ def test_shard_assignment_is_bit_exact(E, seed, N, B):
                 assert idx.dtype == np.int64 and np.array_equal(idx, io) and np.array_equal(off, oo)
 
 
-@pytest.mark.parametrize("N,B", [(4096, 1), (65536, 16), (100000, 250), (262144, 512), (1 << 20, 64)])
+@pytest.mark.parametrize("N,B", [(4096, 1), (65536, 16), (100000, 250), (262144, 512), (500000, 1000), (1 << 20, 64)])
 def test_shard_assignment_by_followed_entries(E, N, B):
     """Mini-batches that are a small part of a large data set are not walked to but followed back: every part of the epoch,
     its first and last mini-batch, against the whole permutation."""
