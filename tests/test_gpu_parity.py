@@ -728,6 +728,58 @@ def test_unequal_shards_weigh_in_with_their_share(model, dtype):
         assert ei.value.code == code, (bad, ei.value)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("workers", [1, 2, 3, 4, 5, 6, 7, 8, 9, 16])
+def test_unequal_shares_are_applied_at_every_number_of_workers(workers, dtype):
+    """The update of unequal shards has a kernel for each number of gradients up to 8 and one for more; parameters that do not end on
+    a vector.  (An empty shard leaves its worker out.)  Float32 sums of up to 16 products: 1e-6."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    sizes = [k % 3 + 1 for k in range(workers)]
+    if workers < 16:
+        sizes.insert(workers // 2, 0)
+    B = sum(sizes)
+    job = E.Job(make_config("mlp", dtype=dtype, N=2 * B, B=B, p_max=16, max_shard=max(sizes), lr=0.05, H=1, W=1, C_=7, arch=(34, 9), classes=5), 3)
+    assert job.P % 4 != 0
+    x, y = synth_inputs.dataset(1, 2 * B, 1, 1, 7, 5)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    idx, _ = job.shard(B, 1, 0, 0)
+    job.set_momentum(synth_inputs.vector(4, job.P, 0.05))
+    w0, v0 = job.params().astype(np.float64), job.momentum().astype(np.float64)
+    job.gradients(len(sizes), idx, np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64))
+    live = [k for k, n in enumerate(sizes) if n]
+    G = [job.grad(k).astype(np.float64) for k in live]
+    job.apply(len(sizes))
+    w1, v1 = O.sgd_momentum_update(w0, v0, G, 0.05, 0.9, 5e-4, weights=[sizes[k] / B for k in live])
+    assert relerr(job.momentum(), v1) < 1e-6 and relerr(job.params(), w1) < 1e-6
+    job.shutdown()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes", [2, 63, 64, 65])
+@pytest.mark.parametrize("n", [1, 16, 17, 64, 65])
+def test_loss_of_small_shards_and_few_classes(n, classes, dtype):
+    """Losses and their gradients on both sides of what the kernel of small shards takes (64 samples, 64 classes), against float64 on
+    the logits as they are: float32 exponentials and a sum of up to 65, 1e-5; a bf16 gradient rounds by up to 2^-8.  (A probability near
+    1 is known to 2^-24, and so is what is left of it when 1 is taken off.)"""
+    case = Case("mlp", dtype, n, H=1, W=1, C=8, classes=classes, arch=(16, 16), perturb=0.5)
+    job = case.job
+    logits = len(case.tensors) - 1
+    job.debug_forward(np.arange(n))
+    z = 4.0 * job.debug_get(logits, n).reshape(n, classes)
+    job.debug_set(logits, z.reshape(n, 1, 1, classes))
+    job.debug_forward_op(job.debug_op_count() - 1, n)
+    z = z.astype(np.float64)
+    e = np.exp(z - z.max(1, keepdims=True))
+    prob, label = e / e.sum(1, keepdims=True), case.y[:n]
+    assert abs(job.losses(1)[0] + np.log(prob[np.arange(n), label]).mean()) < 1e-5 * max(1.0, np.abs(z).max())
+    prob[np.arange(n), label] -= 1.0
+    off = np.linalg.norm(job.debug_get(logits, n, which=1).reshape(n, classes) - prob / n)
+    assert off < (1e-5 if dtype == "f32" else 4e-3) * np.linalg.norm(prob / n) + 2.0 ** -23 / np.sqrt(n)
+    case.close()
+
+
 def test_a_tail_batch_of_the_pipeline_trains():
     """Two partitions of 12 half read by two workers, then a third worker joins when nothing is unassigned:
     the pipeline's tail mini-batch has shards 6 + 6 + 0; edl_step takes it as it is."""
@@ -1338,6 +1390,8 @@ def test_input_gradients_of_small_layers_add_to_what_is_there(classes, dtype, bo
 def test_small_shards_leave_their_bias_gradients(cut):
     """Shards of one row block (their sums are stored as bias gradients where they are formed) and of several, together."""
     test_shards_of_one_pass_are_computed_as_each_alone("mlp", "f32", dict(H=1, W=1, C=48, classes=10, arch=(64, 256)), cut)
+    # input gradients whose reduction is cut: the finishing kernel masks, sums and stores
+    test_shards_of_one_pass_are_computed_as_each_alone("mlp", "bf16", dict(H=1, W=1, C=48, classes=16, arch=(1024, 2048)), cut)
 
 
 @pytest.mark.parametrize("model,dtype,kw,cut", [
