@@ -1847,7 +1847,7 @@ static RowCut tile_cut(const ShardSet& S, int rows_per_sample, int bm, bool want
 // forward 128x128 tiles lose 2% (full-length steps have fewer barriers than strips there), 64x64 tiles gain nothing.
 static bool takes_strips(int dtype, int mode, const ConvGeom& g, TileCfg t) {
     const int inner = mode == CONV_FWD ? g.C : g.K, row = dtype == 1 ? 32 : 16;
-    return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && inner % row == 0 &&
+    return g.R == 3 && g.S == 3 && g.stride == 1 && g.pad == 1 && g.Ho == g.H && g.Wo == g.W && inner % row == 0 &&
            (mode == CONV_DGRAD || t == T128x64 || t == T128x32);
 }
 

@@ -724,50 +724,96 @@ __global__ __launch_bounds__(256) void gather_pad_kernel(const float* __restrict
     if (blockIdx.x == 0 && threadIdx.x == 0) out_y[i] = data_y[s];
 }
 
-void launch_gather_pad(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n, int64_t pixels,
-                       int C, void* out_x, int32_t* out_y, hipStream_t st) {
+// Images of three channels with F x F pixels as one (InputFold): a lane writes one such pixel, F rows of 3 F floats in,
+// whole vectors out.  grid: (pixel chunks, n)
+template <typename T, int F>
+__global__ __launch_bounds__(256) void gather_fold_kernel(const float* __restrict__ data_x, const int32_t* __restrict__ data_y,
+                                                          const int64_t* __restrict__ idx, int H, int W, InputFold in,
+                                                          T* __restrict__ out_x, int32_t* __restrict__ out_y) {
+    constexpr int VEC = Elem<T>::VEC, ROW = 3 * F, VECS = (F * ROW + VEC - 1) / VEC;
+    const int i = blockIdx.y;
+    const int64_t s = idx[i];
+    const float* src = data_x + s * H * W * 3;
+    const int pixels = in.H * in.W;
+    T* dst = out_x + (int64_t)i * pixels * (VECS * VEC);
+    for (int q = blockIdx.x * blockDim.x + threadIdx.x; q < pixels; q += gridDim.x * blockDim.x) {
+        const int hb = q / in.W, h0 = hb * F - in.lead, w0 = (q - hb * in.W) * F - in.lead;
+        Vec16<T> v[VECS];
+        #pragma unroll
+        for (int k = 0; k < VECS; ++k)
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) v[k].e[e] = Elem<T>::from_f32(0.f);
+        #pragma unroll
+        for (int r = 0; r < F; ++r)
+            #pragma unroll
+            for (int c = 0; c < ROW; ++c) {
+                const int h = h0 + r, w = w0 + c / 3;
+                const bool ok = (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W;
+                const int64_t at = ok ? ((int64_t)h * W + w0) * 3 + c : 0;
+                const float f = src[at];
+                v[(r * ROW + c) / VEC].e[(r * ROW + c) % VEC] = Elem<T>::from_f32(ok ? f : 0.f);
+            }
+        #pragma unroll
+        for (int k = 0; k < VECS; ++k) store_vec(dst + ((int64_t)q * VECS + k) * VEC, v[k]);
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) out_y[i] = data_y[s];
+}
+
+void launch_gather_pad(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n, int H, int W, int C,
+                       const InputFold& in, void* out_x, int32_t* out_y, hipStream_t st) {
+    const int64_t pixels = (int64_t)in.H * in.W;
     dim3 grid(grid_for(pixels, 256, 256), n);
-    ProfScope ps("gather", 0.0, (4.0 * C + 16.0) * (double)pixels * n, st);
-    if (dtype == 1)
+    ProfScope ps("gather", 0.0, (4.0 * C * H * W + (dtype == 1 ? 2.0 : 4.0) * in.C * (double)pixels) * n, st);
+    if (in.f == 2)
+        hipLaunchKernelGGL((gather_fold_kernel<bf16_t, 2>), grid, dim3(256), 0, st, data_x, data_y, idx, H, W, in, (bf16_t*)out_x, out_y);
+    else if (in.f == 4)
+        hipLaunchKernelGGL((gather_fold_kernel<bf16_t, 4>), grid, dim3(256), 0, st, data_x, data_y, idx, H, W, in, (bf16_t*)out_x, out_y);
+    else if (dtype == 1)
         hipLaunchKernelGGL(gather_pad_kernel<bf16_t>, grid, dim3(256), 0, st, data_x, data_y, idx, pixels, C, (bf16_t*)out_x, out_y);
     else
         hipLaunchKernelGGL(gather_pad_kernel<float>, grid, dim3(256), 0, st, data_x, data_y, idx, pixels, C, (float*)out_x, out_y);
 }
 
-// dst[k][t][0..Cp) = cast(src[k][t][0..C)), zero beyond C  (weights of a convolution on padded images)
+// dst[k][r][s][0..in.C) = cast of the weights of tap (r f + i, s f + j) at ((i f + j) C + c), zero where there are none
 template <typename T>
-__global__ __launch_bounds__(256) void pad_weights_kernel(const float* __restrict__ src, T* __restrict__ dst, int64_t rows, int C, int Cp) {
-    const int64_t total = rows * Cp;
+__global__ __launch_bounds__(256) void pad_weights_kernel(const float* __restrict__ src, T* __restrict__ dst, int K, int R, int S, int C, InputFold in) {
+    const int f = in.f, Sf = (S + f - 1) / f, Rf = (R + f - 1) / f;
+    const int64_t total = (int64_t)K * Rf * Sf * in.C;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / Cp;
-        const int c = (int)(i - r * Cp);
-        dst[i] = Elem<T>::from_f32(c < C ? src[r * C + c] : 0.f);
+        const int64_t t = i / in.C, kr = t / Sf;
+        const int ch = (int)(i - t * in.C), sub = ch / C, k = (int)(kr / Rf);
+        const int r = (int)(kr - (int64_t)k * Rf) * f + sub / f, s = (int)(t - kr * Sf) * f + sub % f;
+        const bool ok = sub < f * f && r < R && s < S;
+        dst[i] = Elem<T>::from_f32(ok ? src[(((int64_t)k * R + r) * S + s) * C + (ch - sub * C)] : 0.f);
     }
 }
 
-void launch_pad_weights(int dtype, const float* src, void* dst, int64_t rows, int C, int Cp, hipStream_t st) {
-    const int grid = grid_for(rows * Cp, 256, 4096);
-    ProfScope ps("pad_weights", 0.0, 4.0 * (double)rows * C + (dtype == 1 ? 2.0 : 4.0) * (double)rows * Cp, st);
-    if (dtype == 1) hipLaunchKernelGGL(pad_weights_kernel<bf16_t>, dim3(grid), dim3(256), 0, st, src, (bf16_t*)dst, rows, C, Cp);
-    else hipLaunchKernelGGL(pad_weights_kernel<float>, dim3(grid), dim3(256), 0, st, src, (float*)dst, rows, C, Cp);
+void launch_pad_weights(int dtype, const float* src, void* dst, int K, int R, int S, int C, const InputFold& in, hipStream_t st) {
+    const double from = (double)K * R * S * C, to = (double)K * ((R + in.f - 1) / in.f) * ((S + in.f - 1) / in.f) * in.C;
+    const int grid = grid_for((int64_t)to, 256, 4096);
+    ProfScope ps("pad_weights", 0.0, 4.0 * from + (dtype == 1 ? 2.0 : 4.0) * to, st);
+    if (dtype == 1) hipLaunchKernelGGL(pad_weights_kernel<bf16_t>, dim3(grid), dim3(256), 0, st, src, (bf16_t*)dst, K, R, S, C, in);
+    else hipLaunchKernelGGL(pad_weights_kernel<float>, dim3(grid), dim3(256), 0, st, src, (float*)dst, K, R, S, C, in);
 }
 
-// dst[r][0..C) = src[r][0..C) of rows of Cp floats (gradient of the padded weights back to the flat vectors);
-// grid: (chunks, shards)
-__global__ __launch_bounds__(256) void unpad_rows_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t dst_stride,
-                                                         ShardSet S, int64_t rows, int C, int Cp) {
-    const int64_t total = rows * C;
-    src += (int64_t)blockIdx.y * rows * Cp;
-    dst += (int64_t)S.k[blockIdx.y] * dst_stride;
+// the same elements of the padded weights' gradient back to the flat vectors; grid: (chunks, shards)
+__global__ __launch_bounds__(256) void unpad_weights_kernel(const float* __restrict__ src, float* __restrict__ dst, int64_t dst_stride,
+                                                            ShardSet set, int K, int R, int S, int C, InputFold in) {
+    const int f = in.f, Sf = (S + f - 1) / f, Rf = (R + f - 1) / f;
+    const int64_t total = (int64_t)K * R * S * C;
+    src += (int64_t)blockIdx.y * K * Rf * Sf * in.C;
+    dst += (int64_t)set.k[blockIdx.y] * dst_stride;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / C;
-        dst[i] = src[r * Cp + (i - r * C)];
+        const int64_t t = i / C, kr = t / S;
+        const int c = (int)(i - t * C), s = (int)(t - kr * S), k = (int)(kr / R), r = (int)(kr - (int64_t)k * R);
+        dst[i] = src[(((int64_t)k * Rf + r / f) * Sf + s / f) * in.C + ((r % f) * f + s % f) * C + c];
     }
 }
 
-void launch_unpad_rows(const float* src, GradDst dst, const ShardSet& S, int64_t rows, int C, int Cp, hipStream_t st) {
-    ProfScope ps("unpad_rows", 0.0, 8.0 * (double)rows * C * S.p, st);
-    hipLaunchKernelGGL(unpad_rows_kernel, dim3(grid_for(rows * C, 256, 4096), S.p), dim3(256), 0, st, src, dst.g, dst.stride, S, rows, C, Cp);
+void launch_unpad_weights(const float* src, GradDst dst, const ShardSet& set, int K, int R, int S, int C, const InputFold& in, hipStream_t st) {
+    const int64_t n = (int64_t)K * R * S * C;
+    ProfScope ps("unpad_weights", 0.0, 8.0 * (double)n * set.p, st);
+    hipLaunchKernelGGL(unpad_weights_kernel, dim3(grid_for(n, 256, 4096), set.p), dim3(256), 0, st, src, dst.g, dst.stride, set, K, R, S, C, in);
 }
 
 void launch_gather(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n,

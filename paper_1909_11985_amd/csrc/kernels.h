@@ -99,13 +99,17 @@ void launch_cast_bf16(const float* src, uint16_t* dst, int64_t n, hipStream_t st
 void launch_gather(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n,
                    int64_t sample_elems, void* out_x, int32_t* out_y, hipStream_t st);
 
-// images with C channels written as pixels of one zero-padded 16-byte vector each
-void launch_gather_pad(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n, int64_t pixels,
-                       int C, void* out_x, int32_t* out_y, hipStream_t st);
-// weights [rows][C] float32 -> [rows][Cp] dtype, zero padded; and the way back for their gradient (one per shard:
-// src holds the shards' one after another)
-void launch_pad_weights(int dtype, const float* src, void* dst, int64_t rows, int C, int Cp, hipStream_t st);
-void launch_unpad_rows(const float* src, GradDst dst, const ShardSet& S, int64_t rows, int C, int Cp, hipStream_t st);
+// How the input images are stored: f x f blocks of pixels as one pixel of C channels, (row in the block, column in the
+// block, channel) one after another and zeros up to C; `lead` rows and columns of zeros stand before the image's first.
+// f = 1: pixels padded to one vector, or as they are.
+struct InputFold { int f = 1, lead = 0, H = 0, W = 0, C = 0; };
+// images of H x W x C written that way (C less than a vector; f > 1: C = 3)
+void launch_gather_pad(int dtype, const float* data_x, const int32_t* data_y, const int64_t* idx, int n, int H, int W, int C,
+                       const InputFold& in, void* out_x, int32_t* out_y, hipStream_t st);
+// float32 weights [K][R][S][C] of the convolution that reads them as [K][R/f][S/f][in.C] dtype, zero padded; and the way
+// back for their gradient (one per shard: src holds the shards' one after another)
+void launch_pad_weights(int dtype, const float* src, void* dst, int K, int R, int S, int C, const InputFold& in, hipStream_t st);
+void launch_unpad_weights(const float* src, GradDst dst, const ShardSet& set, int K, int R, int S, int C, const InputFold& in, hipStream_t st);
 
 // ---- implicit-GEMM convolution --------------------------------------------
 enum ConvMode { CONV_FWD = 0, CONV_DGRAD = 1, CONV_WGRAD = 2 };

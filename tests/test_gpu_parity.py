@@ -1235,6 +1235,19 @@ def test_strided_and_padded_geometries_layerwise():
         _assert_layerwise(layerwise_parity("resnet50", dtype, 3, verbose=False, **geom), dtype)
 
 
+@pytest.mark.parametrize("model,H,W,C", [
+    ("resnet50", 33, 40, 3), ("resnet50", 40, 33, 3), ("resnet50", 35, 37, 3), ("resnet50", 34, 36, 1), ("resnet50", 33, 34, 7),
+    ("alexnet", 63, 66, 3), ("alexnet", 64, 65, 3), ("alexnet", 65, 64, 3), ("alexnet", 66, 67, 3), ("alexnet", 67, 63, 2),
+])
+def test_first_convolutions_on_blocks_of_pixels(model, H, W, C):
+    """bf16 images of three channels are stored as blocks of stride x stride pixels: every remainder of the image by the
+    stride, and channel counts that keep one pixel per vector."""
+    arch = (8, 1, 1, 1, 0) if model == "resnet50" else (8, 16)
+    geom = dict(H=H, W=W, C=C, classes=7, arch=arch)
+    for n in (1, 5):
+        _assert_layerwise(layerwise_parity(model, "bf16", n, verbose=False, **geom), "bf16")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("classes,arch,n", [
     (10, (64, 256), 40), (3, (30, 70), 5), (17, (65, 9), 1), (127, (64, 64), 130), (129, (64, 64), 33), (6, (128, 1024), 1030),
