@@ -10,6 +10,7 @@
 #include <mutex>
 #include <vector>
 
+#include "bn_pointwise.h"
 #include "graph.h"
 #include "kernels.h"
 #include "profiler.h"
@@ -431,6 +432,7 @@ struct edl_handle {
     std::vector<char> written;           // backward pass: which gradient buffers hold something (per tensor)
     std::vector<size_t> wgrad_waiting;   // a backward pass: layers whose weight gradient is yet to be launched
     std::vector<char> bias_waiting;      // ... of them, those whose bias gradient goes with it (2: from the pool after the layer)
+    std::vector<char> dw_in_pieces;      // ... those whose weight gradient is there in pieces that are yet to be added up
     bool has_bn = false;
     std::vector<char> op_done;           // a pass: layers already launched out of list order (on the branch stream)
     // backward pass, per tensor: where the gradient "already there" is to be read from if not from the tensor's
@@ -730,6 +732,7 @@ int32_t edl_init(edl_handle** out, const edl_config* cfg, uint64_t seed, void* d
     h->op_done.assign(h->g.ops.size(), 0);
     h->wgrad_waiting.reserve(h->g.ops.size());
     h->bias_waiting.assign(h->g.ops.size(), 0);
+    h->dw_in_pieces.assign(h->g.ops.size(), 0);
     for (const Op& op : h->g.ops) h->has_bn = h->has_bn || op.kind == OP_BN;
     h->grad_alias.assign(h->g.tensors.size(), nullptr);
     h->shard_n.reserve(kMaxP);
@@ -1051,8 +1054,70 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
     hipEvent_t join_event = nullptr;
     size_t fused_for = (size_t)-1;   // the layer whose masked gradient and column sums the dgrad after it left
     RowCut fused_sums;
-    const SumsBuf sums_buf = {partial, (size_t)h->L.partial_floats};
+    float* fused_at = partial;       // ... and where the sums are
     size_t premasked_for = (size_t)-1;   // the layer whose gradient the max pool after it left masked by its ReLU
+    // If the layer just before in the list produced a convolution's input and ends in a ReLU, and
+    // the convolution is the first reader of that tensor in the list (so every other reader, such as
+    // the shortcut of a residual block, has already added its part), that layer's backward starts with
+    // the masked gradient and its column sums: the dgrad's epilogue can leave both (see DgradMask),
+    // and that layer then skips its own reduction pass.
+    auto producer_mask = [&](size_t ii, bool acc, float* sums) {
+        DgradMask mask = {};
+        const Op& op = g.ops[ii];
+        const int sx = storage_of(g, op.x);
+        const bool fuse_joins = tune().fused_mask_join != 0;
+        const bool last_writer = h->first_reader[(size_t)sx] == (int)ii &&
+                                 (h->readers[(size_t)sx] == 1 ? !acc : (fuse_joins && acc));
+        if (ii > op_lo && last_writer) {
+            const Op& prod = g.ops[ii - 1];
+            if (prod.relu && storage_of(g, prod.y) == sx && (prod.kind == OP_BN || prod.kind == OP_CONV)) {
+                mask.act = h->act(op.x);
+                if (prod.kind == OP_BN) mask.sign = h->sign(op.x);
+                mask.sums = SumsBuf{sums, (size_t)h->L.partial_floats};
+                if (prod.kind == OP_CONV && prod.bias) mask.dbias = grads_at(prod.b_off);
+                if (prod.kind == OP_BN) {
+                    mask.xin = h->act(prod.x);
+                    mask.mean_rstd = h->at<float>(h->L.bn_save[ii - 1]);
+                }
+            }
+        }
+        return mask;
+    };
+    // The convolution whose output batch norm ii normalises, if the two go backward in one launch (k_bn_pointwise.hip): a plain
+    // 1x1 convolution of many pixels, the gradient of whose output nothing else wants, the gradient of whose input nothing
+    // has been added to, and a batch norm whose own gradient is there masked.  Else ops.size().
+    auto conv_behind = [&](size_t ii) {
+        const size_t none = g.ops.size();
+        const Op& bn = g.ops[ii];
+        if (dt != EDL_DTYPE_BF16 || (bn.relu && fused_for != ii) || h->readers[(size_t)storage_of(g, bn.x)] != 1) return none;
+        size_t ic = ii;
+        while (ic > op_lo && !(g.ops[ic].kind == OP_CONV && g.ops[ic].y == bn.x)) --ic;
+        const Op& op = g.ops[ic];
+        if (op.kind != OP_CONV || op.y != bn.x || done[ic] || op.bias || op.relu || h->L.wT[ic] < 0 || h->L.wpad[ic] >= 0) return none;
+        const int sx = storage_of(g, op.x);
+        if (sx == 0 || written[(size_t)sx] != 0 || h->grad_alias[(size_t)sx] != nullptr) return none;
+        const DgradMask mask = producer_mask(ic, false, nullptr);
+        if (mask.act != nullptr && (mask.xin == nullptr || tune().fused_mask == 0)) return none;
+        return bn_pointwise_takes(dt, geom_stored(g, op, n, h->L.in), S) ? ic : none;
+    };
+    // ... and that launch, behind the batch norm's sums.  The pieces of the weight gradient lie where the gradient of the
+    // batch norm's input would; the column sums in a buffer of their own (a block's projection may come before they are read).
+    auto backward_through = [&](size_t ii, size_t ic, const void* dy, const float* bn_coef, hipStream_t bs) {
+        const Op& bn = g.ops[ii];
+        const Op& op = g.ops[ic];
+        const DgradMask mask = producer_mask(ic, false, h->sc<float>(h->L.partial_held));
+        BnPointwiseTask t = {};
+        t.x = h->act(bn.x); t.dy = dy;
+        t.gamma = h->w() + bn.w_off; t.save = h->at<float>(h->L.bn_save[ii]); t.coef = bn_coef;
+        t.act = h->act(op.x); t.wT = dgrad_weights(h, ic); t.dact = h->grad(op.x);
+        t.mask = mask.act != nullptr ? &mask : nullptr;
+        t.partial = (float*)h->grad(op.y);
+        const RowCut left = launch_bn_pointwise_backward(geom_stored(g, op, n, h->L.in), S, t, bs);
+        if (left.p > 0) { fused_for = ic - 1; fused_sums = left; fused_at = h->sc<float>(h->L.partial_held); }
+        written[(size_t)storage_of(g, op.x)] = 1;
+        h->dw_in_pieces[ic] = 1;
+        done[ic] = 1;
+    };
     auto bias_gradient = [&](size_t ii, bool premasked, const RowCut& sums, float* part, hipStream_t bs) {
         const Op& op = g.ops[ii];
         const GradDst dst = op.bias ? grads_at(op.b_off) : no_grads;
@@ -1068,6 +1133,11 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
     auto weight_gradient = [&](size_t ii, hipStream_t ws, float* scratch) {
         const Op& op = g.ops[ii];
         const ConvGeom q = geom_stored(g, op, n, h->L.in);
+        if (h->dw_in_pieces[ii] != 0) {       // its contraction went with the batch norm's backward
+            launch_bn_pointwise_reduce(q, S, (const float*)h->grad(op.y), grads_at(op.w_off), ws);
+            h->dw_in_pieces[ii] = 0;
+            return;
+        }
         if (h->bias_waiting[ii] != 0) {
             bias_gradient(ii, h->bias_waiting[ii] == 2, RowCut(), ws == h->side ? h->sc<float>(h->L.partial_side) : h->sc<float>(h->L.partial_held), ws);
             h->bias_waiting[ii] = 0;
@@ -1125,7 +1195,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 // gradient (VGG-16, shard of 32: 21 us a layer on the chain; jobs with batch norms use the second
                 // buffer of partial sums on their branch stream).
                 const bool aside = op.bias && !on_main && !h->has_bn && fused_for != ii && (premasked_for == ii || !op.relu);
-                if (!aside) bias_gradient(ii, premasked_for == ii, fused_for == ii ? fused_sums : RowCut(), partial, st);
+                if (!aside) bias_gradient(ii, premasked_for == ii, fused_for == ii ? fused_sums : RowCut(), fused_for == ii ? fused_at : partial, st);
                 const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
                 const bool early = early_p > 0 && overlap && !on_main && h->upd != nullptr && tune().early_update > 0 && own >= tune().early_update;
                 bool handed_over = false;
@@ -1189,34 +1259,13 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 if (!reads_weights) update_early();
                 const int sx = storage_of(g, op.x);
                 if (sx != 0) {
-                    // If the layer just before in the list produced this convolution's input and ends in a ReLU, and
-                    // this convolution is the first reader of that tensor in the list (so every other reader, such as
-                    // the shortcut of a residual block, has already added its part), that layer's backward starts with
-                    // the masked gradient and its column sums: the dgrad's epilogue can leave both (see DgradMask),
-                    // and that layer then skips its own reduction pass.
-                    DgradMask mask = {};
                     const bool acc = written[(size_t)sx] != 0;
-                    const bool fuse_joins = tune().fused_mask_join != 0;
-                    const bool last_writer = h->first_reader[(size_t)sx] == ii &&
-                                             (h->readers[(size_t)sx] == 1 ? !acc : (fuse_joins && acc));
-                    if (ii > op_lo && last_writer) {
-                        const Op& prod = g.ops[ii - 1];
-                        if (prod.relu && storage_of(g, prod.y) == sx && (prod.kind == OP_BN || prod.kind == OP_CONV)) {
-                            mask.act = h->act(op.x);
-                            if (prod.kind == OP_BN) mask.sign = h->sign(op.x);
-                            mask.sums = sums_buf;
-                            if (prod.kind == OP_CONV && prod.bias) mask.dbias = grads_at(prod.b_off);
-                            if (prod.kind == OP_BN) {
-                                mask.xin = h->act(prod.x);
-                                mask.mean_rstd = h->at<float>(h->L.bn_save[ii - 1]);
-                            }
-                        }
-                    }
+                    const DgradMask mask = producer_mask(ii, acc, partial);
                     const RowCut left = launch_conv_dgrad(dt, q, S, h->grad(op.y), dgrad_weights(h, ii), acc, h->grad(op.x),
                                                           h->sc<float>(h->L.splitk_scratch), (size_t)h->L.splitk_scratch_bytes,
                                                           mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr, reads_weights);
                     h->grad_alias[(size_t)sx] = nullptr;
-                    if (left.p > 0) { fused_for = ii - 1; fused_sums = left; }
+                    if (left.p > 0) { fused_for = ii - 1; fused_sums = left; fused_at = partial; }
                     written[(size_t)sx] = 1;
                 }
                 if (reads_weights) update_early();
@@ -1253,9 +1302,10 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 const size_t sy = (size_t)storage_of(g, op.y);
                 const void* const dy_src = h->grad_alias[sy] ? h->grad_alias[sy] : h->grad(op.y);
                 h->grad_alias[sy] = nullptr;
-                launch_bn_backward(dt, h->act(op.x), h->act(op.y), dy_src, h->grad(op.x), dres, dres_acc,
+                const size_t behind = dres == nullptr ? conv_behind(ii) : g.ops.size();
+                launch_bn_backward(dt, h->act(op.x), h->act(op.y), dy_src, behind < ii ? nullptr : h->grad(op.x), dres, dres_acc,
                                    h->w() + op.w_off, h->at<float>(h->L.bn_save[ii]), grads_at(op.w_off), grads_at(op.b_off),
-                                   S, t.H * t.W, t.C, op.relu && premasked_for != ii, partial, coef,
+                                   S, t.H * t.W, t.C, op.relu && premasked_for != ii, fused_for == ii ? fused_at : partial, coef,
                                    fused_for == ii ? fused_sums : RowCut(), st);
                 written[(size_t)sx] = 1;
                 // The gradient of the shortcut is final now.  If the shortcut is a projection (the convolution and
@@ -1280,27 +1330,33 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                             const size_t spy = (size_t)storage_of(g, pb.y);
                             const void* const pdy = h->grad_alias[spy] ? h->grad_alias[spy] : h->grad(pb.y);
                             h->grad_alias[spy] = nullptr;
-                            launch_bn_backward(dt, h->act(pb.x), h->act(pb.y), pdy, h->grad(pb.x), nullptr, false,
+                            const size_t pbehind = conv_behind(ii - 1);
+                            launch_bn_backward(dt, h->act(pb.x), h->act(pb.y), pdy, pbehind < ii ? nullptr : h->grad(pb.x), nullptr, false,
                                                h->w() + pb.w_off, h->at<float>(h->L.bn_save[ii - 1]), grads_at(pb.w_off), grads_at(pb.b_off),
                                                S, tb.H * tb.W, tb.C, pb.relu, ps, h->sc<float>(h->L.coef_side), RowCut(), bs);
                             written[(size_t)storage_of(g, pb.x)] = 1;
                             const ConvGeom qj = geom_stored(g, pj, n, h->L.in);
-                            launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? grads_at(pj.b_off) : no_grads, S,
-                                                      qj.Ho * qj.Wo, pj.K, pj.relu, ps, RowCut(), bs);
+                            if (pbehind < ii) backward_through(ii - 1, pbehind, pdy, h->sc<float>(h->L.coef_side), bs);
+                            else launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? grads_at(pj.b_off) : no_grads, S,
+                                                           qj.Ho * qj.Wo, pj.K, pj.relu, ps, RowCut(), bs);
                             // weight gradient: on the first side stream like every other, behind this stream's work
                             hipStream_t ws = bs;
                             if (hipEventRecord(wg, bs) == hipSuccess && hipStreamWaitEvent(h->side, wg, 0) == hipSuccess) {
                                 ws = h->side;
                                 used_side = true;
                             }
-                            launch_conv_wgrad(dt, qj, S, h->act(pj.x), h->grad(pj.y), grads_at(pj.w_off),
-                                              ws == h->side ? h->sc<float>(h->L.wgrad_scratch) : nullptr,
-                                              ws == h->side ? (size_t)h->L.wgrad_scratch_bytes : 0, ws);
-                            // input gradient, with this stream's own split-reduction scratch; nothing to hand over (the
-                            // block's first convolution is the last to add to this gradient)
-                            launch_conv_dgrad(dt, qj, S, h->grad(pj.y), dgrad_weights(h, ii - 2), written[(size_t)pj_sx] != 0,
-                                              h->grad(pj.x), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, nullptr, bs,
-                                              nullptr, h->L.wT[ii - 2] < 0);
+                            if (pbehind < ii) {
+                                weight_gradient(pbehind, ws, nullptr);
+                            } else {
+                                launch_conv_wgrad(dt, qj, S, h->act(pj.x), h->grad(pj.y), grads_at(pj.w_off),
+                                                  ws == h->side ? h->sc<float>(h->L.wgrad_scratch) : nullptr,
+                                                  ws == h->side ? (size_t)h->L.wgrad_scratch_bytes : 0, ws);
+                                // input gradient, with this stream's own split-reduction scratch; nothing to hand over (the
+                                // block's first convolution is the last to add to this gradient)
+                                launch_conv_dgrad(dt, qj, S, h->grad(pj.y), dgrad_weights(h, ii - 2), written[(size_t)pj_sx] != 0,
+                                                  h->grad(pj.x), h->sc<float>(h->L.splitk_side), (size_t)h->L.splitk_scratch_bytes, nullptr, bs,
+                                                  nullptr, h->L.wT[ii - 2] < 0);
+                            }
                             written[(size_t)pj_sx] = 1;
                             (void)hipEventRecord(dn, bs);
                             done[ii - 1] = done[ii - 2] = 1;
@@ -1308,6 +1364,15 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                             join_event = dn;
                             used_upd = true;
                         }
+                    }
+                }
+                if (behind < ii) {
+                    backward_through(ii, behind, dy_src, coef, st);
+                    if (overlap) {       // the pieces are added up beside the chain, with the next weight gradient handed over
+                        waiting.push_back(behind);
+                        waiting_us += 8;
+                    } else {
+                        weight_gradient(behind, st, nullptr);
                     }
                 }
                 break;

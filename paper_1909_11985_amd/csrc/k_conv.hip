@@ -2202,6 +2202,8 @@ size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S) {
     return wgrad_partial_bytes(g, S.p, plan_wgrad(dtype, one, S.plan_p).splits);
 }
 
+int conv_wgrad_chain(int dtype, const ConvGeom& g) { return plan_wgrad(dtype, g, 1).ksplit; }
+
 void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* dy, GradDst dw, float* scratch,
                        size_t scratch_bytes, hipStream_t st) {
     if (thin_wgrad_takes(dtype, g, S)) {
@@ -2229,7 +2231,7 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
     a.splits = p.splits;
     ConvGeom small = g;
     small.N = S.plan_smallest;
-    a.fold = plan_wgrad(dtype, small, 1).ksplit;     // no longer chains than those of the smallest shard alone
+    a.fold = conv_wgrad_chain(dtype, small);     // no longer chains than those of the smallest shard alone
     a.cut = cut_rows(S, g.Ho * g.Wo, p.ksplit);
     a.zdirect = direct;
     // (a kernel with the table of shards finds the worker's gradient itself)

@@ -499,6 +499,7 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
         ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
         EDL_FINALIZE(bn_bwd_finalize_kernel, cut, C, dgamma.g, dbeta.g, dgamma.stride, coef);
     }
+    if (dx == nullptr) return;
     // the dgrad that left the sums also left dy masked: the activation is then not read again
     const bool mask = relu && !fused;
     const bool acc = dres && dres_acc;

@@ -165,6 +165,8 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
 // what any p shards need of which the largest has up to g.N samples; and what those of one pass do
 size_t conv_wgrad_scratch_bytes(int dtype, const ConvGeom& g, int p);
 size_t conv_wgrad_needs(int dtype, const ConvGeom& g, const ShardSet& S);
+// pixels that the weight gradient of one shard of g.N samples sums in one chain, at most
+int conv_wgrad_chain(int dtype, const ConvGeom& g);
 
 // ---- batch norm, bias / ReLU backward --------------------------------------
 // floats the column reductions below take as scratch over the given rows of p shards
@@ -178,7 +180,8 @@ void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const
 // sign[i] = bits (act[8i + e] > 0) of n elements (a multiple of 8)
 void launch_signs(const void* act_bf16, unsigned char* sign, int64_t n, hipStream_t st);
 // sums.p > 0: partial already holds the two backward sums (left there by the dgrad that produced dy, which is then
-// also masked already); coef: 2C floats per shard
+// also masked already); coef: 2C floats per shard: means over the shard of dy and of dy * xhat.  dx null: these and the
+// gradients of the parameters only
 void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy, void* dx, void* dres,
                         bool dres_accumulate, const float* gamma, const float* save, GradDst dgamma, GradDst dbeta,
                         const ShardSet& S, int hw, int C, bool relu, float* partial, float* coef, const RowCut& sums,

@@ -53,6 +53,7 @@ const Entry kEntries[] = {
     {"bn_nt_bytes", &Tune::bn_nt_bytes},
     {"pointwise_rows", &Tune::pointwise_rows},
     {"pointwise_blocks", &Tune::pointwise_blocks},
+    {"bn_pointwise_rows", &Tune::bn_pointwise_rows},
     {"spare0", &Tune::spare0},
     {"spare1", &Tune::spare1},
 };

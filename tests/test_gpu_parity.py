@@ -5,7 +5,7 @@ import pytest
 
 import synth_inputs
 from oracle import oracle as O
-from parity_util import (TIGHT, TOL, Case, conv_bn_pair_parity, forced_parity, layerwise_ok, layerwise_parity, relerr,
+from parity_util import (TIGHT, TOL, Case, conv_bn_pair_parity, elementwise_excess, forced_parity, layerwise_ok, layerwise_parity, relerr,
                          per_tensor_relerr, relu_producer_pair_parity, run_parity, stepwise_parity, tid)
 
 pytestmark = pytest.mark.gpu
@@ -363,6 +363,91 @@ def test_streaming_pointwise_convolutions_keep_to_their_shard(blocks, together):
     kw = dict(H=50, W=42, C=3, classes=10, arch=(64, 1, 2, 1, 2))
     with E.options(pointwise_rows=0, pointwise_blocks=blocks):
         test_equal_shards_are_summed_in_the_same_order_wherever_they_run("resnet50", "bf16", kw, 9, 7, together)
+
+
+# a batch norm and the expanding convolution before it in one launch, at sizes far below those it is chosen for: runs of 4K rows
+_THROUGH = dict(bn_pointwise_rows=0, wgrad_blocks=1, wgrad_long_blocks=0)
+
+
+@pytest.mark.parametrize("n,H,W", [
+    (13, 50, 42),        # odd images: 1,859 rows of 256 channels, 546 of 512; the last run ends inside a tile
+    (8, 64, 64),         # 2,048 rows in eight full runs, 512 in one
+])
+def test_batch_norm_and_the_expanding_convolution_before_it_go_backward_together(n, H, W):
+    """The projection of the first stage (no mask) and the last convolutions of the first two stages (masked, with the column
+    sums of the batch norm before) against float64 on the tensors the launch was given: the gradient between the two layers
+    is rounded to bf16 on both sides, so that float32 sums are within roundings of that which fall otherwise (one in 10^4
+    by 2^-8: 1e-4 in the norm), and the bf16 output within its own rounding."""
+    import paper_1909_11985_amd as E
+    case = Case("resnet50", "bf16", n, H=H, W=W, C=3, classes=10, arch=(64, 2, 2, 1, 1), perturb=0.1)
+    job, rng = case.job, np.random.default_rng(0)
+    ops = [op for op in case.oracle(False).graph.ops if op["kind"] != "flatten"]
+    at = {op.get("name"): i for i, op in enumerate(ops)}
+    w = job.params().astype(np.float64)
+
+    def tensor(name, which=0):
+        a = job.debug_get(tid(name), n, which).astype(np.float64)
+        return a.reshape(-1, a.shape[-1])
+
+    def random_gradient(name):
+        th, tw, tc, _ = case.tensors[tid(name)]
+        job.debug_set(tid(name), rng.standard_normal((n, th, tw, tc), dtype=np.float32), which=1)
+
+    with E.options(**_THROUGH):
+        job.debug_forward(np.arange(n, dtype=np.int64))
+        for conv, bn, lo, hi in [("s1.b1.proj", "s1.b1.projbn", "s1.b1.proj", "s1.b1.projbn"), ("s1.b2.conv3", "s1.b2.bn3", "s1.b2.conv1", "s2.b1.conv1"),
+                                 ("s2.b2.conv3", "s2.b2.bn3", "s2.b2.conv1", "s3.b1.conv1")]:
+            c, b = ops[at[conv]], ops[at[bn]]
+            masked = bn != "s1.b1.projbn"
+            if masked:
+                random_gradient(ops[at[hi]]["y"])
+                random_gradient(b["y"])       # the shortcut's part
+            else:
+                random_gradient(b["y"])
+            E.edl_profile(True)
+            try:
+                job.debug_backward_range_from(at[lo], at[hi] + 1, n, [tid(b["y"])] if masked else [])
+                assert sum(r["launches"] for r in E.edl_profile_report() if r["name"] == "bn_pointwise_bwd") == 1, bn
+            finally:
+                E.edl_profile(False)
+            x, g, act = tensor(b["x"]), tensor(b["y"], 1), tensor(c["x"])
+            mean, rstd = x.mean(0), 1 / np.sqrt(x.var(0) + 1e-5)
+            xh = (x - mean) * rstd
+            dx = O.round_bf16(w[b["g_off"]:][:b["C"]] * rstd * (g - g.mean(0) - xh * (g * xh).mean(0)))
+            wc = O.round_bf16(w[c["w_off"]:][:c["K"] * act.shape[1]].reshape(c["K"], -1))
+            want, got = (dx @ wc) * ((act > 0) if masked else 1.0), tensor(c["x"], 1)
+            e, (ratio, where) = relerr(got, want), elementwise_excess(got, want, 2e-2)
+            print(conv, "dact", e, ratio, flush=True)
+            assert e < 4e-3 and ratio <= 1.0, (conv, e, ratio, where)
+            dw = job.grad_slice(0, c["w_off"], wc.size).reshape(wc.shape)
+            e, (ratio, where) = relerr(dw, dx.T @ act), elementwise_excess(dw, dx.T @ act, 2e-2)
+            print(conv, "dw", e, ratio, flush=True)
+            assert e < 5e-4 and ratio <= 1.0, (conv, e, ratio, where)
+            if masked:       # the sums of the stored gradient, which are the gradients of the batch norm before
+                pb = ops[at[conv] - 1]
+                px = tensor(pb["x"])
+                for off, want in ((pb["b_off"], got.sum(0)), (pb["g_off"], (got * (px - px.mean(0)) / np.sqrt(px.var(0) + 1e-5)).sum(0))):
+                    assert relerr(job.grad_slice(0, off, want.size), want) < 1e-4, pb["name"]
+    case.close()
+
+
+@pytest.mark.parametrize("together", [0, 18])
+def test_batch_norms_that_go_backward_with_their_convolutions_keep_to_their_shard(together):
+    """The same bits wherever a shard lies; shards of unequal size; and whichever streams the launch and the sum of its pieces
+    run on, with projections beside the chain and in it."""
+    import paper_1909_11985_amd as E
+    kw = dict(H=96, W=96, C=3, classes=10, arch=(64, 2, 2, 1, 1))
+    with E.options(**_THROUGH):
+        test_equal_shards_are_summed_in_the_same_order_wherever_they_run("resnet50", "bf16", kw, 9, 3, together)
+        if together == 0:
+            test_bf16_gradients_of_residual_shards_are_those_of_each_alone("resnet50", kw, [7, 9, 6], -1)
+            geom = dict(H=96, W=96, classes=10, arch=(64, 2, 2, 1, 1), unequal=True)
+            base = _digest_after_steps({}, **geom)
+            for options in ({"wgrad_stream": 0}, {"branch_stream": 0}, {"branch_stream": 0, "wgrad_stream": 0}, {"wgrad_batch_us": 0},
+                            {"wgrad_batch_us": 1000000, "early_update": 1}):
+                assert _digest_after_steps(options, **geom) == base, options
+            assert _digest_after_steps({}, side_streams="torch", **geom) == base
+            assert _digest_after_steps({}, side_streams=None, **geom) == base
 
 
 def test_residual_join_epilogue_at_the_benchmark_shape():
