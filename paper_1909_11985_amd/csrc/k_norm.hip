@@ -401,6 +401,245 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__
     }
 }
 
+// ---- both finishing steps inside the element-wise pass -------------------------------------------------------------------
+// Where a shard's sums are few, every workgroup of the element-wise pass adds up those of the channels that it owns: a launch
+// of 4 us between two dependent ones falls away for some hundred loads from the caches, issued behind those of the
+// workgroup's own rows.  A workgroup owns a slice of up to 64 channels (all of them in narrow layers) of 256 * U vectors; the
+// first of a slice also stores what later passes read.  Latency bounds the pass then: all its loads (rows, sums, scales) are
+// issued before the first wait, none behind a branch.
+//
+// Taken up to 128 blocks of a channel in a shard and 20 MB of sums read by all workgroups together: a workgroup of 98 blocks
+// reads 50 KB, and from some 400 workgroups of that on it takes longer than the launch that it saves (us per step at
+// 20 / 40 / 80 MB: ResNet-50, shard of 32, 4,050 / 4,050 / 4,064; three shards of 161x161 images 4,545 / 4,575 / 4,596).
+// Two launches -> one: ResNet-20, 8 shards of 16, 1,390 -> 1,313 us a step; ResNet-50 4,108 -> 4,050 and 4,644 -> 4,545.
+
+constexpr int kSlice = 64;
+
+// Sums over a shard's row blocks, of SLICE channels from c_lo on: out[kind * SLICE + channel], in float64.  Eight lanes per sum,
+// 32 sums at a time, four blocks per load and two loads of each sum in flight.  A load that would end behind the shard
+// starts earlier, and what it repeats is not counted (with fewer than four blocks it reads up to three floats behind them,
+// which belong to the scratch).
+template <int SLICE>
+__device__ __forceinline__ void slice_sums(const float* __restrict__ partial, const RowCut& cut, int sh, int C, int c_lo, double* out) {
+    const int tid = threadIdx.x, sub = tid & 7, stride = cut.blk0[cut.p], first = cut.blk0[sh], end = cut.blk0[sh + 1];
+    constexpr int P = 2 * SLICE / 32;
+    struct __attribute__((packed, aligned(4))) Four { float v[4]; };
+    const float* p[P];
+    double a[P];
+    #pragma unroll
+    for (int i = 0; i < P; ++i) {
+        const int col = i * 32 + (tid >> 3), kind = col / SLICE;
+        p[i] = partial + (int64_t)(kind * C + c_lo + col % SLICE) * stride;
+        a[i] = 0;
+    }
+    for (int j0 = first; j0 < end; j0 += 64) {
+        Four v[2][P];
+        #pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = j0 + 32 * h + 4 * sub, at = max(min(j, end - 4), first);
+            #pragma unroll
+            for (int i = 0; i < P; ++i) v[h][i] = *reinterpret_cast<const Four*>(p[i] + at);
+        }
+        #pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int j = j0 + 32 * h + 4 * sub, at = max(min(j, end - 4), first);
+            #pragma unroll
+            for (int i = 0; i < P; ++i)
+                #pragma unroll
+                for (int k = 0; k < 4; ++k) a[i] += (at + k >= j && at + k < end) ? (double)v[h][i].v[k] : 0.0;
+        }
+    }
+    #pragma unroll
+    for (int i = 0; i < P; ++i) {
+        #pragma unroll
+        for (int o = 4; o > 0; o >>= 1) a[i] += __shfl_xor(a[i], o, 64);
+        if (sub == 0) out[i * 32 + (tid >> 3)] = a[i];
+    }
+}
+
+// 16 bytes that are not converted yet, so that the load stays in flight
+__device__ __forceinline__ uint4 raw_vec(const void* base, int64_t i) { return reinterpret_cast<const uint4*>(base)[i]; }
+template <typename T> __device__ __forceinline__ void unpack(const uint4& u, float (&out)[Elem<T>::VEC]) {
+    Vec16<T> v;
+    v.u = u;
+    #pragma unroll
+    for (int e = 0; e < Elem<T>::VEC; ++e) out[e] = Elem<T>::to_f32(v.e[e]);
+}
+
+// The rows and channels of a workgroup: vectors at(u) of the tensor, `inside` the shard or not (then at() is the last row's)
+template <int VEC, int SLICE, int U>
+struct SliceTile {
+    static constexpr int LANES = SLICE / VEC, STEP = 256 / LANES;
+    int lane_vec, c_lo, row, rows, cvecs;
+    int64_t base;
+    __device__ __forceinline__ SliceTile(const RowCut& cut, int sh, int C) {
+        cvecs = C / VEC;
+        c_lo = blockIdx.y * SLICE;
+        lane_vec = (int)threadIdx.x % LANES;
+        row = (int)blockIdx.x * (STEP * U) + (int)threadIdx.x / LANES;
+        rows = cut.row0[sh + 1] - cut.row0[sh];
+        base = (int64_t)cut.row0[sh] * cvecs + blockIdx.y * LANES + lane_vec;
+    }
+    __device__ __forceinline__ bool empty() const { return (int)blockIdx.x * (STEP * U) >= rows; }
+    __device__ __forceinline__ bool inside(int u) const { return row + u * STEP < rows; }
+    __device__ __forceinline__ int64_t at(int u) const { return base + (int64_t)(inside(u) ? row + u * STEP : rows - 1) * cvecs; }
+};
+
+// bn_stats_finalize_kernel and bn_apply_kernel in one.  grid: (groups of rows of the largest shard, slices, shards)
+template <typename T, int SLICE, int U, bool RES>
+__global__ __launch_bounds__(256) void bn_finish_apply_kernel(const T* __restrict__ x, const T* __restrict__ res, T* __restrict__ y,
+                                                              const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                              const float* __restrict__ partial, RowCut cut, int C, int relu,
+                                                              float* __restrict__ mean_rstd, float* running, unsigned char* __restrict__ sign) {
+    constexpr int VEC = Elem<T>::VEC;
+    __shared__ double sums[2 * SLICE];
+    __shared__ __attribute__((aligned(16))) float cf[3][SLICE];
+    const int sh = blockIdx.z, tid = threadIdx.x;
+    const SliceTile<VEC, SLICE, U> t(cut, sh, C);
+    if (t.empty()) return;
+    uint4 xr[U], rr[U];
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        xr[u] = raw_vec(x, t.at(u));
+        if (RES) rr[u] = raw_vec(res, t.at(u));
+    }
+    // what the sums are finished with is fetched beside them
+    const int c = t.c_lo + (tid < SLICE ? tid : 0);
+    const bool keeps = blockIdx.x == 0 && running != nullptr && sh == 0;
+    const float *const rm = keeps ? running + c : gamma + c, *const rv0 = keeps ? running + C + c : gamma + c;
+    const float ga = gamma[c], be0 = beta[c], run_mean = *rm, run_var = *rv0;
+    const double M = t.rows, per_row = 1.0 / M;
+    slice_sums<SLICE>(partial, cut, sh, C, t.c_lo, sums);
+    __syncthreads();
+    if (tid < SLICE) {
+        const double mean = sums[tid] * per_row;
+        double var = sums[SLICE + tid] * per_row - mean * mean;
+        if (var < 0) var = 0;
+        const float mu = (float)mean, rs = (float)rsqrt(var + (double)kBnEps);
+        cf[0][tid] = mu;
+        cf[1][tid] = ga * rs;
+        cf[2][tid] = be0;
+        if (blockIdx.x == 0) {
+            mean_rstd[(int64_t)sh * 2 * C + c] = mu;
+            mean_rstd[(int64_t)sh * 2 * C + C + c] = rs;
+            if (keeps) {
+                const double unbiased = t.rows > 1 ? var * M / (M - 1) : var;
+                running[c] = (1.f - kBnRunningMomentum) * run_mean + kBnRunningMomentum * mu;
+                running[C + c] = (1.f - kBnRunningMomentum) * run_var + kBnRunningMomentum * (float)unbiased;
+            }
+        }
+    }
+    __syncthreads();
+    float mu[VEC], sc[VEC], be[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) { mu[e] = cf[0][t.lane_vec * VEC + e]; sc[e] = cf[1][t.lane_vec * VEC + e]; be[e] = cf[2][t.lane_vec * VEC + e]; }
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (!t.inside(u)) break;
+        float out[VEC], xv[VEC], rv[VEC];
+        unpack<T>(xr[u], xv);
+        if (RES) unpack<T>(rr[u], rv);
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            out[e] = (xv[e] - mu[e]) * sc[e] + be[e];
+            if (RES) out[e] += rv[e];
+            if (relu) out[e] = out[e] > 0.f ? out[e] : 0.f;
+        }
+        store_row<T, VEC>(y, t.at(u), VEC, 0, out);
+        if (VEC == 8 && sign != nullptr) {
+            unsigned bits = 0;      // of the stored values
+            #pragma unroll
+            for (int e = 0; e < VEC; ++e) bits |= (Elem<T>::to_f32(Elem<T>::from_f32(out[e])) > 0.f ? 1u : 0u) << e;
+            sign[t.at(u)] = (unsigned char)bits;
+        }
+    }
+}
+
+// bn_bwd_finalize_kernel and bn_bwd_apply_kernel in one
+template <typename T, int SLICE, int U, bool MASK>
+__global__ __launch_bounds__(256) void bn_finish_bwd_kernel(const T* __restrict__ x, const T* __restrict__ y, const T* __restrict__ dy,
+                                                            T* __restrict__ dx, T* dres, const float* __restrict__ gamma,
+                                                            const float* __restrict__ mean_rstd, const float* __restrict__ partial, RowCut cut, int C,
+                                                            float* __restrict__ dgamma, float* __restrict__ dbeta, int64_t grad_stride) {
+    constexpr int VEC = Elem<T>::VEC;
+    __shared__ double sums[2 * SLICE];
+    __shared__ __attribute__((aligned(16))) float cf[5][SLICE];
+    const int sh = blockIdx.z, tid = threadIdx.x;
+    const SliceTile<VEC, SLICE, U> t(cut, sh, C);
+    if (t.empty()) return;
+    uint4 xr[U], yr[U], gr[U];
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        xr[u] = raw_vec(x, t.at(u));
+        gr[u] = raw_vec(dy, t.at(u));
+        if (MASK) yr[u] = raw_vec(y, t.at(u));
+    }
+    const int c = t.c_lo + (tid < SLICE ? tid : 0);
+    const float mu0 = mean_rstd[(int64_t)sh * 2 * C + c], rs0 = mean_rstd[(int64_t)sh * 2 * C + C + c], ga0 = gamma[c];
+    const double per_row = 1.0 / (double)t.rows;
+    slice_sums<SLICE>(partial, cut, sh, C, t.c_lo, sums);
+    __syncthreads();
+    if (tid < SLICE) {
+        const double s = sums[tid], q = sums[SLICE + tid];
+        cf[0][tid] = mu0;
+        cf[1][tid] = rs0;
+        cf[2][tid] = ga0 * rs0;
+        cf[3][tid] = (float)(s * per_row);
+        cf[4][tid] = (float)(q * per_row);
+        if (blockIdx.x == 0) {
+            const int64_t to = (int64_t)cut.k[sh] * grad_stride + c;
+            dbeta[to] = (float)s;
+            dgamma[to] = (float)q;
+        }
+    }
+    __syncthreads();
+    float mu[VEC], rs[VEC], ga[VEC], k0[VEC], k1[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        const int i = t.lane_vec * VEC + e;
+        mu[e] = cf[0][i]; rs[e] = cf[1][i]; ga[e] = cf[2][i]; k0[e] = cf[3][i]; k1[e] = cf[4][i];
+    }
+    #pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (!t.inside(u)) break;
+        float out[VEC], xv[VEC], yv[VEC], g[VEC];
+        unpack<T>(xr[u], xv);
+        unpack<T>(gr[u], g);
+        if (MASK) unpack<T>(yr[u], yv);
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            if (MASK) g[e] = yv[e] > 0.f ? g[e] : 0.f;
+            const float xh = (xv[e] - mu[e]) * rs[e];
+            out[e] = ga[e] * (g[e] - k0[e] - xh * k1[e]);
+        }
+        store_row<T, VEC>(dx, t.at(u), VEC, 0, out);
+        if (dres) store_row<T, VEC>(dres, t.at(u), VEC, 0, g);
+    }
+}
+
+// How a pass over S with these sums is cut for the kernels above; slice == 0: it takes two launches
+struct SlicePlan { int slice = 0, U = 1; dim3 grid; };
+static SlicePlan plan_slices(const ShardSet& S, int hw, int C, int VEC, const RowCut& sums) {
+    SlicePlan p;
+    if (VEC == 1 || !(C == 16 || C == 32 || C % kSlice == 0) || sums.most > tune().bn_finish_blocks) return p;
+    const int slice = std::min(C, kSlice);
+    const int64_t groups = (int64_t)S.plan * hw * (C / VEC) / 256;
+    p.U = groups >= 4 * 384 ? 4 : groups >= 2 * 384 ? 2 : 1;
+    // what the workgroups read of the sums together
+    if (groups / p.U * sums.most * slice * 8 > tune().bn_finish_bytes) return p;
+    p.slice = slice;
+    const int rows = 256 / (slice / VEC) * p.U;
+    p.grid = dim3((unsigned)(((int64_t)S.largest() * hw + rows - 1) / rows), C / slice, S.p);
+    return p;
+}
+// LAUNCH(slice, U) for the plan
+#define EDL_BN_SLICES(P, LAUNCH)                                                                                      \
+    do {                                                                                                              \
+        if ((P).slice == 16) { if ((P).U == 4) LAUNCH(16, 4); else if ((P).U == 2) LAUNCH(16, 2); else LAUNCH(16, 1); }  \
+        else if ((P).slice == 32) { if ((P).U == 4) LAUNCH(32, 4); else if ((P).U == 2) LAUNCH(32, 2); else LAUNCH(32, 1); } \
+        else { if ((P).U == 4) LAUNCH(64, 4); else if ((P).U == 2) LAUNCH(64, 2); else LAUNCH(64, 1); }                  \
+    } while (0)
+
 // a finishing kernel over all channels and shards: four waves per channel where a shard has many row blocks
 #define EDL_FINALIZE(KERNEL, CUT, CH, ...)                                                                                     \
     do {                                                                                                                       \
@@ -447,6 +686,22 @@ static void bn_forward_t(const void* x, const void* res, void* y, const float* g
         ProfScope ps(prof_shape_label("bn_stats", M, C), 0.0, tb, st);
         cut = cut_rows(S, hw, s.rows_per_block);
         launch_colreduce<T, VEC, 0>(s, long_blocks(S, hw, C, VEC, s), (const T*)x, (const T*)nullptr, (T*)nullptr, (const float*)nullptr, cut, C, 0, partial, st);
+    }
+    if constexpr (VEC > 1) {
+        const SlicePlan p = plan_slices(S, hw, C, VEC, cut);
+        if (p.slice > 0) {
+            ProfScope ps(prof_shape_label("bn_finish_apply", M, C), 0.0, tb * ((res ? 3.0 : 2.0) + (sign ? 1.0 / 16 : 0.0)), st);
+#define EDL_BN_FINISH(SLICE, U)                                                                                       \
+    do {                                                                                                              \
+        if (res) hipLaunchKernelGGL((bn_finish_apply_kernel<T, SLICE, U, true>), p.grid, dim3(256), 0, st, (const T*)x, (const T*)res, (T*)y, \
+                                    gamma, beta, partial, cut, C, relu ? 1 : 0, save, running, sign);                 \
+        else hipLaunchKernelGGL((bn_finish_apply_kernel<T, SLICE, U, false>), p.grid, dim3(256), 0, st, (const T*)x, (const T*)res, (T*)y, \
+                                gamma, beta, partial, cut, C, relu ? 1 : 0, save, running, sign);                     \
+    } while (0)
+            EDL_BN_SLICES(p, EDL_BN_FINISH);
+#undef EDL_BN_FINISH
+            return;
+        }
     }
     {
         ProfScope ps("bn_stats_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
@@ -495,18 +750,35 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
         cut = cut_rows(S, hw, s.rows_per_block);
         launch_colreduce<T, VEC, 1>(s, long_blocks(S, hw, C, VEC, s), (const T*)x, (const T*)(relu ? y : x), (T*)dy, save, cut, C, relu ? 1 : 0, partial, st);
     }
+    // the dgrad that left the sums also left dy masked: the activation is then not read again
+    const bool mask = relu && !fused;
+    const bool acc = dres && dres_acc;
+    const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
+    const double bytes = tb * ((mask ? 3.0 : 2.0) + 1.0 + (dres ? (acc ? 2.0 : 1.0) : 0.0));
+    if constexpr (VEC > 1) {
+        const SlicePlan p = dx == nullptr || acc ? SlicePlan() : plan_slices(S, hw, C, VEC, cut);
+        if (p.slice > 0) {
+            ProfScope ps(prof_shape_label("bn_finish_bwd", M, C), 0.0, bytes, st);
+#define EDL_BN_FINISH(SLICE, U)                                                                                       \
+    do {                                                                                                              \
+        if (mask) hipLaunchKernelGGL((bn_finish_bwd_kernel<T, SLICE, U, true>), p.grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
+                                     (T*)dx, (T*)dres, gamma, save, partial, cut, C, dgamma.g, dbeta.g, dgamma.stride);  \
+        else hipLaunchKernelGGL((bn_finish_bwd_kernel<T, SLICE, U, false>), p.grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
+                                (T*)dx, (T*)dres, gamma, save, partial, cut, C, dgamma.g, dbeta.g, dgamma.stride);       \
+    } while (0)
+            EDL_BN_SLICES(p, EDL_BN_FINISH);
+#undef EDL_BN_FINISH
+            return;
+        }
+    }
     {
         ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
         EDL_FINALIZE(bn_bwd_finalize_kernel, cut, C, dgamma.g, dbeta.g, dgamma.stride, coef);
     }
     if (dx == nullptr) return;
-    // the dgrad that left the sums also left dy masked: the activation is then not read again
-    const bool mask = relu && !fused;
-    const bool acc = dres && dres_acc;
-    ProfScope ps(prof_shape_label("bn_bwd_apply", M, C), 0.0, tb * ((mask ? 3.0 : 2.0) + 1.0 + (dres ? (acc ? 2.0 : 1.0) : 0.0)), st);
+    ProfScope ps(prof_shape_label("bn_bwd_apply", M, C), 0.0, bytes, st);
     const int u = vectors_per_lane(S, hw, s.cvecs);
     const dim3 grid = ew_grid(S, hw, s.cvecs, u);
-    const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
 #define EDL_BN_BWD_APPLY(U, MASK, ACC)                                                                                    \
     do {                                                                                                                  \
         if (nt) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, U, MASK, ACC, true>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \

@@ -54,6 +54,8 @@ const Entry kEntries[] = {
     {"pointwise_rows", &Tune::pointwise_rows},
     {"pointwise_blocks", &Tune::pointwise_blocks},
     {"bn_pointwise_rows", &Tune::bn_pointwise_rows},
+    {"bn_finish_blocks", &Tune::bn_finish_blocks},
+    {"bn_finish_bytes", &Tune::bn_finish_bytes},
     {"spare0", &Tune::spare0},
     {"spare1", &Tune::spare1},
 };

@@ -365,6 +365,41 @@ def test_streaming_pointwise_convolutions_keep_to_their_shard(blocks, together):
         test_equal_shards_are_summed_in_the_same_order_wherever_they_run("resnet50", "bf16", kw, 9, 7, together)
 
 
+@pytest.mark.parametrize("n", [1, 3, 4, 5, 32, 33, 64, 65, 128, 129])
+def test_batch_norms_that_finish_their_own_sums(n):
+    """A batch norm's pass adds up the partial sums itself where they are few: here n of them a channel in the first stage (blocks of
+    128 rows), at the edges of the loads of four, of the rounds of 32 and 64, and of what is taken (129 blocks take two launches), in
+    slices of 16, 32 and 64 channels, forward and backward, against the oracle's layers."""
+    kw = dict(H=16, W=8, C=3, classes=10, arch=(16, 3, 1))
+    import paper_1909_11985_amd as E
+    case = Case("resnet20", "f32", n, **kw)
+    E.edl_profile(True)
+    try:
+        case.job.gradients(1)
+        got = {r["name"]: r["launches"] for r in E.edl_profile_report()}
+    finally:
+        E.edl_profile(False)
+    case.close()
+    assert got["bn_finish_apply"] + got.get("bn_apply", 0) == got["bn_finish_bwd"] + got.get("bn_bwd_apply", 0) == 9, got
+    assert got["bn_finish_apply"] == 9 if n <= 64 else 0 < got["bn_finish_apply"] < (9 if n > 128 else 10), got
+    _assert_layerwise(conv_bn_pair_parity("resnet20", "f32", n, **kw), "f32")
+    _assert_layerwise(relu_producer_pair_parity("resnet20", "f32", n, **kw), "f32")
+
+
+@pytest.mark.parametrize("blocks", [0, 128])
+@pytest.mark.parametrize("model,dtype,n,kw", [
+    ("resnet20", "f32", 7, dict(H=24, W=20, C=3, classes=10, arch=(16, 3, 1))), ("resnet20", "bf16", 7, dict(H=24, W=20, C=3, classes=10, arch=(16, 3, 1))),
+    ("resnet50", "bf16", 5, dict(H=50, W=42, C=3, classes=10, arch=(64, 1, 2, 1, 1))),
+])
+def test_batch_norms_in_one_launch_and_in_two(model, dtype, n, kw, blocks):
+    """Both forms at the same shapes: with residuals, ragged rows, sums left by convolutions and by reduction passes."""
+    import paper_1909_11985_amd as E
+    with E.options(bn_finish_blocks=blocks):
+        _assert_layerwise(layerwise_parity(model, dtype, n, **kw), dtype)
+        _assert_layerwise(conv_bn_pair_parity(model, dtype, n, **kw), dtype)
+        _assert_layerwise(relu_producer_pair_parity(model, dtype, n, **kw), dtype)
+
+
 # a batch norm and the expanding convolution before it in one launch, at sizes far below those it is chosen for: runs of 4K rows
 _THROUGH = dict(bn_pointwise_rows=0, wgrad_blocks=1, wgrad_long_blocks=0)
 
