@@ -14,6 +14,7 @@
 #include "graph.h"
 #include "kernels.h"
 #include "profiler.h"
+#include "thin.h"
 #include "tune.h"
 
 using namespace edl;
@@ -875,16 +876,40 @@ int32_t edl_shard(const edl_handle* h, int64_t B, int32_t p, int64_t epoch, int6
 // Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
 // op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
 // single layers from the debugging hooks, which then skip the gather)
-static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_idx, float* dev_losses, bool update_running,
-                         size_t op_lo = 0, size_t op_hi = (size_t)-1) {
+// Whether the last layer, op i, the loss and their backward pass go in one launch: few outputs over a ReLU layer with a bias that
+// nothing else reads.
+static bool classifier_together(const edl_handle* h, size_t i, const ShardSet& S, const void* weights) {
+    const Graph& g = h->g;
+    const Op& op = g.ops[i];
+    if (i == 0 || op.kind != OP_CONV || op.relu || !op.bias || g.ops[i + 1].kind != OP_LOSS || g.ops[i + 1].x != op.y) return false;
+    const Op& prod = g.ops[i - 1];
+    const int sx = storage_of(g, op.x);
+    return prod.kind == OP_CONV && prod.relu && prod.bias && storage_of(g, prod.y) == sx && sx != 0 && h->readers[(size_t)sx] == 1 &&
+           h->L.wT[i] < 0 && h->L.wpad[i] < 0 && op.K == g.classes && thin_head_takes(h->cfg.dtype, geom_stored(g, op, S.samples(), h->L.in), S, h->act(op.x), weights);
+}
+
+// Whether the first layer takes a pass's samples from the data set itself, their numbers in the launch's arguments: no copy of
+// the numbers to the GPU and no gather then.
+static bool gathers_itself(const edl_handle* h, const ShardSet& S) {
+    const Graph& g = h->g;
+    const Op& op = g.ops[0];
+    return op.kind == OP_CONV && storage_of(g, op.x) == 0 && !stored_apart(g, h->L.in) && h->L.wpad[0] < 0 && h->cfg.dtype != EDL_DTYPE_BF16 &&
+           h->cfg.N <= INT32_MAX && conv_fwd_gathers(h->cfg.dtype, geom_stored(g, op, S.samples(), h->L.in), S, h->data_x, h->act(0), h->w() + op.w_off);
+}
+
+// host_idx: the samples' numbers where the first layer gathers them itself (gathers_itself), else null.
+// train: a backward pass over the same shards follows.  Returns whether the last layer's part of it is done (thin_head_takes).
+static bool forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_idx, float* dev_losses, bool update_running,
+                         size_t op_lo = 0, size_t op_hi = (size_t)-1, const int64_t* host_idx = nullptr, bool train = false) {
     const int n = S.samples();
     const Graph& g = h->g;
+    bool head = false;
     const int dt = h->cfg.dtype;
     hipStream_t st = h->st;
     const bool bf = dt == EDL_DTYPE_BF16;
     float* partial = h->sc<float>(h->L.partial);
     const Tensor& tin = g.tensors[0];
-    if (dev_idx) {
+    if (dev_idx && !host_idx) {
         if (stored_apart(g, h->L.in))
             launch_gather_pad(dt, h->data_x, h->data_y, dev_idx, n, tin.H, tin.W, tin.C, h->L.in, h->act(0),
                               h->at<int32_t>(h->L.labels), st);
@@ -946,6 +971,27 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
         switch (op.kind) {
             case OP_CONV: {
                 const void* wsrc = weights_of(i);
+                if (host_idx && i == 0) {
+                    const SmallInput in = {h->data_x, h->data_y, host_idx, (float*)h->act(0), h->at<int32_t>(h->L.labels)};
+                    launch_small_fc_fwd(geom_stored(g, op, n, h->L.in), S, (const float*)h->act(op.x), (const float*)wsrc, op.bias ? h->w() + op.b_off : nullptr,
+                                        op.relu, (float*)h->act(op.y), &in, st);
+                    break;
+                }
+                // The classifier, the loss and what their backward pass leaves: the next op is done then
+                if (train && i + 2 == op_hi && op_hi == g.ops.size() && !prof_enabled() && classifier_together(h, i, S, wsrc)) {
+                    const Op& prod = g.ops[i - 1];
+                    ThinHead t = {};
+                    t.x = h->act(op.x); t.w = wsrc; t.bias = h->w() + op.b_off; t.labels = h->at<int32_t>(h->L.labels);
+                    t.logits = (float*)h->act(op.y); t.row_loss = h->sc<float>(h->L.row_loss); t.loss = dev_losses;
+                    t.dlogits = h->grad(op.y); t.dx = h->grad(op.x);
+                    t.dw = GradDst{h->grad_buf(0) + op.w_off, h->L.grad_stride};
+                    t.db = GradDst{h->grad_buf(0) + op.b_off, h->L.grad_stride};
+                    t.dbias = GradDst{h->grad_buf(0) + prod.b_off, h->L.grad_stride};
+                    launch_thin_head(dt, geom_stored(g, op, n, h->L.in), S, t, st);
+                    done[i + 1] = 1;
+                    head = true;
+                    break;
+                }
                 // the batch norm that follows (in this call) can take its sums from the convolution's epilogue
                 const bool bn_next = i + 1 < op_hi && g.ops[i + 1].kind == OP_BN && g.ops[i + 1].x == op.y;
                 // ... or a later one of this call, if the held buffer is free
@@ -1001,6 +1047,7 @@ static void forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
         }
     }
     if (join_tensor >= 0) (void)hipStreamWaitEvent(st, join_event, 0);   // a branch nobody joined (cannot happen)
+    return head;
 }
 
 static int apply_range(edl_handle* h, int32_t p, int64_t lo, int64_t hi, hipStream_t st, int max_blocks = 0);
@@ -1021,9 +1068,10 @@ static double weight_gradient_us(int dt, const ConvGeom& q, int shards) {
 
 // early_p > 0: this is the last backward pass of a step of early_p shards, so gradients that are final may be
 // applied while the pass goes on.
+// head: the forward pass has done the last layer's part (forward_pass).
 // held (debugging hook only): tensors whose gradient buffers already hold a contribution the pass adds to.
 static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, size_t op_hi = (size_t)-1, int early_p = 0,
-                          const std::vector<int>* held = nullptr) {
+                          const std::vector<int>* held = nullptr, bool head = false) {
     const int n = S.samples();
     // the workers' gradients of the parameters from offset `off` of the flat vector on
     auto grads_at = [&](int64_t off) { return GradDst{h->grad_buf(0) + off, h->L.grad_stride}; };
@@ -1180,6 +1228,13 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 written[(size_t)storage_of(g, op.x)] = 1;
                 break;
             case OP_CONV: {
+                if (head && ii + 2 == g.ops.size()) {
+                    written[(size_t)storage_of(g, op.x)] = 1;
+                    fused_for = ii - 1;
+                    fused_sums = cut_rows(S, 1, n);
+                    fused_sums.stored = true;
+                    break;
+                }
                 const ConvGeom q = geom_stored(g, op, n, h->L.in);
                 // The weight gradient needs only dy (final from here on) and the layer's input, and nothing
                 // before the update reads it: it runs on the second stream, beside the chain of input
@@ -1194,14 +1249,16 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 // pool after the layer, or without a ReLU, what is left is the bias gradient's sum, which goes with the weight
                 // gradient (VGG-16, shard of 32: 21 us a layer on the chain; jobs with batch norms use the second
                 // buffer of partial sums on their branch stream).
-                const bool aside = op.bias && !on_main && !h->has_bn && fused_for != ii && (premasked_for == ii || !op.relu);
+                // a small layer's weight gradient is left by the launch of its input gradient
+                const bool with_dgrad = storage_of(g, op.x) != 0 && h->L.wT[ii] < 0 && h->L.wpad[ii] < 0 && conv_gradients_together(dt, q, S, true);
+                const bool aside = op.bias && !on_main && !with_dgrad && !h->has_bn && fused_for != ii && (premasked_for == ii || !op.relu);
                 if (!aside) bias_gradient(ii, premasked_for == ii, fused_for == ii ? fused_sums : RowCut(), fused_for == ii ? fused_at : partial, st);
                 const int64_t own = (int64_t)op.K * op.R * op.S * g.tensors[(size_t)op.x].C;
                 const bool early = early_p > 0 && overlap && !on_main && h->upd != nullptr && tune().early_update > 0 && own >= tune().early_update;
                 bool handed_over = false;
-                if (on_main) {
+                if (on_main && !with_dgrad) {
                     weight_gradient(ii, st, h->sc<float>(overlap ? h->L.wgrad_scratch2 : h->L.wgrad_scratch));
-                } else {
+                } else if (!with_dgrad) {
                     waiting.push_back(ii);
                     if (aside) h->bias_waiting[ii] = premasked_for == ii ? 2 : 1;
                     // From 15 us of work on, and a layer of 8 or 10 us at once.  us per step: each layer by itself / from 15 with 10 at
@@ -1261,9 +1318,11 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 if (sx != 0) {
                     const bool acc = written[(size_t)sx] != 0;
                     const DgradMask mask = producer_mask(ii, acc, partial);
+                    const BothGradients both = {h->act(op.x), grads_at(op.w_off)};
                     const RowCut left = launch_conv_dgrad(dt, q, S, h->grad(op.y), dgrad_weights(h, ii), acc, h->grad(op.x),
                                                           h->sc<float>(h->L.splitk_scratch), (size_t)h->L.splitk_scratch_bytes,
-                                                          mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr, reads_weights);
+                                                          mask.act ? &mask : nullptr, st, acc ? h->grad_alias[(size_t)sx] : nullptr, reads_weights,
+                                                          with_dgrad ? &both : nullptr);
                     h->grad_alias[(size_t)sx] = nullptr;
                     if (left.p > 0) { fused_for = ii - 1; fused_sums = left; fused_at = partial; }
                     written[(size_t)sx] = 1;
@@ -1479,8 +1538,33 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
     h->shard_n.assign(sizes, sizes + p);
     h->shards_equal = equal;
     int64_t* dev_idx = h->at<int64_t>(h->L.idx);
-    HIP_TRY(hipMemcpyAsync(dev_idx, stage, sizeof(int64_t) * (size_t)B, hipMemcpyHostToDevice, h->st));
-    HIP_TRY(hipEventRecord(h->idx_event[slot], h->st));
+    // The shards of the pass from shard k on
+    auto shards_from = [&](int& k, int last_k) {
+        ShardSet S = {};
+        for (; k <= last_k; ++k) {
+            if (sizes[k] == 0) continue;
+            if (S.p > 0 && (alone || S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
+            S.k[S.p] = k;
+            S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
+            S.p += 1;
+        }
+        if (equal && !alone) S.plan_equal((int)sizes[0], shards_per_pass(h, sizes[0], p));
+        else S.plan_itself();
+        return S;
+    };
+    int last_k = -1;
+    for (int k = 0; k < p; ++k)
+        if (sizes[k] > 0) last_k = k;
+    bool in_arguments = false;       // the samples' numbers: where one pass of one part takes the whole mini-batch
+    if (last_k >= 0) {
+        int k = 0;
+        const ShardSet S = shards_from(k, last_k);
+        in_arguments = k > last_k && S.p <= h->L.scratch_shards && S.samples() <= h->L.scratch_samples && gathers_itself(h, S);
+    }
+    if (!in_arguments) {
+        HIP_TRY(hipMemcpyAsync(dev_idx, stage, sizeof(int64_t) * (size_t)B, hipMemcpyHostToDevice, h->st));
+        HIP_TRY(hipEventRecord(h->idx_event[slot], h->st));
+    }
     if (h->weights_dirty) {
         refresh_weight_copies(h);
         h->weights_dirty = false;
@@ -1499,21 +1583,9 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
     float* dev_losses = h->at<float>(h->L.losses);
     int64_t at = 0;
     bool first = true;       // the first worker that has samples keeps the running statistics
-    int last_k = -1;
-    for (int k = 0; k < p; ++k)
-        if (sizes[k] > 0) last_k = k;
     // consecutive shards in passes of as many as the workspace holds
     for (int k = 0; k <= last_k;) {
-        ShardSet S = {};
-        for (; k <= last_k; ++k) {
-            if (sizes[k] == 0) continue;
-            if (S.p > 0 && (alone || S.p == h->L.pass_shards || S.off[S.p] + sizes[k] > h->L.pass_samples)) break;
-            S.k[S.p] = k;
-            S.off[S.p + 1] = S.off[S.p] + (int)sizes[k];
-            S.p += 1;
-        }
-        if (equal && !alone) S.plan_equal((int)sizes[0], shards_per_pass(h, sizes[0], p));
-        else S.plan_itself();
+        const ShardSet S = shards_from(k, last_k);
         // ... and a pass in parts, if its scratch takes no more
         for (int s = 0; s < S.p;) {
             ShardSet part = S;
@@ -1524,8 +1596,8 @@ static int gradient_passes(edl_handle* h, int32_t p, const int64_t* idx, const i
                 part.off[part.p + 1] = part.off[part.p] + n;
                 part.p += 1;
             }
-            forward_pass(h, part, dev_idx + at, dev_losses, first && !alone);
-            backward_pass(h, part, 0, (size_t)-1, k > last_k && s == S.p ? h->early_p : 0);
+            const bool head = forward_pass(h, part, dev_idx + at, dev_losses, first && !alone, 0, (size_t)-1, in_arguments ? stage : nullptr, true);
+            backward_pass(h, part, 0, (size_t)-1, k > last_k && s == S.p ? h->early_p : 0, nullptr, head);
             first = false;
             at += part.samples();
         }

@@ -1924,15 +1924,23 @@ size_t conv_splitk_scratch_bytes(int dtype, const ConvGeom& g, int samples) {
     return need;
 }
 
+static bool small_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w) {
+    return small_fc_takes(dtype, g, g.C, g.K, S.plan) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && tune().force_tile < 0;
+}
+
+bool conv_fwd_gathers(int dtype, const ConvGeom& g, const ShardSet& S, const void* data, const void* x, const void* w) {
+    return g.N <= kSmallGather && ((uintptr_t)data & 15) == 0 && small_fwd(dtype, g, S, x, w) && !thin_fwd_takes(dtype, g, S.plan, true);
+}
+
 RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
                        bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st) {
-    const bool small = small_fc_takes(dtype, g, g.C, g.K, S.plan) && (((uintptr_t)x | (uintptr_t)w) & 15) == 0 && tune().force_tile < 0;
+    const bool small = small_fwd(dtype, g, S, x, w);
     if (thin_fwd_takes(dtype, g, S.plan, small)) {
         launch_thin_fwd(dtype, g, x, w, bias, relu, out_fp32, y, st);
         return RowCut();
     }
     if (small) {
-        launch_small_fc_fwd(g, (const float*)x, (const float*)w, bias, relu, (float*)y, st);
+        launch_small_fc_fwd(g, S, (const float*)x, (const float*)w, bias, relu, (float*)y, nullptr, st);
         return RowCut();
     }
     const int VEC = dtype == 1 ? 8 : 4;
@@ -1991,15 +1999,20 @@ bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off) {
            g.K % 8 == 0 && g.C % 8 == 0 && w_off % 8 == 0;
 }
 
+bool conv_gradients_together(int dtype, const ConvGeom& g, const ShardSet& S, bool w_rows) {
+    return w_rows && dtype != 1 && g.K % 4 == 0 && small_wgrad_takes(dtype, g, S);
+}
+
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
-                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows) {
+                         float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st, const void* acc_src, bool w_rows, const BothGradients* wgrad) {
     RowCut left;
     const bool ragged = g.K % (dtype == 1 ? 8 : 4) != 0;
     if (w_rows && (dtype != 1 || ragged)) {
         const void* const old = accumulate ? (acc_src != nullptr ? acc_src : dx) : nullptr;
         const DgradMask* const m = tune().fused_mask != 0 && (!accumulate || tune().fused_mask_join != 0) ? mask : nullptr;
         if (ragged) return launch_thin_dgrad(dtype, g, S, dy, wT, old, dx, m, st);
-        return launch_small_fc_dgrad(g, S, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx, m, st);
+        const SmallWgrad both = wgrad != nullptr ? SmallWgrad{(const float*)wgrad->x, wgrad->dw} : SmallWgrad{};
+        return launch_small_fc_dgrad(g, S, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx, m, wgrad != nullptr ? &both : nullptr, st);
     }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
@@ -2208,6 +2221,10 @@ void launch_conv_wgrad(int dtype, const ConvGeom& g, const ShardSet& S, const vo
                        size_t scratch_bytes, hipStream_t st) {
     if (thin_wgrad_takes(dtype, g, S)) {
         launch_thin_wgrad(dtype, g, S, x, dy, dw, st);
+        return;
+    }
+    if (small_wgrad_takes(dtype, g, S)) {
+        launch_small_wgrad(g, S, (const float*)x, (const float*)dy, dw, st);
         return;
     }
     const int VEC = dtype == 1 ? 8 : 4;

@@ -844,6 +844,14 @@ static void bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias
     }
 }
 
+int bias_sums_rows(int dtype, const ShardSet& S, int hw, int C, int* side_by_side, bool* in_double) {
+    if (C % (dtype == 1 ? 8 : 4) == 0) return 0;
+    const RedShape s = red_shape((int64_t)S.plan * hw, C, 1);
+    *side_by_side = s.TX;
+    *in_double = long_blocks(S, hw, C, 1, s);
+    return s.rows_per_block;
+}
+
 void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
                                float* partial, const RowCut& sums, hipStream_t st) {
     if (!relu && !dbias.g) return;

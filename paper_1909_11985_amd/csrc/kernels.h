@@ -127,6 +127,8 @@ struct SumsBuf { float* buf; size_t floats; };
 // and returns how they are cut; p == 0 if it left none.
 RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const void* x, const void* w, const float* bias, bool relu,
                        bool out_fp32, void* y, float* scratch, size_t scratch_bytes, SumsBuf stats, hipStream_t st);
+// Whether the first layer of a net can take its rows from the data set itself (launch_small_fc_fwd with SmallInput)
+bool conv_fwd_gathers(int dtype, const ConvGeom& g, const ShardSet& S, const void* data, const void* x, const void* w);
 // The most samples (65535 at most) of which a launch, forward and with dgrad also of the input gradient, keeps to the
 // vector kernel: its multiply-shift divisions are exact up to some number of pixels (g.N is ignored).
 int conv_vector_samples(const ConvGeom& g, bool dgrad);
@@ -144,6 +146,7 @@ struct DgradMask {
     GradDst dbias;            // without xin: the workers' bias gradients, which are these sums; a launch whose row blocks are whole
                               // shards may store them there itself (RowCut::stored).  g may be null
 };
+struct BothGradients { const void* x; GradDst dw; };
 // dx (+)= conv^T(dy, wT); wT is the [C][R][S][K] copy.  mask (may be null): if the launch can (stride 1, one
 // launch over all pixels, writing), dx is stored already masked and the sums are left in mask->sums; returns
 // how they are cut (what the producer's backward takes), else p == 0 and dx is the plain gradient.
@@ -152,7 +155,9 @@ struct DgradMask {
 // w_rows (only where conv_dgrad_reads_weights): wT is not a copy but the weights (bf16: their copy) as they lie, [K][C].
 RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const void* dy, const void* wT, bool accumulate, void* dx,
                          float* scratch, size_t scratch_bytes, const DgradMask* mask, hipStream_t st,
-                         const void* acc_src = nullptr, bool w_rows = false);
+                         const void* acc_src = nullptr, bool w_rows = false, const BothGradients* wgrad = nullptr);
+// whether that launch can leave the layer's weight gradient too (BothGradients: its input, where the gradient goes)
+bool conv_gradients_together(int dtype, const ConvGeom& g, const ShardSet& S, bool w_rows);
 // whether the input gradient of a layer whose weights start at element w_off reads them where they lie, in passes of up to
 // g.N samples
 bool conv_dgrad_reads_weights(int dtype, const ConvGeom& g, int64_t w_off);
@@ -190,6 +195,9 @@ void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy,
 // sums.p > 0: dy is masked already and partial holds its column sums.
 void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,
                                float* partial, const RowCut& sums, hipStream_t st);
+// how launch_bias_relu_backward sums C channels that are no whole vectors: rows of a block, channels side by side in one, and
+// whether its lanes are added in float64
+int bias_sums_rows(int dtype, const ShardSet& S, int hw, int C, int* side_by_side, bool* in_double);
 // The same bias gradient of a ReLU layer whose output only a max pool reads, from the pool's output and its gradient: the pool
 // hands each of its gradients to one element, whose activation is the pooled value, so that the sum over the layer's masked
 // gradient is that of dpooled * (pooled > 0), of fewer elements.  hw: pooled pixels per sample.

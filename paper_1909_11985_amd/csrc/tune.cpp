@@ -56,6 +56,7 @@ const Entry kEntries[] = {
     {"bn_pointwise_rows", &Tune::bn_pointwise_rows},
     {"bn_finish_blocks", &Tune::bn_finish_blocks},
     {"bn_finish_bytes", &Tune::bn_finish_bytes},
+    {"thin_head", &Tune::thin_head},
     {"spare0", &Tune::spare0},
     {"spare1", &Tune::spare1},
 };

@@ -51,6 +51,7 @@ struct Tune {
     int64_t bn_pointwise_rows = 65536;  // a batch norm and the expanding 1x1 convolution before it go backward in one launch from this many rows on
     int64_t bn_finish_blocks = 128;   // a batch norm's pass adds up the partial sums itself where a shard has at most this many of a channel ...
     int64_t bn_finish_bytes = 20000000;  // ... and its workgroups read at most this many bytes of them
+    int64_t thin_head = 1;            // a small classifier goes forward, through the loss and backward in one launch
     int64_t spare0 = 0, spare1 = 0;   // free slots for experiments (EDL_TUNE_SPARE0 / 1)
 };
 

@@ -1497,6 +1497,66 @@ def test_which_layers_the_float32_kernel_of_few_tiles_takes(dtype, C0, n, fwd, d
     job.shutdown()
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes,C,cut", [
+    (10, 256, [16, 16, 16, 16]), (1, 64, [1]), (15, 72, [17, 3, 64, 1]), (6, 1024, [16, 15]), (3, 8, [33, 64]), (9, 200, [64]), (13, 128, [5, 0, 48, 32]),
+])
+def test_a_classifier_in_one_launch_and_in_five(classes, C, cut, dtype):
+    """Bit for bit what the launches leave that it replaces: logits, losses, all gradients, at up to four blocks of 16 rows, in
+    float64 and float32 column sums, ragged columns, one row and one output."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    if dtype == "bf16" and (classes % 8 == 0 or C % 8 != 0):
+        pytest.skip("not taken")
+    n, p = sum(cut), len(cut)
+    x, y = synth_inputs.dataset(1, n, 1, 1, 12, classes)
+    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    out = []
+    for head in (1, 0):
+        with E.options(thin_head=head):
+            job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=p, max_shard=n, H=1, W=1, C_=12, arch=(24, C), classes=classes), 2)
+            job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+            job.gradients(p, np.arange(n, dtype=np.int64)[::-1].copy(), off)
+            logits = len(job.debug_tensors()) - 1
+            held = [k for k in range(p) if cut[k] > 0]      # (an empty shard has no loss and no gradient)
+            out.append([job.losses(p)[held], job.debug_get(logits, n), job.debug_get(logits, n, which=1)] + [job.grad(k) for k in held])
+            job.shutdown()
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n,p", [(1, 1), (64, 4), (256, 4), (257, 1)])
+@pytest.mark.parametrize("C0,C1", [(784, 256), (4, 36), (12, 700)])
+def test_first_layers_that_gather_their_samples(C0, C1, n, p):
+    """A step whose first layer reads its samples from the data set (up to 256 of them) leaves what the hooks do, which gather
+    them first: the input, the labels (in the loss) and every gradient, bit for bit."""
+    torch = _torch()
+    import paper_1909_11985_amd as E
+    from paper_1909_11985_amd.binding import make_config
+    N = 2 * n
+    x, y = synth_inputs.dataset(1, N, 1, 1, C0, 10)
+    job = E.Job(make_config("mlp", dtype="f32", N=N, B=n, p_max=p, max_shard=n, H=1, W=1, C_=C0, arch=(C1, 64), classes=10), 2)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    one = np.random.default_rng(0).permutation(N)[:n // p].astype(np.int64)
+    idx, off = np.tile(one, p), np.arange(p + 1, dtype=np.int64) * (n // p)
+    E.edl_profile(True)
+    try:
+        job.gradients(p, idx, off)
+        gathered = sum(r["launches"] for r in E.edl_profile_report() if r["name"] == "gather")
+    finally:
+        E.edl_profile(False)
+    assert gathered == (0 if n <= 256 else 1)
+    job.gradients(p, idx, off)
+    loss, grads, given = job.losses(p), [job.grad(k) for k in range(p)], job.debug_get(0, n)
+    assert np.array_equal(given.reshape(n, C0), x.reshape(N, C0)[idx])
+    job.debug_forward(one)
+    job.debug_backward(n // p, 0)
+    for k in range(p):
+        assert loss[k] == loss[0] and np.array_equal(grads[k], job.grad(0)), k
+    job.shutdown()
+
+
 @pytest.mark.parametrize("dtype,bound", [("f32", 1e-5), ("bf16", 4e-3)])
 @pytest.mark.parametrize("classes", [10, 16, 100])
 def test_input_gradients_of_small_layers_add_to_what_is_there(classes, dtype, bound):
