@@ -10,6 +10,10 @@
 
 #include "graph.h"
 
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+#include <immintrin.h>
+#endif
+
 namespace edl {
 
 // ---------------------------------------------------------------- errors
@@ -70,6 +74,58 @@ static DrawPartners pick_draw_partners() {
     return draw_partners_plain;
 }
 
+// Draws kAhead partners as above and sifts them: bit t of the result is clear where partner[t] is none of the locations that
+// the sieve holds (it may be set for others: 250 locations let one in 2,000 through).  Five tables of 1,024 bits stay in
+// registers, looked up by byte permutes; a location has a bit in each, found by five fields of it and of its product with an odd
+// constant.
+struct alignas(64) Sieve {
+    unsigned char bits[5][128];
+    void add(uint32_t x) {
+        const unsigned char bit = (unsigned char)(1u << (x & 7));
+        const uint32_t h = x * 0x9E3779B1u;
+        bits[0][(x >> 3) & 127] |= bit;
+        bits[1][(x >> 10) & 127] |= bit;
+        bits[2][(h >> 25) & 127] |= bit;
+        bits[3][(h >> 18) & 127] |= bit;
+        bits[4][(h >> 11) & 127] |= bit;
+    }
+};
+typedef uint64_t (*SiftPartners)(uint64_t, uint64_t, int64_t, uint32_t*, const Sieve&);
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+__attribute__((target("avx512f,avx512dq,avx512vl,avx512bw,avx512vbmi"))) static uint64_t sift_partners_avx512(uint64_t key, uint64_t draw, int64_t i,
+                                                                                                             uint32_t* partner, const Sieve& sieve) {
+    draw_partners_avx512(key, draw, i, partner);
+    __m512i table[10];
+    for (int t = 0; t < 10; ++t) table[t] = _mm512_load_si512((const char*)sieve.bits + 64 * t);
+    const __m512i one = _mm512_set1_epi32(1), seven = _mm512_set1_epi32(7), odd = _mm512_set1_epi32((int)0x9E3779B1u);
+    uint64_t hits = 0;
+    for (int t = 0; t < kAhead; t += 16) {
+        // (of each lane's four bytes the lowest counts: the bit asked for lies there)
+        const __m512i x = _mm512_loadu_si512(partner + t), bit = _mm512_sllv_epi32(one, _mm512_and_si512(x, seven)), h = _mm512_mullo_epi32(x, odd);
+        __m512i in = _mm512_permutex2var_epi8(table[0], _mm512_srli_epi32(x, 3), table[1]);
+        in = _mm512_and_si512(in, _mm512_permutex2var_epi8(table[2], _mm512_srli_epi32(x, 10), table[3]));
+        in = _mm512_and_si512(in, _mm512_permutex2var_epi8(table[4], _mm512_srli_epi32(h, 25), table[5]));
+        in = _mm512_and_si512(in, _mm512_permutex2var_epi8(table[6], _mm512_srli_epi32(h, 18), table[7]));
+        in = _mm512_and_si512(in, _mm512_permutex2var_epi8(table[8], _mm512_srli_epi32(h, 11), table[9]));
+        hits |= (uint64_t)_mm512_test_epi32_mask(in, bit) << t;
+    }
+    return hits;
+}
+#endif
+static SiftPartners pick_sift_partners() {
+#if defined(__x86_64__) && !defined(__HIP_DEVICE_COMPILE__)
+    __builtin_cpu_init();
+    if (__builtin_cpu_supports("avx512f") && __builtin_cpu_supports("avx512dq") && __builtin_cpu_supports("avx512vl") &&
+        __builtin_cpu_supports("avx512bw") && __builtin_cpu_supports("avx512vbmi")) return sift_partners_avx512;
+#endif
+    return nullptr;
+}
+static const SiftPartners& sift_partners() {
+    static const SiftPartners f = pick_sift_partners();
+    return f;
+}
+constexpr int64_t kSieved = 400;       // entries that the sieve still tells apart: a third of its bits set, one draw in 280 let through
+
 template <typename I>
 static void shuffle_down_to(uint64_t key, int64_t N, int64_t from, I* perm) {
     static const DrawPartners draw_partners = pick_draw_partners();
@@ -127,6 +183,7 @@ public:
         entry_.resize(slots);
         where_.assign((size_t)count, 0);
         maybe_.assign(kFilter / 64, 0);
+        std::memset(&sieve_, 0, sizeof(sieve_));
     }
     // entry e is now followed at location x
     void put(uint32_t x, uint32_t e) {
@@ -139,6 +196,7 @@ public:
     }
     bool may_be(uint32_t x) const { return (maybe_[(x & (kFilter - 1)) / 64] >> (x & 63)) & 1; }
     const uint64_t* filter() const { return maybe_.data(); }
+    const Sieve& sieve() const { return sieve_; }
     // the step k with partner x: an entry followed at x comes from location k
     bool step(uint32_t x, uint32_t k) {
         size_t s = slot(x);
@@ -164,6 +222,11 @@ public:
     closed:
         put(k, e);
         // bits of locations left behind stay set; many of them would let too many steps through
+        if (++sifted_ == 48) {
+            sifted_ = 0;
+            std::memset(&sieve_, 0, sizeof(sieve_));
+            for (uint32_t x : where_) sieve_.add(x);
+        }
         if (++moved_ == 256 + where_.size() / 2) {
             moved_ = 0;
             std::fill(maybe_.begin(), maybe_.end(), 0);
@@ -177,11 +240,15 @@ public:
 
 private:
     static constexpr uint32_t kNone = 0xffffffffu;      // (locations are below N < 2^32 - 1)
-    void mark(uint32_t x) { maybe_[(x & (kFilter - 1)) / 64] |= 1ull << (x & 63); }
+    void mark(uint32_t x) {
+        maybe_[(x & (kFilter - 1)) / 64] |= 1ull << (x & 63);
+        sieve_.add(x);
+    }
     size_t slot(uint32_t x) const { return (size_t)((x * 0x9E3779B1u) >> 7) & (key_.size() - 1); }
     std::vector<uint32_t> key_, entry_, where_;
     std::vector<uint64_t> maybe_;
-    uint32_t moved_ = 0;
+    Sieve sieve_;
+    uint32_t moved_ = 0, sifted_ = 0;
 };
 }  // namespace
 
@@ -199,6 +266,19 @@ static void follow_entries(uint64_t key, int64_t N, int64_t from, int64_t count,
         f.put(j, (uint32_t)(k - from));
     }
     uint32_t partner[kAhead];
+    if (const SiftPartners sift = count <= kSieved ? sift_partners() : nullptr)
+        for (; k + kAhead <= N; k += kAhead) {
+            uint64_t hits = sift(key, (uint64_t)(N - k - kAhead), k + kAhead - 1, partner, f.sieve());
+            while (hits != 0) {       // (the last of them is the first step)
+                const int t = 63 - __builtin_clzll(hits);
+                hits &= ~(1ull << t);
+                if (!f.may_be(partner[t]) || !f.step(partner[t], (uint32_t)(k + kAhead - 1 - t))) continue;
+                // an entry has moved: the rest of the steps have been sifted for where it was
+                for (int u = t - 1; u >= 0; --u)
+                    if (f.may_be(partner[u])) f.step(partner[u], (uint32_t)(k + kAhead - 1 - u));
+                break;
+            }
+        }
     for (; k + kAhead <= N; k += kAhead) {
         // partner[t] belongs to step k + kAhead - 1 - t
         draw_partners(key, (uint64_t)(N - k - kAhead), k + kAhead - 1, partner);
@@ -226,9 +306,14 @@ void epoch_permutation_slice(uint64_t seed, int64_t epoch, int64_t N, int64_t fr
     // quarter's 15 / 11; 500,000 in 1,000, the first 371 / 507, the last 1% 28 / 9; 2.5 million in 4,000, the first 2,029 / 3,153, the last
     // 10% 310 / 192; in 250, the first 2,018 / 1,303.  Over 2,000 to 5 million samples in mini-batches of 1 to 30,000 the rule's choice
     // takes 0.5% longer than the better one in the mean, 10% at most where it follows.
+    // With the sieve (up to kSieved entries, 512-bit vectors with byte permutes): 0.28 a step and 36 a move.  us, before / with it:
+    // 1.2 million in 250, the first 679 / 433, the middle one 294 / 174; in 400 723 / 563 and 307 / 202; 2.5 million in 250 1,326 / 803
+    // and 609 / 351; 100,000 in 100 81 / 53 and 28 / 20.
     const double steps = (double)(N - from), entries = (double)count;
-    const double follow = 1000.0 + 3.0 * entries + 25.0 * entries * std::log((double)N / (double)(from + count)) + 20.0 * steps * entries / (double)(1 << 18);
-    if (N < (int64_t)0xffffffffll && follow < 0.047 * (double)N + 0.26 * steps) {
+    const bool sieved = count <= kSieved && sift_partners() != nullptr;
+    const double follow = 1000.0 + 3.0 * entries + (sieved ? 36.0 : 25.0) * entries * std::log((double)N / (double)(from + count)) +
+                          (sieved ? 2.0 : 20.0) * steps * entries / (double)(1 << 18);
+    if (N < (int64_t)0xffffffffll && follow < 0.047 * (double)N + (sieved ? 0.42 : 0.26) * steps) {
         follow_entries(epoch_key(seed, epoch), N, from, count, out);
         return;
     }

@@ -53,6 +53,13 @@ def test_shard_assignment_by_followed_entries(E, N, B):
             assert np.array_equal(idx, perm[t * B:(t + 1) * B]), (epoch, t)
 
 
+@pytest.mark.parametrize("N,B", [(1200000, 400), (401 * 2500, 401), (64 * 1563 + 8, 8), (2500000, 250)])
+def test_shard_assignment_at_the_ends_of_the_sieve(E, N, B):
+    """Steps sifted 64 at a time by the register tables and, from 401 entries on, by the table in memory; ends of the epoch that are
+    no whole 64 steps."""
+    test_shard_assignment_by_followed_entries(E, N, B)
+
+
 def test_shard_errors(E):
     for args, code in [((0, 64, 8, 3, 0, 0), -2), ((0, 60, 8, 2, 0, 0), -2), ((0, 64, 8, 2, 0, 8), -4),
                        ((0, 64, 8, 0, 0, 0), -1), ((0, 64, 8, 2, -1, 0), -1)]:
