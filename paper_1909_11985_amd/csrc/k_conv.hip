@@ -45,6 +45,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "narrow.h"
 #include "pointwise.h"
 #include "profiler.h"
 #include "thin.h"
@@ -1943,6 +1944,8 @@ RowCut launch_conv_fwd(int dtype, const ConvGeom& g, const ShardSet& S, const vo
         launch_small_fc_fwd(g, S, (const float*)x, (const float*)w, bias, relu, (float*)y, nullptr, st);
         return RowCut();
     }
+    if (bias == nullptr && !relu && narrow_takes(dtype, g, S))
+        return launch_narrow(g, S, {(const float*)x, (const float*)w, (float*)y, false, nullptr, tune().fused_stats != 0 ? stats : SumsBuf{nullptr, 0}, nullptr}, st);
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);
     a.A = x; a.B = w; a.out = y; a.bias = bias;
@@ -2013,6 +2016,12 @@ RowCut launch_conv_dgrad(int dtype, const ConvGeom& g, const ShardSet& S, const 
         if (ragged) return launch_thin_dgrad(dtype, g, S, dy, wT, old, dx, m, st);
         const SmallWgrad both = wgrad != nullptr ? SmallWgrad{(const float*)wgrad->x, wgrad->dw} : SmallWgrad{};
         return launch_small_fc_dgrad(g, S, (const float*)dy, (const float*)wT, (const float*)old, (float*)dx, m, wgrad != nullptr ? &both : nullptr, st);
+    }
+    const bool mask_here = tune().fused_mask != 0 && mask != nullptr && mask->act != nullptr && (!accumulate || tune().fused_mask_join != 0);
+    if (!w_rows && (!mask_here || mask->xin != nullptr) && narrow_takes(dtype, g, S)) {
+        const float* const old = accumulate ? (const float*)(acc_src != nullptr ? acc_src : dx) : nullptr;
+        return launch_narrow(g, S, {(const float*)dy, (const float*)wT, (float*)dx, true, old, mask_here ? mask->sums : SumsBuf{nullptr, 0},
+                                    mask_here ? mask : nullptr}, st);
     }
     const int VEC = dtype == 1 ? 8 : 4;
     ConvArgsShards a = base_args(g);

@@ -57,6 +57,7 @@ const Entry kEntries[] = {
     {"bn_finish_blocks", &Tune::bn_finish_blocks},
     {"bn_finish_bytes", &Tune::bn_finish_bytes},
     {"thin_head", &Tune::thin_head},
+    {"narrow_blocks", &Tune::narrow_blocks},
     {"spare0", &Tune::spare0},
     {"spare1", &Tune::spare1},
 };

@@ -52,6 +52,7 @@ struct Tune {
     int64_t bn_finish_blocks = 128;   // a batch norm's pass adds up the partial sums itself where a shard has at most this many of a channel ...
     int64_t bn_finish_bytes = 20000000;  // ... and its workgroups read at most this many bytes of them
     int64_t thin_head = 1;            // a small classifier goes forward, through the loss and backward in one launch
+    int64_t narrow_blocks = 600;      // float32 3x3 convolutions of 16 channels, and of 32 and 64 up to this many workgroups, have a kernel of their own (0: none)
     int64_t spare0 = 0, spare1 = 0;   // free slots for experiments (EDL_TUNE_SPARE0 / 1)
 };
 

@@ -529,6 +529,42 @@ def test_layerwise_3x3_convolutions_at_image_borders(H, W, n, dtype):
     _assert_layerwise(layerwise_parity("resnet20", dtype, n, H=H, W=W, verbose=False), dtype)
 
 
+@pytest.mark.parametrize("n,H,W", [
+    (1, 1, 1), (1, 4, 4),      # one pixel; sixteen, four and one
+    (1, 127, 1), (128, 1, 1),  # a block of 128 less one pixel, full, every neighbour outside
+    (3, 43, 1), (1, 3, 43),    # and one pixel more, in columns and in a row
+    (2, 3, 260), (5, 33, 20),  # rows longer than two blocks; the last row and column of odd images
+    (2, 272, 280),             # 595 blocks of 32 channels, 299 of 64: with one shard inside the rule
+    (2, 272, 284),             # 604 of 32: the tiled kernel
+])
+def test_narrow_3x3_convolutions(n, H, W):
+    """float32 convolutions of 16, 32 and 64 channels and stride 1 with the sums, masks and joins behind them, against the oracle and
+    the tiled kernel: both lie within the same bar, the worst error against float64 no more than a tenth larger than the tiled kernel's
+    (chains are shorter here; a tenth is the scatter where an image has few values)."""
+    import paper_1909_11985_amd as E
+    kw = dict(H=H, W=W, C=3, classes=10, arch=(16, 3, 2))
+    worst = {}
+    for blocks in (0, 600):
+        with E.options(narrow_blocks=blocks):
+            case = Case("resnet20", "f32", n, **kw)
+            E.edl_profile(True)
+            try:
+                case.job.gradients(1)
+                got = {r["name"]: r["launches"] for r in E.edl_profile_report()}
+            finally:
+                E.edl_profile(False)
+            case.close()
+            here = sum(v for k, v in got.items() if k.startswith("narrow"))
+            assert here == (0 if blocks == 0 else 14 if W == 284 else 20), got
+            r = layerwise_parity("resnet20", "f32", n, verbose=False, **kw)
+            _assert_layerwise(r, "f32")
+            worst[blocks] = r
+            _assert_layerwise(conv_bn_pair_parity("resnet20", "f32", n, **kw), "f32")
+            _assert_layerwise(relu_producer_pair_parity("resnet20", "f32", n, **kw), "f32")
+    for kind in ("fwd", "dx"):
+        assert worst[600]["plain"][kind].norm <= 1.1 * worst[0]["plain"][kind].norm, worst
+
+
 def test_layerwise_vgg16_bf16_at_full_size():
     """Every layer of VGG-16 at 224x224 (reductions up to 25088 long, 200704-row outputs), four samples."""
     r = layerwise_parity("vgg16", "bf16", 4, verbose=False)
