@@ -1442,17 +1442,14 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 const int sx = storage_of(g, op.x);
                 if (sx != 0) {
                     // a ReLU layer just before in the list whose output only this pool reads: its gradient can leave
-                    // the pool already masked
-                    const void* relu_act = nullptr;
-                    if (ii > op_lo && written[(size_t)sx] == 0 && h->readers[(size_t)sx] == 1) {
-                        const Op& prod = g.ops[ii - 1];
-                        if (prod.relu && storage_of(g, prod.y) == sx && (prod.kind == OP_BN || prod.kind == OP_CONV))
-                            relu_act = h->act(op.x);
-                    }
+                    // the pool already masked, and with a batch norm's sums
+                    const DgradMask mask = h->readers[(size_t)sx] == 1 ? producer_mask(ii, written[(size_t)sx] != 0, tune().fused_mask != 0 ? partial : nullptr) : DgradMask{};
+                    RowCut left;
                     if (launch_maxpool_backward(dt, h->grad(op.y), h->at<uint8_t>(h->L.pool_arg[ii]), h->grad(op.x),
-                                                written[(size_t)sx] != 0, n, tx.H, tx.W, tx.C, op.R, op.stride, op.pad, ty.H,
-                                                ty.W, relu_act, h->act(op.y), st))
+                                                written[(size_t)sx] != 0, S, tx.H, tx.W, tx.C, op.R, op.stride, op.pad, ty.H,
+                                                ty.W, mask.act != nullptr ? &mask : nullptr, h->act(op.y), &left, st))
                         premasked_for = ii - 1;
+                    if (left.p > 0) { fused_for = ii - 1; fused_sums = left; fused_at = partial; }
                     written[(size_t)sx] = 1;
                 }
                 break;

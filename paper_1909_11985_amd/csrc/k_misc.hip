@@ -96,10 +96,17 @@ static RowItems row_items(int W, int C, int vec) {
         if (r.cv == 1 << k) r.cv_shift = k;
     return r;
 }
+// A die gets a contiguous run of blocks: rows that several windows read stay in its L2 (forward, 256 images of 112x112x64 in windows of
+// 3x3: 153 us with neighbours on different dies, 136 so).
+__device__ __forceinline__ int block_of_die() {
+    const int q = gridDim.x >> 3, r = gridDim.x & 7, die = blockIdx.x & 7;
+    return die * q + min(die, r) + (blockIdx.x >> 3);
+}
 // row of the image stack, pixel and first vector of this lane; false for the lanes past the row's end
 __device__ __forceinline__ bool locate_vector(const RowItems& r, int& row, int& pixel, int& cvec) {
-    row = blockIdx.x / r.per_row;
-    const int v = (blockIdx.x - row * r.per_row) * 256 + threadIdx.x;
+    const int block = block_of_die();
+    row = block / r.per_row;
+    const int v = (block - row * r.per_row) * 256 + threadIdx.x;
     pixel = r.cv_shift >= 0 ? v >> r.cv_shift : v / r.cv;
     cvec = v - pixel * r.cv;
     return v < r.vecs;
@@ -208,6 +215,107 @@ __global__ __launch_bounds__(256) void maxpool_bwd_vec_kernel(const T* __restric
     }
 }
 
+// The backward of a pool of 3x3 windows with stride 2: a lane has the square of (up to) four pixels that the same four windows reach
+// - rows h + pad = 2 i - 1 and 2 i, from windows i - 1 and i, and so with the columns - so that four loads of each of the pooled tensors
+// serve four pixels; pixel by pixel they were read sixteen times.  MASK: as below, and since a window's gradient goes to the pixel
+// whose value the pool's output is, the ReLU's sign is read from that output, a quarter of the activation's bytes.
+// SUMS: the producer is a batch norm, whose own gradients are sums over what is stored here and its input: they are left as
+// column sums (DgradMask's), and its pass over both falls away.
+// Measured (256 images of 112x112x64 in bf16, with the mask): 233 us, and 179 for the sums, before; 224 for all of it now (1.08 GB at
+// 4.8 TB/s; held to 128 registers instead of 153 it spills and takes 583).  Without sums, AlexNet's three at 128 images: 73 us before, 54 now.
+struct PoolQuads {
+    int H, W, Ho, Wo, pad, cv, C;
+    int i0, j0, cols, quads;      // first row and column of squares, squares per row and per image
+    int groups, per_group;        // blocks per image, squares of each
+};
+template <typename T, bool MASK, bool SUMS>
+__global__ __launch_bounds__(256) void maxpool_bwd_quad_kernel(const T* __restrict__ dy, const uint8_t* __restrict__ arg, T* __restrict__ dx,
+                                                               const T* __restrict__ pooled, const T* __restrict__ xin,
+                                                               const float* __restrict__ mean_rstd, float* __restrict__ sums, RowCut cut, PoolQuads a) {
+    constexpr int VEC = Elem<T>::VEC;
+    __shared__ float red[SUMS ? 2 * VEC : 1][SUMS ? 256 : 1];
+    const int block = block_of_die();
+    const int tid = threadIdx.x, n = block / a.groups, group = block - n * a.groups;
+    const int side = 256 / a.cv, mine = tid / a.cv, c0 = (tid - mine * a.cv) * VEC;       // squares at a time, this lane's among them
+    const int first = group * a.per_group, end = min(first + a.per_group, a.quads);
+    float mu[VEC], rs[VEC], s1[VEC], s2[VEC];
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) { mu[e] = rs[e] = s1[e] = s2[e] = 0.f; }
+    if (SUMS) {
+        const float* const ms = mean_rstd + (size_t)shard_of_block(cut, block) * 2 * a.C + c0;
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) { mu[e] = ms[e]; rs[e] = ms[a.C + e]; }
+    }
+    for (int q = first + mine; q < end && mine < side; q += side) {
+        const int iq = q / a.cols, i = a.i0 + iq, j = a.j0 + q - iq * a.cols;
+        Vec16<T> v[2][2], sign[2][2], x[2][2];
+        uint8_t am[2][2][VEC];
+        int64_t to[2][2];
+        bool in[2][2], ok[2][2];
+        #pragma unroll
+        for (int r = 0; r < 2; ++r)
+            #pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int ho = i - 1 + r, wo = j - 1 + s;       // window, and the square's pixel
+                ok[r][s] = ho >= 0 && wo >= 0 && ho < a.Ho && wo < a.Wo;
+                const int64_t o = ok[r][s] ? (((int64_t)n * a.Ho + ho) * a.Wo + wo) * a.C + c0 : c0;
+                v[r][s] = load_vec(dy + o);
+                if (VEC == 8) *reinterpret_cast<uint2*>(am[r][s]) = *reinterpret_cast<const uint2*>(arg + o);
+                else *reinterpret_cast<uint32_t*>(am[r][s]) = *reinterpret_cast<const uint32_t*>(arg + o);
+                if (MASK) sign[r][s] = load_vec(pooled + o);
+                const int h = 2 * i - 1 + r - a.pad, w = 2 * j - 1 + s - a.pad;
+                in[r][s] = h >= 0 && w >= 0 && h < a.H && w < a.W;
+                to[r][s] = in[r][s] ? (((int64_t)n * a.H + h) * a.W + w) * a.C + c0 : c0;
+                if (SUMS) x[r][s] = load_vec(xin + to[r][s]);
+            }
+        Vec16<T> out[2][2];
+        #pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            float g[2][2];
+            int t[2][2];
+            #pragma unroll
+            for (int r = 0; r < 2; ++r)
+                #pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    g[r][s] = Elem<T>::to_f32(v[r][s].e[e]) + 0.f;       // (-0 goes as 0)
+                    t[r][s] = ok[r][s] && (!MASK || Elem<T>::to_f32(sign[r][s].e[e]) > 0.f) ? am[r][s][e] : 255;
+                }
+            // a pixel's windows in the order of the kernel below: the later row first, in it the later column
+            float d[2][2];
+            d[0][0] = t[0][0] == 4 ? g[0][0] : 0.f;
+            d[0][1] = (t[0][1] == 3 ? g[0][1] : 0.f) + (t[0][0] == 5 ? g[0][0] : 0.f);
+            d[1][0] = (t[1][0] == 1 ? g[1][0] : 0.f) + (t[0][0] == 7 ? g[0][0] : 0.f);
+            d[1][1] = (((t[1][1] == 0 ? g[1][1] : 0.f) + (t[1][0] == 2 ? g[1][0] : 0.f)) + (t[0][1] == 6 ? g[0][1] : 0.f)) + (t[0][0] == 8 ? g[0][0] : 0.f);
+            #pragma unroll
+            for (int r = 0; r < 2; ++r)
+                #pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    out[r][s].e[e] = Elem<T>::from_f32(d[r][s]);
+                    if (SUMS) {
+                        const float stored = in[r][s] ? Elem<T>::to_f32(out[r][s].e[e]) : 0.f;
+                        s1[e] += stored;
+                        s2[e] += in[r][s] ? stored * ((Elem<T>::to_f32(x[r][s].e[e]) - mu[e]) * rs[e]) : 0.f;
+                    }
+                }
+        }
+        #pragma unroll
+        for (int r = 0; r < 2; ++r)
+            #pragma unroll
+            for (int s = 0; s < 2; ++s)
+                if (in[r][s]) store_vec(dx + to[r][s], out[r][s]);
+    }
+    if (!SUMS) return;
+    #pragma unroll
+    for (int e = 0; e < VEC; ++e) { red[e][tid] = s1[e]; red[VEC + e][tid] = s2[e]; }
+    __syncthreads();
+    for (int o = tid; o < 2 * a.C; o += 256) {
+        const int kind = o / a.C, c = o - kind * a.C;
+        float s = 0.f;
+        for (int l = 0; l < side; ++l) s += red[kind * VEC + c % VEC][l * a.cv + c / VEC];
+        sums[(size_t)o * gridDim.x + block] = s;
+    }
+}
+
 // The same with the window positions that can reach an input pixel enumerated without branches: at most
 // NC = ceil(k / stride) per dimension.  All NC*NC loads are issued before the first use (a position outside
 // the output reads a clamped one and is ignored), instead of one load and one wait per tap.
@@ -298,11 +406,49 @@ void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int
                            W, C, k, stride, pad, Ho, Wo);
 }
 
-bool launch_maxpool_backward(int dtype, const void* dy, const uint8_t* arg, void* dx, bool accumulate, int N, int H,
-                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const void* relu_act, const void* relu_pooled, hipStream_t st) {
+// The squares' kernel, for a pool that it takes (launch_maxpool_backward).  A block has four rounds of squares, fewer where that
+// leaves less than eight blocks per CU.
+static RowCut launch_maxpool_quads(int dtype, const void* dy, const uint8_t* arg, void* dx, const ShardSet& S, int H, int W, int C, int pad,
+                                   int Ho, int Wo, const DgradMask* mask, const void* relu_pooled, hipStream_t st) {
+    const int vec = dtype == 1 ? 8 : 4;
+    PoolQuads a = {H, W, Ho, Wo, pad, C / vec, C, pad, pad, (W + pad) / 2 - pad + 1, 0, 0, 0};
+    a.quads = ((H + pad) / 2 - pad + 1) * a.cols;
+    const int side = 256 / a.cv, rounds = (a.quads + side - 1) / side;
+    const int64_t all = (int64_t)S.plan * rounds;
+    a.per_group = side * (int)std::max<int64_t>(1, std::min<int64_t>(4, all / 2048));
+    a.groups = (a.quads + a.per_group - 1) / a.per_group;
+    RowCut cut;
+    const int blocks = S.samples() * a.groups;
+    const bool masked = mask != nullptr, sums = masked && mask->xin != nullptr && mask->sums.buf != nullptr && mask->sums.floats >= (size_t)2 * C * blocks;
+    if (sums) {      // (blocks of squares, not of rows; who reads the sums goes by the blocks of each shard)
+        cut = cut_rows(S, H * W, H * W);
+        for (int s = 0; s <= S.p; ++s) cut.blk0[s] = S.off[s] * a.groups;
+        cut.most = S.plan_largest * a.groups;
+    }
+    const double esz = dtype == 1 ? 2.0 : 4.0, N = S.samples();
+    ProfScope ps(sums ? "maxpool_bwd_sums" : "maxpool_bwd", 0.0, esz * N * H * W * C * (sums ? 2.0 : 1.0) + (esz * (masked ? 2.0 : 1.0) + 1.0) * N * Ho * Wo * C, st);
+#define EDL_POOL_QUADS(TT, MM, SS)                                                                                                  \
+    hipLaunchKernelGGL((maxpool_bwd_quad_kernel<TT, MM, SS>), dim3(blocks), dim3(256), 0, st, (const TT*)dy, arg, (TT*)dx, (const TT*)relu_pooled, \
+                       (const TT*)(sums ? mask->xin : nullptr), sums ? mask->mean_rstd : nullptr, sums ? mask->sums.buf : nullptr, cut, a)
+    if (dtype == 1) { if (sums) EDL_POOL_QUADS(bf16_t, true, true); else if (masked) EDL_POOL_QUADS(bf16_t, true, false); else EDL_POOL_QUADS(bf16_t, false, false); }
+    else { if (sums) EDL_POOL_QUADS(float, true, true); else if (masked) EDL_POOL_QUADS(float, true, false); else EDL_POOL_QUADS(float, false, false); }
+#undef EDL_POOL_QUADS
+    return cut;
+}
+
+bool launch_maxpool_backward(int dtype, const void* dy, const uint8_t* arg, void* dx, bool accumulate, const ShardSet& S, int H,
+                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const DgradMask* mask, const void* relu_pooled, RowCut* sums,
+                             hipStream_t st) {
+    const int N = S.samples();
     const int grid = ew_grid((int64_t)N * H * W * C);
     const double esz = dtype == 1 ? 2.0 : 4.0;
     const int vec = dtype == 1 ? 8 : 4;
+    const void* const relu_act = mask != nullptr ? mask->act : nullptr;
+    // (pad 0 or 1: every window starts inside the image or one before it; up to 256 vectors per pixel; blocks counted in 31 bits)
+    if (k == 3 && stride == 2 && pad <= 1 && !accumulate && C % vec == 0 && C / vec <= 256 && (double)N * H * W < 2147483648.0) {
+        *sums = launch_maxpool_quads(dtype, dy, arg, dx, S, H, W, C, pad, Ho, Wo, relu_act != nullptr ? mask : nullptr, relu_pooled, st);
+        return relu_act != nullptr;
+    }
     const int nc = (k + stride - 1) / stride;
     const RowItems items = row_items(W, C, vec);
     const bool win = C % vec == 0 && nc <= 2 && (double)N * H * items.per_row < 2147483648.0;

@@ -207,11 +207,13 @@ void launch_pooled_bias_backward(int dtype, const void* pooled, const void* dpoo
 // ---- pooling --------------------------------------------------------------
 void launch_maxpool_forward(int dtype, const void* x, void* y, uint8_t* arg, int N, int H, int W, int C, int k,
                             int stride, int pad, int Ho, int Wo, hipStream_t st);
-// relu_act, relu_pooled: if the pooled tensor is the output of a ReLU layer with no other reader, that output and the
-// pool's; the gradient is then stored multiplied by (relu_act > 0) where the kernel taken supports it.  Returns whether
-// it was.
-bool launch_maxpool_backward(int dtype, const void* dy, const uint8_t* arg, void* dx, bool accumulate, int N, int H,
-                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const void* relu_act, const void* relu_pooled, hipStream_t st);
+// mask (may be null), relu_pooled: if the pooled tensor is the output of a ReLU layer with no other reader, that layer's part of
+// DgradMask and the pool's output; the gradient is then stored multiplied by (act > 0) where the kernel taken supports it.
+// Returns whether it was.  sums: how the column sums left in mask->sums are cut, if the producer is a batch norm and the kernel
+// leaves them (else p == 0).
+bool launch_maxpool_backward(int dtype, const void* dy, const uint8_t* arg, void* dx, bool accumulate, const ShardSet& S, int H,
+                             int W, int C, int k, int stride, int pad, int Ho, int Wo, const DgradMask* mask, const void* relu_pooled, RowCut* sums,
+                             hipStream_t st);
 void launch_gavgpool_forward(int dtype, const void* x, void* y, int N, int HW, int C, hipStream_t st);
 void launch_gavgpool_backward(int dtype, const void* dy, void* dx, bool accumulate, int N, int HW, int C,
                               hipStream_t st);

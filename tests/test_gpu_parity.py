@@ -5,7 +5,7 @@ import pytest
 
 import synth_inputs
 from oracle import oracle as O
-from parity_util import (TIGHT, TOL, Case, conv_bn_pair_parity, elementwise_excess, forced_parity, layerwise_ok, layerwise_parity, relerr,
+from parity_util import (TIGHT, TOL, Case, _qin, conv_bn_pair_parity, elementwise_excess, forced_parity, layerwise_ok, layerwise_parity, relerr,
                          per_tensor_relerr, relu_producer_pair_parity, run_parity, stepwise_parity, tid)
 
 pytestmark = pytest.mark.gpu
@@ -1289,6 +1289,52 @@ def test_bias_gradients_before_a_pool(model, dtype, n, kw, options):
             assert relerr(job.debug_get(tid(conv["y"]), n, which=1), dy) < (1e-6 if dtype == "f32" else 4e-3), conv["name"]
             pairs += 1
         assert pairs == (5 if model == "vgg16" else 3)
+        case.close()
+
+
+@pytest.mark.parametrize("sums", [1, 0])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("n,H,W,base", [
+    (3, 5, 2, 16), (2, 2, 9, 8), (3, 33, 47, 16), (2, 66, 29, 24),     # one or two windows; odd and even sides in turn; vectors that do not divide a block
+    (40, 64, 160, 64),                                                   # blocks of more than one round
+])
+def test_a_batch_norm_before_a_pool(n, H, W, base, dtype, sums):
+    """The pool's backward stores the gradient masked by the ReLU before it and leaves the batch norm's sums (sums = 0: a pass of their
+    own forms them): the stored gradient, the batch norm's own and its parameters' against float64 on the same tensors.  A
+    channel's sum runs in float32 chains of at most 256 terms: 256 times 2^-24 of the sum of their sizes, and 1e-5 of it for the
+    mean and deviation in them."""
+    import paper_1909_11985_amd as E
+    rng = np.random.default_rng(7)
+    with E.options(fused_mask=sums):
+        case = Case("resnet50", dtype, n, perturb=0.05, H=H, W=W, C=3, classes=10, arch=(base, 1, 1, 1, 1))
+        job, orc = case.job, case.oracle(False)
+        job.debug_forward(np.arange(n))
+        ops = [(oi, op) for oi, op in enumerate(orc.graph.ops) if op["kind"] != "flatten"]
+        gi = [op["kind"] for _, op in ops].index("maxpool")
+        (bi, bn), (pi, pool) = ops[gi - 1], ops[gi]
+        x, act = (job.debug_get(tid(bn[v]), n).astype(np.float64) for v in ("x", "y"))
+        pooled, arg = O.maxpool_forward(np.ascontiguousarray(act), pool["k"], pool["stride"], pool["pad"])
+        assert np.array_equal(job.debug_get(tid(pool["y"]), n), pooled)
+        dpool = O.round_bf16(rng.standard_normal(pooled.shape))
+        job.debug_set(tid(pool["y"]), dpool, which=1)
+        E.edl_profile(True)
+        try:
+            job.debug_backward_range(gi - 1, gi + 1, n)
+            got = {r["name"] for r in E.edl_profile_report()}
+        finally:
+            E.edl_profile(False)
+        assert ("maxpool_bwd_sums" in got) == (sums == 1) and ("bn_bwd_reduce" in got) == (sums == 0), got
+        dy = _qin(case, O.maxpool_backward(np.ascontiguousarray(dpool), arg, act.shape) * (act > 0))
+        assert relerr(job.debug_get(tid(bn["y"]), n, which=1), dy) < (1e-6 if dtype == "f32" else 4e-3)
+        dy = job.debug_get(tid(bn["y"]), n, which=1).astype(np.float64)
+        _, saved = orc.op_forward(bi, x)
+        dxs, dps, _ = orc.op_backward(bi, dy, x, act, saved)
+        assert relerr(job.debug_get(tid(bn["x"]), n, which=1), dxs[bn["x"]]) < (2e-5 if dtype == "f32" else 4e-3)
+        axes = tuple(range(x.ndim - 1))
+        xhat = (x - x.mean(axes)) / np.sqrt(x.var(axes) + 1e-5)
+        for off, terms in ((bn["b_off"], np.abs(dy)), (bn["g_off"], np.abs(dy * xhat) + np.abs(dy))):
+            err = np.abs(job.grad_slice(0, off, bn["C"]) - dps[off])
+            assert (err <= (256 * 2.0 ** -24 + 1e-5) * terms.sum(axes)).all(), err.max()
         case.close()
 
 
