@@ -221,7 +221,7 @@ __global__ __launch_bounds__(256) void maxpool_bwd_vec_kernel(const T* __restric
 // whose value the pool's output is, the ReLU's sign is read from that output, a quarter of the activation's bytes.
 // SUMS: the producer is a batch norm, whose own gradients are sums over what is stored here and its input: they are left as
 // column sums (DgradMask's), and its pass over both falls away.
-// Measured (256 images of 112x112x64 in bf16, with the mask): 233 us, and 179 for the sums, before; 224 for all of it now (1.08 GB at
+// Measured (256 images of 112x112x64 in bf16, with the mask): 233 us, and 179 for the sums, before; 225 for all of it now (1.08 GB at
 // 4.8 TB/s; held to 128 registers instead of 153 it spills and takes 583).  Without sums, AlexNet's three at 128 images: 73 us before, 54 now.
 struct PoolQuads {
     int H, W, Ho, Wo, pad, cv, C;
@@ -310,9 +310,9 @@ __global__ __launch_bounds__(256) void maxpool_bwd_quad_kernel(const T* __restri
     __syncthreads();
     for (int o = tid; o < 2 * a.C; o += 256) {
         const int kind = o / a.C, c = o - kind * a.C;
-        float s = 0.f;
-        for (int l = 0; l < side; ++l) s += red[kind * VEC + c % VEC][l * a.cv + c / VEC];
-        sums[(size_t)o * gridDim.x + block] = s;
+        double s = 0.0;      // (as the pass of sums: float32 chains of 16 terms, float64 across lanes)
+        for (int l = 0; l < side; ++l) s += (double)red[kind * VEC + c % VEC][l * a.cv + c / VEC];
+        sums[(size_t)o * gridDim.x + block] = (float)s;
     }
 }
 
