@@ -388,6 +388,8 @@ int32_t edl_debug_side_streams(const edl_handle* h, void** wgrad_stream, void** 
  * are cut into, and the bytes that the arena's plan has for them.  Host only.  EDL_ERANGE if the shards do not run
  * in one pass. */
 int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t* sizes, int64_t* out_needed, int64_t* out_there);
+/* How many convolutions of such a pass run on the kernel for float32 3x3 layers of few channels.  Host only; errors as above. */
+int32_t edl_debug_narrow_layers(const edl_config* cfg, int32_t p, const int64_t* sizes, int32_t* out_layers);
 
 int32_t edl_shutdown(edl_handle* h);
 

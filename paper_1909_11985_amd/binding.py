@@ -103,6 +103,7 @@ _SIGS = {
     "edl_debug_side_streams": [C.c_void_p, C.POINTER(C.c_void_p), C.POINTER(C.c_void_p)],
     "edl_arena_bytes": [C.POINTER(Config), C.c_int64, _i64p],
     "edl_debug_wgrad_scratch": [C.POINTER(Config), C.c_int32, _i64p, _i64p, _i64p],
+    "edl_debug_narrow_layers": [C.POINTER(Config), C.c_int32, _i64p, C.POINTER(C.c_int32)],
     "edl_set_side_streams": [C.c_void_p, C.c_void_p, C.c_void_p],
     "edl_set_option": [C.c_char_p, C.c_int64],
     "edl_get_option": [C.c_char_p, _i64p],
@@ -178,6 +179,14 @@ def edl_debug_wgrad_scratch(cfg, sizes):
     need, there = C.c_int64(), C.c_int64()
     _check(lib.edl_debug_wgrad_scratch(C.byref(cfg), len(sizes), sizes.ctypes.data_as(_i64p), C.byref(need), C.byref(there)))
     return need.value, there.value
+
+
+def edl_debug_narrow_layers(cfg, sizes):
+    """Convolutions of one pass over shards of these sizes that run on the kernel for float32 3x3 layers of few channels."""
+    sizes = np.ascontiguousarray(sizes, dtype=np.int64)
+    n = C.c_int32()
+    _check(lib.edl_debug_narrow_layers(C.byref(cfg), len(sizes), sizes.ctypes.data_as(_i64p), C.byref(n)))
+    return n.value
 
 
 def edl_tensor_table(cfg):

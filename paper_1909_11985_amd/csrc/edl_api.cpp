@@ -13,6 +13,7 @@
 #include "bn_pointwise.h"
 #include "graph.h"
 #include "kernels.h"
+#include "narrow.h"
 #include "profiler.h"
 #include "thin.h"
 #include "tune.h"
@@ -522,17 +523,15 @@ int32_t edl_debug_side_streams(const edl_handle* h, void** wgrad_stream, void** 
     return EDL_OK;
 }
 
-int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t* sizes, int64_t* out_needed, int64_t* out_there) {
-    if (!cfg || !sizes || !out_needed || !out_there) { set_error("null argument"); return EDL_EINVAL; }
+// What a job of this configuration runs, and p shards of these sizes as one pass of it.
+static int one_pass(const edl_config* cfg, int32_t p, const int64_t* sizes, Graph& g, Layout& L, ShardSet& S) {
     int rc = validate(*cfg);
     if (rc) return rc;
     if (p <= 0 || p > cfg->p_max) { set_error("p=%d outside [1, p_max=%d]", p, cfg->p_max); return EDL_EINVAL; }
-    Graph g;
     rc = build_graph(*cfg, g);
     if (rc) return rc;
-    Layout L;
     plan_layout(*cfg, g, L);
-    ShardSet S = {};
+    S = {};
     for (int k = 0; k < p; ++k) {
         if (sizes[k] <= 0 || sizes[k] > cfg->max_shard) { set_error("shard %d outside [1, max_shard]", k); return EDL_EINVAL; }
         S.off[k + 1] = S.off[k] + (int)sizes[k];
@@ -541,11 +540,34 @@ int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t*
     S.p = p;
     S.plan_itself();
     if (p > L.pass_shards || S.samples() > L.pass_samples) { set_error("these shards do not run in one pass"); return EDL_ERANGE; }
+    return EDL_OK;
+}
+
+int32_t edl_debug_wgrad_scratch(const edl_config* cfg, int32_t p, const int64_t* sizes, int64_t* out_needed, int64_t* out_there) {
+    if (!cfg || !sizes || !out_needed || !out_there) { set_error("null argument"); return EDL_EINVAL; }
+    Graph g;
+    Layout L;
+    ShardSet S;
+    const int rc = one_pass(cfg, p, sizes, g, L, S);
+    if (rc) return rc;
     *out_needed = 0;
     *out_there = L.wgrad_scratch_bytes;
     for (const Op& op : g.ops)
         if (op.kind == OP_CONV)
             *out_needed = std::max(*out_needed, (int64_t)conv_wgrad_needs(cfg->dtype, geom_stored(g, op, S.samples(), L.in), S));
+    return EDL_OK;
+}
+
+int32_t edl_debug_narrow_layers(const edl_config* cfg, int32_t p, const int64_t* sizes, int32_t* out_layers) {
+    if (!cfg || !sizes || !out_layers) { set_error("null argument"); return EDL_EINVAL; }
+    Graph g;
+    Layout L;
+    ShardSet S;
+    const int rc = one_pass(cfg, p, sizes, g, L, S);
+    if (rc) return rc;
+    *out_layers = 0;
+    for (const Op& op : g.ops)
+        if (op.kind == OP_CONV) *out_layers += narrow_takes(cfg->dtype, geom_stored(g, op, S.samples(), L.in), S);
     return EDL_OK;
 }
 

@@ -45,6 +45,7 @@
 
 #include "dev_common.h"
 #include "kernels.h"
+#include "magic.h"
 #include "narrow.h"
 #include "pointwise.h"
 #include "profiler.h"
@@ -1566,18 +1567,6 @@ static TileCfg pick_tile(int M, int Nn, int Kred, int* bm, int* bn, bool short_f
         default: *bm = 64; *bn = 64; break;
     }
     return t;
-}
-
-static unsigned long long magic_of(int d) {
-    if (d <= 0) return 0;
-    return ((1ull << 40) + (unsigned long long)d - 1) / (unsigned long long)d;
-}
-
-// n / d == (n * magic_of(d)) >> 40 for every 0 <= n <= n_max: the error term needs n * d < 2^40 and the
-// product must fit 64 bits
-static bool magic_fits(double n_max, int d) {
-    if (d <= 0) return true;
-    return n_max * (double)d < 1.0e12 && n_max * (double)magic_of(d) < 9.0e18;
 }
 
 template <typename T, int MODE, int KIND>

@@ -13,6 +13,7 @@
 // Measured (pixels x channels, forward / input gradient with mask and sums, with the events' 2 us): 131,072 x 16: 20.8 / 24.5 us
 // before, 14.8 / 16.2 now; 32,768 x 32: 15.2 / 15.8 and 14.8 / 15.9; 8,192 x 64: 17.7 and 7.7 for the second launch, 17.1 now.
 #include "dev_common.h"
+#include "magic.h"
 #include "narrow.h"
 #include "profiler.h"
 #include "tune.h"
@@ -28,7 +29,7 @@ struct NarrowArgs {
     const float *old, *act, *xin, *mean_rstd;     // act, xin: see DgradMask; mean_rstd of shard s at 2 * C * s
     float* sums;                                  // [2][C][blocks] or null
     int H, W, flip, gx;
-    unsigned long long magic_hw, magic_w;         // ceil(2^40 / d): n / d == (n * magic) >> 40 for n * d < 2^40
+    unsigned long long magic_hw, magic_w;         // magic_of
     unsigned bytes;                               // of x
     RowCut cut;
 };
@@ -197,8 +198,10 @@ bool narrow_takes(int dtype, const ConvGeom& g, const ShardSet& S) {
     if (dtype == 1 || g.R != 3 || g.S != 3 || g.stride != 1 || g.pad != 1 || g.K != C || tune().force_tile >= 0 || tune().narrow_blocks == 0) return false;
     if (C != 16 && C != 32 && C != 64) return false;
     const int64_t M = (int64_t)S.plan * g.H * g.W;
+    // (the kernel divides the numbers of pixels, the last block's own among them, by H W and by W)
+    const double last = (double)M + narrow_rows(C);
     return (C == 16 || M / narrow_rows(C) + S.plan_p <= tune().narrow_blocks) && M * C * 4 < 2147483648ll &&
-           (M + (int64_t)g.H * g.W) * g.H * g.W < (1ll << 40);
+           magic_fits(last, g.H * g.W) && magic_fits(last, g.W);
 }
 
 RowCut launch_narrow(const ConvGeom& g, const ShardSet& S, const NarrowTask& t, hipStream_t st) {
@@ -210,8 +213,8 @@ RowCut launch_narrow(const ConvGeom& g, const ShardSet& S, const NarrowTask& t, 
     a.gx = a.cut.blk0[a.cut.p];
     const double M = (double)S.samples() * g.H * g.W;
     a.bytes = (unsigned)(M * C * 4);
-    a.magic_hw = ((1ull << 40) + g.H * g.W - 1) / (unsigned long long)(g.H * g.W);
-    a.magic_w = ((1ull << 40) + g.W - 1) / (unsigned long long)g.W;
+    a.magic_hw = magic_of(g.H * g.W);
+    a.magic_w = magic_of(g.W);
     const bool sums = t.sums.buf != nullptr && t.sums.floats >= (size_t)2 * C * a.gx && (!t.flip || t.mask != nullptr);
     if (sums) a.sums = t.sums.buf;
     if (sums && t.mask != nullptr) {

@@ -284,6 +284,21 @@ def test_a_job_can_be_held_to_the_memory_of_one_shard(E, model, dtype, kw):
         E.edl_arena_bytes(cfg, -1)
 
 
+@pytest.mark.parametrize("H,W,n,layers", [
+    (1000, 1, 8000, 6), (1000, 1, 16770, 0), (1000, 1, 16800, 0),       # 2^24 rows of one pixel and more: the product has no room
+    (4096, 1, 4100, 0), (2, 1, 5000, 16), (1000, 2, 8000, 6), (1000, 3, 8000, 6), (32, 32, 30000, 6),
+])
+def test_the_narrow_kernel_is_taken_only_where_its_divisions_are_exact(E, H, W, n, layers):
+    """It numbers the pixels of a pass (up to 2^25) and divides those numbers by H W and by W with a product of 64 bits."""
+    from paper_1909_11985_amd.binding import edl_debug_narrow_layers, make_config
+    cfg = make_config("resnet20", N=n, B=n, p_max=1, max_shard=n, H=H, W=W)
+    taken, M = edl_debug_narrow_layers(cfg, [n]), n * H * W
+    assert taken == layers        # of 16 channels six, of 32 and 64 ten in all (not in passes of many blocks)
+    numbers = sorted({x for c in (0, M // 2, 1 << 23, 1 << 24, M) for x in range(c - 130, c + 127) if 0 <= x < M + 127})
+    exact = all(((x * (-(-(1 << 40) // d))) % (1 << 64)) >> 40 == x // d for x in numbers for d in (H * W, W))
+    assert exact or taken == 0
+
+
 # ---------------------------------------------------------------- device code of the streaming 1x1 convolutions
 def _device_code(*flags):
     """k_pointwise.hip as the library is built of it, in text."""
