@@ -1092,8 +1092,9 @@ static double weight_gradient_us(int dt, const ConvGeom& q, int shards) {
 // applied while the pass goes on.
 // head: the forward pass has done the last layer's part (forward_pass).
 // held (debugging hook only): tensors whose gradient buffers already hold a contribution the pass adds to.
+// hook: gradients that the pass needs no more are left in their buffers as well (a debugging hook hands them out).
 static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, size_t op_hi = (size_t)-1, int early_p = 0,
-                          const std::vector<int>* held = nullptr, bool head = false) {
+                          const std::vector<int>* held = nullptr, bool head = false, bool hook = false) {
     const int n = S.samples();
     // the workers' gradients of the parameters from offset `off` of the flat vector on
     auto grads_at = [&](int64_t off) { return GradDst{h->grad_buf(0) + off, h->L.grad_stride}; };
@@ -1236,6 +1237,13 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
         waiting.clear();
         waiting_us = 0;
         return ok;
+    };
+    // For a hook: the gradient of the input of batch norm ii, which went backward with convolution ic, in the place of the pieces
+    auto instead_of_pieces = [&](size_t ii, size_t ic, const void* dy, const float* bn_coef, hipStream_t bs) {
+        const Op& bn = g.ops[ii];
+        const Tensor& t = g.tensors[(size_t)bn.x];
+        weight_gradient(ic, bs, nullptr);
+        launch_bn_backward_apply(h->act(bn.x), dy, h->grad(bn.x), h->w() + bn.w_off, h->at<float>(h->L.bn_save[ii]), bn_coef, S, t.H * t.W, t.C, bs);
     };
     for (size_t ii = op_hi; ii-- > op_lo;) {
         const Op& op = g.ops[ii];
@@ -1417,9 +1425,13 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                                                S, tb.H * tb.W, tb.C, pb.relu, ps, h->sc<float>(h->L.coef_side), RowCut(), bs);
                             written[(size_t)storage_of(g, pb.x)] = 1;
                             const ConvGeom qj = geom_stored(g, pj, n, h->L.in);
-                            if (pbehind < ii) backward_through(ii - 1, pbehind, pdy, h->sc<float>(h->L.coef_side), bs);
-                            else launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? grads_at(pj.b_off) : no_grads, S,
-                                                           qj.Ho * qj.Wo, pj.K, pj.relu, ps, RowCut(), bs);
+                            if (pbehind < ii) {
+                                backward_through(ii - 1, pbehind, pdy, h->sc<float>(h->L.coef_side), bs);
+                                if (hook) instead_of_pieces(ii - 1, pbehind, pdy, h->sc<float>(h->L.coef_side), bs);
+                            } else {
+                                launch_bias_relu_backward(dt, h->act(pj.y), h->grad(pj.y), pj.bias ? grads_at(pj.b_off) : no_grads, S,
+                                                          qj.Ho * qj.Wo, pj.K, pj.relu, ps, RowCut(), bs);
+                            }
                             // weight gradient: on the first side stream like every other, behind this stream's work
                             hipStream_t ws = bs;
                             if (hipEventRecord(wg, bs) == hipSuccess && hipStreamWaitEvent(h->side, wg, 0) == hipSuccess) {
@@ -1427,7 +1439,7 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                                 used_side = true;
                             }
                             if (pbehind < ii) {
-                                weight_gradient(pbehind, ws, nullptr);
+                                if (!hook) weight_gradient(pbehind, ws, nullptr);
                             } else {
                                 launch_conv_wgrad(dt, qj, S, h->act(pj.x), h->grad(pj.y), grads_at(pj.w_off),
                                                   ws == h->side ? h->sc<float>(h->L.wgrad_scratch) : nullptr,
@@ -1449,7 +1461,9 @@ static void backward_pass(edl_handle* h, const ShardSet& S, size_t op_lo = 0, si
                 }
                 if (behind < ii) {
                     backward_through(ii, behind, dy_src, coef, st);
-                    if (overlap) {       // the pieces are added up beside the chain, with the next weight gradient handed over
+                    if (hook) {
+                        instead_of_pieces(ii, behind, dy_src, coef, st);
+                    } else if (overlap) {       // the pieces are added up beside the chain, with the next weight gradient handed over
                         waiting.push_back(behind);
                         waiting_us += 8;
                     } else {
@@ -1986,7 +2000,7 @@ int32_t edl_debug_backward(edl_handle* h, int32_t n, int32_t k) {
     const Graph& g = h->g;
     launch_softmax_ce(h->cfg.dtype, (const float*)h->act(g.logits), h->at<int32_t>(h->L.labels), h->grad(g.logits),
                       h->sc<float>(h->L.row_loss), h->at<float>(h->L.losses), one_shard(h, n, 0), g.classes, h->st);
-    backward_pass(h, one_shard(h, n, k));
+    backward_pass(h, one_shard(h, n, k), 0, (size_t)-1, 0, nullptr, false, true);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -2023,7 +2037,7 @@ int32_t edl_debug_backward_op(edl_handle* h, int32_t op, int32_t n, int32_t k) {
     if (rc) return rc;
     if (op < 0 || (size_t)op >= h->g.ops.size()) { set_error("layer %d out of range", op); return EDL_ERANGE; }
     if (k < 0 || k >= h->cfg.p_max) { set_error("gradient buffer %d outside [0,p_max)", k); return EDL_EINVAL; }
-    backward_pass(h, one_shard(h, n, k), (size_t)op, (size_t)op + 1);
+    backward_pass(h, one_shard(h, n, k), (size_t)op, (size_t)op + 1, 0, nullptr, false, true);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;
@@ -2045,7 +2059,7 @@ int32_t edl_debug_backward_range_from(edl_handle* h, int32_t op_lo, int32_t op_h
         if (held[i] <= 0 || (size_t)held[i] >= h->g.tensors.size()) { set_error("held tensor %d out of range", held[i]); return EDL_ERANGE; }
         hv.push_back(held[i]);
     }
-    backward_pass(h, one_shard(h, n, k), (size_t)op_lo, (size_t)op_hi, 0, &hv);
+    backward_pass(h, one_shard(h, n, k), (size_t)op_lo, (size_t)op_hi, 0, &hv, false, true);
     HIP_TRY(hipStreamSynchronize(h->st));
     HIP_TRY(hipGetLastError());
     return EDL_OK;

@@ -736,6 +736,37 @@ void launch_bn_forward(int dtype, const void* x, const void* res, void* y, const
     }
 }
 
+// what the element-wise pass moves, of tensors of tb bytes
+static double bn_backward_bytes(double tb, bool mask, bool dres, bool acc) { return tb * ((mask ? 3.0 : 2.0) + 1.0 + (dres ? (acc ? 2.0 : 1.0) : 0.0)); }
+
+// The element-wise pass, its coefficients given.  mask: dy is yet to be multiplied by y > 0.
+template <typename T, int VEC>
+static void bn_backward_apply_t(const void* x, const void* y, const void* dy, void* dx, void* dres, bool acc, bool mask, const float* gamma,
+                                const float* save, const float* coef, const RowCut& cut, const ShardSet& S, int hw, int C, hipStream_t st) {
+    const int64_t M = (int64_t)S.samples() * hw;
+    const double tb = (double)sizeof(T) * (double)M * C;
+    const int cvecs = (C + VEC - 1) / VEC;
+    const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
+    ProfScope ps(prof_shape_label("bn_bwd_apply", M, C), 0.0, bn_backward_bytes(tb, mask, dres != nullptr, acc), st);
+    const int u = vectors_per_lane(S, hw, cvecs);
+    const dim3 grid = ew_grid(S, hw, cvecs, u);
+#define EDL_BN_BWD_APPLY(U, MASK, ACC)                                                                                    \
+    do {                                                                                                                  \
+        if (nt) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, U, MASK, ACC, true>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
+                                   (T*)dx, (T*)dres, gamma, save, coef, cut, C, cvecs);                                \
+        else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, U, MASK, ACC, false>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
+                                (T*)dx, (T*)dres, gamma, save, coef, cut, C, cvecs);                                   \
+    } while (0)
+#define EDL_BN_BWD_APPLY_U(U)                                                                                             \
+    do {                                                                                                                  \
+        if (mask) { if (acc) EDL_BN_BWD_APPLY(U, true, true); else EDL_BN_BWD_APPLY(U, true, false); }                    \
+        else { if (acc) EDL_BN_BWD_APPLY(U, false, true); else EDL_BN_BWD_APPLY(U, false, false); }                       \
+    } while (0)
+    if (u == 4) EDL_BN_BWD_APPLY_U(4); else if (u == 2) EDL_BN_BWD_APPLY_U(2); else EDL_BN_BWD_APPLY_U(1);
+#undef EDL_BN_BWD_APPLY_U
+#undef EDL_BN_BWD_APPLY
+}
+
 template <typename T, int VEC>
 static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx, void* dres, bool dres_acc,
                           const float* gamma, const float* save, GradDst dgamma, GradDst dbeta, const ShardSet& S, int hw, int C,
@@ -753,12 +784,10 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
     // the dgrad that left the sums also left dy masked: the activation is then not read again
     const bool mask = relu && !fused;
     const bool acc = dres && dres_acc;
-    const bool nt = tune().bn_nt != 0 && tb >= (double)tune().bn_nt_bytes;
-    const double bytes = tb * ((mask ? 3.0 : 2.0) + 1.0 + (dres ? (acc ? 2.0 : 1.0) : 0.0));
     if constexpr (VEC > 1) {
         const SlicePlan p = dx == nullptr || acc ? SlicePlan() : plan_slices(S, hw, C, VEC, cut);
         if (p.slice > 0) {
-            ProfScope ps(prof_shape_label("bn_finish_bwd", M, C), 0.0, bytes, st);
+            ProfScope ps(prof_shape_label("bn_finish_bwd", M, C), 0.0, bn_backward_bytes(tb, mask, dres != nullptr, acc), st);
 #define EDL_BN_FINISH(SLICE, U)                                                                                       \
     do {                                                                                                              \
         if (mask) hipLaunchKernelGGL((bn_finish_bwd_kernel<T, SLICE, U, true>), p.grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
@@ -775,25 +804,7 @@ static void bn_backward_t(const void* x, const void* y, const void* dy, void* dx
         ProfScope ps("bn_bwd_finalize", 0.0, 8.0 * (double)cut.blk0[cut.p] * C, st);
         EDL_FINALIZE(bn_bwd_finalize_kernel, cut, C, dgamma.g, dbeta.g, dgamma.stride, coef);
     }
-    if (dx == nullptr) return;
-    ProfScope ps(prof_shape_label("bn_bwd_apply", M, C), 0.0, bytes, st);
-    const int u = vectors_per_lane(S, hw, s.cvecs);
-    const dim3 grid = ew_grid(S, hw, s.cvecs, u);
-#define EDL_BN_BWD_APPLY(U, MASK, ACC)                                                                                    \
-    do {                                                                                                                  \
-        if (nt) hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, U, MASK, ACC, true>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
-                                   (T*)dx, (T*)dres, gamma, save, coef, cut, C, s.cvecs);                                \
-        else hipLaunchKernelGGL((bn_bwd_apply_kernel<T, VEC, U, MASK, ACC, false>), grid, dim3(256), 0, st, (const T*)x, (const T*)y, (const T*)dy, \
-                                (T*)dx, (T*)dres, gamma, save, coef, cut, C, s.cvecs);                                   \
-    } while (0)
-#define EDL_BN_BWD_APPLY_U(U)                                                                                             \
-    do {                                                                                                                  \
-        if (mask) { if (acc) EDL_BN_BWD_APPLY(U, true, true); else EDL_BN_BWD_APPLY(U, true, false); }                    \
-        else { if (acc) EDL_BN_BWD_APPLY(U, false, true); else EDL_BN_BWD_APPLY(U, false, false); }                       \
-    } while (0)
-    if (u == 4) EDL_BN_BWD_APPLY_U(4); else if (u == 2) EDL_BN_BWD_APPLY_U(2); else EDL_BN_BWD_APPLY_U(1);
-#undef EDL_BN_BWD_APPLY_U
-#undef EDL_BN_BWD_APPLY
+    if (dx != nullptr) bn_backward_apply_t<T, VEC>(x, y, dy, dx, dres, acc, mask, gamma, save, coef, cut, S, hw, C, st);
 }
 
 void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy, void* dx, void* dres,
@@ -807,6 +818,12 @@ void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy,
         if (C % 4 == 0) bn_backward_t<float, 4>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
         else bn_backward_t<float, 1>(x, y, dy, dx, dres, dres_accumulate, gamma, save, dgamma, dbeta, S, hw, C, relu, partial, coef, sums, st);
     }
+}
+
+void launch_bn_backward_apply(const void* x, const void* dy, void* dx, const float* gamma, const float* save, const float* coef,
+                              const ShardSet& S, int hw, int C, hipStream_t st) {
+    // (of the cut only which rows are whose is read)
+    bn_backward_apply_t<bf16_t, 8>(x, nullptr, dy, dx, nullptr, false, false, gamma, save, coef, cut_rows(S, hw, hw), S, hw, C, st);
 }
 
 // store: the masked gradient is written back (dy <- dy')

@@ -191,6 +191,9 @@ void launch_bn_backward(int dtype, const void* x, const void* y, const void* dy,
                         bool dres_accumulate, const float* gamma, const float* save, GradDst dgamma, GradDst dbeta,
                         const ShardSet& S, int hw, int C, bool relu, float* partial, float* coef, const RowCut& sums,
                         hipStream_t st);
+// dx alone, from a gradient that is masked already and its coef (bf16, C a multiple of 8)
+void launch_bn_backward_apply(const void* x, const void* dy, void* dx, const float* gamma, const float* save, const float* coef,
+                              const ShardSet& S, int hw, int C, hipStream_t st);
 // dy <- dy * (y > 0) in place if relu; dbias[c] = sum_rows dy of each shard (if dbias.g).
 // sums.p > 0: dy is masked already and partial holds its column sums.
 void launch_bias_relu_backward(int dtype, const void* y, void* dy, GradDst dbias, const ShardSet& S, int hw, int C, bool relu,

@@ -450,6 +450,7 @@ def test_batch_norm_and_the_expanding_convolution_before_it_go_backward_together
             xh = (x - mean) * rstd
             dx = O.round_bf16(w[b["g_off"]:][:b["C"]] * rstd * (g - g.mean(0) - xh * (g * xh).mean(0)))
             wc = O.round_bf16(w[c["w_off"]:][:c["K"] * act.shape[1]].reshape(c["K"], -1))
+            assert relerr(tensor(b["x"], 1), dx) < 4e-3, bn        # (the hook's: a step keeps it in LDS)
             want, got = (dx @ wc) * ((act > 0) if masked else 1.0), tensor(c["x"], 1)
             e, (ratio, where) = relerr(got, want), elementwise_excess(got, want, 2e-2)
             print(conv, "dact", e, ratio, flush=True)
@@ -463,6 +464,40 @@ def test_batch_norm_and_the_expanding_convolution_before_it_go_backward_together
                 px = tensor(pb["x"])
                 for off, want in ((pb["b_off"], got.sum(0)), (pb["g_off"], (got * (px - px.mean(0)) / np.sqrt(px.var(0) + 1e-5)).sum(0))):
                     assert relerr(job.grad_slice(0, off, want.size), want) < 1e-4, pb["name"]
+    case.close()
+
+
+def test_a_hook_leaves_the_gradients_that_a_step_does_not_store():
+    """A whole backward pass of the hooks, streams and all: the gradient of each batch norm's input that went backward with the
+    convolution before it, against float64 on the gradient of its output (a projection's is the block's)."""
+    import paper_1909_11985_amd as E
+    n = 8
+    case = Case("resnet50", "bf16", n, H=64, W=64, C=3, classes=10, arch=(64, 2, 2, 1, 1), perturb=0.1)
+    job = case.job
+    ops = {op.get("name"): op for op in case.oracle(False).graph.ops if op["kind"] != "flatten"}
+    w = job.params().astype(np.float64)
+
+    def tensor(name, which=0):
+        a = job.debug_get(tid(name), n, which).astype(np.float64)
+        return a.reshape(-1, a.shape[-1])
+
+    def check():
+        job.debug_backward(n, 0)
+        for bn, of in (("s1.b1.projbn", "s1.b1.bn3"), ("s1.b1.bn3", "s1.b1.bn3"), ("s1.b2.bn3", "s1.b2.bn3"), ("s2.b1.bn3", "s2.b1.bn3"), ("s2.b2.bn3", "s2.b2.bn3")):
+            b = ops[bn]
+            x, g = tensor(b["x"]), tensor(ops[of]["y"], 1)
+            rstd = 1 / np.sqrt(x.var(0) + 1e-5)
+            xh = (x - x.mean(0)) * rstd
+            dx = w[b["g_off"]:][:b["C"]] * rstd * (g - g.mean(0) - xh * (g * xh).mean(0))
+            assert relerr(tensor(b["x"], 1), dx) < 4e-3, bn
+        return job.grad(0)
+
+    job.debug_forward(np.arange(n, dtype=np.int64))
+    with E.options(**_THROUGH):
+        beside = check()
+        with E.options(branch_stream=0):
+            assert np.array_equal(check(), beside)
+    check()
     case.close()
 
 
