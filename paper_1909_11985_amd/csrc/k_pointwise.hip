@@ -61,15 +61,6 @@ __device__ __forceinline__ uint4 rows_load(__amdgpu_buffer_rsrc_t r, unsigned at
     return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// What lanes of a wave have written to the wave's part of LDS is there for its other lanes, and what they have read may be
-// overwritten.  The hardware keeps a wave's LDS accesses in order; the fence keeps the compiler from moving one across this
-// point (a wave barrier alone says nothing about memory).  It orders LDS only: one over all memory, or two of them, cost the
-// joins at K = 128 3%.
-__device__ __forceinline__ void wave_lds_handover() {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-    __builtin_amdgcn_wave_barrier();
-}
-
 template <int K, int NW, int SUB, bool JOIN>
 __global__ __launch_bounds__(64 * NW, 2) void pointwise_kernel(PointwiseArgs a) {
     constexpr int NT = 64 * NW, TN = 8 / NW;                                  // lanes; MFMA tiles of 32 columns per wave

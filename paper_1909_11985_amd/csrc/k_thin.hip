@@ -245,7 +245,8 @@ __global__ __launch_bounds__(1024) void thin_head_kernel(HeadArgs a) {
             wr += e + 1 < K ? C : 0;
         }
     }
-    // loss and the gradient of the logits (softmax_ce_small_kernel); a row's logits are this wave's own
+    // loss and the gradient of the logits (softmax_ce_small_kernel); a row's logits are this wave's own, from other lanes
+    wave_lds_handover();
     const float invn = 1.f / (float)n;
     #pragma unroll 1
     for (int r = wave; r < n; r += NW) {
@@ -270,7 +271,9 @@ __global__ __launch_bounds__(1024) void thin_head_kernel(HeadArgs a) {
             if (first) a.row_loss[lo + r] = l;
         }
     }
-    // input gradient (thin_dgrad_kernel) and a wave's part of the weight gradient (thin_wgrad_kernel: every 16th row)
+    // input gradient (thin_dgrad_kernel) and a wave's part of the weight gradient (thin_wgrad_kernel: every 16th row); all lanes
+    // read the row's gradients
+    wave_lds_handover();
     float acc[kHeadOutputs];
     #pragma unroll
     for (int e = 0; e < kHeadOutputs; ++e) acc[e] = 0.f;

@@ -299,12 +299,12 @@ def test_the_narrow_kernel_is_taken_only_where_its_divisions_are_exact(E, H, W, 
     assert exact or taken == 0
 
 
-# ---------------------------------------------------------------- device code of the streaming 1x1 convolutions
-def _device_code(*flags):
-    """k_pointwise.hip as the library is built of it, in text."""
+# ---------------------------------------------------------------- device code
+def _device_code(*flags, source="k_pointwise.hip"):
+    """A source as the library is built of it, in text."""
     import subprocess
     from paper_1909_11985_amd import build
-    cmd = ["hipcc", "-x", "hip", "-S", "--cuda-device-only", os.path.join(build.CSRC, "k_pointwise.hip"), "-o", "-"] + build.FLAGS
+    cmd = ["hipcc", "-x", "hip", "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", "-"] + build.FLAGS
     return subprocess.run(cmd + list(flags), check=True, capture_output=True, text=True).stdout
 
 
@@ -329,3 +329,11 @@ def test_streaming_kernels_keep_everything_in_registers():
     spills = dict(zip(re.findall(r"\.name: +(\S*pointwise_kernel\S*)", code), re.findall(r"\.vgpr_spill_count: +(\d+)", code)))
     assert len(spills) == 8 and set(spills.values()) == {"0"}, spills
     assert set(re.findall(r"\.private_segment_fixed_size: +(\d+)", code)) == {"0"}
+
+
+def test_the_classifier_in_one_launch_orders_its_lds_accesses():
+    """Logits and their gradients pass between the lanes of a wave through LDS: a fence before either is read."""
+    kernels = re.findall(r"^define [^\n]*thin_head_kernel[^\n]*\n(.*?)^}", _device_code("-emit-llvm", source="k_thin.hip"), flags=re.S | re.M)
+    assert len(kernels) == 2
+    for body in kernels:
+        assert len(re.findall(r'fence syncscope\("wavefront"\) acq_rel', body)) == 2
