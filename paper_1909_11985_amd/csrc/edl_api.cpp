@@ -1000,7 +1000,7 @@ static bool forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_id
                     break;
                 }
                 // The classifier, the loss and what their backward pass leaves: the next op is done then
-                if (train && i + 2 == op_hi && op_hi == g.ops.size() && !prof_enabled() && classifier_together(h, i, S, wsrc)) {
+                if (train && i + 2 == op_hi && op_hi == g.ops.size() && classifier_together(h, i, S, wsrc)) {
                     const Op& prod = g.ops[i - 1];
                     ThinHead t = {};
                     t.x = h->act(op.x); t.w = wsrc; t.bias = h->w() + op.b_off; t.labels = h->at<int32_t>(h->L.labels);

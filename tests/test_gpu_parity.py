@@ -1522,14 +1522,16 @@ def _launches(job, p):
     ("f32", 10, 1000, 10000, 10, "dgrad wgrad"), ("f32", 10, 1000, 10010, 10, "dgrad"),
 ])
 def test_which_layers_the_kernels_of_few_outputs_take(dtype, classes, C, n, p, taken):
-    """The rules of the kernels for few ragged outputs, at both sides of each of their ends."""
+    """The rules of the kernels for few ragged outputs, at both sides of each of their ends (without the launch that takes
+    some of these layers through the loss as well)."""
     torch = _torch()
     import paper_1909_11985_amd as E
     from paper_1909_11985_amd.binding import make_config
     job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=p, max_shard=n // p, H=1, W=1, C_=8, arch=(8, C), classes=classes), 2)
     x, y = synth_inputs.dataset(1, n, 1, 1, 8, classes)
     job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
-    got = _launches(job, p)
+    with E.options(thin_head=0):
+        got = _launches(job, p)
     expected = {"thin_" + t: 1 for t in taken.split() if t != "small"}
     assert {k: v for k, v in got.items() if k.startswith("thin_")} == expected, got
     if "small" in taken:
@@ -1614,33 +1616,68 @@ def test_which_layers_the_float32_kernel_of_few_tiles_takes(dtype, C0, n, fwd, d
     job.shutdown()
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("classes,C,cut", [
-    (10, 256, [16, 16, 16, 16]), (1, 64, [1]), (15, 72, [17, 3, 64, 1]), (6, 1024, [16, 15]), (3, 8, [33, 64]), (9, 200, [64]), (13, 128, [5, 0, 48, 32]),
-])
-def test_a_classifier_in_one_launch_and_in_five(classes, C, cut, dtype):
-    """Bit for bit what the launches leave that it replaces: logits, losses, all gradients, at up to four blocks of 16 rows, in
-    float64 and float32 column sums, ragged columns, one row and one output."""
+def _head_job(dtype, classes, C, n, p):
     torch = _torch()
     import paper_1909_11985_amd as E
     from paper_1909_11985_amd.binding import make_config
+    x, y = synth_inputs.dataset(1, n, 1, 1, 12, classes)
+    job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=p, max_shard=n, H=1, W=1, C_=12, arch=(24, C), classes=classes), 2)
+    job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
+    return job
+
+
+def _head_launches(job, p, idx, off):
+    import paper_1909_11985_amd as E
+    E.edl_profile(True)
+    try:
+        job.gradients(p, idx, off)
+        got = {r["name"]: r["launches"] for r in E.edl_profile_report()}
+    finally:
+        E.edl_profile(False)
+    return got.get("thin_head", 0), sum(got.get(k, 0) for k in ("thin_fwd", "thin_dgrad", "thin_wgrad", "softmax_ce"))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("classes,C,cut", [
+    (10, 256, [16, 16, 16, 16]), (1, 64, [1]), (15, 72, [17, 3, 43, 1]), (6, 1024, [16, 15]), (3, 8, [33, 64]), (9, 200, [64]), (13, 128, [5, 0, 32, 27]),
+    (11, 64, [64, 64]),
+])
+def test_a_classifier_in_one_launch_and_in_five(classes, C, cut, dtype):
+    """Bit for bit what the launches leave that it replaces: logits, losses, all gradients, at up to four blocks of 16 rows, in
+    float64 and float32 column sums, ragged columns, one row and one output, an empty shard, and up to the 15 outputs with which
+    every wave has a part in the end.  The profiler sees the launch that was made."""
     if dtype == "bf16" and (classes % 8 == 0 or C % 8 != 0):
         pytest.skip("not taken")
+    import paper_1909_11985_amd as E
     n, p = sum(cut), len(cut)
-    x, y = synth_inputs.dataset(1, n, 1, 1, 12, classes)
-    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    off, idx = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64), np.arange(n, dtype=np.int64)[::-1].copy()
     out = []
     for head in (1, 0):
         with E.options(thin_head=head):
-            job = E.Job(make_config("mlp", dtype=dtype, N=n, B=n, p_max=p, max_shard=n, H=1, W=1, C_=12, arch=(24, C), classes=classes), 2)
-            job.bind_dataset(torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda())
-            job.gradients(p, np.arange(n, dtype=np.int64)[::-1].copy(), off)
+            job = _head_job(dtype, classes, C, n, p)
+            assert _head_launches(job, p, idx, off) == ((1, 0) if head else (0, 4))
+            job.gradients(p, idx, off)
             logits = len(job.debug_tensors()) - 1
             held = [k for k in range(p) if cut[k] > 0]      # (an empty shard has no loss and no gradient)
             out.append([job.losses(p)[held], job.debug_get(logits, n), job.debug_get(logits, n, which=1)] + [job.grad(k) for k in held])
             job.shutdown()
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,classes,C,cut,taken", [
+    ("f32", 15, 72, [17, 3, 64, 1], 0), ("bf16", 13, 128, [5, 0, 48, 32], 0),      # a shard is longer than a block of the bias gradient's sums
+    ("f32", 10, 64, [64], 1), ("f32", 10, 64, [65], 0),                              # rows of a shard
+    ("f32", 10, 1024, [16], 1), ("f32", 10, 1024, [17], 0), ("bf16", 10, 1024, [32], 1), ("bf16", 10, 1024, [33], 0),      # 64 KB of them
+    ("f32", 10, 1028, [8], 0), ("f32", 10, 66, [8], 0), ("bf16", 10, 68, [8], 0),    # columns: too many, no whole vectors
+    ("f32", 15, 64, [8], 1), ("f32", 17, 64, [8], 0), ("f32", 12, 64, [8], 0), ("bf16", 12, 64, [8], 1),     # outputs: too many, whole vectors
+])
+def test_which_classifiers_go_in_one_launch(dtype, classes, C, cut, taken):
+    n, p = sum(cut), len(cut)
+    job = _head_job(dtype, classes, C, n, p)
+    off = np.concatenate([[0], np.cumsum(cut)]).astype(np.int64)
+    assert _head_launches(job, p, np.arange(n, dtype=np.int64), off)[0] == taken
+    job.shutdown()
 
 
 @pytest.mark.parametrize("n,p", [(1, 1), (64, 4), (256, 4), (257, 1)])
