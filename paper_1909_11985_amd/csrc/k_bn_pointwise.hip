@@ -334,7 +334,7 @@ static int rows_per_run(const ConvGeom& g, const ShardSet& S) {
 // (98 workgroups) 46 us for 46 in three launches of which one ran beside the chain: the step 4,041 -> 4,058 us.
 bool bn_pointwise_takes(int dtype, const ConvGeom& g, const ShardSet& S) {
     if (dtype != 1 || g.R != 1 || g.S != 1 || g.stride != 1 || g.pad != 0 || tune().force_tile >= 0) return false;
-    if (!((g.K == 256 && g.C == 64) || (g.K == 512 && (g.C == 64 || g.C == 128)))) return false;
+    if (g.K != 4 * g.C || (g.C != 64 && g.C != 128)) return false;
     const int64_t hw = (int64_t)g.H * g.W;
     if (S.plan * hw < tune().bn_pointwise_rows || S.plan_smallest * hw < 4 * g.C) return false;
     const int R = rows_per_run(g, S);
