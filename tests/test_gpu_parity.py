@@ -1336,9 +1336,10 @@ def test_bias_gradients_before_a_pool(model, dtype, n, kw, options):
 ])
 def test_a_batch_norm_before_a_pool(n, H, W, base, dtype, sums):
     """The pool's backward stores the gradient masked by the ReLU before it and leaves the batch norm's sums (sums = 0: a pass of their
-    own forms them): the stored gradient, the batch norm's own and its parameters' against float64 on the same tensors.  A
-    channel's sum runs in float32 chains of at most 256 terms: 256 times 2^-24 of the sum of their sizes, and 1e-5 of it for the
-    mean and deviation in them."""
+    own forms them): the stored gradient, the batch norm's own and its parameters' against float64 on the same tensors.  A lane
+    of the pool's kernel adds up to 16 terms in float32 (four rounds of four pixels), lanes are added in float64, a block's sum
+    and the channel's are rounded once each: 18 times 2^-24 of the sum of the terms' sizes; the scale's terms take three roundings
+    more and 1e-5 for the mean and deviation in them.  (The pass of sums: chains of at most 256 terms.)"""
     import paper_1909_11985_amd as E
     rng = np.random.default_rng(7)
     with E.options(fused_mask=sums):
@@ -1368,10 +1369,54 @@ def test_a_batch_norm_before_a_pool(n, H, W, base, dtype, sums):
         assert relerr(job.debug_get(tid(bn["x"]), n, which=1), dxs[bn["x"]]) < (2e-5 if dtype == "f32" else 4e-3)
         axes = tuple(range(x.ndim - 1))
         xhat = (x - x.mean(axes)) / np.sqrt(x.var(axes) + 1e-5)
-        for off, terms in ((bn["b_off"], np.abs(dy)), (bn["g_off"], np.abs(dy * xhat) + np.abs(dy))):
+        chain = 18 if sums else 256
+        for off, terms, bar in ((bn["b_off"], np.abs(dy), chain * 2.0 ** -24),
+                                (bn["g_off"], np.abs(dy * xhat) + np.abs(dy), (chain + 3) * 2.0 ** -24 + 1e-5)):
             err = np.abs(job.grad_slice(0, off, bn["C"]) - dps[off])
-            assert (err <= (256 * 2.0 ** -24 + 1e-5) * terms.sum(axes)).all(), err.max()
+            assert (err <= bar * terms.sum(axes)).all(), err.max()
         case.close()
+
+
+def test_the_pools_sums_for_a_batch_norm_are_added_across_lanes_in_float64():
+    """Gradients of 1 + 10 * 2^-23 at every window: up to four of them add up exactly in float32, and a lane has one square of four
+    pixels, so that all that is lost is the rounding of a block's sum (128 squares) and of the channel's: 2 * 2^-24.  Added up in
+    float32 from lane to lane the sum loses the low bits of every term once it has passed 64: shown here on the host for the
+    same squares."""
+    import paper_1909_11985_amd as E
+    n, C, side = 2, 8, 128
+    case = Case("resnet50", "f32", n, perturb=0.05, H=64, W=64, C=3, classes=10, arch=(C, 1, 1, 1, 1))
+    job, orc = case.job, case.oracle(False)
+    job.debug_forward(np.arange(n))
+    ops = [op for op in orc.graph.ops if op["kind"] != "flatten"]
+    gi = [op["kind"] for op in ops].index("maxpool")
+    bn, pool = ops[gi - 1], ops[gi]
+    act = job.debug_get(tid(bn["y"]), n).astype(np.float64)
+    pooled, _ = O.maxpool_forward(np.ascontiguousarray(act), pool["k"], pool["stride"], pool["pad"])
+    job.debug_set(tid(pool["y"]), np.full(pooled.shape, 1 + 10 * 2.0 ** -23, np.float32), which=1)
+    E.edl_profile(True)
+    try:
+        job.debug_backward_range(gi - 1, gi + 1, n)
+        assert "maxpool_bwd_sums" in {r["name"] for r in E.edl_profile_report()}
+    finally:
+        E.edl_profile(False)
+    dy = job.debug_get(tid(bn["y"]), n, which=1)
+    want = dy.astype(np.float64).sum((0, 1, 2))
+    bar = 2.001 * 2.0 ** -24 * want
+    assert (np.abs(job.grad_slice(0, bn["b_off"], C) - want) <= bar).all()
+    # the squares (rows 2i and 2i + 1 of the image: pad 1) of an image in blocks of 128, one behind the other in float32
+    assert dy.shape[1:3] == (32, 32) and pool["pad"] == 1
+    lanes = dy.reshape(n, 16, 2, 16, 2, C).transpose(0, 1, 3, 2, 4, 5).reshape(n * 256, 4, C)
+    in_f32 = np.zeros(C)
+    for block in lanes.reshape(-1, side, 4, C):
+        run = np.zeros(C, np.float32)
+        for square in block:
+            part = np.zeros(C, np.float32)
+            for pixel in square:
+                part = part + pixel
+            run = run + part
+        in_f32 += run
+    assert (np.abs(in_f32 - want) > bar).all(), (in_f32 - want) / bar
+    case.close()
 
 
 def test_the_update_started_during_the_backward_pass_does_not_change_the_result():
