@@ -224,10 +224,18 @@ int32_t edl_set_side_streams(edl_handle* h, void* wgrad_stream, void* update_str
  * early_blocks, join_tile, fused_stats, held_stats, fused_mask, fused_mask_cut, fused_mask_join,
  * min128, min128_long, bk64_kred, xcd, order, splitk_tiles, splitk_target, wgrad_blocks, wgrad_long_blocks,
  * small_tail_from, small_tail_to (64x64 launches of that many workgroups run with two LDS stages, all resident at once),
- * wgrad_long_ks, wgrad_deep_max (weight gradients of at most this many workgroups keep a third tile in flight), upd_vpt, upd_wide, upd_nt, upd_blocks (shape and cache hints of the update kernel's memory
- * walk), branch_stream (projection shortcuts on the second side stream), transpose_stream, alias_shortcut
- * (a shortcut's gradient read from the block output's gradient instead of copied), bn_nt, bn_nt_bytes
- * (non-temporal loads in the batch-norm passes for tensors of at least that many bytes), spare0, spare1. */
+ * wgrad_long_ks, wgrad_deep_max (weight gradients of at most this many workgroups keep a third tile in flight),
+ * wgrad_batch_us (about how many us of weight gradients are handed to the second stream together),
+ * upd_vpt, upd_wide, upd_nt, upd_blocks (shape and cache hints of the update kernel's memory walk),
+ * branch_stream (projection shortcuts on the second side stream), transpose_stream, alias_shortcut (a shortcut's gradient read from the block output's gradient instead of copied), bn_nt, bn_nt_bytes
+ * (non-temporal loads in the batch-norm passes for tensors of at least that many bytes), pointwise_rows,
+ * pointwise_blocks (1x1 convolutions with a short reduction stream from that many rows on, with that many workgroups),
+ * bn_pointwise_rows (a batch norm and the expanding 1x1 convolution before it go backward in one launch from that many
+ * rows on), bn_finish_blocks, bn_finish_bytes (a batch norm's element-wise pass adds up the partial sums itself where a
+ * shard has at most that many of a channel and all workgroups read at most that many bytes of them), thin_head (0: a
+ * small classifier goes forward, through the loss and backward in separate launches), narrow_blocks (float32 3x3
+ * convolutions of 16 channels, and of 32 and 64 up to that many workgroups, have a kernel of their own; 0: none),
+ * spare0, spare1. */
 int32_t edl_set_option(const char* name, int64_t value);
 int32_t edl_get_option(const char* name, int64_t* out_value);
 

@@ -895,9 +895,6 @@ int32_t edl_shard(const edl_handle* h, int64_t B, int32_t p, int64_t epoch, int6
     return edl_shard_host(h->seed, h->cfg.N, B, p, epoch, step_in_epoch, out_idx, out_off);
 }
 
-// Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
-// op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
-// single layers from the debugging hooks, which then skip the gather)
 // Whether the last layer, op i, the loss and their backward pass go in one launch: few outputs over a ReLU layer with a bias that
 // nothing else reads.
 static bool classifier_together(const edl_handle* h, size_t i, const ShardSet& S, const void* weights) {
@@ -919,6 +916,9 @@ static bool gathers_itself(const edl_handle* h, const ShardSet& S) {
            h->cfg.N <= INT32_MAX && conv_fwd_gathers(h->cfg.dtype, geom_stored(g, op, S.samples(), h->L.in), S, h->data_x, h->act(0), h->w() + op.w_off);
 }
 
+// Forward pass of a set of shards whose samples' indices start at dev_idx; mean losses into dev_losses[worker].
+// op_lo..op_hi: the slice of the layer list to run (the whole list in normal use;
+// single layers from the debugging hooks, which then skip the gather)
 // host_idx: the samples' numbers where the first layer gathers them itself (gathers_itself), else null.
 // train: a backward pass over the same shards follows.  Returns whether the last layer's part of it is done (thin_head_takes).
 static bool forward_pass(edl_handle* h, const ShardSet& S, const int64_t* dev_idx, float* dev_losses, bool update_running,

@@ -409,9 +409,9 @@ __global__ __launch_bounds__(256) void bn_bwd_apply_kernel(const T* __restrict__
 // issued before the first wait, none behind a branch.
 //
 // Taken up to 128 blocks of a channel in a shard and 20 MB of sums read by all workgroups together: a workgroup of 98 blocks
-// reads 50 KB, and from some 400 workgroups of that on it takes longer than the launch that it saves (us per step at
-// 20 / 40 / 80 MB: ResNet-50, shard of 32, 4,050 / 4,050 / 4,064; three shards of 161x161 images 4,545 / 4,575 / 4,596).
-// Two launches -> one: ResNet-20, 8 shards of 16, 1,390 -> 1,313 us a step; ResNet-50 4,108 -> 4,050 and 4,644 -> 4,545.
+// reads 50 KB, and with some 400 to 1,600 workgroups of that it takes as long as the launch that it saves, or longer (us per step
+// without / at 20 / 40 / 80 MB: ResNet-50, shard of 32, 4,036 / 3,975 / 3,976 / 3,976; three shards of 161x161 images 4,535 / 4,440 /
+// 4,439 / 4,457; ResNet-20, 8 shards of 16, 1,383 / 1,224).
 
 constexpr int kSlice = 64;
 
