@@ -486,6 +486,10 @@ template <int TS> using SmallRed = float[kSmallWaves][TS][TS + 1];
 template <bool DGRAD, int TS, bool GATHER = false>
 __device__ __forceinline__ void small_fc_tile(const SmallArgs& a, int bx, int by, int blocks, SmallRed<TS>& red, const SmallGather* in = nullptr) {
     constexpr int SLICES = 64 / TS, STEP = 4 * SLICES, Q = TS * TS / 64;      // reduction elements per step, outputs per lane
+    // Chains of a wave: a 16x16 step has twice the elements of a 32x32 one, so that with two chains, turn and turn about by steps, they
+    // were longer (256 elements: one of 16 products where two of 8 were; error against float64 1.04 of the larger tiles').  Four, by
+    // the elements of a vector, cost no more.
+    constexpr int CHAINS = TS == 16 ? 4 : 2;
     int r0, r1;
     const int shard = locate_block(a.cut, by, r0, r1);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, slice = lane / TS;
@@ -493,9 +497,11 @@ __device__ __forceinline__ void small_fc_tile(const SmallArgs& a, int bx, int by
     const float* const Ar = (GATHER ? in->data + (size_t)in->idx[row] * a.K : a.A + (size_t)row * a.K);
     const float* const Br = DGRAD ? a.B + colc : a.B + (size_t)colc * a.K;
     if (GATHER && bx == 0 && (int)threadIdx.x < r1 - r0) in->labels[r0 + threadIdx.x] = in->data_y[in->idx[r0 + threadIdx.x]];
-    typename Mma<TS>::acc acc[2];
+    typename Mma<TS>::acc acc[CHAINS];
     #pragma unroll
-    for (int q = 0; q < Q; ++q) acc[0][q] = acc[1][q] = 0.f;
+    for (int c = 0; c < CHAINS; ++c)
+        #pragma unroll
+        for (int q = 0; q < Q; ++q) acc[c][q] = 0.f;
     const int steps = (a.K + STEP - 1) / STEP;
     // neighbouring steps share their cache lines; with four waves (and 32 KB in flight per workgroup) 784 -> 256 took 14 us
     const int piece = (steps + kSmallWaves - 1) / kSmallWaves, begin = wave * piece, end = min(begin + piece, steps);
@@ -515,11 +521,11 @@ __device__ __forceinline__ void small_fc_tile(const SmallArgs& a, int bx, int by
         #pragma unroll
         for (int i = 0; i < N; ++i) {
             if (s + i >= end || (s + i) * STEP + slice * 4 >= a.K) { x[i] = make_float4(0.f, 0.f, 0.f, 0.f); w[i] = x[i]; }
-            auto& c = acc[i & 1];
-            c = Mma<TS>::mul(x[i].x, w[i].x, c);
-            c = Mma<TS>::mul(x[i].y, w[i].y, c);
-            c = Mma<TS>::mul(x[i].z, w[i].z, c);
-            c = Mma<TS>::mul(x[i].w, w[i].w, c);
+            auto chain = [&](int e) -> auto& { return acc[CHAINS == 4 ? e : i & 1]; };
+            chain(0) = Mma<TS>::mul(x[i].x, w[i].x, chain(0));
+            chain(1) = Mma<TS>::mul(x[i].y, w[i].y, chain(1));
+            chain(2) = Mma<TS>::mul(x[i].z, w[i].z, chain(2));
+            chain(3) = Mma<TS>::mul(x[i].w, w[i].w, chain(3));
         }
     };
     // (784 -> 256, seven steps a wave: 11 us with a wait every two steps)
@@ -527,7 +533,8 @@ __device__ __forceinline__ void small_fc_tile(const SmallArgs& a, int bx, int by
     else if (piece <= 4) { if (begin < end) batch(begin, std::integral_constant<int, 4>()); }
     else for (int s = begin; s < end; s += 8) batch(s, std::integral_constant<int, 8>());
     #pragma unroll
-    for (int q = 0; q < Q; ++q) red[wave][Mma<TS>::out_row(q, slice)][lane % TS] = acc[0][q] + acc[1][q];
+    for (int q = 0; q < Q; ++q)
+        red[wave][Mma<TS>::out_row(q, slice)][lane % TS] = CHAINS == 4 ? (acc[0][q] + acc[1][q]) + (acc[2][q] + acc[CHAINS - 1][q]) : acc[0][q] + acc[1][q];
     __syncthreads();
     const int rl = threadIdx.x / TS, cl = threadIdx.x % TS, r = r0 + rl, c = bx * TS + cl;
     const bool mine = rl < TS, live = mine && r < r1 && c < a.N;
